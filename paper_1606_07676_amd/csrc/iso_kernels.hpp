@@ -97,18 +97,33 @@ struct ShiftArgs {
     FastDiv d_group_k, d_group;   // group * k; group
 };
 
+// Entries of a launch that moves equal blocks by full offset vectors (the s-exchange) on a torus of at most
+// kVectorDims dimensions: all that a lane needs of its entry in 48 bytes, so that no second table is read.
+// `c` are the residues of the last kVectorDims dimensions, the last one first; absent dimensions hold 0.
+constexpr int kVectorDims = 5;
+struct alignas(16) VectorEntry {
+    uint64_t src, dst;     // addresses of rank 0's blocks
+    uint32_t back;         // sum of c_j * inner_j: ranks back where no dimension wraps
+    uint32_t c[kVectorDims];
+    uint32_t reserved[2];
+};
+static_assert(sizeof(VectorEntry) == sizeof(DevEntry), "staged by the same code");
+
 struct VectorArgs {
-    const DevEntry *entries;
+    const DevEntry *entries;   // VectorEntry records instead for the kernels of at most kVectorDims dimensions
     const uint32_t *offsets;   // [s][d] residues
     TileMap map;
     uint32_t total;
     uint32_t k;
     int32_t d;
     uint32_t entry_major;
+    uint32_t src_stride, dst_stride;          // the same for all entries (VectorEntry launches)
     FastDiv d_chunks, d_k, d_p;
+    FastDiv d_last[kVectorDims];              // VectorEntry launches: the dimensions from the last to the first
+    uint32_t wrap[kVectorDims];               // p_j * inner_j of those
+    uint64_t last_offset;
     FastDiv d_dims[ISO_MAX_DIMS];
     uint32_t inner[ISO_MAX_DIMS];
-    uint64_t last_offset;
 };
 
 typedef uint32_t vec16_t __attribute__((ext_vector_type(4)));
@@ -368,23 +383,49 @@ __global__ __launch_bounds__(kThreads) void shift_round_uniform_kernel(const Shi
     move_unit<vec16_t, NTL>(dst, src, (uint64_t)(ch0 + (threadIdx.x & 63u)) * sizeof(vec16_t));
 }
 
-// (the decode constants of the first three dimensions with the rest: few tori have more, and each
-// further dimension's are fetched where the decode reaches it)
+// The s-exchange of equal blocks: every entry moves by a full offset vector.  D: dimensions the rank is
+// decoded into (3 or kVectorDims, absent ones of size 1 in front); D = 0: any torus, from the general tables.
+template <int D>
 __device__ __forceinline__ void fetch_now(const VectorArgs &a) {
-    asm volatile("" ::"s"(a.entries), "s"(a.offsets), "s"(a.map.n_tiles), "s"(a.map.run_log2), "s"(a.map.per_xcd),
-                 "s"(a.total), "s"(a.k), "s"(a.d), "s"(a.entry_major), "s"(a.inner[0]), "s"(a.inner[1]),
-                 "s"(a.inner[2]));
+    asm volatile("" ::"s"(a.entries), "s"(a.map.n_tiles), "s"(a.map.run_log2), "s"(a.map.per_xcd), "s"(a.total),
+                 "s"(a.k), "s"(a.entry_major));
     fetch_now(a.d_chunks);
     fetch_now(a.d_k);
     fetch_now(a.d_p);
-    fetch_now(a.d_dims[0]);
-    fetch_now(a.d_dims[1]);
-    fetch_now(a.d_dims[2]);
+    if constexpr (D == 0) {
+        asm volatile("" ::"s"(a.offsets), "s"(a.d));
+    } else {
+        asm volatile("" ::"s"(a.src_stride), "s"(a.dst_stride));
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            asm volatile("" ::"s"(a.wrap[j]));
+            if (j + 1 < D) fetch_now(a.d_last[j]);
+        }
+    }
 }
 
-template <typename V, bool LDS, bool TAIL>
+// Coordinates of R, last dimension first.
+template <int D>
+__device__ __forceinline__ void last_coordinates(uint32_t R, const VectorArgs &a, uint32_t (&r)[D]) {
+    uint32_t rem = R;
+#pragma unroll
+    for (int j = 0; j + 1 < D; ++j) {
+        uint32_t q;
+        fast_divmod(rem, a.d_last[j], q, r[j]);
+        rem = q;
+    }
+    r[D - 1] = rem;
+}
+
+// What bounds this kernel is the time a wavefront holds its slot before its one load is under way.  Two things
+// keep that short: one table, in LDS, holds all that an entry needs (a second one with the residues, read from
+// global memory after the barrier, was a dependent load in front of the block's own), and the rank's
+// coordinates are worked out while the table's load is in flight.  Fused s-exchange, before and after: 64^3,
+// 26 neighbours, 128-byte blocks 342 -> 294 us all-to-all, 188 -> 166 us allgather (fill rate: 128 us);
+// 200-byte allgather on 60 x 50 x 41 142 -> 130 us; 7-byte blocks on 50^3 26 -> 22 us.
+template <typename V, int D, bool LDS, bool NTL, bool TAIL>
 __global__ __launch_bounds__(kThreads) void vector_round_kernel(const VectorArgs a) {
-    fetch_now(a);
+    fetch_now<D>(a);
     __shared__ DevEntry lds[LDS ? kLdsEntries : 1];
     uint32_t tile;
     if (!tile_of_block(a.map, tile)) return;
@@ -395,12 +436,52 @@ __global__ __launch_bounds__(kThreads) void vector_round_kernel(const VectorArgs
     fast_divmod(u, a.d_chunks, t, ch);
     if (a.entry_major) fast_divmod(t, a.d_p, e, R);
     else fast_divmod(t, a.d_k, R, e);
-    staging.commit(lds);
-    if (u >= a.total) return;
-    const DevEntry en = LDS ? lds[e] : a.entries[e];
-    const uint32_t srcR = vector_source_rank(R, a.offsets + (size_t)en.shift * a.d, a.d, a.d_dims, a.inner);
-    move_unit<V, false>(block_address(en.dst, R, en.dst_stride), block_address(en.src, srcR, en.src_stride),
-                        unit_offset_if<V, TAIL>(ch, a.last_offset));
+    const uint64_t off = unit_offset_if<V, TAIL>(ch, a.last_offset);
+    if constexpr (D == 0) {
+        staging.commit(lds);
+        if (u >= a.total) return;
+        const DevEntry en = LDS ? lds[e] : a.entries[e];
+        const uint32_t srcR = vector_source_rank(R, a.offsets + (size_t)en.shift * a.d, a.d, a.d_dims, a.inner);
+        move_unit<V, NTL>(block_address(en.dst, R, en.dst_stride), block_address(en.src, srcR, en.src_stride), off);
+    } else {
+        uint32_t r[D];
+        last_coordinates<D>(R, a, r);
+        staging.commit(lds);
+        if (u >= a.total) return;
+        const VectorEntry &en = ((const VectorEntry *)(LDS ? lds : a.entries))[e];
+        uint32_t srcR = R - en.back;                    // modulo 2^32, see vector_source_rank
+#pragma unroll
+        for (int j = 0; j < D; ++j)
+            if (r[j] < en.c[j]) srcR += a.wrap[j];
+        move_unit<V, NTL>(block_address(en.dst, R, a.dst_stride), block_address(en.src, srcR, a.src_stride), off);
+    }
+}
+
+// The same for blocks that are a multiple of 1 KiB: one block per wavefront, so that rank, entry and source
+// rank are worked out once, in scalar registers (see shift_round_uniform_kernel).  Fused all-to-all, before and
+// after: 256^2, 12 neighbours, 1 KiB 298 -> 259 us, 8^5, 40 neighbours, 4 KiB 2070 -> 1800 us.
+template <int D, bool NTL>
+__global__ __launch_bounds__(kThreads) void vector_round_uniform_kernel(const VectorArgs a) {
+    fetch_now<D>(a);
+    uint32_t tile;
+    if (!tile_of_block(a.map, tile)) return;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t u0 = tile * (uint32_t)kThreads + wave * 64u;      // first unit of this wavefront
+    if (u0 >= a.total) return;                                       // total is a multiple of 64
+    uint32_t t, ch0, R, e;
+    fast_divmod(u0, a.d_chunks, t, ch0);
+    if (a.entry_major) fast_divmod(t, a.d_p, e, R);
+    else fast_divmod(t, a.d_k, R, e);
+    typedef const VectorEntry __attribute__((address_space(4))) *const_entry_ptr;
+    const const_entry_ptr en = (const_entry_ptr)(uintptr_t)((const VectorEntry *)a.entries + e);
+    uint32_t r[D];
+    last_coordinates<D>(R, a, r);
+    uint32_t srcR = R - en->back;
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+        if (r[j] < en->c[j]) srcR += a.wrap[j];
+    move_unit<vec16_t, NTL>(block_address(en->dst, R, a.dst_stride), block_address(en->src, srcR, a.src_stride),
+                            (uint64_t)(ch0 + (threadIdx.x & 63u)) * sizeof(vec16_t));
 }
 
 // Irregular blocks (the v/w interfaces of Section 2): every entry has its own

@@ -1,0 +1,73 @@
+"""The fused s-exchange of equal blocks at the edges of its dispatch: the kernels for up to three and up to
+five dimensions and the general one, one block per wavefront or not, tables in LDS or not, streaming loads,
+both layouts.  The oracle says which rank each received block comes from (its exchange of rank numbers); the
+blocks themselves are compared on the GPU, every byte."""
+import numpy as np
+import pytest
+import torch
+
+import iso_inputs as gen
+import paper_1606_07676_amd as iso
+from oracle import iso_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _source_ranks(dims, offsets):
+    """[p][s]: the rank whose block the oracle delivers as block i of rank R."""
+    p, s = int(np.prod(dims)), len(offsets)
+    ids = np.arange(p, dtype=np.int32).reshape(p, 1).view(np.uint8).copy()
+    return orc.allgather(dims, offsets, ids).reshape(p, s, 4).view(np.int32)[:, :, 0]
+
+
+def check_exchange(dims, offsets, op, alg, m, layout, send_off=0, recv_off=0):
+    """One collective with the receive buffer's surroundings watched; returns nothing, raises on a wrong byte."""
+    p, s = int(np.prod(dims)), len(offsets)
+    a2a, slot = op == iso.ISO_OP_ALLTOALL, layout == iso.ISO_LAYOUT_SLOT_MAJOR
+    comm = iso.iso_neighborhood_create(dims, np.asarray(offsets, np.int32).reshape(s, len(dims)))
+    n_send, n_recv = p * m * (s if a2a else 1), p * s * m
+    g = torch.Generator(device=DEV)
+    g.manual_seed(p * 31 + s * 7 + m)
+    send = torch.randint(0, 256, (n_send + send_off,), dtype=torch.uint8, device=DEV, generator=g)[send_off:]
+    store = torch.full((n_recv + recv_off + 64,), 0xEE, dtype=torch.uint8, device=DEV)
+    recv = store[recv_off:recv_off + n_recv]
+    work = torch.empty(max(1, iso.iso_workspace_bytes(comm, op, alg, m)), dtype=torch.uint8, device=DEV)
+    init = iso.iso_neighbor_alltoall_init_layout if a2a else iso.iso_neighbor_allgather_init_layout
+    req = init(send, recv, m, layout, work, comm, alg)
+    for _ in range(2):
+        iso.iso_start(req)
+    iso.iso_wait(req)
+    iso.iso_request_free(req)
+    src = torch.from_numpy(_source_ranks(dims, offsets).astype(np.int64)).to(DEV)
+    for i in range(s):
+        got = recv.view(s, p, m)[i] if slot else recv.view(p, s, m)[:, i]
+        if a2a:
+            block = send.view(s, p, m)[i] if slot else send.view(p, s, m)[:, i]
+        else:
+            block = send.view(p, m)
+        assert torch.equal(got, block.index_select(0, src[:, i])), (dims, m, layout, i)
+    assert bool((store[:recv_off] == 0xEE).all()) and bool((store[recv_off + n_recv:] == 0xEE).all())
+
+
+TORI = [((700,), [(1,), (-3,), (0,), (699,)]), ((37, 21), gen.moore(2, 1)), ((1, 60), [(1, 1), (0, -2)]),
+        ((7, 5, 11), gen.moore(3, 1)), ((3, 5, 4, 6), gen.von_neumann(4, 1)),
+        ((3, 4, 2, 5, 3), gen.random_distinct(5, -3, 3, 20, 5)), ((2, 3, 2, 3, 2, 4), gen.von_neumann(6, 1)),
+        ((6, 5, 5), gen.random_distinct(3, -3, 3, 129, 8))]           # one entry more than the LDS table takes
+
+
+@pytest.mark.parametrize("layout", [iso.ISO_LAYOUT_RANK_MAJOR, iso.ISO_LAYOUT_SLOT_MAJOR])
+@pytest.mark.parametrize("op", [iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER])
+@pytest.mark.parametrize("torus", range(len(TORI)))
+def test_fused_exchange_over_dimensions_and_block_sizes(torus, op, layout):
+    dims, offsets = TORI[torus]
+    for m in (3, 16, 100, 1024, 1040, 3072):
+        check_exchange(dims, offsets, op, iso.ISO_ALG_SX_FUSED, m, layout, recv_off=16)
+    check_exchange(dims, offsets, op, iso.ISO_ALG_SX_FUSED, 2048, layout, send_off=5, recv_off=3)
+
+
+@pytest.mark.parametrize("m", [8192, 8200])
+def test_send_buffers_beyond_the_last_level_cache(m):
+    """More than 256 MiB to send: streaming loads, in both forms of the kernel."""
+    check_exchange((64, 65), gen.moore(2, 1), iso.ISO_OP_ALLTOALL, iso.ISO_ALG_SX_FUSED, m, iso.ISO_LAYOUT_RANK_MAJOR)
