@@ -42,6 +42,7 @@ struct Launch {
     bool stream_loads;     // every source block is read exactly once in this launch: non-temporal loads
     bool tail;             // regular kernels: the last unit of a block overlaps the one before it
     bool uniform_waves;    // shift kernel, 16-byte units, blocks a multiple of 64 units: one block per wavefront
+    bool eighths;          // one contiguous eighth of the tiles per XCD, whatever page_resonant says
     int vector_dims;       // vector kernel: dimensions its VectorEntry records hold (0: the general tables)
     bool block_groups;     // block kernel: ranks taken in groups of kBlockGroup
     int round;             // the plan's round this launch belongs to (a large round is split over several launches)
@@ -224,6 +225,7 @@ struct KernelRef {
 // The s-exchange with VectorEntry records (see vector_launch).
 template <typename V, int D, bool TAIL>
 KernelRef select_vector(const Launch &l) {
+    if (l.vec.per) return {(const void *)&push_round_kernel<V, D, TAIL>, &l.vec};
     if constexpr (sizeof(V) == 16) {
         if (l.uniform_waves) {
             if (l.stream_loads) return {(const void *)&vector_round_uniform_kernel<D, true>, &l.vec};
@@ -686,7 +688,7 @@ private:
             src_sides.push_back(Side{he.de.src, he.de.src_stride, he.size});
             dst_sides.push_back(Side{he.de.dst, he.de.dst_stride, he.size});
         }
-        set_grid(l, (uint32_t)total, k, page_resonant(src_sides) || page_resonant(dst_sides));
+        set_grid(l, (uint32_t)total, k, l.eighths || page_resonant(src_sides) || page_resonant(dst_sides));
         pending.push_back(pd);
         done += k;
         return ISO_SUCCESS;
@@ -784,6 +786,8 @@ private:
             l.vec.entry_major = lay.slot_major || all_planes;
             l.vec.last_offset = size0 - width;
             vector_launch(l, ents.data() + done, k, chunks);
+            if (op == ISO_OP_ALLGATHER && r.entries.size() > 1) allgather_order(l, ents.data() + done, k);
+            if (l.vec.per) total = per_entry * ((k + l.vec.per - 1) / l.vec.per);
             if (l.vector_dims) return ISO_SUCCESS;
         } else if (l.kernel == kMeshShiftKernel) {
             MeshArgs &ma = l.mesh_shift;
@@ -845,9 +849,7 @@ private:
             packed = ents[q].de.src_stride == ents[0].de.src_stride && ents[q].de.dst_stride == ents[0].de.dst_stride;
         if (!packed) return;
         l.vector_dims = c.d <= 3 ? 3 : kVectorDims;
-        // (not the allgather, which the slower start of the general kernel serves better where its reads miss
-        // the L2: 8^5, 40 neighbours, 4 KiB 1420 us against 1570)
-        l.uniform_waves = op == ISO_OP_ALLTOALL && min_log2 == 4 && !l.tail && chunks % 64 == 0;
+        l.uniform_waves = min_log2 == 4 && !l.tail && chunks % 64 == 0;
         va.src_stride = ents[0].de.src_stride;
         va.dst_stride = ents[0].de.dst_stride;
         for (int j = 0; j < kVectorDims; ++j) {                  // last dimension first, absent ones of size 1
@@ -867,6 +869,45 @@ private:
             DevEntry slot;
             std::memcpy(&slot, &ve, sizeof(slot));
             table.push_back(slot);
+        }
+    }
+
+    // The fused s-exchange of an allgather reads every block once per neighbour; which L2 those reads find it in
+    // decides between three forms.
+    //   Rank-major: one contiguous eighth of the ranks per XCD (l.eighths) keeps a neighbourhood's blocks in that
+    //   XCD's 4 MiB (64^3, 26 neighbours, 128 B 166 -> 144 us, 60 x 50 x 41, 200 B 129 -> 113, 256^2 star, 1 KiB
+    //   150 -> 128; send buffers that every L2 holds whole are up to 9 % faster with interleaved runs).  Where the
+    //   ranks between the outermost neighbours hold far more than an L2, push (8^5, 40 random neighbours, 4 KiB
+    //   1421 -> 985 us, 1 KiB 344 -> 268; a window of 8.4 MiB still pulls faster, 512 against 652 us, unless what
+    //   misses the L2 misses the last-level cache as well, 200^2 star, 8 KiB 989 -> 845).  Push writes the
+    //   blocks of a row from distant places: only for blocks that are whole 128-byte lines (200 B: 320 us).
+    //   Slot-major: the ranks of an entry's plane come in order, so each XCD reads the same eighth of the send
+    //   buffer for every entry.  Push from where that eighth no longer fits its L2 (64^3, 128 B 231 -> 152 us,
+    //   300 B 563 -> 491; 25 MiB to send: pull 126, push 166).  Here push writes runs of consecutive ranks, 4
+    //   entries at a time being 2 to 8 % faster than 8 or all.
+    void allgather_order(Launch &l, const HostEntry *ents, uint32_t k) {
+        const uint64_t l2 = uint64_t(4) << 20, sent = p * size0;
+        if (lay.slot_major) {
+            if (l.vector_dims && sent > 7 * l2) l.vec.per = std::min(k, 4u);
+            return;
+        }
+        l.eighths = sent > l2;
+        int64_t lo = 0, hi = 0;                                  // the neighbours' linear distances, shortest way round
+        bool lines = true;
+        for (uint32_t q = 0; q < k; ++q) {
+            int64_t at = 0;
+            for (int j = 0; j < c.d; ++j) {
+                const int64_t cj = c.c((int)ents[q].de.shift, j), pj = c.dims[(size_t)j];
+                at += (2 * cj > pj ? cj - pj : cj) * c.inner[(size_t)j];
+            }
+            lo = std::min(lo, at);
+            hi = std::max(hi, at);
+            lines = lines && ((ents[q].de.dst | ents[q].de.dst_stride | size0) & 127u) == 0;
+        }
+        const uint64_t window = std::min<uint64_t>(p, (uint64_t)(hi - lo) + 1) * size0;
+        if (l.vector_dims && lines && (window > 3 * l2 || (window > l2 && sent > kLastLevelCacheBytes))) {
+            l.vec.per = std::min(k, 8u);
+            l.eighths = false;
         }
     }
 

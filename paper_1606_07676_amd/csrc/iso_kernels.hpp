@@ -117,6 +117,7 @@ struct VectorArgs {
     uint32_t k;
     int32_t d;
     uint32_t entry_major;
+    uint32_t per;                             // push kernel: entries a lane writes to
     uint32_t src_stride, dst_stride;          // the same for all entries (VectorEntry launches)
     FastDiv d_chunks, d_k, d_p;
     FastDiv d_last[kVectorDims];              // VectorEntry launches: the dimensions from the last to the first
@@ -482,6 +483,47 @@ __global__ __launch_bounds__(kThreads) void vector_round_uniform_kernel(const Ve
         if (r[j] < en->c[j]) srcR += a.wrap[j];
     move_unit<vec16_t, NTL>(block_address(en->dst, R, a.dst_stride), block_address(en->src, srcR, a.src_stride),
                             (uint64_t)(ch0 + (threadIdx.x & 63u)) * sizeof(vec16_t));
+}
+
+// The allgather's s-exchange the other way round: a lane reads one unit of rank S's block and writes it into
+// the receive blocks of `per` neighbours (R = S (+) C^e), so the send buffer is read k / per times instead of
+// k times.  Taken where the pull form's reads miss the L2 (see vector_launch): they then cross the fabric
+// beside the writes, and both together were what bounded it.
+template <typename V, int D, bool TAIL>
+__global__ __launch_bounds__(kThreads) void push_round_kernel(const VectorArgs a) {
+    fetch_now<D>(a);
+    asm volatile("" ::"s"(a.per));
+    __shared__ DevEntry lds[kLdsEntries];
+    uint32_t tile;
+    if (!tile_of_block(a.map, tile)) return;
+    StagedEntries<true> staging;
+    staging.issue(a.entries, a.k);
+    const uint32_t u = tile * (uint32_t)kThreads + threadIdx.x;
+    uint32_t t, ch, S, g;
+    fast_divmod(u, a.d_chunks, t, ch);
+    fast_divmod(t, a.d_p, g, S);                         // (entry group, rank, chunk)
+    const uint64_t off = unit_offset_if<V, TAIL>(ch, a.last_offset);
+    uint32_t r[D];
+    last_coordinates<D>(S, a, r);
+    staging.commit(lds);
+    if (u >= a.total) return;
+    typedef typename Unaligned<V>::type UV;
+    typedef const UV __attribute__((address_space(1))) *src_ptr;
+    typedef UV __attribute__((address_space(1))) *dst_ptr;
+    const VectorEntry *entries = (const VectorEntry *)lds;
+    const V v = *(src_ptr)(block_address(entries[0].src, S, a.src_stride) + off);
+    const uint32_t e1 = a.k - g * a.per < a.per ? a.k : (g + 1) * a.per;
+#pragma unroll 2
+    for (uint32_t e = g * a.per; e < e1; ++e) {
+        const VectorEntry &en = entries[e];
+        uint32_t R = S + en.back;                        // modulo 2^32, see vector_source_rank
+#pragma unroll
+        for (int j = 0; j < D; ++j)
+            if (r[j] + en.c[j] >= a.d_last[j].div) R -= a.wrap[j];
+        const dst_ptr dp = (dst_ptr)(block_address(en.dst, R, a.dst_stride) + off);
+        if constexpr (sizeof(V) == 16) __builtin_nontemporal_store(v, dp);
+        else *dp = v;
+    }
 }
 
 // Irregular blocks (the v/w interfaces of Section 2): every entry has its own

@@ -71,3 +71,16 @@ def test_fused_exchange_over_dimensions_and_block_sizes(torus, op, layout):
 def test_send_buffers_beyond_the_last_level_cache(m):
     """More than 256 MiB to send: streaming loads, in both forms of the kernel."""
     check_exchange((64, 65), gen.moore(2, 1), iso.ISO_OP_ALLTOALL, iso.ISO_ALG_SX_FUSED, m, iso.ISO_LAYOUT_RANK_MAJOR)
+
+
+@pytest.mark.parametrize("dims,s,m,layout", [
+    ((8, 9, 8, 7, 5), 9, 1024, iso.ISO_LAYOUT_RANK_MAJOR),       # far neighbours, whole lines: push, 20.6 MB to send
+    ((8, 9, 8, 7, 5), 9, 1040, iso.ISO_LAYOUT_RANK_MAJOR),       # no whole lines: pull
+    ((61, 64, 33), 7, 128, iso.ISO_LAYOUT_RANK_MAJOR),
+    ((33, 31, 35), 6, 896, iso.ISO_LAYOUT_SLOT_MAJOR),           # 32 MB to send: push, groups of 4 entries and of 2
+    ((33, 31, 35), 1, 997, iso.ISO_LAYOUT_SLOT_MAJOR),
+    ((300, 301), 8, 331, iso.ISO_LAYOUT_SLOT_MAJOR),
+    ((5, 6, 4, 7, 41), 5, 1024, iso.ISO_LAYOUT_SLOT_MAJOR)])
+def test_allgather_forms_follow_where_the_reads_are_found(dims, s, m, layout):
+    offsets = gen.random_distinct(len(dims), -3, 3, s, 17)
+    check_exchange(dims, offsets, iso.ISO_OP_ALLGATHER, iso.ISO_ALG_SX_FUSED, m, layout, recv_off=128)
