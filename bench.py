@@ -55,7 +55,7 @@ def parse():
     ap.add_argument("--layout", choices=("rank", "slot"), default="rank",
                     help="buffers of the timed requests: rank = the paper's [p][s][m] (default), slot = [s][p][m]")
     ap.add_argument("--algorithm", choices=("combined", "bydim", "sx_fused", "sx_rounds", "onehop", "staged"),
-                    default="combined", help="algorithm of the timed requests (default: combined, one kernel per round)")
+                    default="combined", help="algorithm of the timed requests (default: combined, one kernel per dimension)")
     ap.add_argument("--pad", type=int, default=0,
                     help="all-to-all only: every rank's row padded by this many bytes (irregular interface, equal blocks)")
     ap.add_argument("--mesh", action="store_true", help="the torus taken as a box: no dimension wraps (Section 7)")
@@ -167,11 +167,27 @@ def median(xs):
     return xs[n // 2] if n % 2 else 0.5 * (xs[n // 2 - 1] + xs[n // 2])
 
 
+def kernels_per_start(iso, req, graph=False):
+    """Kernels that one iso_start of `req` enqueues: the request's launch list, except that the
+    message-combining schedule takes the rounds of one dimension together (a graph replays the list)."""
+    info = iso.iso_request_info(req)
+    n = info["launches"]
+    if info["algorithm"] != iso.ISO_ALG_COMBINED or graph:
+        return n
+    plan = iso.iso_request_plan(req)
+    if iso.iso_plan_info(plan)["launches"] != n:       # a round was split over several launches
+        return n
+    rounds = [iso.iso_plan_round(plan, q) for q in range(n)]
+    return sum(1 for q, r in enumerate(rounds)
+               if q == 0 or r["kind"] != iso.ISO_ROUND_SHIFT or (rounds[q - 1]["kind"], rounds[q - 1]["dim"])
+               != (r["kind"], r["dim"]))
+
+
 def small_sweep():
     """Section 4's setting carried over: Moore neighbourhoods on tori of about 500 processes,
     block sizes from a few bytes to 2 KiB.  Here every size is bound by the per-launch cost, the
     GPU's counterpart of the message start-up latency, so the time follows the number of launches:
-    D for the message-combining schedules, s for the straightforward algorithm."""
+    one per dimension for the message-combining schedules, s for the straightforward algorithm."""
     import numpy as np
     import torch
     import iso_inputs as gen
@@ -211,7 +227,7 @@ def small_sweep():
                         row[an]["graph_us"] = round(e0.elapsed_time(e1) / 200 * 1e3, 2)
                     else:
                         row[an] = {"us": round(e0.elapsed_time(e1) / 200 * 1e3, 2),
-                                   "launches": iso.iso_request_info(req)["launches"]}
+                                   "launches": kernels_per_start(iso, req)}
                 iso.iso_request_free(req)
             log(row)
             rows.append(row)
@@ -366,7 +382,7 @@ class Bench:
         self.infos = [iso.iso_request_info(r) for r in self.reqs]
         self.delivered = sum(i["delivered_bytes"] for i in self.infos)
         self.moved = sum(i["bytes_read"] + i["bytes_written"] for i in self.infos)
-        self.launches = sum(i["launches"] for i in self.infos)
+        self.launches = sum(kernels_per_start(iso, r, args.graph) for r in self.reqs)
         if args.graph:
             for r in self.reqs:
                 iso.iso_request_set_graph(r, args.graph)
@@ -531,7 +547,7 @@ class Bench:
                 "workload": f"{cfg.name if m == cfg.m else cfg.name.rsplit('_m', 1)[0] + f'_m{m}'}: torus "
                             f"{'x'.join(map(str, cfg.dims))} (p={p}), s={s}, m={m} B, "
                             f"{'+'.join(self.op_name[o] for o in self.ops)} per step, "
-                            + ("message-combining schedule, one kernel per round" if args.algorithm == "combined"
+                            + ("message-combining schedule, one kernel per dimension" if args.algorithm == "combined"
                                else f"algorithm {args.algorithm}"),
                 "layout": "[s][p][m] (slot-major)" if self.slot else "[p][s][m] (rank-major, the paper's)",
                 "algorithm": args.algorithm, "seed": args.seed, "profile_tag": tag,
@@ -616,7 +632,7 @@ class Bench:
             mv = sum(iso.iso_request_info(r)["bytes_read"] * 2 for r in rs)
             dl = sum(iso.iso_request_info(r)["delivered_bytes"] for r in rs)
             d = {"ms_per_step": round(ms, 5), "delivered_GBs": round(dl / ms / 1e6, 1),
-                 "launches": sum(iso.iso_request_info(r)["launches"] for r in rs)}
+                 "launches": sum(kernels_per_start(iso, r) for r in rs)}
             if hbm_label:
                 d["moved_GBs"] = round(mv / ms / 1e6, 1)
                 d["frac_of_peak"] = round(mv / ms / 1e6 / HBM_PEAK_GBS, 4)

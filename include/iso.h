@@ -53,13 +53,16 @@ enum iso_op {
 
 enum iso_algorithm {
     /* Message-combining, torus-direct schedule (Section 5): one round per
-     * dimension j and distinct non-zero coordinate value v; one kernel launch
-     * per round.  All-to-all uses the alternating receive/intermediate buffer
+     * dimension j and distinct non-zero coordinate value v.  The request's launch
+     * list has one entry per round (iso_start_range, graphs); iso_start itself
+     * takes the rounds of one dimension, which touch disjoint blocks, in one
+     * kernel launch.  All-to-all uses the alternating receive/intermediate buffer
      * rule of Algorithm 1; allgather routes along the prefix trie of
      * Section 3.2. */
     ISO_ALG_COMBINED       = 0,
-    /* Same schedule, all rounds of one dimension issued as a single launch
-     * (they touch disjoint blocks; the k-ported remark of Section 3). */
+    /* Same schedule, all rounds of one dimension as a single round of the plan and
+     * of the launch list (they touch disjoint blocks; the k-ported remark of
+     * Section 3). */
     ISO_ALG_COMBINED_BYDIM = 1,
     /* Straightforward algorithm (first listing of Section 3): one exchange,
      * here one launch, per neighbour; s launches. */
@@ -136,7 +139,7 @@ typedef struct {
 
 typedef struct {
     int32_t op, algorithm;
-    int32_t launches;            /* kernel launches per iso_start (= rounds of the plan)   */
+    int32_t launches;            /* rounds of the plan                                     */
     int32_t work_slots;          /* blocks per rank held in the workspace                  */
     int64_t entries;             /* block-moves per rank per collective (incl. self)       */
     int32_t dim_order[ISO_MAX_DIMS]; /* allgather: order in which dimensions are routed    */
@@ -172,7 +175,9 @@ typedef struct {
 
 typedef struct {
     int32_t op, algorithm;
-    int32_t launches;
+    int32_t launches;            /* length of the launch list: what iso_start_range counts
+                                  * through and a graph holds.  iso_start enqueues as many
+                                  * kernels, fewer with ISO_ALG_COMBINED (see there)          */
     int32_t vector_bytes;        /* width of the loads/stores: the largest power of two that is
                                   * at most 16 and at most the smallest non-empty block; buffer
                                   * addresses need no alignment                               */
@@ -344,9 +349,9 @@ int iso_neighbor_allgatherw_init(const void *sendbuf, size_t send_size, size_t s
                                  void *workspace, size_t workspace_bytes, iso_comm_t comm, int algorithm,
                                  iso_request_t *req);
 
-/* Enqueues the launches of one collective on `hip_stream` (a hipStream_t; NULL
- * = the default stream) and returns without waiting.  Rounds are ordered by the
- * stream.  Calls on one request must not overlap in time on the device. */
+/* Enqueues the kernels of one collective on `hip_stream` (a hipStream_t; NULL
+ * = the default stream) and returns without waiting.  Rounds that depend on each
+ * other are ordered by the stream.  Calls on one request must not overlap in time on the device. */
 int iso_start(iso_request_t req, void *hip_stream);
 /* Enqueues only launches [first, first+count) of the request's launch list, in
  * order (0 <= first, first+count <= launches of iso_request_info).  For timing

@@ -520,7 +520,7 @@ int iso_neighbor_alltoall_noalloc(const void *sendbuf, void *recvbuf, size_t m, 
                                ptr + ISO_NOALLOC_TABLE_BYTES, ISO_NOALLOC_SCRATCH_BYTES - ISO_NOALLOC_TABLE_BYTES,
                                &arena);
         if (st != ISO_SUCCESS) return st;
-        for (const iso::Launch &l : b.launches)
+        for (const iso::Launch &l : b.start_list())
             if ((st = iso::enqueue(b.info.vector_bytes, l, stream)) != ISO_SUCCESS) return st;
         return ISO_SUCCESS;
     });
@@ -604,7 +604,7 @@ int iso_start(iso_request_t req, void *hip_stream) {
     if (req->use_graph) {
         ISO_HIP_TRY(hipGraphLaunch(req->graph_exec, stream));
     } else {
-        for (const iso::Launch &l : req->b.launches) {
+        for (const iso::Launch &l : req->b.start_list()) {
             int st = iso::enqueue(req->b.info.vector_bytes, l, stream);
             if (st != ISO_SUCCESS) return st;
         }
