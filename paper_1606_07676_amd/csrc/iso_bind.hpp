@@ -253,6 +253,9 @@ KernelRef select_regular(const Launch &l) {
         }
         return {(const void *)&mesh_shift_round_kernel<V, LDS, false, TAIL>, &l.mesh_shift};
     }
+    if (l.shift.k_all) {
+        return {(const void *)&shift_push_kernel<V, TAIL>, &l.shift};
+    }
     if constexpr (sizeof(V) == 16) {
         if (l.uniform_waves) {
             if (l.shift.group) {
@@ -736,7 +739,7 @@ private:
             src_sides.push_back(Side{he.de.src, he.de.src_stride, he.size});
             dst_sides.push_back(Side{he.de.dst, he.de.dst_stride, he.size});
         }
-        set_grid(l, (uint32_t)total, k, l.eighths || page_resonant(src_sides) || page_resonant(dst_sides));
+        set_grid(l, (uint32_t)total, l.shift.k_all ? l.shift.k : k, l.eighths || page_resonant(src_sides) || page_resonant(dst_sides));
         pending.push_back(pd);
         done += k;
         return ISO_SUCCESS;
@@ -878,9 +881,52 @@ private:
             l.shift.last_offset = size0 - width;
             l.shift.d_inner = make_fastdiv(l.shift.inner);
             l.shift.d_pj = make_fastdiv(l.shift.pj);
+            if (op == ISO_OP_ALLGATHER && push_launch(l, ents.data() + done, k, per_entry)) {
+                total = per_entry * l.shift.k;
+                return ISO_SUCCESS;
+            }
         }
         for (uint32_t q = 0; q < k; ++q) table.push_back(ents[done + q].de);
         return ISO_SUCCESS;
+    }
+
+    // Allgather rounds in push form: where the launch's entries read at most three quarters as many blocks as they
+    // write (64^3, 26 neighbours, 128 B, one launch per dimension 276 -> 201 us; 200^2, 24 neighbours, 512 B 139
+    // -> 105; with 40 random neighbours in 8^5 nearly every block has a single child in most dimensions and the
+    // pull form is 1 to 2 % faster), and where that many reads still fill the chip (16^3, 24 neighbours, 16 B, 16
+    // workgroups: 10.0 -> 12.2 us).  What a workgroup writes then lies at different ranks, so every block has to
+    // be part of a dense plane (slot-major 64^3, 300 B 600 -> 521 us) or whole 64-byte sectors, from 1 KiB on 32
+    // (200 B on rank-major rows 238 -> 284 us, 320 B 92 -> 74, 64 B level, 2080 B 130 -> 111).
+    bool push_launch(Launch &l, const HostEntry *ents, uint32_t k, uint64_t per_entry) {
+        if (k > kLdsEntries) return false;
+        const uint32_t mask = size0 >= 1024 ? 31u : 63u;
+        for (uint32_t q = 0; q < k; ++q) {
+            const DevEntry &de = ents[q].de;
+            if (de.dst_stride != size0 && ((de.dst | de.dst_stride | size0) & mask)) return false;
+        }
+        std::vector<DevEntry> by_source;
+        std::vector<uint32_t> first;
+        std::vector<bool> taken(k, false);
+        for (uint32_t q = 0; q < k; ++q) {
+            if (taken[q]) continue;
+            first.push_back((uint32_t)by_source.size());
+            for (uint32_t w = q; w < k; ++w)
+                if (!taken[w] && ents[w].de.src == ents[q].de.src && ents[w].de.src_stride == ents[q].de.src_stride) {
+                    taken[w] = true;
+                    by_source.push_back(ents[w].de);
+                }
+        }
+        const uint32_t n = (uint32_t)first.size();
+        if (4 * n > 3 * k || per_entry * n < 256 * kThreads) return false;
+        first.push_back(k);
+        table.insert(table.end(), by_source.begin(), by_source.end());
+        prefixes.insert(prefixes.end(), first.begin(), first.end());
+        l.uniform_waves = false;
+        l.shift.group = 0;
+        l.shift.k_all = k;
+        l.shift.k = n;
+        l.shift.d_k = make_fastdiv(n);
+        return true;
     }
 
     // The s-exchange of equal blocks on a torus.  Up to kVectorDims dimensions and as many entries as the LDS
@@ -1064,6 +1110,7 @@ private:
                 pd.l.block.offsets = dev_offsets;
             } else {
                 pd.l.shift.entries = dev_entries + pd.first_entry;
+                pd.l.shift.groups = dev_prefix + pd.first_prefix;
             }
             (rq.launches.size() < n_listed ? rq.launches : rq.start_launches).push_back(pd.l);
         }

@@ -95,6 +95,9 @@ struct ShiftArgs {
     // the ranks after them keep the plain order.
     uint32_t group, grouped;
     FastDiv d_group_k, d_group;   // group * k; group
+    // Push form (k counts sources then): [k + 1] first entry of every source; entries in all.
+    const uint32_t *groups;
+    uint32_t k_all;
 };
 
 // Entries of a launch that moves equal blocks by full offset vectors (the s-exchange) on a torus of at most
@@ -382,6 +385,50 @@ __global__ __launch_bounds__(kThreads) void shift_round_uniform_kernel(const Shi
     const uint64_t src = block_address(en->src, srcR, en->src_stride);
     const uint64_t dst = block_address(en->dst, R, en->dst_stride);
     move_unit<vec16_t, NTL>(dst, src, (uint64_t)(ch0 + (threadIdx.x & 63u)) * sizeof(vec16_t));
+}
+
+// Allgather rounds the other way round: the trie sends one copy on to several children, and the kernel above
+// reads it once for each.  Here the entries of a launch are ordered by source, and a lane reads one unit of
+// rank S's copy and writes it to every child, which sits `shift` steps on.
+template <typename V, bool TAIL>
+__global__ __launch_bounds__(kThreads) void shift_push_kernel(const ShiftArgs a) {
+    fetch_now(a);
+    asm volatile("" ::"s"(a.groups), "s"(a.k_all));
+    __shared__ DevEntry lds[kLdsEntries];
+    __shared__ uint32_t lds_first[kLdsEntries + 1];
+    uint32_t tile;
+    if (!tile_of_block(a.map, tile)) return;
+    StagedEntries<true> staging;
+    staging.issue(a.entries, a.k_all);
+    const uint32_t q = kThreads - 1 - threadIdx.x;       // the workgroup's last lanes, as in the block kernel
+    const bool stages = q <= a.k;
+    const uint32_t first = stages ? a.groups[q] : 0u;
+    const uint32_t u = tile * (uint32_t)kThreads + threadIdx.x;
+    uint32_t t, ch, S, g;
+    fast_divmod(u, a.d_chunks, t, ch);
+    if (a.entry_major) fast_divmod(t, a.d_p, g, S);
+    else fast_divmod(t, a.d_k, S, g);
+    const uint32_t qq = fast_div(S, a.d_inner);
+    const uint32_t sj = qq - fast_div(qq, a.d_pj) * a.pj;
+    const uint64_t off = unit_offset_if<V, TAIL>(ch, a.last_offset);
+    if (stages) lds_first[q] = first;
+    staging.commit(lds);
+    if (u >= a.total) return;
+    typedef typename Unaligned<V>::type UV;
+    typedef const UV __attribute__((address_space(1))) *src_ptr;
+    typedef UV __attribute__((address_space(1))) *dst_ptr;
+    uint32_t e = lds_first[g];
+    const uint32_t e1 = lds_first[g + 1];
+    const src_ptr sp = (src_ptr)(block_address(lds[e].src, S, lds[e].src_stride) + off);
+    const V v = *sp;                                     // (streaming: 2 to 12 % slower)
+    for (; e < e1; ++e) {
+        const DevEntry &en = lds[e];
+        uint32_t R = S + en.shift * a.inner;             // modulo 2^32; the true result lies in [0, p)
+        if (sj + en.shift >= a.pj) R -= a.pj * a.inner;
+        const dst_ptr dp = (dst_ptr)(block_address(en.dst, R, en.dst_stride) + off);
+        if constexpr (sizeof(V) == 16) __builtin_nontemporal_store(v, dp);
+        else *dp = v;
+    }
 }
 
 // The s-exchange of equal blocks: every entry moves by a full offset vector.  D: dimensions the rank is

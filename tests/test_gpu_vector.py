@@ -84,3 +84,15 @@ def test_send_buffers_beyond_the_last_level_cache(m):
 def test_allgather_forms_follow_where_the_reads_are_found(dims, s, m, layout):
     offsets = gen.random_distinct(len(dims), -3, 3, s, 17)
     check_exchange(dims, offsets, iso.ISO_OP_ALLGATHER, iso.ISO_ALG_SX_FUSED, m, layout, recv_off=128)
+
+
+@pytest.mark.parametrize("alg", [iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM, iso.ISO_ALG_COMBINED_STAGED])
+@pytest.mark.parametrize("dims,offsets,m,layout", [
+    ((41, 40, 39), gen.moore(3, 1), 64, iso.ISO_LAYOUT_RANK_MAJOR),          # whole sectors: one read for two children
+    ((41, 40, 39), gen.moore(3, 1), 80, iso.ISO_LAYOUT_RANK_MAJOR),          # not: every child reads for itself
+    ((53, 67), gen.moore(2, 2) + [(0, 0), (1, 2), (1, 2)], 1056, iso.ISO_LAYOUT_RANK_MAJOR),   # repeated neighbours
+    ((29, 31, 17), gen.moore(3, 1) + [(2, 0, 0), (2, 1, 0), (-2, 0, 1)], 100, iso.ISO_LAYOUT_SLOT_MAJOR),
+    ((300, 299), gen.von_neumann(2, 2), 5, iso.ISO_LAYOUT_SLOT_MAJOR),
+    ((2, 3, 1, 29, 211), gen.von_neumann(5, 1), 192, iso.ISO_LAYOUT_RANK_MAJOR)])   # sides of 1, 2 and 3: both ways alias
+def test_allgather_rounds_that_read_a_block_once_for_all_its_children(dims, offsets, m, layout, alg):
+    check_exchange(dims, [tuple(c) for c in offsets], iso.ISO_OP_ALLGATHER, alg, m, layout, recv_off=64)
