@@ -9,6 +9,7 @@
 #include <cstring>
 #include <initializer_list>
 #include <numeric>
+#include <type_traits>
 #include <vector>
 
 #include "iso.h"
@@ -39,7 +40,7 @@ struct Launch {
     uint32_t grid;
     bool lds_table;
     bool mesh;
-    bool stream_loads;     // every source block is read exactly once in this launch: non-temporal loads
+    int policy;            // kStreamLoads, kPlainStores (see cache_policy)
     bool tail;             // regular kernels: the last unit of a block overlaps the one before it
     bool uniform_waves;    // shift kernel, 16-byte units, blocks a multiple of 64 units: one block per wavefront
     bool eighths;          // one contiguous eighth of the tiles per XCD, whatever page_resonant says
@@ -222,22 +223,35 @@ struct KernelRef {
     const void *arg;
 };
 
+// f(std::integral_constant<int, policy>) for the launch's cache policy: 16-byte units only (narrower ones are
+// always loaded through the caches and stored plainly).
+template <typename V, typename F>
+KernelRef with_policy(const Launch &l, F &&f) {
+    if constexpr (sizeof(V) == 16) {
+        switch (l.policy) {
+            case kStreamLoads: return f(std::integral_constant<int, kStreamLoads>());
+            case kPlainStores: return f(std::integral_constant<int, kPlainStores>());
+            case kStreamLoads | kPlainStores: return f(std::integral_constant<int, kStreamLoads | kPlainStores>());
+            default: break;
+        }
+    }
+    return f(std::integral_constant<int, 0>());
+}
+
 // The s-exchange with VectorEntry records (see vector_launch).
 template <typename V, int D, bool TAIL>
 KernelRef select_vector(const Launch &l) {
     if (l.vec.per) return {(const void *)&push_round_kernel<V, D, TAIL>, &l.vec};
     if constexpr (sizeof(V) == 16) {
         if (l.uniform_waves) {
-            if (l.stream_loads) return {(const void *)&vector_round_uniform_kernel<D, true>, &l.vec};
-            return {(const void *)&vector_round_uniform_kernel<D, false>, &l.vec};
+            if (l.policy & kStreamLoads) return {(const void *)&vector_round_uniform_kernel<D, kStreamLoads>, &l.vec};
+            return {(const void *)&vector_round_uniform_kernel<D, 0>, &l.vec};
         }
-        if (l.stream_loads) return {(const void *)&vector_round_kernel<V, D, true, true, TAIL>, &l.vec};
+        if (l.policy & kStreamLoads) return {(const void *)&vector_round_kernel<V, D, true, kStreamLoads, TAIL>, &l.vec};
     }
-    return {(const void *)&vector_round_kernel<V, D, true, false, TAIL>, &l.vec};
+    return {(const void *)&vector_round_kernel<V, D, true, 0, TAIL>, &l.vec};
 }
 
-// Streaming loads exist for the shift kernel at the 16-byte width only (narrower
-// units are the slow path anyway).
 template <typename V, bool LDS, bool TAIL>
 KernelRef select_regular(const Launch &l) {
     if (l.kernel == kVectorKernel) {
@@ -245,33 +259,23 @@ KernelRef select_regular(const Launch &l) {
             if (l.vector_dims == 3) return select_vector<V, 3, TAIL>(l);
             if (l.vector_dims == kVectorDims) return select_vector<V, kVectorDims, TAIL>(l);
         }
-        return {(const void *)&vector_round_kernel<V, 0, LDS, false, TAIL>, &l.vec};
+        return {(const void *)&vector_round_kernel<V, 0, LDS, 0, TAIL>, &l.vec};
     }
-    if (l.kernel == kMeshShiftKernel) {
+    if (l.kernel == kMeshShiftKernel)
+        return with_policy<V>(l, [&](auto pol) -> KernelRef {
+            return {(const void *)&mesh_shift_round_kernel<V, LDS, pol(), TAIL>, &l.mesh_shift};
+        });
+    if (l.shift.k_all) return {(const void *)&shift_push_kernel<V, TAIL>, &l.shift};
+    return with_policy<V>(l, [&](auto pol) -> KernelRef {
         if constexpr (sizeof(V) == 16) {
-            if (l.stream_loads) return {(const void *)&mesh_shift_round_kernel<V, LDS, true, TAIL>, &l.mesh_shift};
-        }
-        return {(const void *)&mesh_shift_round_kernel<V, LDS, false, TAIL>, &l.mesh_shift};
-    }
-    if (l.shift.k_all) {
-        return {(const void *)&shift_push_kernel<V, TAIL>, &l.shift};
-    }
-    if constexpr (sizeof(V) == 16) {
-        if (l.uniform_waves) {
-            if (l.shift.group) {
-                if (l.stream_loads) return {(const void *)&shift_round_uniform_kernel<true, true>, &l.shift};
-                return {(const void *)&shift_round_uniform_kernel<false, true>, &l.shift};
+            if (l.uniform_waves) {
+                if (l.shift.group) return {(const void *)&shift_round_uniform_kernel<pol(), true>, &l.shift};
+                return {(const void *)&shift_round_uniform_kernel<pol()>, &l.shift};
             }
-            if (l.stream_loads) return {(const void *)&shift_round_uniform_kernel<true>, &l.shift};
-            return {(const void *)&shift_round_uniform_kernel<false>, &l.shift};
+            if (l.shift.group) return {(const void *)&shift_round_kernel<V, LDS, pol(), TAIL, true>, &l.shift};
         }
-        if (l.shift.group) {
-            if (l.stream_loads) return {(const void *)&shift_round_kernel<V, LDS, true, TAIL, true>, &l.shift};
-            return {(const void *)&shift_round_kernel<V, LDS, false, TAIL, true>, &l.shift};
-        }
-        if (l.stream_loads) return {(const void *)&shift_round_kernel<V, LDS, true, TAIL>, &l.shift};
-    }
-    return {(const void *)&shift_round_kernel<V, LDS, false, TAIL>, &l.shift};
+        return {(const void *)&shift_round_kernel<V, LDS, pol(), TAIL>, &l.shift};
+    });
 }
 
 template <typename V>
@@ -288,29 +292,29 @@ KernelRef select_width(const Launch &l) {
 
 template <bool LDS, bool MESH>
 KernelRef select_block(const Launch &l) {
-    if (l.block_groups) {
-        if (l.stream_loads) return {(const void *)&block_round_kernel<LDS, MESH, true, true>, &l.block};
-        return {(const void *)&block_round_kernel<LDS, MESH, false, true>, &l.block};
+    if (l.policy & kPlainStores) {
+        if (l.block_groups) return {(const void *)&block_round_kernel<LDS, MESH, kPlainStores, true>, &l.block};
+        return {(const void *)&block_round_kernel<LDS, MESH, kPlainStores>, &l.block};
     }
-    if (l.stream_loads) return {(const void *)&block_round_kernel<LDS, MESH, true>, &l.block};
-    return {(const void *)&block_round_kernel<LDS, MESH, false>, &l.block};
+    if (l.block_groups) return {(const void *)&block_round_kernel<LDS, MESH, 0, true>, &l.block};
+    return {(const void *)&block_round_kernel<LDS, MESH, 0>, &l.block};
 }
 
 inline KernelRef select_kernel(int vector_bytes, const Launch &l) {
     if (l.kernel == kStagedRoundKernel) {                 // blocks of whole 16-byte units only
         if (l.tile_units == kSmallTileUnits) {
-            if (l.stream_loads) return {(const void *)&staged_round_kernel<vec16_t, true, kSmallTileUnits / kThreads>, &l.staged};
+            if (l.policy & kStreamLoads) return {(const void *)&staged_round_kernel<vec16_t, true, kSmallTileUnits / kThreads>, &l.staged};
             return {(const void *)&staged_round_kernel<vec16_t, false, kSmallTileUnits / kThreads>, &l.staged};
         }
-        if (l.stream_loads) return {(const void *)&staged_round_kernel<vec16_t, true, kTileUnits / kThreads>, &l.staged};
+        if (l.policy & kStreamLoads) return {(const void *)&staged_round_kernel<vec16_t, true, kTileUnits / kThreads>, &l.staged};
         return {(const void *)&staged_round_kernel<vec16_t, false, kTileUnits / kThreads>, &l.staged};
     }
     if (l.kernel == kDeliverKernel) {
         if (l.tile_units == kSmallTileUnits) {
-            if (l.stream_loads) return {(const void *)&deliver_kernel<vec16_t, true, kSmallTileUnits / kThreads>, &l.deliver};
+            if (l.policy & kStreamLoads) return {(const void *)&deliver_kernel<vec16_t, true, kSmallTileUnits / kThreads>, &l.deliver};
             return {(const void *)&deliver_kernel<vec16_t, false, kSmallTileUnits / kThreads>, &l.deliver};
         }
-        if (l.stream_loads) return {(const void *)&deliver_kernel<vec16_t, true, kTileUnits / kThreads>, &l.deliver};
+        if (l.policy & kStreamLoads) return {(const void *)&deliver_kernel<vec16_t, true, kTileUnits / kThreads>, &l.deliver};
         return {(const void *)&deliver_kernel<vec16_t, false, kTileUnits / kThreads>, &l.deliver};
     }
     if (l.kernel == kBlockKernel) {
@@ -723,16 +727,7 @@ private:
             const int st = block_launch(pd, r, ents, done, k, total);
             if (st != ISO_SUCCESS) return st;
         }
-        // streaming loads: all-to-all shift rounds of equal blocks (irregular blocks are faster with
-        // cacheable loads), and the all-to-all s-exchange where the send buffer exceeds the last-level cache
-        // (326 MB -4 %, 805 MB -4.6 %, 5.4 GB -3.8 %; below it the cache serves most reads: 218 MB +17 %,
-        // 109 MB +40 %; an allgather reads every block several times: +60 %)
-        l.stream_loads = op == ISO_OP_ALLTOALL && r.kind != ISO_ROUND_VECTOR &&
-                         (l.kernel == kShiftKernel || l.kernel == kMeshShiftKernel || l.kernel == kStagedRoundKernel ||
-                          l.kernel == kDeliverKernel ||
-                          (l.kernel == kBlockKernel && l.block.equal_units));
-        if (l.kernel == kVectorKernel && l.vector_dims && op == ISO_OP_ALLTOALL)
-            l.stream_loads = inf.delivered_bytes > kLastLevelCacheBytes;
+        l.policy = cache_policy(l, r);
         std::vector<Side> src_sides, dst_sides;
         for (uint32_t q = 0; q < k; ++q) {
             const HostEntry &he = ents[done + q];
@@ -743,6 +738,38 @@ private:
         pending.push_back(pd);
         done += k;
         return ISO_SUCCESS;
+    }
+
+    // Cache policy of a launch whose kernel and arguments are set.  What decides is whether the blocks of the
+    // whole collective (the receive buffer's size) stay in the last-level cache from one round to the next.
+    //   All-to-all rounds read every block once: streaming loads and stores where they do not.  Up to half that
+    //   cache neither (26 neighbours, one launch per dimension: 24^3, 256 B 73 -> 60 us, 20^3, 64 B 21 -> 17,
+    //   64^3, 16 B 239 -> 154, 8^5, 100 B 440 -> 285; at 146 MB 112 -> 122).  A little above it, blocks that do
+    //   not fill whole 64-byte sectors of rank-major rows still gain from plain stores, which let neighbouring
+    //   blocks meet in the cache before a sector is written (32^3, 200 B 214 -> 153 us, 64^3, 40 B 560 -> 409;
+    //   426 MB 402 -> 471, whole sectors 160 -> 168, 1000-byte blocks, which have few of them, 152 -> 161).
+    //   Allgather rounds may read a block several times: cached loads; plain stores while all of it fits
+    //   (64^3, 36 B 148 -> 139 us, box 40^3, 100 B 86 -> 69; 640 MB 239 -> 324).
+    //   Unequal blocks: cached loads, plain stores up to a quarter (4-byte stencil on 64^3 126 -> 119 us; at
+    //   133 MB 73 -> 93; streaming loads 20 % slower wherever the blocks fit the cache).
+    //   The s-exchange writes whole rows and is indifferent to the stores; streaming loads where the send buffer
+    //   of an all-to-all exceeds the cache (805 MB -4.6 %, 5.4 GB -3.8 %; 218 MB +17 %, an allgather +60 %) and no
+    //   two blocks of a rank-major row share a 128-byte line (64 B +9 %, 100 B +7 %, 300 B +9 %).
+    int cache_policy(const Launch &l, const Round &r) const {
+        const uint64_t bytes = inf.delivered_bytes;
+        const uint64_t above = kLastLevelCacheBytes * 9 / 8;      // what still gains from the cache
+        const bool a2a = op == ISO_OP_ALLTOALL;
+        if (l.kernel == kStagedRoundKernel || l.kernel == kDeliverKernel) return a2a ? kStreamLoads : 0;
+        if (l.kernel == kVectorKernel) {
+            const bool lines = size0 % 128 == 0 || lay.slot_major;
+            return a2a && l.vector_dims && lines && bytes > above ? kStreamLoads : 0;
+        }
+        if (r.kind == ISO_ROUND_VECTOR) return 0;
+        if (l.kernel == kBlockKernel) return bytes <= kLastLevelCacheBytes / 4 ? kPlainStores : 0;
+        if (!a2a) return bytes <= kLastLevelCacheBytes ? kPlainStores : 0;
+        if (bytes <= kLastLevelCacheBytes / 2) return kPlainStores;
+        const bool part_sectors = size0 % 64 && size0 < 512 && !lay.slot_major;
+        return part_sectors && bytes <= above ? kStreamLoads | kPlainStores : kStreamLoads;
     }
 
     // Staged schedule, last launch: every rank's receive row written in one piece.
@@ -837,6 +864,10 @@ private:
             l.vec.entry_major = lay.slot_major || all_planes;
             l.vec.last_offset = size0 - width;
             vector_launch(l, ents.data() + done, k, chunks);
+            // several blocks of a rank-major row to a line, read by ranks that lie near each other: one eighth of the
+            // ranks per XCD keeps the line in its L2 (64^3, 16 B 46.5 -> 38 us, 28 B 79 -> 73, 50^3 star, 20 B 10.2 ->
+            // 5.9; 40 B 105 -> 112)
+            if (op == ISO_OP_ALLTOALL && !l.vec.entry_major && r.entries.size() > 1) l.eighths = size0 <= 32;
             if (op == ISO_OP_ALLGATHER && r.entries.size() > 1) allgather_order(l, ents.data() + done, k);
             if (l.vec.per) total = per_entry * ((k + l.vec.per - 1) / l.vec.per);
             if (l.vector_dims) return ISO_SUCCESS;

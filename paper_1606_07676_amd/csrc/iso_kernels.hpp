@@ -21,14 +21,9 @@
 // 256-lane workgroup covers 4 KiB of consecutive units.  Measured on MI355X,
 // one unit per lane with the maximum number of resident wavefronts beats any
 // per-lane unrolling (2, 4, 8 units per lane lose 3 %, 15 %, 50 %), for plain
-// copies as well as for these gathers.  Stores are streaming (non-temporal):
-// a block written in one round is next touched a whole round later (+8 % on
-// the all-to-all rounds).  Loads are streaming too in the message-combining
-// rounds of an all-to-all, where every source block is read exactly once
-// (+1 to +9 %).  Everything else keeps cacheable loads: allgather rounds read
-// one source block for several entries (streaming loads cost them 15 %), and
-// the s-exchange kernels lose 25 % with streaming loads where the buffers fit
-// the last-level cache and gain nothing where they do not.
+// copies as well as for these gathers.  Which loads and stores are streaming
+// (non-temporal) depends on how the collective's blocks compare with the
+// last-level cache: see cache_policy in iso_bind.hpp.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -144,22 +139,25 @@ struct Unaligned {
     typedef V type __attribute__((aligned(1)));
 };
 
+// Cache policy of the accesses of a launch (see cache_policy in iso_bind.hpp for when each is taken).
+constexpr int kStreamLoads = 1, kPlainStores = 2;
+
 // The unit at byte offset `off` of the block at byte address `src` to the same offset of the
 // block at `dst`, both in global memory (the address space is spelled out so that the accesses
-// are global_load / global_store, not flat ones).  NTL: streaming load.
-template <typename V, bool NTL>
+// are global_load / global_store, not flat ones).
+template <typename V, int POLICY>
 __device__ __forceinline__ void move_unit(uint64_t dst, uint64_t src, uint64_t off) {
     typedef typename Unaligned<V>::type UV;
     typedef const UV __attribute__((address_space(1))) *src_ptr;
     typedef UV __attribute__((address_space(1))) *dst_ptr;
     const src_ptr sp = (src_ptr)(src + off);
     V v;
-    if constexpr (NTL) v = __builtin_nontemporal_load(sp);
+    if constexpr (POLICY & kStreamLoads) v = __builtin_nontemporal_load(sp);
     else v = *sp;
-    // Streaming stores for 16-byte units only.  Narrower units belong to blocks of a few bytes, of
+    // Streaming stores at most for 16-byte units.  Narrower units belong to blocks of a few bytes, of
     // which several wavefronts write different bytes of one cache line: plain stores let the L2
     // merge them before the line goes to memory.
-    if constexpr (sizeof(V) == 16) __builtin_nontemporal_store(v, (dst_ptr)(dst + off));
+    if constexpr (sizeof(V) == 16 && !(POLICY & kPlainStores)) __builtin_nontemporal_store(v, (dst_ptr)(dst + off));
     else *(dst_ptr)(dst + off) = v;
 }
 
@@ -298,7 +296,7 @@ __device__ __forceinline__ void fetch_now(const ShiftArgs &a) {
     fetch_now(a.d_p);
 }
 
-template <typename V, bool LDS, bool NTL, bool TAIL, bool GROUPS = false>
+template <typename V, bool LDS, int POLICY, bool TAIL, bool GROUPS = false>
 __global__ __launch_bounds__(kThreads) void shift_round_kernel(const ShiftArgs a) {
     fetch_now(a);
     if constexpr (GROUPS) {
@@ -340,7 +338,7 @@ __global__ __launch_bounds__(kThreads) void shift_round_kernel(const ShiftArgs a
     // the true result lies in [0, p))
     uint32_t srcR = R - en.shift * a.inner;
     if (rj < en.shift) srcR += a.pj * a.inner;
-    move_unit<V, NTL>(block_address(en.dst, R, en.dst_stride), block_address(en.src, srcR, en.src_stride),
+    move_unit<V, POLICY>(block_address(en.dst, R, en.dst_stride), block_address(en.src, srcR, en.src_stride),
                       unit_offset_if<V, TAIL>(ch, a.last_offset));
 }
 
@@ -349,7 +347,7 @@ __global__ __launch_bounds__(kThreads) void shift_round_kernel(const ShiftArgs a
 // and are computed once, in scalar registers, the entry fetched with scalar loads.  No staging of the
 // table through LDS, no barrier, no vector-memory access in front of the one load that matters: what
 // bounds these kernels is how long a wavefront holds its slot before that load is under way.
-template <bool NTL, bool GROUPS = false>
+template <int POLICY, bool GROUPS = false>
 __global__ __launch_bounds__(kThreads) void shift_round_uniform_kernel(const ShiftArgs a) {
     fetch_now(a);
     uint32_t tile;
@@ -384,7 +382,7 @@ __global__ __launch_bounds__(kThreads) void shift_round_uniform_kernel(const Shi
     if (rj < shift) srcR += a.pj * a.inner;
     const uint64_t src = block_address(en->src, srcR, en->src_stride);
     const uint64_t dst = block_address(en->dst, R, en->dst_stride);
-    move_unit<vec16_t, NTL>(dst, src, (uint64_t)(ch0 + (threadIdx.x & 63u)) * sizeof(vec16_t));
+    move_unit<vec16_t, POLICY>(dst, src, (uint64_t)(ch0 + (threadIdx.x & 63u)) * sizeof(vec16_t));
 }
 
 // Allgather rounds the other way round: the trie sends one copy on to several children, and the kernel above
@@ -471,7 +469,7 @@ __device__ __forceinline__ void last_coordinates(uint32_t R, const VectorArgs &a
 // coordinates are worked out while the table's load is in flight.  Fused s-exchange, before and after: 64^3,
 // 26 neighbours, 128-byte blocks 342 -> 294 us all-to-all, 188 -> 166 us allgather (fill rate: 128 us);
 // 200-byte allgather on 60 x 50 x 41 142 -> 130 us; 7-byte blocks on 50^3 26 -> 22 us.
-template <typename V, int D, bool LDS, bool NTL, bool TAIL>
+template <typename V, int D, bool LDS, int POLICY, bool TAIL>
 __global__ __launch_bounds__(kThreads) void vector_round_kernel(const VectorArgs a) {
     fetch_now<D>(a);
     __shared__ DevEntry lds[LDS ? kLdsEntries : 1];
@@ -490,7 +488,7 @@ __global__ __launch_bounds__(kThreads) void vector_round_kernel(const VectorArgs
         if (u >= a.total) return;
         const DevEntry en = LDS ? lds[e] : a.entries[e];
         const uint32_t srcR = vector_source_rank(R, a.offsets + (size_t)en.shift * a.d, a.d, a.d_dims, a.inner);
-        move_unit<V, NTL>(block_address(en.dst, R, en.dst_stride), block_address(en.src, srcR, en.src_stride), off);
+        move_unit<V, POLICY>(block_address(en.dst, R, en.dst_stride), block_address(en.src, srcR, en.src_stride), off);
     } else {
         uint32_t r[D];
         last_coordinates<D>(R, a, r);
@@ -501,14 +499,14 @@ __global__ __launch_bounds__(kThreads) void vector_round_kernel(const VectorArgs
 #pragma unroll
         for (int j = 0; j < D; ++j)
             if (r[j] < en.c[j]) srcR += a.wrap[j];
-        move_unit<V, NTL>(block_address(en.dst, R, a.dst_stride), block_address(en.src, srcR, a.src_stride), off);
+        move_unit<V, POLICY>(block_address(en.dst, R, a.dst_stride), block_address(en.src, srcR, a.src_stride), off);
     }
 }
 
 // The same for blocks that are a multiple of 1 KiB: one block per wavefront, so that rank, entry and source
 // rank are worked out once, in scalar registers (see shift_round_uniform_kernel).  Fused all-to-all, before and
 // after: 256^2, 12 neighbours, 1 KiB 298 -> 259 us, 8^5, 40 neighbours, 4 KiB 2070 -> 1800 us.
-template <int D, bool NTL>
+template <int D, int POLICY>
 __global__ __launch_bounds__(kThreads) void vector_round_uniform_kernel(const VectorArgs a) {
     fetch_now<D>(a);
     uint32_t tile;
@@ -528,7 +526,7 @@ __global__ __launch_bounds__(kThreads) void vector_round_uniform_kernel(const Ve
 #pragma unroll
     for (int j = 0; j < D; ++j)
         if (r[j] < en->c[j]) srcR += a.wrap[j];
-    move_unit<vec16_t, NTL>(block_address(en->dst, R, a.dst_stride), block_address(en->src, srcR, a.src_stride),
+    move_unit<vec16_t, POLICY>(block_address(en->dst, R, a.dst_stride), block_address(en->src, srcR, a.src_stride),
                             (uint64_t)(ch0 + (threadIdx.x & 63u)) * sizeof(vec16_t));
 }
 
@@ -718,7 +716,7 @@ __device__ __forceinline__ void fetch_now(const BlockArgs &a) {
     fetch_now(a.d_group_row);
 }
 
-template <bool LDS, bool MESH, bool NTL, bool GROUPS = false>
+template <bool LDS, bool MESH, int POLICY, bool GROUPS = false>
 __global__ __launch_bounds__(kThreads) void block_round_kernel(const BlockArgs a) {
     if constexpr (!MESH) fetch_now(a);
     __shared__ DevEntry lds[LDS ? kLdsEntries : 1];
@@ -793,11 +791,11 @@ __global__ __launch_bounds__(kThreads) void block_round_kernel(const BlockArgs a
     const uint64_t src = block_address(en.src, srcR, en.src_stride);
     const uint64_t dst = block_address(en.dst, R, en.dst_stride);
     switch (en.meta & 0xFFu) {
-        case 4: move_unit<vec16_t, NTL>(dst, src, unit_offset<vec16_t>(ch, en.last_offset)); break;
-        case 3: move_unit<vec8_t, false>(dst, src, unit_offset<vec8_t>(ch, en.last_offset)); break;
-        case 2: move_unit<uint32_t, false>(dst, src, unit_offset<uint32_t>(ch, en.last_offset)); break;
-        case 1: move_unit<uint16_t, false>(dst, src, unit_offset<uint16_t>(ch, en.last_offset)); break;
-        default: move_unit<uint8_t, false>(dst, src, ch); break;
+        case 4: move_unit<vec16_t, POLICY>(dst, src, unit_offset<vec16_t>(ch, en.last_offset)); break;
+        case 3: move_unit<vec8_t, 0>(dst, src, unit_offset<vec8_t>(ch, en.last_offset)); break;
+        case 2: move_unit<uint32_t, 0>(dst, src, unit_offset<uint32_t>(ch, en.last_offset)); break;
+        case 1: move_unit<uint16_t, 0>(dst, src, unit_offset<uint16_t>(ch, en.last_offset)); break;
+        default: move_unit<uint8_t, 0>(dst, src, ch); break;
     }
 }
 
@@ -828,7 +826,7 @@ struct MeshArgs {
     uint64_t last_offset;
 };
 
-template <typename V, bool LDS, bool NTL, bool TAIL>
+template <typename V, bool LDS, int POLICY, bool TAIL>
 __global__ __launch_bounds__(kThreads) void mesh_shift_round_kernel(const MeshArgs a) {
     __shared__ DevEntry lds[LDS ? kLdsEntries : 1];
     uint32_t tile;
@@ -857,7 +855,7 @@ __global__ __launch_bounds__(kThreads) void mesh_shift_round_kernel(const MeshAr
     } else if (!mesh_source_rank(a, en, R, srcR)) {
         return;                                           // no source: leave the destination as it is
     }
-    move_unit<V, NTL>(block_address(en.dst, R, en.dst_stride), block_address(en.src, srcR, en.src_stride),
+    move_unit<V, POLICY>(block_address(en.dst, R, en.dst_stride), block_address(en.src, srcR, en.src_stride),
                       unit_offset_if<V, TAIL>(ch, a.last_offset));
 }
 

@@ -96,3 +96,39 @@ def test_allgather_forms_follow_where_the_reads_are_found(dims, s, m, layout):
     ((2, 3, 1, 29, 211), gen.von_neumann(5, 1), 192, iso.ISO_LAYOUT_RANK_MAJOR)])   # sides of 1, 2 and 3: both ways alias
 def test_allgather_rounds_that_read_a_block_once_for_all_its_children(dims, offsets, m, layout, alg):
     check_exchange(dims, [tuple(c) for c in offsets], iso.ISO_OP_ALLGATHER, alg, m, layout, recv_off=64)
+
+
+@pytest.mark.parametrize("alg", [iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_STAGED])
+@pytest.mark.parametrize("op", [iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER])
+@pytest.mark.parametrize("dims,offsets,m,layout", [
+    ((24, 25, 23), gen.moore(3, 1), 450, iso.ISO_LAYOUT_RANK_MAJOR),     # 161 MB: between half the last-level cache and all
+    ((24, 25, 23), gen.moore(3, 1), 450, iso.ISO_LAYOUT_SLOT_MAJOR),
+    ((24, 25, 23), gen.moore(3, 1), 1001, iso.ISO_LAYOUT_RANK_MAJOR),    # 359 MB: beyond it
+    ((24, 25, 23), gen.moore(3, 1), 1024, iso.ISO_LAYOUT_SLOT_MAJOR),
+    ((61, 70), gen.moore(2, 2), 3000, iso.ISO_LAYOUT_RANK_MAJOR),        # ranks in groups
+    ((7, 6, 41), gen.random_distinct(3, -3, 3, 140, 2), 1300, iso.ISO_LAYOUT_RANK_MAJOR)])   # tables beyond LDS
+def test_rounds_by_what_the_last_level_cache_holds(dims, offsets, m, layout, op, alg):
+    check_exchange(dims, [tuple(c) for c in offsets], op, alg, m, layout, recv_off=3)
+
+
+@pytest.mark.parametrize("op", [iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER])
+@pytest.mark.parametrize("m", [400, 1000])
+def test_mesh_rounds_by_what_the_last_level_cache_holds(m, op):
+    dims, periodic, offsets = (25, 24, 26), (False, True, False), gen.moore(3, 1)
+    p, s, a2a = int(np.prod(dims)), len(offsets), op == iso.ISO_OP_ALLTOALL
+    comm = iso.iso_neighborhood_create_mesh(dims, periodic, np.asarray(offsets, np.int32))
+    send = torch.randint(0, 256, (p, s if a2a else 1, m), dtype=torch.uint8, device=DEV)
+    recv = torch.full((p, s, m), 0xEE, dtype=torch.uint8, device=DEV)
+    work = torch.empty(max(1, iso.iso_workspace_bytes(comm, op, iso.ISO_ALG_COMBINED, m)), dtype=torch.uint8, device=DEV)
+    init = iso.iso_neighbor_alltoall_init if a2a else iso.iso_neighbor_allgather_init
+    req = init(send, recv, m, work, comm, iso.ISO_ALG_COMBINED)
+    iso.iso_start(req)
+    iso.iso_wait(req)
+    iso.iso_request_free(req)
+    src, valid = orc.source_ranks_mesh(dims, periodic, offsets)
+    for i in range(s):
+        v = torch.from_numpy(np.ascontiguousarray(valid[:, i])).to(DEV)
+        at = torch.from_numpy(np.where(valid[:, i], src[:, i], 0).astype(np.int64)).to(DEV)
+        want = send[:, i if a2a else 0].index_select(0, at)
+        want[~v] = 0xEE
+        assert torch.equal(recv[:, i], want), (m, i)
