@@ -33,7 +33,7 @@ constexpr uint32_t kMaxUnits = 0xFFF00000u;   // flat 32-bit work index per laun
         }                                              \
     } while (0)
 
-enum LaunchKernel { kShiftKernel = 0, kVectorKernel = 1, kBlockKernel = 2, kMeshShiftKernel = 3, kDeliverKernel = 4, kStagedRoundKernel = 5 };
+enum LaunchKernel { kShiftKernel = 0, kVectorKernel = 1, kBlockKernel = 2, kMeshShiftKernel = 3, kDeliverKernel = 4, kStagedRoundKernel = 5, kChainKernel = 6 };
 
 struct Launch {
     int kernel;            // LaunchKernel
@@ -56,6 +56,8 @@ struct Launch {
     DeliverArgs deliver;
     StagedRoundArgs staged;
     uint32_t tile_units;   // the staged schedule's kernels: kTileUnits or kSmallTileUnits
+    ChainArgs chain;
+    uint32_t threads;      // per workgroup, where not kThreads (chain kernel)
 };
 
 // Sizes and displacements (bytes) of the s blocks inside one rank's send and
@@ -254,6 +256,7 @@ KernelRef select_vector(const Launch &l) {
 
 template <typename V, bool LDS, bool TAIL>
 KernelRef select_regular(const Launch &l) {
+    if (l.kernel == kChainKernel) return {(const void *)&chain_kernel<V, TAIL>, &l.chain};
     if (l.kernel == kVectorKernel) {
         if constexpr (LDS) {
             if (l.vector_dims == 3) return select_vector<V, 3, TAIL>(l);
@@ -333,7 +336,7 @@ inline KernelRef select_kernel(int vector_bytes, const Launch &l) {
 inline int enqueue(int vector_bytes, const Launch &l, hipStream_t stream) {
     const KernelRef k = select_kernel(vector_bytes, l);
     void *args[1] = {const_cast<void *>(k.arg)};
-    ISO_HIP_TRY(hipLaunchKernel(k.func, dim3(l.grid), dim3(kThreads), args, l.dyn_lds, stream));
+    ISO_HIP_TRY(hipLaunchKernel(k.func, dim3(l.grid), dim3(l.threads ? l.threads : kThreads), args, l.dyn_lds, stream));
     return ISO_SUCCESS;
 }
 
@@ -380,7 +383,7 @@ inline int store_table(const StaticArena &arena, size_t at, const void *host, si
 struct HostEntry {
     DevEntry de;
     uint64_t size;
-    int dim, dst_slot;
+    int dim, dst_slot, neighbor;
 };
 
 // Mesh shift launches of equal blocks: one bit per tile of kThreads units, set where every rank of the tile has
@@ -464,15 +467,18 @@ public:
         int st = describe_and_check();
         if (st != ISO_SUCCESS || inf.delivered_bytes == 0) return st;       // nothing to move: no launches
         rounds_as_launched();
-        if (pl.algorithm == ISO_ALG_COMBINED) {
-            if (!arena && (st = bind_rounds()) != ISO_SUCCESS) return st;
+        const bool merges = pl.algorithm == ISO_ALG_COMBINED;
+        const bool chains = merges || pl.algorithm == ISO_ALG_COMBINED_BYDIM || pl.algorithm == ISO_ALG_COMBINED_STAGED;
+        if (arena && chains && (st = host_entries()) == ISO_SUCCESS && chain_launch()) return upload();
+        if (!arena || !merges) {
+            if ((st = bind_rounds()) != ISO_SUCCESS) return st;
             n_listed = pending.size();
+        }
+        if (!arena && chains && chain_launch()) return upload();
+        if (merges) {
             const size_t n_rounds = bound_rounds.size();
             merge_rounds();
             if ((arena || bound_rounds.size() < n_rounds) && (st = bind_rounds()) != ISO_SUCCESS) return st;
-        } else {
-            if ((st = bind_rounds()) != ISO_SUCCESS) return st;
-            n_listed = pending.size();
         }
         return upload();
     }
@@ -512,6 +518,75 @@ private:
             for (size_t done = 0; done < rounds[ri].size();)
                 if ((st = next_launch(ri, done)) != ISO_SUCCESS) return st;
         return ISO_SUCCESS;
+    }
+
+    // iso_start of a small all-to-all: all rounds in one launch (see chain_kernel), if its hops fit the arguments
+    // and a workgroup the ranks.  Against a launch per dimension: 8 x 8, 32 B 10.2 -> 7.8 us, 8^3, 26 neighbours, 64 B
+    // 13.5 -> 7.4 (allocation-free call 31 -> 17), 12^3, 16 B 13.1 -> 7.1, 5^4 star, 300 B 17.2 -> 7.3.  A workgroup's
+    // accesses are a column of units per rank, at best a few sectors each: the limits are 6144 sectors for one
+    // workgroup over all its hops (60^2, 64 B: 7200, 10.1 -> 12.7; 16^3, 16 B: 12288, 13.3 -> 16.4) and 128 Ki for
+    // one hop of all of them (10^3, 100 B: 52 Ki, 13.4 -> 12.2; 500 B: 208 Ki, 17 -> 28).
+    bool chain_launch() {
+        if (op != ISO_OP_ALLTOALL || c.mesh || !uniform || !size0 || p > kChainThreads * kChainUnitsPerLane ||
+            c.d > (int)kChainDims || (size0 >> min_log2) > 0xFFFF)
+            return false;
+        std::vector<std::vector<std::pair<const HostEntry *, int>>> chains(s);
+        size_t n_hops = 0;
+        for (size_t ri = 0; ri < rounds.size(); ++ri)
+            for (const HostEntry &he : rounds[ri]) {
+                if (he.neighbor < 0) return false;
+                chains[(size_t)he.neighbor].push_back({&he, he.dim});
+                ++n_hops;
+            }
+        if (!n_hops || n_hops > kChainHops) return false;
+        Pending pd{};
+        std::memset(&pd.l, 0, sizeof(pd.l));
+        Launch &l = pd.l;
+        l.kernel = kChainKernel;
+        l.lds_table = true;
+        ChainArgs &ca = l.chain;
+        const uint64_t width = uint64_t(1) << min_log2;
+        l.tail = (size0 & (width - 1)) != 0;
+        ca.last_offset = size0 - width;
+        ca.chunks = (uint32_t)((size0 + width - 1) >> min_log2);
+        ca.column = std::min<uint32_t>(ca.chunks, kChainThreads * kChainUnitsPerLane / (uint32_t)p);
+        // A last unit that overlaps the one before it goes into the same column: two workgroups are not at the
+        // same hop, and one would read bytes that the other has already replaced.
+        while (l.tail && ca.column > 1 && ca.column < ca.chunks && (ca.chunks - 1) % ca.column == 0) --ca.column;
+        if (l.tail && ca.chunks > 1 && ca.column == 1) return false;
+        ca.groups = (ca.chunks + ca.column - 1) / ca.column;
+        ca.n_units = (uint32_t)p * ca.column;
+        ca.d_column = make_fastdiv(ca.column);
+        ca.d_groups = make_fastdiv(ca.groups);
+        for (int j = 0; j < c.d; ++j) {
+            ca.d_inner[j] = make_fastdiv((uint32_t)c.inner[(size_t)j]);
+            ca.d_pj[j] = make_fastdiv((uint32_t)c.dims[(size_t)j]);
+        }
+        uint32_t at = 0, n_chains = 0, longest = 0;
+        for (const auto &chain : chains) {
+            if (chain.empty()) continue;
+            longest = std::max(longest, (uint32_t)chain.size());
+            ca.first[n_chains++] = (uint8_t)at;
+            for (const auto &[he, dim] : chain) {
+                ChainHop &hop = ca.hops[at++];
+                hop.src = he->de.src;
+                hop.dst = he->de.dst;
+                hop.src_stride = he->de.src_stride;
+                hop.dst_stride = he->de.dst_stride;
+                if (dim < 0) continue;                            // same-rank copy: shift 0
+                hop.dim = (uint32_t)dim;
+                hop.shift = he->de.shift;
+                hop.back = hop.shift * (uint32_t)c.inner[(size_t)dim];
+                hop.wrap = (uint32_t)c.dims[(size_t)dim] * (uint32_t)c.inner[(size_t)dim];
+            }
+        }
+        ca.first[n_chains] = (uint8_t)at;
+        l.grid = n_chains * ca.groups;
+        const uint64_t sectors = p * ((ca.column * width + 63) / 64);
+        if (sectors * longest > 6144 || sectors * l.grid > 128 * 1024) return false;
+        l.threads = std::min<uint32_t>(kChainThreads, (ca.n_units + 63) & ~63u);
+        pending.push_back(pd);
+        return true;
     }
 
     // iso_start of ISO_ALG_COMBINED: the consecutive rounds of one dimension, which touch disjoint blocks, in one
@@ -654,6 +729,8 @@ private:
                 he.size = entry_size(pe);
                 he.dim = pe.dim;
                 he.dst_slot = pe.dst_slot;
+                he.neighbor = pe.neighbor;
+                if (he.dim < 0 && r.kind == ISO_ROUND_SHIFT) he.dim = r.dim;
                 if (he.size == 0) continue;                       // empty blocks make no move
                 uint64_t src_stride = 0, dst_stride = 0;
                 place(pe.src_buf, pe.src_slot, he.de.src, src_stride);
@@ -744,7 +821,9 @@ private:
     // whole collective (the receive buffer's size) stay in the last-level cache from one round to the next.
     //   All-to-all rounds read every block once: streaming loads and stores where they do not.  Up to half that
     //   cache neither (26 neighbours, one launch per dimension: 24^3, 256 B 73 -> 60 us, 20^3, 64 B 21 -> 17,
-    //   64^3, 16 B 239 -> 154, 8^5, 100 B 440 -> 285; at 146 MB 112 -> 122).  A little above it, blocks that do
+    //   64^3, 16 B 239 -> 154, 8^5, 100 B 440 -> 285; at 146 MB 112 -> 122), the plain stores only up to three
+    //   eighths where sectors are written whole (box 45 x 37 x 29, slot-major, 126 MB: 120 us, plain stores 113,
+    //   streaming stores 107).  A little above it, blocks that do
     //   not fill whole 64-byte sectors of rank-major rows still gain from plain stores, which let neighbouring
     //   blocks meet in the cache before a sector is written (32^3, 200 B 214 -> 153 us, 64^3, 40 B 560 -> 409;
     //   426 MB 402 -> 471, whole sectors 160 -> 168, 1000-byte blocks, which have few of them, 152 -> 161).
@@ -767,9 +846,10 @@ private:
         if (r.kind == ISO_ROUND_VECTOR) return 0;
         if (l.kernel == kBlockKernel) return bytes <= kLastLevelCacheBytes / 4 ? kPlainStores : 0;
         if (!a2a) return bytes <= kLastLevelCacheBytes ? kPlainStores : 0;
+        if (size0 % 64 == 0 || lay.slot_major)
+            return bytes <= kLastLevelCacheBytes * 3 / 8 ? kPlainStores : bytes <= kLastLevelCacheBytes * 5 / 8 ? 0 : kStreamLoads;
         if (bytes <= kLastLevelCacheBytes / 2) return kPlainStores;
-        const bool part_sectors = size0 % 64 && size0 < 512 && !lay.slot_major;
-        return part_sectors && bytes <= above ? kStreamLoads | kPlainStores : kStreamLoads;
+        return size0 < 512 && bytes <= above ? kStreamLoads | kPlainStores : kStreamLoads;
     }
 
     // Staged schedule, last launch: every rank's receive row written in one piece.
@@ -1124,7 +1204,9 @@ private:
         const uint32_t *dev_offsets = (const uint32_t *)(dev + entry_bytes);
         const uint32_t *dev_prefix = (const uint32_t *)(dev + entry_bytes + off_bytes);
         for (Pending &pd : pending) {
-            if (pd.l.kernel == kVectorKernel) {
+            if (pd.l.kernel == kChainKernel) {
+                // its hops are among its arguments
+            } else if (pd.l.kernel == kVectorKernel) {
                 pd.l.vec.entries = dev_entries + pd.first_entry;
                 pd.l.vec.offsets = dev_offsets;
             } else if (pd.l.kernel == kMeshShiftKernel) {

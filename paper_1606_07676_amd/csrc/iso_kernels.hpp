@@ -1062,6 +1062,69 @@ __global__ __launch_bounds__(kThreads) void deliver_kernel(const DeliverArgs a) 
     }
 }
 
+// ---- small all-to-alls in one launch ------------------------------------------------------------
+// Block i of an all-to-all only ever moves between its own places (send slot, workspace slots, receive slot),
+// and so does every column of its units: a workgroup takes one block's column of all p ranks through all its
+// hops, one hop after the other with a barrier between, through the same buffers as the rounds.  What bounds
+// these collectives is the cost of a launch per dimension.  The hops travel in the kernel's arguments, so the
+// launch needs no table in device memory (8 x 8 x 8, 26 neighbours, 64 B, allocation-free call: the table took
+// launches of its own).
+constexpr uint32_t kChainThreads = 1024, kChainUnitsPerLane = 4;
+constexpr uint32_t kChainHops = 72, kChainDims = 8;
+struct ChainHop {
+    uint64_t src, dst;                 // addresses of rank 0's blocks
+    uint32_t src_stride, dst_stride;
+    uint32_t shift, back, wrap;        // residue v along the hop's dimension; v * inner_j; p_j * inner_j
+    uint32_t dim;
+};
+struct ChainArgs {
+    uint32_t n_units;                  // p * column
+    uint32_t chunks, column, groups;   // units of a block, of a workgroup's column; columns of a block
+    FastDiv d_column, d_groups;
+    uint64_t last_offset;
+    FastDiv d_inner[kChainDims], d_pj[kChainDims];
+    ChainHop hops[kChainHops];         // chain after chain
+    uint8_t first[kChainHops + 4];     // first hop of every chain
+};
+static_assert(sizeof(ChainArgs) <= 4096, "kernel arguments");
+
+template <typename V, bool TAIL>
+__global__ __launch_bounds__(kChainThreads) void chain_kernel(const ChainArgs a) {
+    typedef typename Unaligned<V>::type UV;
+    typedef const UV __attribute__((address_space(1))) *src_ptr;
+    typedef UV __attribute__((address_space(1))) *dst_ptr;
+    uint32_t chain, group;
+    fast_divmod(blockIdx.x, a.d_groups, chain, group);
+    const uint32_t n_threads = blockDim.x;
+    const uint32_t h1 = a.first[chain + 1];
+    for (uint32_t h = a.first[chain]; h < h1; ++h) {
+        const ChainHop hop = a.hops[h];
+        const FastDiv d_inner = a.d_inner[hop.dim], d_pj = a.d_pj[hop.dim];
+        V v[kChainUnitsPerLane];
+        uint64_t to[kChainUnitsPerLane];
+#pragma unroll
+        for (uint32_t it = 0; it < kChainUnitsPerLane; ++it) {
+            const uint32_t u = threadIdx.x + it * n_threads;
+            uint32_t R, c;
+            fast_divmod(u, a.d_column, R, c);
+            const uint32_t ch = group * a.column + c;
+            to[it] = 0;
+            if (u < a.n_units && ch < a.chunks) {
+                const uint32_t q = fast_div(R, d_inner);
+                const uint32_t rj = q - fast_div(q, d_pj) * d_pj.div;
+                const uint32_t srcR = R - hop.back + (rj < hop.shift ? hop.wrap : 0u);
+                const uint64_t off = unit_offset_if<V, TAIL>(ch, a.last_offset);
+                v[it] = *(src_ptr)(block_address(hop.src, srcR, hop.src_stride) + off);
+                to[it] = block_address(hop.dst, R, hop.dst_stride) + off;
+            }
+        }
+#pragma unroll
+        for (uint32_t it = 0; it < kChainUnitsPerLane; ++it)
+            if (to[it]) *(dst_ptr)to[it] = v[it];
+        __syncthreads();                                 // the next hop reads what other wavefronts wrote
+    }
+}
+
 // Plain streaming copy with the same access shape: the measured ceiling.
 template <typename V>
 __global__ __launch_bounds__(kThreads) void copy_kernel(const V *__restrict__ src, V *__restrict__ dst,

@@ -132,3 +132,20 @@ def test_mesh_rounds_by_what_the_last_level_cache_holds(m, op):
         want = send[:, i if a2a else 0].index_select(0, at)
         want[~v] = 0xEE
         assert torch.equal(recv[:, i], want), (m, i)
+
+
+CHAINS = [((8, 8), gen.moore(2, 1), (1, 7, 32, 64, 1000, 8192, 8200)), ((8, 8, 8), gen.moore(3, 1), (2, 16, 40, 64, 144)),
+          ((2048,), [(1,), (-5,), (0,), (2047,)], (16, 20, 36, 64)), ((64, 64), [(0, 1), (-1, 0), (0, 0)], (16, 33, 48)),
+          ((45, 91), [(1, 1), (3, -2)], (16, 17, 8)), ((3, 1, 2, 5, 2, 3, 2, 2), gen.von_neumann(8, 1), (12, 100, 112)),
+          ((4, 3), [(1, 1), (1, 1), (0, 0), (0, 0), (5, -7), (2, 0)], (5, 16, 100000)),
+          ((17, 19), gen.random_distinct(2, -3, 3, 36, 6), (64, 100, 208)),       # 72 hops and fewer
+          ((7, 3, 15, 7), gen.random_distinct(4, -2, 2, 1, 3), (4100,))]          # a column of one unit: not where it overlaps
+
+
+@pytest.mark.parametrize("alg", [iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM, iso.ISO_ALG_COMBINED_STAGED])
+@pytest.mark.parametrize("layout", [iso.ISO_LAYOUT_RANK_MAJOR, iso.ISO_LAYOUT_SLOT_MAJOR])
+@pytest.mark.parametrize("case", range(len(CHAINS)))
+def test_small_alltoall_in_one_launch(case, layout, alg):
+    dims, offsets, sizes = CHAINS[case]
+    for m in sizes:
+        check_exchange(dims, [tuple(c) for c in offsets], iso.ISO_OP_ALLTOALL, alg, m, layout, send_off=1, recv_off=5)
