@@ -304,22 +304,16 @@ KernelRef select_block(const Launch &l) {
 }
 
 inline KernelRef select_kernel(int vector_bytes, const Launch &l) {
-    if (l.kernel == kStagedRoundKernel) {                 // blocks of whole 16-byte units only
-        if (l.tile_units == kSmallTileUnits) {
-            if (l.policy & kStreamLoads) return {(const void *)&staged_round_kernel<vec16_t, true, kSmallTileUnits / kThreads>, &l.staged};
-            return {(const void *)&staged_round_kernel<vec16_t, false, kSmallTileUnits / kThreads>, &l.staged};
-        }
-        if (l.policy & kStreamLoads) return {(const void *)&staged_round_kernel<vec16_t, true, kTileUnits / kThreads>, &l.staged};
-        return {(const void *)&staged_round_kernel<vec16_t, false, kTileUnits / kThreads>, &l.staged};
-    }
-    if (l.kernel == kDeliverKernel) {
-        if (l.tile_units == kSmallTileUnits) {
-            if (l.policy & kStreamLoads) return {(const void *)&deliver_kernel<vec16_t, true, kSmallTileUnits / kThreads>, &l.deliver};
-            return {(const void *)&deliver_kernel<vec16_t, false, kSmallTileUnits / kThreads>, &l.deliver};
-        }
-        if (l.policy & kStreamLoads) return {(const void *)&deliver_kernel<vec16_t, true, kTileUnits / kThreads>, &l.deliver};
-        return {(const void *)&deliver_kernel<vec16_t, false, kTileUnits / kThreads>, &l.deliver};
-    }
+    if (l.kernel == kStagedRoundKernel || l.kernel == kDeliverKernel)       // blocks of whole 16-byte units only
+        return with_policy<vec16_t>(l, [&](auto pol) -> KernelRef {
+            constexpr uint32_t kSmall = kSmallTileUnits / kThreads, kLarge = kTileUnits / kThreads;
+            const bool small = l.tile_units == kSmallTileUnits;
+            if (l.kernel == kDeliverKernel)
+                return small ? KernelRef{(const void *)&deliver_kernel<vec16_t, pol(), kSmall>, &l.deliver}
+                             : KernelRef{(const void *)&deliver_kernel<vec16_t, pol(), kLarge>, &l.deliver};
+            return small ? KernelRef{(const void *)&staged_round_kernel<vec16_t, pol(), kSmall>, &l.staged}
+                         : KernelRef{(const void *)&staged_round_kernel<vec16_t, pol(), kLarge>, &l.staged};
+        });
     if (l.kernel == kBlockKernel) {
         if (l.mesh) return l.lds_table ? select_block<true, true>(l) : select_block<false, true>(l);
         return l.lds_table ? select_block<true, false>(l) : select_block<false, false>(l);
@@ -829,6 +823,10 @@ private:
     //   426 MB 402 -> 471, whole sectors 160 -> 168, 1000-byte blocks, which have few of them, 152 -> 161).
     //   Allgather rounds may read a block several times: cached loads; plain stores while all of it fits
     //   (64^3, 36 B 148 -> 139 us, box 40^3, 100 B 86 -> 69; 640 MB 239 -> 324).
+    //   The staged schedule's kernels: what a round writes the last launch finds in the cache up to half of it, and
+    //   the rows that one writes are not read again (64^3, 16 B 116 -> 97 us, 8^5, 64 B 144 -> 116, 300^2, 48 B 77 ->
+    //   66); up to 7/4 of it the rounds still gain from cached loads (64^3, 32 B 197 -> 177, 64 B 353 -> 335; 872 MB
+    //   622 -> 634).  Allgather: 64^3, 32 B 87.5 -> 84, 32^3, 64 B 31 -> 28.6.
     //   Unequal blocks: cached loads, plain stores up to a quarter (4-byte stencil on 64^3 126 -> 119 us; at
     //   133 MB 73 -> 93; streaming loads 20 % slower wherever the blocks fit the cache).
     //   The s-exchange writes whole rows and is indifferent to the stores; streaming loads where the send buffer
@@ -838,7 +836,14 @@ private:
         const uint64_t bytes = inf.delivered_bytes;
         const uint64_t above = kLastLevelCacheBytes * 9 / 8;      // what still gains from the cache
         const bool a2a = op == ISO_OP_ALLTOALL;
-        if (l.kernel == kStagedRoundKernel || l.kernel == kDeliverKernel) return a2a ? kStreamLoads : 0;
+        if (l.kernel == kStagedRoundKernel) {
+            if (!a2a) return 0;
+            return bytes <= kLastLevelCacheBytes / 2 ? kPlainStores : bytes <= kLastLevelCacheBytes * 7 / 4 ? 0 : kStreamLoads;
+        }
+        if (l.kernel == kDeliverKernel) {
+            if (!a2a) return bytes <= kLastLevelCacheBytes ? kPlainStores : 0;
+            return bytes <= kLastLevelCacheBytes / 2 ? 0 : kStreamLoads;
+        }
         if (l.kernel == kVectorKernel) {
             const bool lines = size0 % 128 == 0 || lay.slot_major;
             return a2a && l.vector_dims && lines && bytes > above ? kStreamLoads : 0;

@@ -895,7 +895,7 @@ __device__ __forceinline__ void fetch_now(const StagedRoundArgs &a) {
     fetch_now(a.d_pj);
 }
 
-template <typename V, bool NTL, uint32_t UPL>
+template <typename V, int POLICY, uint32_t UPL>
 __global__ __launch_bounds__(kThreads) void staged_round_kernel(const StagedRoundArgs a) {
     fetch_now(a);
     __shared__ DevEntry lds[kLdsEntries];
@@ -933,7 +933,7 @@ __global__ __launch_bounds__(kThreads) void staged_round_kernel(const StagedRoun
         c = has_unit ? c : 0u;
         const DevEntry en = table[e];
         const src_ptr sp = (src_ptr)(block_address(en.src, R0 + r, en.src_stride) + (uint64_t)c * sizeof(V));
-        if constexpr (NTL && sizeof(V) == 16) regs[it] = __builtin_nontemporal_load(sp);
+        if constexpr ((POLICY & kStreamLoads) && sizeof(V) == 16) regs[it] = __builtin_nontemporal_load(sp);
         else regs[it] = *sp;
         at[it] = has_unit ? e * pitch + r * a.upb + c : ~0u;
     }
@@ -956,7 +956,7 @@ __global__ __launch_bounds__(kThreads) void staged_round_kernel(const StagedRoun
             uint32_t R = S + en.shift * a.inner;
             R -= sj + en.shift >= a.pj ? a.pj * a.inner : 0u;
             const dst_ptr dp = (dst_ptr)(block_address(en.dst, R, en.dst_stride) + (uint64_t)c * sizeof(V));
-            if constexpr (sizeof(V) == 16) __builtin_nontemporal_store(tile[e * pitch + rem], dp);
+            if constexpr (sizeof(V) == 16 && !(POLICY & kPlainStores)) __builtin_nontemporal_store(tile[e * pitch + rem], dp);
             else *dp = tile[e * pitch + rem];
         }
     }
@@ -997,7 +997,7 @@ __device__ __forceinline__ void fetch_now(const DeliverArgs &a) {
     fetch_now(a.d_row);
 }
 
-template <typename V, bool NTL, uint32_t UPL>
+template <typename V, int POLICY, uint32_t UPL>
 __global__ __launch_bounds__(kThreads) void deliver_kernel(const DeliverArgs a) {
     fetch_now(a);
     __shared__ DeliverEntry lds[kLdsEntries];
@@ -1039,7 +1039,7 @@ __global__ __launch_bounds__(kThreads) void deliver_kernel(const DeliverArgs a) 
         const uint32_t rj = qq - fast_div(qq, en.d_pj) * en.pj;
         const uint32_t srcR = R - en.back + (rj < en.shift ? en.wrap : 0u);
         const src_ptr sp = (src_ptr)(block_address(en.src, srcR, en.src_stride) + (uint64_t)c * sizeof(V));
-        if constexpr (NTL && sizeof(V) == 16) regs[it] = __builtin_nontemporal_load(sp);
+        if constexpr ((POLICY & kStreamLoads) && sizeof(V) == 16) regs[it] = __builtin_nontemporal_load(sp);
         else regs[it] = *sp;
         at[it] = has_unit ? en.slot * pitch + r * a.upb + c : ~0u;
     }
@@ -1056,7 +1056,7 @@ __global__ __launch_bounds__(kThreads) void deliver_kernel(const DeliverArgs a) 
         fast_divmod(rem, a.d_upb, i, c);
         if (r < n) {
             const dst_ptr dp = (dst_ptr)(out + (uint64_t)q * sizeof(V));
-            if constexpr (sizeof(V) == 16) __builtin_nontemporal_store(tile[i * pitch + r * a.upb + c], dp);
+            if constexpr (sizeof(V) == 16 && !(POLICY & kPlainStores)) __builtin_nontemporal_store(tile[i * pitch + r * a.upb + c], dp);
             else *dp = tile[i * pitch + r * a.upb + c];
         }
     }

@@ -149,3 +149,10 @@ def test_small_alltoall_in_one_launch(case, layout, alg):
     dims, offsets, sizes = CHAINS[case]
     for m in sizes:
         check_exchange(dims, [tuple(c) for c in offsets], iso.ISO_OP_ALLTOALL, alg, m, layout, send_off=1, recv_off=5)
+
+
+@pytest.mark.parametrize("op", [iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER])
+@pytest.mark.parametrize("dims,m", [((23, 24, 25), 48), ((51, 52, 49), 48), ((51, 52, 49), 80), ((61, 62, 63), 80)])
+def test_staged_schedule_by_what_the_last_level_cache_holds(dims, m, op):
+    """17, 162, 270 and 496 MB of blocks."""
+    check_exchange(dims, gen.moore(3, 1), op, iso.ISO_ALG_COMBINED_STAGED, m, iso.ISO_LAYOUT_RANK_MAJOR, recv_off=16)
