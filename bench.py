@@ -170,7 +170,7 @@ def median(xs):
 def kernels_per_start(iso, req, graph=False):
     """Kernels that one iso_start of `req` enqueues (workloads of bandwidth size): the request's launch list,
     except that the message-combining schedule takes the rounds of one dimension together (a graph replays
-    the list).  Small all-to-alls run in fewer."""
+    the list).  Small collectives run in fewer."""
     info = iso.iso_request_info(req)
     n = info["launches"]
     if info["algorithm"] != iso.ISO_ALG_COMBINED or graph:

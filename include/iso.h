@@ -178,7 +178,7 @@ typedef struct {
     int32_t launches;            /* length of the launch list: what iso_start_range counts
                                   * through and a graph holds.  iso_start enqueues as many
                                   * kernels, or fewer: ISO_ALG_COMBINED takes the rounds of a
-                                  * dimension together, small all-to-alls of the three combined
+                                  * dimension together, small collectives of the three combined
                                   * algorithms run all their rounds in one kernel             */
     int32_t vector_bytes;        /* width of the loads/stores: the largest power of two that is
                                   * at most 16 and at most the smallest non-empty block; buffer

@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <cstring>
 #include <initializer_list>
+#include <map>
 #include <numeric>
 #include <type_traits>
 #include <vector>
@@ -377,7 +378,7 @@ inline int store_table(const StaticArena &arena, size_t at, const void *host, si
 struct HostEntry {
     DevEntry de;
     uint64_t size;
-    int dim, dst_slot, neighbor;
+    int dim, dst_buf, dst_slot, neighbor;
 };
 
 // Mesh shift launches of equal blocks: one bit per tile of kThreads units, set where every rank of the tile has
@@ -514,24 +515,40 @@ private:
         return ISO_SUCCESS;
     }
 
-    // iso_start of a small all-to-all: all rounds in one launch (see chain_kernel), if its hops fit the arguments
+    // iso_start of a small collective: all rounds in one launch (see chain_kernel), if its hops fit the arguments
     // and a workgroup the ranks.  Against a launch per dimension: 8 x 8, 32 B 10.2 -> 7.8 us, 8^3, 26 neighbours, 64 B
     // 13.5 -> 7.4 (allocation-free call 31 -> 17), 12^3, 16 B 13.1 -> 7.1, 5^4 star, 300 B 17.2 -> 7.3.  A workgroup's
     // accesses are a column of units per rank, at best a few sectors each: the limits are 6144 sectors for one
-    // workgroup over all its hops (60^2, 64 B: 7200, 10.1 -> 12.7; 16^3, 16 B: 12288, 13.3 -> 16.4) and 128 Ki for
-    // one hop of all of them (10^3, 100 B: 52 Ki, 13.4 -> 12.2; 500 B: 208 Ki, 17 -> 28).
+    // workgroup over all its hops (60^2, 64 B: 7200, 10.1 -> 12.7; 16^3, 16 B: 12288, 13.3 -> 16.4) and 256 Ki for
+    // all of them (10^3, 100 B: 156 Ki, 13.4 -> 12.2; 8^3, 400 B: 318 Ki, 10.1 -> 12.2; 10^3, 500 B: 624 Ki, 17 -> 28).
+    // Allgather: 8^3, 64 B 10.4 -> 7.0 us, 16^2 radius 2 21.6 -> 6.9.
     bool chain_launch() {
-        if (op != ISO_OP_ALLTOALL || c.mesh || !uniform || !size0 || p > kChainThreads * kChainUnitsPerLane ||
+        if (c.mesh || !uniform || !size0 || p > kChainThreads * kChainUnitsPerLane ||
             c.d > (int)kChainDims || (size0 >> min_log2) > 0xFFFF)
             return false;
-        std::vector<std::vector<std::pair<const HostEntry *, int>>> chains(s);
+        std::vector<std::vector<const HostEntry *>> chains;
         size_t n_hops = 0;
-        for (size_t ri = 0; ri < rounds.size(); ++ri)
-            for (const HostEntry &he : rounds[ri]) {
-                if (he.neighbor < 0) return false;
-                chains[(size_t)he.neighbor].push_back({&he, he.dim});
-                ++n_hops;
+        if (op == ISO_OP_ALLTOALL) {
+            chains.resize(s);
+            for (const std::vector<HostEntry> &round : rounds)
+                for (const HostEntry &he : round) chains[(size_t)he.neighbor].push_back(&he);
+        } else {
+            // Allgather: the way of every receive block from the send buffer down the trie.  Ways share moves, and
+            // each makes them for itself; they write the same bytes, provided that no place is used twice.
+            std::map<uint64_t, const HostEntry *> written_by;
+            for (const std::vector<HostEntry> &round : rounds)
+                for (const HostEntry &he : round)
+                    if (!written_by.emplace(he.de.dst, &he).second) return false;
+            for (const auto &[dst, last] : written_by) {
+                if (last->dst_buf != ISO_BUF_RECV) continue;
+                std::vector<const HostEntry *> way{last};
+                for (auto at = written_by.find(last->de.src); at != written_by.end(); at = written_by.find(at->second->de.src))
+                    way.push_back(at->second);
+                std::reverse(way.begin(), way.end());
+                chains.push_back(std::move(way));
             }
+        }
+        for (const auto &chain : chains) n_hops += chain.size();
         if (!n_hops || n_hops > kChainHops) return false;
         Pending pd{};
         std::memset(&pd.l, 0, sizeof(pd.l));
@@ -561,7 +578,8 @@ private:
             if (chain.empty()) continue;
             longest = std::max(longest, (uint32_t)chain.size());
             ca.first[n_chains++] = (uint8_t)at;
-            for (const auto &[he, dim] : chain) {
+            for (const HostEntry *he : chain) {
+                const int dim = he->dim;
                 ChainHop &hop = ca.hops[at++];
                 hop.src = he->de.src;
                 hop.dst = he->de.dst;
@@ -577,7 +595,7 @@ private:
         ca.first[n_chains] = (uint8_t)at;
         l.grid = n_chains * ca.groups;
         const uint64_t sectors = p * ((ca.column * width + 63) / 64);
-        if (sectors * longest > 6144 || sectors * l.grid > 128 * 1024) return false;
+        if (sectors * longest > 6144 || sectors * l.grid * longest > 256 * 1024) return false;
         l.threads = std::min<uint32_t>(kChainThreads, (ca.n_units + 63) & ~63u);
         pending.push_back(pd);
         return true;
@@ -723,6 +741,7 @@ private:
                 he.size = entry_size(pe);
                 he.dim = pe.dim;
                 he.dst_slot = pe.dst_slot;
+                he.dst_buf = pe.dst_buf;
                 he.neighbor = pe.neighbor;
                 if (he.dim < 0 && r.kind == ISO_ROUND_SHIFT) he.dim = r.dim;
                 if (he.size == 0) continue;                       // empty blocks make no move
@@ -813,14 +832,14 @@ private:
 
     // Cache policy of a launch whose kernel and arguments are set.  What decides is whether the blocks of the
     // whole collective (the receive buffer's size) stay in the last-level cache from one round to the next.
-    //   All-to-all rounds read every block once: streaming loads and stores where they do not.  Up to half that
-    //   cache neither (26 neighbours, one launch per dimension: 24^3, 256 B 73 -> 60 us, 20^3, 64 B 21 -> 17,
-    //   64^3, 16 B 239 -> 154, 8^5, 100 B 440 -> 285; at 146 MB 112 -> 122), the plain stores only up to three
-    //   eighths where sectors are written whole (box 45 x 37 x 29, slot-major, 126 MB: 120 us, plain stores 113,
-    //   streaming stores 107).  A little above it, blocks that do
-    //   not fill whole 64-byte sectors of rank-major rows still gain from plain stores, which let neighbouring
-    //   blocks meet in the cache before a sector is written (32^3, 200 B 214 -> 153 us, 64^3, 40 B 560 -> 409;
-    //   426 MB 402 -> 471, whole sectors 160 -> 168, 1000-byte blocks, which have few of them, 152 -> 161).
+    //   All-to-all rounds read every block once: streaming loads and stores where they do not (26 neighbours, one
+    //   launch per dimension, streaming against cached loads with plain stores: 24^3, 256 B 73 -> 60 us, 20^3, 64 B
+    //   21 -> 17, 64^3, 16 B 239 -> 154, 8^5, 100 B 440 -> 285; at 146 MB 112 -> 122).  From three eighths of the
+    //   cache on streaming stores leave it to the blocks still to be read (box 45 x 37 x 29, slot-major, 126 MB: 120
+    //   us, plain stores 113, streaming ones 107; 30^3 star, 1000 B, 162 MB: 70, streaming stores 55), except for
+    //   blocks of less than 512 bytes that do not fill whole 64-byte sectors of rank-major rows: plain stores let
+    //   neighbouring blocks meet in the cache before a sector is written (32^3, 200 B 214 -> 153 us, 64^3, 40 B
+    //   560 -> 409; 426 MB 402 -> 471, whole sectors 160 -> 168).
     //   Allgather rounds may read a block several times: cached loads; plain stores while all of it fits
     //   (64^3, 36 B 148 -> 139 us, box 40^3, 100 B 86 -> 69; 640 MB 239 -> 324).
     //   The staged schedule's kernels: what a round writes the last launch finds in the cache up to half of it, and
@@ -851,10 +870,12 @@ private:
         if (r.kind == ISO_ROUND_VECTOR) return 0;
         if (l.kernel == kBlockKernel) return bytes <= kLastLevelCacheBytes / 4 ? kPlainStores : 0;
         if (!a2a) return bytes <= kLastLevelCacheBytes ? kPlainStores : 0;
-        if (size0 % 64 == 0 || lay.slot_major)
-            return bytes <= kLastLevelCacheBytes * 3 / 8 ? kPlainStores : bytes <= kLastLevelCacheBytes * 5 / 8 ? 0 : kStreamLoads;
-        if (bytes <= kLastLevelCacheBytes / 2) return kPlainStores;
-        return size0 < 512 && bytes <= above ? kStreamLoads | kPlainStores : kStreamLoads;
+        if (size0 % 64 && size0 < 512 && !lay.slot_major) {
+            if (bytes <= kLastLevelCacheBytes / 2) return kPlainStores;
+            return bytes <= above ? kStreamLoads | kPlainStores : kStreamLoads;
+        }
+        if (bytes <= kLastLevelCacheBytes * 3 / 8) return kPlainStores;
+        return bytes <= (size0 % 64 && !lay.slot_major ? above : kLastLevelCacheBytes * 5 / 8) ? 0 : kStreamLoads;
     }
 
     // Staged schedule, last launch: every rank's receive row written in one piece.

@@ -144,11 +144,12 @@ CHAINS = [((8, 8), gen.moore(2, 1), (1, 7, 32, 64, 1000, 8192, 8200)), ((8, 8, 8
 
 @pytest.mark.parametrize("alg", [iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM, iso.ISO_ALG_COMBINED_STAGED])
 @pytest.mark.parametrize("layout", [iso.ISO_LAYOUT_RANK_MAJOR, iso.ISO_LAYOUT_SLOT_MAJOR])
+@pytest.mark.parametrize("op", [iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER])
 @pytest.mark.parametrize("case", range(len(CHAINS)))
-def test_small_alltoall_in_one_launch(case, layout, alg):
+def test_small_collective_in_one_launch(case, op, layout, alg):
     dims, offsets, sizes = CHAINS[case]
     for m in sizes:
-        check_exchange(dims, [tuple(c) for c in offsets], iso.ISO_OP_ALLTOALL, alg, m, layout, send_off=1, recv_off=5)
+        check_exchange(dims, [tuple(c) for c in offsets], op, alg, m, layout, send_off=1, recv_off=5)
 
 
 @pytest.mark.parametrize("op", [iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER])
