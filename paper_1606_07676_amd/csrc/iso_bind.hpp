@@ -833,13 +833,14 @@ private:
     // Cache policy of a launch whose kernel and arguments are set.  What decides is whether the blocks of the
     // whole collective (the receive buffer's size) stay in the last-level cache from one round to the next.
     //   All-to-all rounds read every block once: streaming loads and stores where they do not (26 neighbours, one
-    //   launch per dimension, streaming against cached loads with plain stores: 24^3, 256 B 73 -> 60 us, 20^3, 64 B
-    //   21 -> 17, 64^3, 16 B 239 -> 154, 8^5, 100 B 440 -> 285; at 146 MB 112 -> 122).  From three eighths of the
-    //   cache on streaming stores leave it to the blocks still to be read (box 45 x 37 x 29, slot-major, 126 MB: 120
-    //   us, plain stores 113, streaming ones 107; 30^3 star, 1000 B, 162 MB: 70, streaming stores 55), except for
-    //   blocks of less than 512 bytes that do not fill whole 64-byte sectors of rank-major rows: plain stores let
-    //   neighbouring blocks meet in the cache before a sector is written (32^3, 200 B 214 -> 153 us, 64^3, 40 B
-    //   560 -> 409; 426 MB 402 -> 471, whole sectors 160 -> 168).
+    //   launch per dimension, streaming against cached loads with plain stores: 20^3, 64 B 21 -> 17 us).  Up to an
+    //   eighth of the cache: a program that takes several sets of buffers in turn needs room for more than one
+    //   (24^3, 256 B, 92 MB: one set repeated 73 -> 60 us, several in turn 74 -> 84; box 45 x 37 x 29, slot-major,
+    //   126 MB: 113 and 124 against 121).
+    //   Blocks that do not fill whole 64-byte sectors of rank-major rows gain further up (boxes 201 -> 146 us at 126 MB): under 512 bytes plain
+    //   stores let neighbouring blocks meet in the cache before a sector is written (32^3, 200 B 214 -> 153 us,
+    //   64^3, 40 B 560 -> 409; 426 MB 402 -> 471, whole sectors 160 -> 168), from there on cached loads with
+    //   streaming stores are better (30^3 star, 1000 B, 162 MB 70 -> 55).
     //   Allgather rounds may read a block several times: cached loads; plain stores while all of it fits
     //   (64^3, 36 B 148 -> 139 us, box 40^3, 100 B 86 -> 69; 640 MB 239 -> 324).
     //   The staged schedule's kernels: what a round writes the last launch finds in the cache up to half of it, and
@@ -860,7 +861,7 @@ private:
             return bytes <= kLastLevelCacheBytes / 2 ? kPlainStores : bytes <= kLastLevelCacheBytes * 7 / 4 ? 0 : kStreamLoads;
         }
         if (l.kernel == kDeliverKernel) {
-            if (!a2a) return bytes <= kLastLevelCacheBytes ? kPlainStores : 0;
+            if (!a2a) return bytes <= kLastLevelCacheBytes / 2 ? kPlainStores : 0;
             return bytes <= kLastLevelCacheBytes / 2 ? 0 : kStreamLoads;
         }
         if (l.kernel == kVectorKernel) {
@@ -874,8 +875,8 @@ private:
             if (bytes <= kLastLevelCacheBytes / 2) return kPlainStores;
             return bytes <= above ? kStreamLoads | kPlainStores : kStreamLoads;
         }
-        if (bytes <= kLastLevelCacheBytes * 3 / 8) return kPlainStores;
-        return bytes <= (size0 % 64 && !lay.slot_major ? above : kLastLevelCacheBytes * 5 / 8) ? 0 : kStreamLoads;
+        if (bytes <= kLastLevelCacheBytes / 8) return kPlainStores;
+        return size0 % 64 && !lay.slot_major && bytes <= above ? 0 : kStreamLoads;
     }
 
     // Staged schedule, last launch: every rank's receive row written in one piece.
