@@ -1205,11 +1205,17 @@ private:
 
     // One device table: the entries, then the [s][d] residues, then what single launches read besides
     // (prefix arrays of irregular launches, the mesh's interior-tile bitmaps, the records of the staged
-    // schedule's last launch); then the launches get their addresses in it.
+    // schedule's last launch); then the launches get their addresses in it.  The residues keep their place in it
+    // but are written only where a kernel reads them (a launch of its own in the allocation-free call: 8^3, 26
+    // neighbours, 64 B 13.5 -> 10.7 us).
     int upload() {
         const size_t entry_bytes = table.size() * sizeof(DevEntry);
-        const size_t off_used = c.can.size() * sizeof(uint32_t);
-        const size_t off_bytes = (off_used + 15) & ~size_t(15);     // what follows starts 16-byte aligned
+        const size_t off_bytes = (c.can.size() * sizeof(uint32_t) + 15) & ~size_t(15);   // what follows: 16-byte aligned
+        bool reads_residues = false;
+        for (const Pending &pd : pending)
+            reads_residues = reads_residues || pd.l.kernel == kMeshShiftKernel || pd.l.kernel == kBlockKernel ||
+                             (pd.l.kernel == kVectorKernel && !pd.l.vector_dims);
+        const size_t off_used = reads_residues ? c.can.size() * sizeof(uint32_t) : 0;
         const size_t pre_bytes = prefixes.size() * sizeof(uint32_t);
         char *dev = nullptr;
         int st;

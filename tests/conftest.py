@@ -28,3 +28,12 @@ def load_golden(name="paper_values.txt"):
 @pytest.fixture(scope="session")
 def golden():
     return load_golden()
+
+
+@pytest.fixture(scope="session")
+def stub_library(tmp_path_factory):
+    """The library for the host only over a stand-in HIP runtime (see stub_library.py)."""
+    import stub_library as sl
+    if not os.path.exists(sl.CLANGXX):
+        pytest.skip("needs the ROCm clang++")
+    return sl.StubLibrary(str(tmp_path_factory.mktemp("stub")))

@@ -2,7 +2,8 @@
 // life cycle of iso_api.hip / iso_bind.hpp (device tables, graphs, the static scratch array) runs
 // against it under AddressSanitizer and LeakSanitizer with no GPU.  "Device" memory is host heap,
 // kernels are never run, and every object the library creates is counted, so that a run can end
-// with the statement that nothing the library made is still alive.
+// with the statement that nothing the library made is still alive.  Launches are logged by kernel
+// name, so that a test can say which kernels a call enqueues.
 #include <hip/hip_runtime_api.h>      // host API declarations only: this file is plain C++
 
 #include <cstdio>
@@ -10,12 +11,16 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <string>
+#include <vector>
 
 namespace {
 std::mutex g_mu;
 std::map<uintptr_t, size_t> g_allocs;          // live hipMalloc ranges
 long g_graphs = 0, g_execs = 0, g_launches = 0, g_graph_launches = 0, g_nodes = 0;
 alignas(256) unsigned char g_symbol_memory[64u << 20];      // what hipGetSymbolAddress hands out
+std::map<const void *, std::string> &kernel_names() { static std::map<const void *, std::string> m; return m; }
+std::vector<std::string> g_log;                // kernels launched since stub_log_clear
 struct StubGraph { int nodes; };
 struct StubExec { int nodes; };
 }  // namespace
@@ -25,7 +30,9 @@ extern "C" {
 extern const char __hip_fatbin[8];
 const char __hip_fatbin[8] = {0};
 void **__hipRegisterFatBinary(const void *) { static void *h; return &h; }
-void __hipRegisterFunction(void **, const void *, char *, const char *, unsigned, void *, void *, void *, void *, int *) {}
+void __hipRegisterFunction(void **, const void *func, char *, const char *name, unsigned, void *, void *, void *, void *, int *) {
+    kernel_names()[func] = name;
+}
 void __hipRegisterVar(void **, void *, char *, const char *, int, size_t, int, int) {}
 void __hipUnregisterFatBinary(void **) {}
 struct StubCall { dim3 grid, block; size_t shmem; hipStream_t stream; };
@@ -75,7 +82,12 @@ hipError_t hipMemGetAddressRange(hipDeviceptr_t *base, size_t *size, hipDevicept
     return hipSuccess;
 }
 hipError_t hipGetSymbolAddress(void **ptr, const void *) { *ptr = g_symbol_memory; return hipSuccess; }
-hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) { ++g_launches; return hipSuccess; }
+hipError_t hipLaunchKernel(const void *func, dim3, dim3, void **, size_t, hipStream_t) {
+    std::lock_guard<std::mutex> lock(g_mu);
+    ++g_launches;
+    g_log.push_back(kernel_names()[func]);
+    return hipSuccess;
+}
 
 hipError_t hipGraphCreate(hipGraph_t *g, unsigned) { *g = (hipGraph_t) new StubGraph{0}; ++g_graphs; return hipSuccess; }
 hipError_t hipGraphAddKernelNode(hipGraphNode_t *node, hipGraph_t g, const hipGraphNode_t *, size_t,
@@ -107,6 +119,9 @@ long stub_live_graph_objects(void) { return g_graphs + g_execs; }
 long stub_kernel_launches(void) { return g_launches; }
 long stub_graph_launches(void) { return g_graph_launches; }
 long stub_graph_nodes(void) { return g_nodes; }
+void stub_log_clear(void) { std::lock_guard<std::mutex> lock(g_mu); g_log.clear(); }
+long stub_log_size(void) { std::lock_guard<std::mutex> lock(g_mu); return (long)g_log.size(); }
+const char *stub_log_name(long i) { std::lock_guard<std::mutex> lock(g_mu); return g_log.at((size_t)i).c_str(); }
 }
 
 // Planted mistake for the test of the test: a build of the library in which hipFree is renamed to

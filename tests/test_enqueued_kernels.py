@@ -1,0 +1,47 @@
+"""Which kernels a call enqueues, on the CPU: the library's host code over a stand-in HIP runtime."""
+import numpy as np
+import pytest
+
+import iso_inputs as gen
+import paper_1606_07676_amd as iso
+
+COMBINED = [iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM, iso.ISO_ALG_COMBINED_STAGED]
+
+
+def _names(kernels):
+    return [k.split("<")[0] for k in kernels]
+
+
+def _noalloc(stub, dims, offsets, m, alg, periodic=None):
+    p, s = int(np.prod(dims)), len(offsets)
+    comm = stub.comm(dims, offsets, periodic)
+    with stub.buffers(p * s * m, p * s * m) as (send, recv):
+        return _names(stub.launched(lambda: stub.iso.iso_neighbor_alltoall_noalloc(send, recv, m, comm, alg, 0)))
+
+
+@pytest.mark.parametrize("alg", COMBINED)
+def test_allocation_free_call_of_a_small_alltoall_is_one_kernel(stub_library, alg):
+    assert _noalloc(stub_library, (8, 8, 8), gen.moore(3, 1), 64, alg) == ["chain_kernel"]
+
+
+def test_allocation_free_call_stores_only_tables_that_its_kernels_read(stub_library):
+    """Entries, and the residues of the offsets where a kernel reads them (a mesh, more than five dimensions)."""
+    for dims, offsets, alg, periodic, want in (
+            ((8, 8, 8), gen.moore(3, 1), iso.ISO_ALG_SX_FUSED, None, ["table_store_kernel", "vector_round_kernel"]),
+            ((16, 16, 16), gen.von_neumann(3, 1), iso.ISO_ALG_ONEHOP, None,
+             ["table_store_kernel"] + 6 * ["shift_round_kernel"]),
+            ((2, 3, 2, 3, 2, 4), gen.von_neumann(6, 1), iso.ISO_ALG_SX_FUSED, None,
+             2 * ["table_store_kernel"] + ["vector_round_kernel"]),
+            ((8, 8), gen.von_neumann(2, 1), iso.ISO_ALG_COMBINED_BYDIM, (0, 0),
+             3 * ["table_store_kernel"] + 2 * ["mesh_shift_round_kernel"])):
+        assert _noalloc(stub_library, dims, offsets, 64, alg, periodic) == want, dims
+
+
+def test_allocation_free_call_refuses_the_tables_it_always_refused(stub_library):
+    """3900 neighbours in five dimensions: the entries alone would fit the table's 256 KiB, with the residues they do
+    not, and the refusal does not depend on whether the kernels read them."""
+    offsets = gen.random_distinct(5, -3, 3, 3900, 1)
+    assert 3900 * 48 < iso.ISO_NOALLOC_TABLE_BYTES < 3900 * (48 + 20)
+    with pytest.raises(stub_library.iso.IsoError) as e:
+        _noalloc(stub_library, (2, 2, 2, 2, 2), offsets, 16, iso.ISO_ALG_SX_ROUNDS)
+    assert e.value.status == iso.ISO_ERR_SCRATCH
