@@ -464,12 +464,12 @@ public:
         rounds_as_launched();
         const bool merges = pl.algorithm == ISO_ALG_COMBINED;
         const bool chains = merges || pl.algorithm == ISO_ALG_COMBINED_BYDIM || pl.algorithm == ISO_ALG_COMBINED_STAGED;
-        if (arena && chains && (st = host_entries()) == ISO_SUCCESS && chain_launch()) return upload();
+        if (arena && chains && (st = host_entries()) == ISO_SUCCESS && chain_launch(launches_of_rounds(merges))) return upload();
         if (!arena || !merges) {
             if ((st = bind_rounds()) != ISO_SUCCESS) return st;
             n_listed = pending.size();
         }
-        if (!arena && chains && chain_launch()) return upload();
+        if (!arena && chains && chain_launch(launches_of_rounds(merges))) return upload();
         if (merges) {
             const size_t n_rounds = bound_rounds.size();
             merge_rounds();
@@ -515,15 +515,31 @@ private:
         return ISO_SUCCESS;
     }
 
+    // Kernels that iso_start takes without the chain: the rounds, with those of a dimension together if they are merged.
+    uint64_t launches_of_rounds(bool merges) const {
+        uint64_t n = 0;
+        for (size_t ri = 0; ri < rounds.size(); ++ri) {
+            const bool joins = merges && ri && bound_rounds[ri].kind == ISO_ROUND_SHIFT &&
+                               bound_rounds[ri - 1].kind == ISO_ROUND_SHIFT && bound_rounds[ri - 1].dim == bound_rounds[ri].dim;
+            n += !joins && !rounds[ri].empty();
+        }
+        return n;
+    }
+
     // iso_start of a small collective: all rounds in one launch (see chain_kernel), if its hops fit the arguments
-    // and a workgroup the ranks.  Against a launch per dimension: 8 x 8, 32 B 10.2 -> 7.8 us, 8^3, 26 neighbours, 64 B
-    // 13.5 -> 7.4 (allocation-free call 31 -> 17), 12^3, 16 B 13.1 -> 7.1, 5^4 star, 300 B 17.2 -> 7.3.  A workgroup's
-    // accesses are a column of units per rank, at best a few sectors each: the limits are 6144 sectors for one
-    // workgroup over all its hops (60^2, 64 B: 7200, 10.1 -> 12.7; 16^3, 16 B: 12288, 13.3 -> 16.4) and 256 Ki for
-    // all of them (10^3, 100 B: 156 Ki, 13.4 -> 12.2; 8^3, 400 B: 318 Ki, 10.1 -> 12.2; 10^3, 500 B: 624 Ki, 17 -> 28).
-    // Allgather: 8^3, 64 B 10.4 -> 7.0 us, 16^2 radius 2 21.6 -> 6.9.
-    bool chain_launch() {
-        if (c.mesh || !uniform || !size0 || p > kChainThreads * kChainUnitsPerLane ||
+    // and a workgroup the ranks.  Against a launch per dimension: 8 x 8, 32 B 9.9 -> 7.2 us, 8^3, 26 neighbours, 64 B
+    // 13.4 -> 7.4, 5^4 star, 400 B 16.4 -> 7.4; allgather the same.  What it saves is 2.7 us of the host's time per
+    // launch less; what it costs is that a workgroup's accesses are a column of units per rank, at best a few sectors
+    // each, which most of the chip does not take part in.  The limits are 6144 sectors for one workgroup over all its
+    // hops (60^2, 64 B: 7200, 10.1 -> 12.7; 16^3, 16 B: 12288, 13.3 -> 16.4), and for all of them 24 Ki per launch
+    // that it saves, measured with buffers that the caches do not hold: 32^2, 12 neighbours, 16 and 100 B (24 and
+    // 48 Ki, one launch less) 9.7 -> 6.5 and 9.7 -> 9.6, 16^2 radius 1, 400 B (32 Ki) 9.0 -> 7.9, 16^2, 1000 B (64 Ki)
+    // 9.3 -> 10.5; two launches less: 8^3, 64 B (39 Ki) 12.9 -> 7.9, 10^3, 64 B (76 Ki) 13.2 -> 13.2, 8^3, 200 B
+    // (156 Ki) 13.0 -> 14.7.  Where a workgroup's own way is short the whole may be twice that: 16^2 star, 3000 B (48 Ki,
+    // one launch less) 8.0 -> 7.3, 8^3 star, 2000 B (96 Ki, two) 10.4 -> 8.9, 5^4 star, 1000 B (107 Ki, three)
+    // 16.5 -> 8.9.  A schedule of one launch gains nothing (4096, 16 B 6.5 -> 6.9).
+    bool chain_launch(uint64_t launches) {
+        if (c.mesh || !uniform || !size0 || launches < 2 || p > kChainThreads * kChainUnitsPerLane ||
             c.d > (int)kChainDims || (size0 >> min_log2) > 0xFFFF)
             return false;
         std::vector<std::vector<const HostEntry *>> chains;
@@ -595,7 +611,8 @@ private:
         ca.first[n_chains] = (uint8_t)at;
         l.grid = n_chains * ca.groups;
         const uint64_t sectors = p * ((ca.column * width + 63) / 64);
-        if (sectors * longest > 6144 || sectors * l.grid * longest > 256 * 1024) return false;
+        const uint64_t own = sectors * longest, per_launch = own <= 1280 ? 48 * 1024 : 24 * 1024;
+        if (own > 6144 || own * l.grid > (launches - 1) * per_launch) return false;
         l.threads = std::min<uint32_t>(kChainThreads, (ca.n_units + 63) & ~63u);
         pending.push_back(pd);
         return true;

@@ -45,3 +45,19 @@ def test_allocation_free_call_refuses_the_tables_it_always_refused(stub_library)
     with pytest.raises(stub_library.iso.IsoError) as e:
         _noalloc(stub_library, (2, 2, 2, 2, 2), offsets, 16, iso.ISO_ALG_SX_ROUNDS)
     assert e.value.status == iso.ISO_ERR_SCRATCH
+
+
+@pytest.mark.parametrize("op", [iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER])
+@pytest.mark.parametrize("dims,offsets,m,kernels", [
+    ((8, 8), gen.moore(2, 1), 64, 1), ((8, 8, 8), gen.moore(3, 1), 64, 1), ((32, 32), gen.von_neumann(2, 2), 64, 1),
+    ((8, 8), [(1, 1), (0, 1), (2, 0)], 2056, 1), ((4, 3), [(1, 1), (1, 1), (0, 0), (0, 0), (5, -7), (2, 0)], 5464, 1),
+    ((5, 5, 5, 5), gen.von_neumann(4, 1), 1000, 1), ((5, 5, 5, 5), gen.von_neumann(4, 1), 2000, 4),
+    ((16, 16), gen.von_neumann(2, 1), 3000, 1), ((16, 16), gen.von_neumann(2, 1), 4000, 2),
+    ((4096,), gen.von_neumann(1, 1), 16, 1), ((16, 16), gen.moore(2, 1), 1000, 2), ((32, 32), gen.von_neumann(2, 2), 300, 2),
+    ((8, 8, 8), gen.moore(3, 1), 200, 3), ((10, 10, 10), gen.moore(3, 1), 100, 3)])
+def test_small_collectives_take_one_launch_where_it_saves_enough(stub_library, dims, offsets, m, kernels, op):
+    """The chain kernel's limit is per launch saved: none for a schedule of one launch."""
+    for alg in (iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM):
+        names = _names(stub_library.start(dims, offsets, op, alg, m))
+        chained = kernels == 1 and len(dims) > 1
+        assert names == ["chain_kernel"] if chained else (len(names) == kernels and "chain_kernel" not in names), (alg, names)

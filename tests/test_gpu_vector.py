@@ -139,7 +139,10 @@ CHAINS = [((8, 8), gen.moore(2, 1), (1, 7, 32, 64, 1000, 8192, 8200)), ((8, 8, 8
           ((45, 91), [(1, 1), (3, -2)], (16, 17, 8)), ((3, 1, 2, 5, 2, 3, 2, 2), gen.von_neumann(8, 1), (12, 100, 112)),
           ((4, 3), [(1, 1), (1, 1), (0, 0), (0, 0), (5, -7), (2, 0)], (5, 16, 100000)),
           ((17, 19), gen.random_distinct(2, -3, 3, 36, 6), (64, 100, 208)),       # 72 hops and fewer
-          ((7, 3, 15, 7), gen.random_distinct(4, -2, 2, 1, 3), (4100,))]          # a column of one unit: not where it overlaps
+          ((7, 3, 15, 7), gen.random_distinct(4, -2, 2, 1, 3), (4100,)),          # a column of one unit: not where it overlaps
+          ((8, 8), [(1, 1), (0, 1), (2, 0)], (1040, 2000, 2056)),                 # two and three columns of 64 units, with and without an overlap
+          ((4, 3), [(1, 1), (1, 1), (0, 0), (0, 0), (5, -7), (2, 0)], (5456, 5464, 10000)),
+          ((5, 5, 5, 5), gen.von_neumann(4, 1), (100, 400, 1000)), ((16, 16), gen.von_neumann(2, 1), (2000, 3000))]
 
 
 @pytest.mark.parametrize("alg", [iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM, iso.ISO_ALG_COMBINED_STAGED])
