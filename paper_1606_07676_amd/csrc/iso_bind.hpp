@@ -858,8 +858,13 @@ private:
     //   stores let neighbouring blocks meet in the cache before a sector is written (32^3, 200 B 214 -> 153 us,
     //   64^3, 40 B 560 -> 409; 426 MB 402 -> 471, whole sectors 160 -> 168), from there on cached loads with
     //   streaming stores are better (30^3 star, 1000 B, 162 MB 70 -> 55).
-    //   Allgather rounds may read a block several times: cached loads; plain stores while all of it fits
-    //   (64^3, 36 B 148 -> 139 us, box 40^3, 100 B 86 -> 69; 640 MB 239 -> 324).
+    //   Allgather rounds may read a block several times: cached loads.  Streaming stores, except for blocks of less than
+    //   a sector in rank-major rows of three and more dimensions, of which several launches write parts, while all of it
+    //   fits (plain against streaming, one set of buffers and many in turn: 64^3, 32 B 120 -> 99 and 174 -> 160 us,
+    //   8^5, 40 random neighbours, 40 B 122 -> 76 and 136 -> 96, 64^3 star, 40 B 53 -> 32 and 54 -> 47).  Plain stores
+    //   of larger blocks and in two dimensions gain only where one set is repeated (30^3 star, 1000 B 47 -> 46 and
+    //   47 -> 64; 32^3, 200 B 70 -> 57 and 82 -> 92; box 40^3, 160 B 106 -> 89 and 118 -> 131; 300^2, 24 neighbours,
+    //   56 B 51 -> 39 and 61 -> 71).
     //   The staged schedule's kernels: what a round writes the last launch finds in the cache up to half of it, and
     //   the rows that one writes are not read again (64^3, 16 B 116 -> 97 us, 8^5, 64 B 144 -> 116, 300^2, 48 B 77 ->
     //   66); up to 7/4 of it the rounds still gain from cached loads (64^3, 32 B 197 -> 177, 64 B 353 -> 335; 872 MB
@@ -887,7 +892,8 @@ private:
         }
         if (r.kind == ISO_ROUND_VECTOR) return 0;
         if (l.kernel == kBlockKernel) return bytes <= kLastLevelCacheBytes / 4 ? kPlainStores : 0;
-        if (!a2a) return bytes <= kLastLevelCacheBytes ? kPlainStores : 0;
+        if (!a2a)
+            return size0 < 64 && c.d >= 3 && !c.mesh && !lay.slot_major && bytes <= kLastLevelCacheBytes ? kPlainStores : 0;
         if (size0 % 64 && size0 < 512 && !lay.slot_major) {
             if (bytes <= kLastLevelCacheBytes / 2) return kPlainStores;
             return bytes <= above ? kStreamLoads | kPlainStores : kStreamLoads;

@@ -51,7 +51,7 @@ hipError_t hipGetDevice(int *dev) { *dev = 0; return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 
 hipError_t hipMalloc(void **ptr, size_t bytes) {
-    void *q = std::malloc(bytes ? bytes : 1);
+    void *q = std::aligned_alloc(256, (bytes + 256) & ~size_t(255));           // the alignment that the runtime gives
     if (!q) return hipErrorOutOfMemory;
     std::lock_guard<std::mutex> lock(g_mu);
     g_allocs[(uintptr_t)q] = bytes;

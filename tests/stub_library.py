@@ -61,14 +61,15 @@ class StubLibrary:
         return self.iso.iso_neighborhood_create_mesh(dims, periodic, offsets)
 
     def launched(self, call):
-        """The kernels that call() enqueues: demangled, without namespace, arguments and type prefixes."""
+        """The kernels that call() enqueues, as name<template arguments>; the vector types are called v8 and v16."""
         self.lib.stub_log_clear()
         call()
         names = [self.lib.stub_log_name(i).decode() for i in range(self.lib.stub_log_size())]
         if not names:
             return []
         out = subprocess.run(["c++filt"], input="\n".join(names), stdout=subprocess.PIPE, text=True, check=True).stdout
-        return [re.sub(r"^void |iso::|\(.*$", "", n) for n in out.split("\n") if n]
+        out = out.replace("unsigned int __vector(4)", "v16").replace("unsigned int __vector(2)", "v8")
+        return [re.sub(r"^void |iso::|\([^()]*\)$", "", n) for n in out.split("\n") if n]
 
     def buffers(self, *sizes):
         """Context manager: one 'device' buffer per size (None for 0)."""

@@ -61,3 +61,31 @@ def test_small_collectives_take_one_launch_where_it_saves_enough(stub_library, d
         names = _names(stub_library.start(dims, offsets, op, alg, m))
         chained = kernels == 1 and len(dims) > 1
         assert names == ["chain_kernel"] if chained else (len(names) == kernels and "chain_kernel" not in names), (alg, names)
+
+
+# cache policies: 0 cached loads, streaming stores; 1 streaming both; 2 cached, plain stores; 3 streaming loads, plain stores
+POLICY_ARGUMENT = {"shift_round_kernel": 2, "mesh_shift_round_kernel": 2, "shift_round_uniform_kernel": 0,
+                   "staged_round_kernel": 1, "deliver_kernel": 1, "block_round_kernel": 2, "vector_round_kernel": 3,
+                   "vector_round_uniform_kernel": 1}
+
+
+def _policies(kernels):
+    out = set()
+    for k in kernels:
+        name, args = k.rstrip(">").split("<")
+        if name in POLICY_ARGUMENT:
+            out.add((name.replace("_kernel", "").replace("_round", ""), int(args.split(", ")[POLICY_ARGUMENT[name]])))
+    return out
+
+
+@pytest.mark.parametrize("dims,offsets,m,layout,periodic,want", [
+    ((30, 30, 30), gen.von_neumann(3, 1), 1000, 0, None, 0), ((32, 32, 32), gen.moore(3, 1), 200, 0, None, 0),
+    ((40, 40, 40), gen.moore(3, 1), 160, 0, (0, 0, 0), 0), ((45, 37, 29), gen.moore(3, 1), 100, 1, (0, 0, 0), 0),
+    ((300, 300), gen.moore(2, 2), 56, 0, None, 0), ((24, 24, 24), gen.von_neumann(3, 2), 36, 0, (0, 0, 0), 0),
+    ((64, 64, 64), gen.moore(3, 1), 32, 0, None, 2), ((64, 64, 64), gen.moore(3, 1), 56, 0, None, 0),
+    ((8, 8, 8, 8, 8), gen.random_distinct(5, -3, 3, 40, 5), 40, 0, None, 2)])
+def test_allgather_rounds_stream_their_stores(stub_library, dims, offsets, m, layout, periodic, want):
+    """Plain stores only for blocks of less than a sector, rank-major, three and more dimensions, up to the cache."""
+    for alg in (iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM):
+        got = _policies(stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, alg, m, layout, periodic))
+        assert got == {("mesh_shift" if periodic else "shift", want)}
