@@ -849,11 +849,10 @@ private:
 
     // Cache policy of a launch whose kernel and arguments are set.  What decides is whether the blocks of the
     // whole collective (the receive buffer's size) stay in the last-level cache from one round to the next.
-    //   All-to-all rounds read every block once: streaming loads and stores where they do not (26 neighbours, one
-    //   launch per dimension, streaming against cached loads with plain stores: 20^3, 64 B 21 -> 17 us).  Up to an
-    //   eighth of the cache: a program that takes several sets of buffers in turn needs room for more than one
-    //   (24^3, 256 B, 92 MB: one set repeated 73 -> 60 us, several in turn 74 -> 84; box 45 x 37 x 29, slot-major,
-    //   126 MB: 113 and 124 against 121).
+    //   All-to-all rounds read every block once: streaming loads and stores, except for collectives of up to 8 MiB
+    //   (plain against streaming, one set of buffers and many in turn: 16^3, 64 B 13.1 -> 12.4 and 16.5 -> 15.3 us).
+    //   Plain stores gain further up only where one set is repeated (16^3, 128 B 17.3 -> 15.9 and 19.5 -> 24; 20^3,
+    //   128 B 26.5 -> 23.3 and 28 -> 33.4; 60^2, 24 neighbours, 128 B 11.6 -> 10.1 and 13.3 -> 15.9).
     //   Blocks that do not fill whole 64-byte sectors of rank-major rows gain further up (boxes 201 -> 146 us at 126 MB): under 512 bytes plain
     //   stores let neighbouring blocks meet in the cache before a sector is written (32^3, 200 B 214 -> 153 us,
     //   64^3, 40 B 560 -> 409; 426 MB 402 -> 471, whole sectors 160 -> 168), from there on cached loads with
@@ -898,7 +897,7 @@ private:
             if (bytes <= kLastLevelCacheBytes / 2) return kPlainStores;
             return bytes <= above ? kStreamLoads | kPlainStores : kStreamLoads;
         }
-        if (bytes <= kLastLevelCacheBytes / 8) return kPlainStores;
+        if (bytes <= kLastLevelCacheBytes / 32) return kPlainStores;
         return size0 % 64 && !lay.slot_major && bytes <= above ? 0 : kStreamLoads;
     }
 

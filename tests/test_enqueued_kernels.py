@@ -89,3 +89,15 @@ def test_allgather_rounds_stream_their_stores(stub_library, dims, offsets, m, la
     for alg in (iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM):
         got = _policies(stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, alg, m, layout, periodic))
         assert got == {("mesh_shift" if periodic else "shift", want)}
+
+
+@pytest.mark.parametrize("dims,offsets,m,layout,periodic,want", [
+    ((16, 16, 16), gen.moore(3, 1), 128, 0, None, 1), ((20, 20, 20), gen.moore(3, 1), 64, 0, None, 1),
+    ((60, 60), gen.moore(2, 2), 128, 0, None, 1), ((24, 24, 24), gen.moore(3, 1), 64, 1, None, 1),
+    ((24, 24, 24), gen.moore(3, 1), 64, 1, (0, 0, 0), 1), ((24, 24, 24), gen.moore(3, 1), 100, 1, None, 1),
+    ((100, 100), gen.von_neumann(2, 2), 256, 1, None, 1),
+    ((16, 16, 16), gen.moore(3, 1), 64, 0, None, 2), ((60, 60), gen.moore(2, 2), 64, 1, None, 2)])
+def test_alltoall_rounds_of_whole_sectors_stream_beyond_8_MiB(stub_library, dims, offsets, m, layout, periodic, want):
+    for alg in (iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM):
+        got = _policies(stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, alg, m, layout, periodic))
+        assert got == {("mesh_shift" if periodic else "shift", want)}
