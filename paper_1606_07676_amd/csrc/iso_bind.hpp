@@ -853,10 +853,17 @@ private:
     //   (plain against streaming, one set of buffers and many in turn: 16^3, 64 B 13.1 -> 12.4 and 16.5 -> 15.3 us).
     //   Plain stores gain further up only where one set is repeated (16^3, 128 B 17.3 -> 15.9 and 19.5 -> 24; 20^3,
     //   128 B 26.5 -> 23.3 and 28 -> 33.4; 60^2, 24 neighbours, 128 B 11.6 -> 10.1 and 13.3 -> 15.9).
-    //   Blocks that do not fill whole 64-byte sectors of rank-major rows gain further up (boxes 201 -> 146 us at 126 MB): under 512 bytes plain
-    //   stores let neighbouring blocks meet in the cache before a sector is written (32^3, 200 B 214 -> 153 us,
-    //   64^3, 40 B 560 -> 409; 426 MB 402 -> 471, whole sectors 160 -> 168), from there on cached loads with
-    //   streaming stores are better (30^3 star, 1000 B, 162 MB 70 -> 55).
+    //   Blocks that do not fill whole 64-byte sectors of rank-major rows gain further up.  Up to half the cache plain
+    //   stores let neighbouring blocks meet there before a sector is written: blocks of less than a sector (64^3, 20 B
+    //   293 -> 185 and 301 -> 214; 300^2, 24 neighbours, 25 B 82 -> 48 and 91 -> 63), and blocks up to 256 B that make
+    //   two hops and more, so that much of what is written is read again (32^3, 100 B 123 -> 74 and 130 -> 107, 8^4, 80
+    //   neighbours, 100 B 64 -> 44 and 76 -> 60; fewer hops: 300^2 star, 100 B 23 -> 20 and 28 -> 31, 200^2, 8
+    //   neighbours, 200 B 46 -> 36 and 49 -> 56; larger blocks: 16^3, 400 B 41 -> 33 and 45 -> 48; small collectives:
+    //   60^2, 24 neighbours, 200 B 15.6 -> 14 and 18.5 -> 20.7).  Other blocks take cached loads there (100^2, 24
+    //   neighbours, 300 B 53 -> 46 and 57 -> 57, 30^3 star, 600 B 47 -> 37 and 49 -> 48).  Between half and 9/8 of the
+    //   cache: streaming loads, plain stores under 512 B (64^3, 36 B 495 -> 336 and 507 -> 395, 32^3, 300 B 281 -> 219
+    //   and 285 -> 262), cached loads from there on (30^3 star, 1000 B 71 -> 55 and 72 -> 72; not on a mesh: 1 to 3 %
+    //   slower with many sets).
     //   Allgather rounds may read a block several times: cached loads.  Streaming stores, except for blocks of less than
     //   a sector in rank-major rows of three and more dimensions, of which several launches write parts, while all of it
     //   fits (plain against streaming, one set of buffers and many in turn: 64^3, 32 B 120 -> 99 and 174 -> 160 us,
@@ -893,12 +900,13 @@ private:
         if (l.kernel == kBlockKernel) return bytes <= kLastLevelCacheBytes / 4 ? kPlainStores : 0;
         if (!a2a)
             return size0 < 64 && c.d >= 3 && !c.mesh && !lay.slot_major && bytes <= kLastLevelCacheBytes ? kPlainStores : 0;
-        if (size0 % 64 && size0 < 512 && !lay.slot_major) {
-            if (bytes <= kLastLevelCacheBytes / 2) return kPlainStores;
-            return bytes <= above ? kStreamLoads | kPlainStores : kStreamLoads;
+        if (size0 % 64 && !lay.slot_major && bytes <= above) {
+            if (bytes > kLastLevelCacheBytes / 2) return size0 < 512 ? kStreamLoads | kPlainStores : c.mesh ? kStreamLoads : 0;
+            if (size0 < 64) return kPlainStores;
+            if (size0 < 256 && inf.entries >= 2 * (int64_t)s && bytes > kLastLevelCacheBytes / 12) return kPlainStores;
+            return bytes > kLastLevelCacheBytes / 8 && !c.mesh ? 0 : kStreamLoads;
         }
-        if (bytes <= kLastLevelCacheBytes / 32) return kPlainStores;
-        return size0 % 64 && !lay.slot_major && bytes <= above ? 0 : kStreamLoads;
+        return bytes <= kLastLevelCacheBytes / 32 ? kPlainStores : kStreamLoads;
     }
 
     // Staged schedule, last launch: every rank's receive row written in one piece.

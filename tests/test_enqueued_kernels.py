@@ -101,3 +101,20 @@ def test_alltoall_rounds_of_whole_sectors_stream_beyond_8_MiB(stub_library, dims
     for alg in (iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM):
         got = _policies(stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, alg, m, layout, periodic))
         assert got == {("mesh_shift" if periodic else "shift", want)}
+
+
+@pytest.mark.parametrize("dims,offsets,m,periodic,want", [
+    ((64, 64, 64), gen.moore(3, 1), 20, None, 3), ((64, 64, 64), gen.moore(3, 1), 16, None, 2),
+    ((300, 300), gen.moore(2, 2), 25, None, 2), ((100, 100), gen.moore(2, 1), 48, (0, 0), 2),
+    ((32, 32, 32), gen.moore(3, 1), 100, None, 2), ((45, 37, 29), gen.moore(3, 1), 100, (0, 0, 0), 2),
+    ((16, 16, 16), gen.moore(3, 1), 100, None, 1), ((16, 16, 16), gen.moore(3, 1), 100, (0, 0, 0), 1),
+    ((60, 60), gen.moore(2, 2), 200, None, 1), ((300, 300), gen.von_neumann(2, 1), 100, None, 0),
+    ((200, 200), gen.moore(2, 1), 200, None, 0), ((200, 200), gen.moore(2, 1), 100, (0, 0), 1),
+    ((16, 16, 16), gen.moore(3, 1), 400, None, 0), ((100, 100), gen.moore(2, 2), 300, None, 0),
+    ((12, 12, 12), gen.moore(3, 1), 600, None, 1), ((30, 30, 30), gen.von_neumann(3, 1), 1000, None, 0),
+    ((30, 30, 30), gen.von_neumann(3, 1), 1000, (0, 0, 0), 1), ((32, 32, 32), gen.moore(3, 1), 300, None, 3),
+    ((32, 32, 32), gen.moore(3, 1), 500, None, 1), ((64, 64, 64), gen.moore(3, 1), 48, None, 1)])
+def test_alltoall_rounds_of_part_sectors(stub_library, dims, offsets, m, periodic, want):
+    """By block size, hops per block, and size of the collective against the last-level cache."""
+    got = _policies(stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_BYDIM, m, 0, periodic))
+    assert got == {("mesh_shift" if periodic else "shift", want)}
