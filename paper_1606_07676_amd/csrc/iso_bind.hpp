@@ -874,7 +874,9 @@ private:
     //   The staged schedule's kernels: what a round writes the last launch finds in the cache up to half of it, and
     //   the rows that one writes are not read again (64^3, 16 B 116 -> 97 us, 8^5, 64 B 144 -> 116, 300^2, 48 B 77 ->
     //   66); up to 7/4 of it the rounds still gain from cached loads (64^3, 32 B 197 -> 177, 64 B 353 -> 335; 872 MB
-    //   622 -> 634).  Allgather: 64^3, 32 B 87.5 -> 84, 32^3, 64 B 31 -> 28.6.
+    //   622 -> 634).  Allgather: cached loads, streaming stores (the
+    //   last launch with plain ones, one set of buffers and many in turn: 64^3, 16 B 45 -> 45 and 43 -> 49, 64^3 star,
+    //   64 B 22 -> 23 and 23 -> 29, 300^2, 24 neighbours, 48 B 37 -> 34 and 33 -> 36).
     //   Unequal blocks: cached loads, plain stores up to a quarter (4-byte stencil on 64^3 126 -> 119 us; at
     //   133 MB 73 -> 93; streaming loads 20 % slower wherever the blocks fit the cache).
     //   The s-exchange writes whole rows and is indifferent to the stores; streaming loads where the send buffer
@@ -889,7 +891,7 @@ private:
             return bytes <= kLastLevelCacheBytes / 2 ? kPlainStores : bytes <= kLastLevelCacheBytes * 7 / 4 ? 0 : kStreamLoads;
         }
         if (l.kernel == kDeliverKernel) {
-            if (!a2a) return bytes <= kLastLevelCacheBytes / 2 ? kPlainStores : 0;
+            if (!a2a) return 0;
             return bytes <= kLastLevelCacheBytes / 2 ? 0 : kStreamLoads;
         }
         if (l.kernel == kVectorKernel) {

@@ -118,3 +118,10 @@ def test_alltoall_rounds_of_part_sectors(stub_library, dims, offsets, m, periodi
     """By block size, hops per block, and size of the collective against the last-level cache."""
     got = _policies(stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_BYDIM, m, 0, periodic))
     assert got == {("mesh_shift" if periodic else "shift", want)}
+
+
+@pytest.mark.parametrize("dims,offsets,m", [((64, 64, 64), gen.moore(3, 1), 16), ((64, 64, 64), gen.von_neumann(3, 1), 64),
+                                            ((32, 32, 32), gen.moore(3, 1), 128)])
+def test_staged_allgather_streams_its_stores(stub_library, dims, offsets, m):
+    got = _policies(stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, iso.ISO_ALG_COMBINED_STAGED, m))
+    assert ("deliver", 0) in got and all(policy == 0 for _, policy in got)
