@@ -871,10 +871,15 @@ private:
     //   of larger blocks and in two dimensions gain only where one set is repeated (30^3 star, 1000 B 47 -> 46 and
     //   47 -> 64; 32^3, 200 B 70 -> 57 and 82 -> 92; box 40^3, 160 B 106 -> 89 and 118 -> 131; 300^2, 24 neighbours,
     //   56 B 51 -> 39 and 61 -> 71).
-    //   The staged schedule's kernels: what a round writes the last launch finds in the cache up to half of it, and
-    //   the rows that one writes are not read again (64^3, 16 B 116 -> 97 us, 8^5, 64 B 144 -> 116, 300^2, 48 B 77 ->
-    //   66); up to 7/4 of it the rounds still gain from cached loads (64^3, 32 B 197 -> 177, 64 B 353 -> 335; 872 MB
-    //   622 -> 634).  Allgather: cached loads, streaming stores (the
+    //   The staged schedule's kernels, all-to-all, one set of buffers and many in turn.  From an eighth of the cache (a
+    //   sixteenth at 16 bytes) up to half of it cached loads in both; the rounds store plainly if blocks do not fill
+    //   sectors (64^3, 16 B 116 -> 97 and 118 -> 107 us, 44^3, 32 B 68 -> 58 and 70 -> 69, 9^4, 80 neighbours, 176 B
+    //   131 -> 86 and 133 -> 111; 32^3, 32 B, under an eighth, 27 -> 27.5 and 29.5 -> 31) and stream at 64 B (40^3 89 ->
+    //   81 and 90.5 -> 89; plain 75 and 93.5).  Up to 7/4 of it the rounds still gain from cached loads (64^3, 32 B 196
+    //   -> 177 and 198 -> 186, 48^3, 80 B 195 -> 182 and 197 -> 188; 872 MB 617 -> 623).  Blocks of two and more whole
+    //   sectors stream throughout (32^3, 256 B 158 -> 148 and 159 -> 162, 9^4, 128 B 73 -> 61 and 75 -> 78).  Rounds
+    //   between planes of the workspace are dense on both sides whatever the block: as whole sectors.
+    //    Allgather: cached loads, streaming stores (the
     //   last launch with plain ones, one set of buffers and many in turn: 64^3, 16 B 45 -> 45 and 43 -> 49, 64^3 star,
     //   64 B 22 -> 23 and 23 -> 29, 300^2, 24 neighbours, 48 B 37 -> 34 and 33 -> 36).
     //   Unequal blocks: cached loads, plain stores up to a quarter (4-byte stencil on 64^3 126 -> 119 us; at
@@ -886,13 +891,13 @@ private:
         const uint64_t bytes = inf.delivered_bytes;
         const uint64_t above = kLastLevelCacheBytes * 9 / 8;      // what still gains from the cache
         const bool a2a = op == ISO_OP_ALLTOALL;
-        if (l.kernel == kStagedRoundKernel) {
+        if (l.kernel == kStagedRoundKernel || l.kernel == kDeliverKernel) {
+            const bool round = l.kernel == kStagedRoundKernel, whole = size0 % 64 == 0;
             if (!a2a) return 0;
-            return bytes <= kLastLevelCacheBytes / 2 ? kPlainStores : bytes <= kLastLevelCacheBytes * 7 / 4 ? 0 : kStreamLoads;
-        }
-        if (l.kernel == kDeliverKernel) {
-            if (!a2a) return 0;
-            return bytes <= kLastLevelCacheBytes / 2 ? 0 : kStreamLoads;
+            if (bytes > kLastLevelCacheBytes * 7 / 4 || (whole && size0 >= 128)) return kStreamLoads;
+            if (bytes > kLastLevelCacheBytes / 2) return round ? 0 : kStreamLoads;
+            if (bytes <= kLastLevelCacheBytes / (size0 < 32 ? 16 : 8)) return kStreamLoads;
+            return round && !whole ? kPlainStores : 0;
         }
         if (l.kernel == kVectorKernel) {
             const bool lines = size0 % 128 == 0 || lay.slot_major;
@@ -902,7 +907,8 @@ private:
         if (l.kernel == kBlockKernel) return bytes <= kLastLevelCacheBytes / 4 ? kPlainStores : 0;
         if (!a2a)
             return size0 < 64 && c.d >= 3 && !c.mesh && !lay.slot_major && bytes <= kLastLevelCacheBytes ? kPlainStores : 0;
-        if (size0 % 64 && !lay.slot_major && bytes <= above) {
+        const bool dense = lay.slot_major || (l.kernel == kShiftKernel && l.shift.entry_major);
+        if (size0 % 64 && !dense && bytes <= above) {
             if (bytes > kLastLevelCacheBytes / 2) return size0 < 512 ? kStreamLoads | kPlainStores : c.mesh ? kStreamLoads : 0;
             if (size0 < 64) return kPlainStores;
             if (size0 < 256 && inf.entries >= 2 * (int64_t)s && bytes > kLastLevelCacheBytes / 12) return kPlainStores;

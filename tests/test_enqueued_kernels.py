@@ -125,3 +125,18 @@ def test_alltoall_rounds_of_part_sectors(stub_library, dims, offsets, m, periodi
 def test_staged_allgather_streams_its_stores(stub_library, dims, offsets, m):
     got = _policies(stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, iso.ISO_ALG_COMBINED_STAGED, m))
     assert ("deliver", 0) in got and all(policy == 0 for _, policy in got)
+
+
+@pytest.mark.parametrize("dims,offsets,m,rounds,last", [
+    ((64, 64, 64), gen.moore(3, 1), 16, 2, 0), ((20, 20, 20), gen.moore(3, 1), 64, 1, 1), ((32, 32, 32), gen.moore(3, 1), 32, 1, 1),
+    ((44, 44, 44), gen.moore(3, 1), 32, 2, 0), ((9, 9, 9, 9), gen.moore(4, 1), 176, 2, 0), ((40, 40, 40), gen.moore(3, 1), 64, 0, 0), ((64, 64, 64), gen.moore(3, 1), 32, 0, 1),
+    ((32, 32, 32), gen.moore(3, 1), 128, 1, 1), ((20, 20, 20), gen.moore(3, 1), 256, 1, 1), ((64, 64, 64), gen.moore(3, 1), 80, 1, 1)])
+def test_staged_alltoall_by_block_size_and_size(stub_library, dims, offsets, m, rounds, last):
+    got = _policies(stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_STAGED, m))
+    assert {("staged", rounds), ("deliver", last)} <= got <= {("staged", rounds), ("deliver", last), ("shift", 1)}
+
+
+def test_staged_rounds_between_planes_stream(stub_library):
+    offsets = gen.random_distinct(5, -3, 3, 40, 5)
+    got = _policies(stub_library.start((6, 6, 6, 6, 6), offsets, iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_STAGED, 48))
+    assert ("shift", 1) in got and all(policy == 1 for _, policy in got)
