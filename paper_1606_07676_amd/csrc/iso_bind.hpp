@@ -861,9 +861,12 @@ private:
     //   neighbours, 200 B 46 -> 36 and 49 -> 56; larger blocks: 16^3, 400 B 41 -> 33 and 45 -> 48; small collectives:
     //   60^2, 24 neighbours, 200 B 15.6 -> 14 and 18.5 -> 20.7).  Other blocks take cached loads there (100^2, 24
     //   neighbours, 300 B 53 -> 46 and 57 -> 57, 30^3 star, 600 B 47 -> 37 and 49 -> 48).  Between half and 9/8 of the
-    //   cache: streaming loads, plain stores under 512 B (64^3, 36 B 495 -> 336 and 507 -> 395, 32^3, 300 B 281 -> 219
-    //   and 285 -> 262), cached loads from there on (30^3 star, 1000 B 71 -> 55 and 72 -> 72; not on a mesh: 1 to 3 %
-    //   slower with many sets).
+    //   cache: streaming loads, plain stores under a sector and for two hops and more under 512 B (64^3, 36 B 495 -> 336
+    //   and 507 -> 395, 32^3, 300 B 281 -> 219 and 285 -> 262; 300^2 star, 400 B 61 -> 57 and 63 -> 85), else cached
+    //   loads (the same 61 -> 50 and 63 -> 61, 64^3 star, 140 B 174 -> 120 and 178 -> 158, 30^3 star, 1000 B 71 -> 55 and
+    //   72 -> 72; not on a mesh from 512 B on: 1 to 3 % slower with many sets).  In the staged schedule blocks of 128
+    //   bytes and more take the cached loads (20^3, 200 B with plain stores 55 -> 41 and 57 -> 61), and an allgather's
+    //   plain stores begin at an eighth of the cache (32^3, 20 B 24 -> 22 and 23.6 -> 25).
     //   Allgather rounds may read a block several times: cached loads.  Streaming stores, except for blocks of less than
     //   a sector in rank-major rows of three and more dimensions, of which several launches write parts, while all of it
     //   fits (plain against streaming, one set of buffers and many in turn: 64^3, 32 B 120 -> 99 and 174 -> 160 us,
@@ -905,14 +908,20 @@ private:
         }
         if (r.kind == ISO_ROUND_VECTOR) return 0;
         if (l.kernel == kBlockKernel) return bytes <= kLastLevelCacheBytes / 4 ? kPlainStores : 0;
+        const bool staged = pl.algorithm == ISO_ALG_COMBINED_STAGED;
         if (!a2a)
-            return size0 < 64 && c.d >= 3 && !c.mesh && !lay.slot_major && bytes <= kLastLevelCacheBytes ? kPlainStores : 0;
+            return size0 < 64 && c.d >= 3 && !c.mesh && !lay.slot_major && bytes <= kLastLevelCacheBytes &&
+                           (!staged || bytes > kLastLevelCacheBytes / 8)
+                       ? kPlainStores
+                       : 0;
         const bool dense = lay.slot_major || (l.kernel == kShiftKernel && l.shift.entry_major);
         if (size0 % 64 && !dense && bytes <= above) {
-            if (bytes > kLastLevelCacheBytes / 2) return size0 < 512 ? kStreamLoads | kPlainStores : c.mesh ? kStreamLoads : 0;
+            const bool read_again = inf.entries >= 2 * (int64_t)s;          // two hops per block and more
+            if (bytes > kLastLevelCacheBytes / 2 && (size0 < 64 || (size0 < 512 && read_again)))
+                return kStreamLoads | kPlainStores;
             if (size0 < 64) return kPlainStores;
-            if (size0 < 256 && inf.entries >= 2 * (int64_t)s && bytes > kLastLevelCacheBytes / 12) return kPlainStores;
-            return bytes > kLastLevelCacheBytes / 8 && !c.mesh ? 0 : kStreamLoads;
+            if (size0 < (staged ? 128u : 256u) && read_again && bytes > kLastLevelCacheBytes / 12) return kPlainStores;
+            return bytes > kLastLevelCacheBytes / 8 && (!c.mesh || size0 < 512) ? 0 : kStreamLoads;
         }
         return bytes <= kLastLevelCacheBytes / 32 ? kPlainStores : kStreamLoads;
     }

@@ -113,6 +113,8 @@ def test_alltoall_rounds_of_whole_sectors_stream_beyond_8_MiB(stub_library, dims
     ((16, 16, 16), gen.moore(3, 1), 400, None, 0), ((100, 100), gen.moore(2, 2), 300, None, 0),
     ((12, 12, 12), gen.moore(3, 1), 600, None, 1), ((30, 30, 30), gen.von_neumann(3, 1), 1000, None, 0),
     ((30, 30, 30), gen.von_neumann(3, 1), 1000, (0, 0, 0), 1), ((32, 32, 32), gen.moore(3, 1), 300, None, 3),
+    ((50, 50, 50), gen.von_neumann(3, 1), 200, None, 0), ((300, 300), gen.von_neumann(2, 1), 400, None, 0),
+    ((64, 64, 64), gen.von_neumann(3, 1), 140, (0, 0, 0), 0), ((100, 100, 100), gen.von_neumann(3, 1), 36, None, 3),
     ((32, 32, 32), gen.moore(3, 1), 500, None, 1), ((64, 64, 64), gen.moore(3, 1), 48, None, 1)])
 def test_alltoall_rounds_of_part_sectors(stub_library, dims, offsets, m, periodic, want):
     """By block size, hops per block, and size of the collective against the last-level cache."""
@@ -140,3 +142,11 @@ def test_staged_rounds_between_planes_stream(stub_library):
     offsets = gen.random_distinct(5, -3, 3, 40, 5)
     got = _policies(stub_library.start((6, 6, 6, 6, 6), offsets, iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_STAGED, 48))
     assert ("shift", 1) in got and all(policy == 1 for _, policy in got)
+
+
+@pytest.mark.parametrize("op,m,want", [(iso.ISO_OP_ALLTOALL, 200, 0), (iso.ISO_OP_ALLTOALL, 100, 1), (iso.ISO_OP_ALLTOALL, 40, 2),
+                                       (iso.ISO_OP_ALLGATHER, 40, 0)])
+def test_staged_schedule_on_the_general_kernels(stub_library, op, m, want):
+    """Blocks that are no multiple of 16 bytes: the rounds that read or write rows."""
+    got = _policies(stub_library.start((20, 20, 20), gen.moore(3, 1), op, iso.ISO_ALG_COMBINED_STAGED, m))
+    assert ("shift", want) in got
