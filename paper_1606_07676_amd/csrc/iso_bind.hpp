@@ -296,12 +296,13 @@ KernelRef select_width(const Launch &l) {
 
 template <bool LDS, bool MESH>
 KernelRef select_block(const Launch &l) {
-    if (l.policy & kPlainStores) {
-        if (l.block_groups) return {(const void *)&block_round_kernel<LDS, MESH, kPlainStores, true>, &l.block};
-        return {(const void *)&block_round_kernel<LDS, MESH, kPlainStores>, &l.block};
-    }
-    if (l.block_groups) return {(const void *)&block_round_kernel<LDS, MESH, 0, true>, &l.block};
-    return {(const void *)&block_round_kernel<LDS, MESH, 0>, &l.block};
+    const auto form = [&](auto pol) -> KernelRef {
+        if (l.block_groups) return {(const void *)&block_round_kernel<LDS, MESH, pol(), true>, &l.block};
+        return {(const void *)&block_round_kernel<LDS, MESH, pol()>, &l.block};
+    };
+    if (l.policy == kStreamLoads) return form(std::integral_constant<int, kStreamLoads>());
+    if (l.policy == kPlainStores) return form(std::integral_constant<int, kPlainStores>());
+    return form(std::integral_constant<int, 0>());
 }
 
 inline KernelRef select_kernel(int vector_bytes, const Launch &l) {
@@ -885,8 +886,12 @@ private:
     //    Allgather: cached loads, streaming stores (the
     //   last launch with plain ones, one set of buffers and many in turn: 64^3, 16 B 45 -> 45 and 43 -> 49, 64^3 star,
     //   64 B 22 -> 23 and 23 -> 29, 300^2, 24 neighbours, 48 B 37 -> 34 and 33 -> 36).
-    //   Unequal blocks: cached loads, plain stores up to a quarter (4-byte stencil on 64^3 126 -> 119 us; at
-    //   133 MB 73 -> 93; streaming loads 20 % slower wherever the blocks fit the cache).
+    //   Unequal blocks: cached loads, and streaming ones in all-to-all rounds whose blocks all have the same number of
+    //   units (40^3, 1024 and 1023 B 1474 against 1487 us; 20^3, 256 and 255 B with plain stores 55 -> 44 and 57 ->
+    //   61).  Plain stores up to a quarter of the cache for rank-major blocks of less than two sectors and unequal or
+    //   single units (stencils 64^3, 4 B 151 -> 119 and 173 -> 152, 48^3, 9 B 89 -> 83 and 116 -> 112; larger blocks
+    //   gain only where one set is repeated: 24^3, 20 B 31 -> 28.5 and 40 -> 41, 20^3, 25 B 27 -> 25 and 34 -> 36.5;
+    //   slot-major 24^3, 16 B 16 -> 17.5 and 22 -> 25).
     //   The s-exchange writes whole rows and is indifferent to the stores; streaming loads where the send buffer
     //   of an all-to-all exceeds the cache (805 MB -4.6 %, 5.4 GB -3.8 %; 218 MB +17 %, an allgather +60 %) and no
     //   two blocks of a rank-major row share a 128-byte line (64 B +9 %, 100 B +7 %, 300 B +9 %).
@@ -907,7 +912,11 @@ private:
             return a2a && l.vector_dims && lines && bytes > above ? kStreamLoads : 0;
         }
         if (r.kind == ISO_ROUND_VECTOR) return 0;
-        if (l.kernel == kBlockKernel) return bytes <= kLastLevelCacheBytes / 4 ? kPlainStores : 0;
+        if (l.kernel == kBlockKernel) {
+            if (inf.block_bytes < 128 && l.block.equal_units <= 1 && !lay.slot_major && bytes <= kLastLevelCacheBytes / 4)
+                return kPlainStores;
+            return a2a && l.block.equal_units ? kStreamLoads : 0;
+        }
         const bool staged = pl.algorithm == ISO_ALG_COMBINED_STAGED;
         if (!a2a)
             return size0 < 64 && c.d >= 3 && !c.mesh && !lay.slot_major && bytes <= kLastLevelCacheBytes &&

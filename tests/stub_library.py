@@ -93,6 +93,19 @@ class StubLibrary:
             iso.iso_request_free(req)
         return out
 
+    def start_unequal(self, dims, offsets, alg, sizes, periodic=None):
+        """The kernels of one iso_start of an all-to-all over blocks of `sizes` bytes, packed rows."""
+        iso, p = self.iso, math.prod(dims)
+        comm = self.comm(dims, offsets, periodic)
+        displs, row = [sum(sizes[:i]) for i in range(len(sizes))], sum(sizes)
+        wsb = iso.iso_workspace_bytes_v(comm, iso.ISO_OP_ALLTOALL, alg, sizes)
+        with self.buffers(p * row, p * row, wsb) as (send, recv, work):
+            req = iso.iso_neighbor_alltoallv_init(send, sizes, displs, row, recv, sizes, displs, row, work, comm, alg,
+                                                  workspace_bytes=wsb)
+            out = self.launched(lambda: iso.iso_start(req, 0))
+            iso.iso_request_free(req)
+        return out
+
 
 class _Buffers:
     def __init__(self, lib, sizes):

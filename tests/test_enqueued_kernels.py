@@ -150,3 +150,16 @@ def test_staged_schedule_on_the_general_kernels(stub_library, op, m, want):
     """Blocks that are no multiple of 16 bytes: the rounds that read or write rows."""
     got = _policies(stub_library.start((20, 20, 20), gen.moore(3, 1), op, iso.ISO_ALG_COMBINED_STAGED, m))
     assert ("shift", want) in got
+
+
+@pytest.mark.parametrize("dims,sizes,periodic,want", [
+    ((20, 20, 20), [256 - i % 2 for i in range(26)], None, 1), ((20, 20, 20), [256 - i % 2 for i in range(26)], (0, 0, 0), 1),
+    ((20, 20, 20), gen.stencil_block_sizes(gen.moore(3, 1), 25), None, 0),
+    ((24, 24, 24), gen.stencil_block_sizes(gen.moore(3, 1), 20), None, 0),
+    ((64, 64, 64), gen.stencil_block_sizes(gen.moore(3, 1), 4), None, 2),
+    ((32, 32, 32), gen.stencil_block_sizes(gen.moore(3, 1), 9), (0, 0, 0), 2),
+    ((64, 64, 64), gen.stencil_block_sizes(gen.moore(3, 1), 9), None, 0)])
+def test_rounds_of_unequal_blocks(stub_library, dims, sizes, periodic, want):
+    """Streaming loads where all blocks have the same number of units, plain stores for small blocks near the cache."""
+    got = _policies(stub_library.start_unequal(dims, gen.moore(3, 1), iso.ISO_ALG_COMBINED_BYDIM, list(sizes), periodic))
+    assert got == {("block", want)}
