@@ -1090,13 +1090,18 @@ private:
     // pull form is 1 to 2 % faster), and where that many reads still fill the chip (16^3, 24 neighbours, 16 B, 16
     // workgroups: 10.0 -> 12.2 us).  What a workgroup writes then lies at different ranks, so every block has to
     // be part of a dense plane (slot-major 64^3, 300 B 600 -> 521 us) or whole 64-byte sectors, from 1 KiB on 32
-    // (200 B on rank-major rows 238 -> 284 us, 320 B 92 -> 74, 64 B level, 2080 B 130 -> 111).
+    // (200 B on rank-major rows 238 -> 284 us, 320 B 92 -> 74, 64 B level, 2080 B 130 -> 111).  A launch of two moves
+    // from one block (a star) saves one read of three accesses: whole 128-byte lines only (50^3, 64 B 13.6 -> 16.3 us,
+    // 32^3, 1056 B 51 -> 60, 256^2, 1056 B 69 -> 77; lines 50^3, 256 B 50 -> 43, 256^2, 512 B 34 -> 28).
     bool push_launch(Launch &l, const HostEntry *ents, uint32_t k, uint64_t per_entry) {
         if (k > kLdsEntries) return false;
         const uint32_t mask = size0 >= 1024 ? 31u : 63u;
+        bool lines = true;
         for (uint32_t q = 0; q < k; ++q) {
             const DevEntry &de = ents[q].de;
-            if (de.dst_stride != size0 && ((de.dst | de.dst_stride | size0) & mask)) return false;
+            if (de.dst_stride == size0) continue;
+            if ((de.dst | de.dst_stride | size0) & mask) return false;
+            lines = lines && ((de.dst | de.dst_stride | size0) & 127u) == 0;
         }
         std::vector<DevEntry> by_source;
         std::vector<uint32_t> first;
@@ -1112,6 +1117,7 @@ private:
         }
         const uint32_t n = (uint32_t)first.size();
         if (4 * n > 3 * k || per_entry * n < 256 * kThreads) return false;
+        if (k == 2 && !lines) return false;
         first.push_back(k);
         table.insert(table.end(), by_source.begin(), by_source.end());
         prefixes.insert(prefixes.end(), first.begin(), first.end());

@@ -163,3 +163,14 @@ def test_rounds_of_unequal_blocks(stub_library, dims, sizes, periodic, want):
     """Streaming loads where all blocks have the same number of units, plain stores for small blocks near the cache."""
     got = _policies(stub_library.start_unequal(dims, gen.moore(3, 1), iso.ISO_ALG_COMBINED_BYDIM, list(sizes), periodic))
     assert got == {("block", want)}
+
+
+@pytest.mark.parametrize("dims,offsets,m,layout,push", [
+    ((50, 50, 50), gen.von_neumann(3, 1), 64, 0, 0), ((32, 32, 32), gen.von_neumann(3, 1), 1056, 0, 0),
+    ((50, 50, 50), gen.von_neumann(3, 1), 128, 0, 3), ((50, 50, 50), gen.von_neumann(3, 1), 1024, 0, 3),
+    ((50, 50, 50), gen.von_neumann(3, 1), 100, 1, 3), ((32, 32, 32), gen.moore(3, 1), 192, 0, 2),
+    ((32, 32, 32), gen.moore(3, 1), 256, 0, 3), ((32, 32, 32), gen.moore(3, 1), 200, 0, 0)])
+def test_allgather_rounds_that_read_a_block_once(stub_library, dims, offsets, m, layout, push):
+    """How many of the three launches take the push form: two moves from one block only as whole lines or dense planes."""
+    got = _names(stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, iso.ISO_ALG_COMBINED_BYDIM, m, layout))
+    assert len(got) == 3 and got.count("shift_push_kernel") == push
