@@ -1170,7 +1170,11 @@ private:
     // decides between three forms.
     //   Rank-major: one contiguous eighth of the ranks per XCD (l.eighths) keeps a neighbourhood's blocks in that
     //   XCD's 4 MiB (64^3, 26 neighbours, 128 B 166 -> 144 us, 60 x 50 x 41, 200 B 129 -> 113, 256^2 star, 1 KiB
-    //   150 -> 128; send buffers that every L2 holds whole are up to 9 % faster with interleaved runs).  Where the
+    //   150 -> 128; send buffers that every L2 holds whole are up to 9 % faster with interleaved runs).  Not where a
+    //   run of tiles holds several times the ranks between the outermost neighbours (one dimension): its reads meet in
+    //   one L2 anyway, and the eight streams of a large launch lie at equal offsets (262144 ranks, 2 neighbours, 256 B
+    //   with many sets of buffers 42 us in runs, 51 in eighths; 131072, 512 B 42 and 52; 262144, 4 neighbours, 64 B 13.8
+    //   and 13.8, one set repeated 13.7 and 12.3).  Where the
     //   ranks between the outermost neighbours hold far more than an L2, push (8^5, 40 random neighbours, 4 KiB
     //   1421 -> 985 us, 1 KiB 344 -> 268; a window of 8.4 MiB still pulls faster, 512 against 652 us, unless what
     //   misses the L2 misses the last-level cache as well, 200^2 star, 8 KiB 989 -> 845).  Push writes the
@@ -1185,7 +1189,6 @@ private:
             if (l.vector_dims && sent > 7 * l2) l.vec.per = std::min(k, 4u);
             return;
         }
-        l.eighths = sent > l2;
         int64_t lo = 0, hi = 0;                                  // the neighbours' linear distances, shortest way round
         bool lines = true;
         for (uint32_t q = 0; q < k; ++q) {
@@ -1198,7 +1201,9 @@ private:
             hi = std::max(hi, at);
             lines = lines && ((ents[q].de.dst | ents[q].de.dst_stride | size0) & 127u) == 0;
         }
-        const uint64_t window = std::min<uint64_t>(p, (uint64_t)(hi - lo) + 1) * size0;
+        const uint64_t window_ranks = std::min<uint64_t>(p, (uint64_t)(hi - lo) + 1), window = window_ranks * size0;
+        const uint64_t run = uint64_t(128) * kThreads << min_log2;      // bytes written by a run of tiles (set_grid)
+        l.eighths = sent > l2 && 4 * window_ranks * k * size0 > run;
         if (l.vector_dims && lines && (window > 3 * l2 || (window > l2 && sent > kLastLevelCacheBytes))) {
             l.vec.per = std::min(k, 8u);
             l.eighths = false;

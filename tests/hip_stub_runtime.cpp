@@ -20,7 +20,8 @@ std::map<uintptr_t, size_t> g_allocs;          // live hipMalloc ranges
 long g_graphs = 0, g_execs = 0, g_launches = 0, g_graph_launches = 0, g_nodes = 0;
 alignas(256) unsigned char g_symbol_memory[64u << 20];      // what hipGetSymbolAddress hands out
 std::map<const void *, std::string> &kernel_names() { static std::map<const void *, std::string> m; return m; }
-std::vector<std::string> g_log;                // kernels launched since stub_log_clear
+std::vector<std::string> g_log;                // kernels launched since stub_log_clear, and their workgroups
+std::vector<unsigned> g_grids;
 struct StubGraph { int nodes; };
 struct StubExec { int nodes; };
 }  // namespace
@@ -82,10 +83,11 @@ hipError_t hipMemGetAddressRange(hipDeviceptr_t *base, size_t *size, hipDevicept
     return hipSuccess;
 }
 hipError_t hipGetSymbolAddress(void **ptr, const void *) { *ptr = g_symbol_memory; return hipSuccess; }
-hipError_t hipLaunchKernel(const void *func, dim3, dim3, void **, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void *func, dim3 grid, dim3, void **, size_t, hipStream_t) {
     std::lock_guard<std::mutex> lock(g_mu);
     ++g_launches;
     g_log.push_back(kernel_names()[func]);
+    g_grids.push_back(grid.x);
     return hipSuccess;
 }
 
@@ -119,8 +121,9 @@ long stub_live_graph_objects(void) { return g_graphs + g_execs; }
 long stub_kernel_launches(void) { return g_launches; }
 long stub_graph_launches(void) { return g_graph_launches; }
 long stub_graph_nodes(void) { return g_nodes; }
-void stub_log_clear(void) { std::lock_guard<std::mutex> lock(g_mu); g_log.clear(); }
+void stub_log_clear(void) { std::lock_guard<std::mutex> lock(g_mu); g_log.clear(); g_grids.clear(); }
 long stub_log_size(void) { std::lock_guard<std::mutex> lock(g_mu); return (long)g_log.size(); }
+long stub_log_grid(long i) { std::lock_guard<std::mutex> lock(g_mu); return (long)g_grids.at((size_t)i); }
 const char *stub_log_name(long i) { std::lock_guard<std::mutex> lock(g_mu); return g_log.at((size_t)i).c_str(); }
 }
 

@@ -51,6 +51,8 @@ class StubLibrary:
         self.lib.stub_device_alloc.argtypes = [ctypes.c_size_t]
         self.lib.stub_device_free.argtypes = [ctypes.c_void_p]
         self.lib.stub_log_size.restype = ctypes.c_long
+        self.lib.stub_log_grid.restype = ctypes.c_long
+        self.lib.stub_log_grid.argtypes = [ctypes.c_long]
         self.lib.stub_log_name.restype = ctypes.c_char_p
         self.lib.stub_log_name.argtypes = [ctypes.c_long]
         self.iso.load_library()
@@ -65,6 +67,7 @@ class StubLibrary:
         self.lib.stub_log_clear()
         call()
         names = [self.lib.stub_log_name(i).decode() for i in range(self.lib.stub_log_size())]
+        self.grids = [self.lib.stub_log_grid(i) for i in range(len(names))]      # workgroups of these launches
         if not names:
             return []
         out = subprocess.run(["c++filt"], input="\n".join(names), stdout=subprocess.PIPE, text=True, check=True).stdout

@@ -174,3 +174,12 @@ def test_allgather_rounds_that_read_a_block_once(stub_library, dims, offsets, m,
     """How many of the three launches take the push form: two moves from one block only as whole lines or dense planes."""
     got = _names(stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, iso.ISO_ALG_COMBINED_BYDIM, m, layout))
     assert len(got) == 3 and got.count("shift_push_kernel") == push
+
+
+@pytest.mark.parametrize("dims,offsets,m,eighths", [((250000,), gen.von_neumann(1, 1), 256, False), ((60, 50, 41), gen.moore(3, 1), 200, True),
+                                                    ((250, 250), gen.von_neumann(2, 1), 256, True), ((4099,), gen.von_neumann(1, 2), 8192, True)])
+def test_fused_allgather_takes_eighths_where_a_run_does_not_hold_the_neighbourhood(stub_library, dims, offsets, m, eighths):
+    got = _names(stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, iso.ISO_ALG_SX_FUSED, m))
+    assert got == ["vector_round_kernel"] or got == ["vector_round_uniform_kernel"]
+    tiles = -(-int(np.prod(dims)) * len(offsets) * (-(-m // 16)) // 256)
+    assert tiles % 1024 and stub_library.grids == [-(-tiles // 8) * 8 if eighths else -(-tiles // 1024) * 1024]
