@@ -532,13 +532,14 @@ private:
     // 13.4 -> 7.4, 5^4 star, 400 B 16.4 -> 7.4; allgather the same.  What it saves is 2.7 us of the host's time per
     // launch less; what it costs is that a workgroup's accesses are a column of units per rank, at best a few sectors
     // each, which most of the chip does not take part in.  The limits are 6144 sectors for one workgroup over all its
-    // hops (60^2, 64 B: 7200, 10.1 -> 12.7; 16^3, 16 B: 12288, 13.3 -> 16.4), and for all of them 24 Ki per launch
-    // that it saves, measured with buffers that the caches do not hold: 32^2, 12 neighbours, 16 and 100 B (24 and
-    // 48 Ki, one launch less) 9.7 -> 6.5 and 9.7 -> 9.6, 16^2 radius 1, 400 B (32 Ki) 9.0 -> 7.9, 16^2, 1000 B (64 Ki)
-    // 9.3 -> 10.5; two launches less: 8^3, 64 B (39 Ki) 12.9 -> 7.9, 10^3, 64 B (76 Ki) 13.2 -> 13.2, 8^3, 200 B
-    // (156 Ki) 13.0 -> 14.7.  Where a workgroup's own way is short the whole may be twice that: 16^2 star, 3000 B (48 Ki,
-    // one launch less) 8.0 -> 7.3, 8^3 star, 2000 B (96 Ki, two) 10.4 -> 8.9, 5^4 star, 1000 B (107 Ki, three)
-    // 16.5 -> 8.9.  A schedule of one launch gains nothing (4096, 16 B 6.5 -> 6.9).
+    // hops (60^2, 64 B: 7200, 10.1 -> 12.7; 16^3, 16 B: 12288, 13.3 -> 16.4), and for all of them 32 Ki per launch that
+    // it saves, measured with buffers that the caches do not hold, on hosts that take 2 to 2.7 us per launch: one launch
+    // less: 16^2 radius 1, 400 B (32 Ki) 8 to 9.7 -> 7.9, 40^2, 64 B (50 Ki) 8 to 9.4 -> 9.0, 16^2, 1000 B (64 Ki) 8 to
+    // 10 -> 10.5; two less: 8^3, 64 B (39 Ki) 10.4 to 12.9 -> 7.9, 10^3, 64 B (76 Ki) 10.4 to 12.9 -> 13.2.  Blocks of
+    // up to 32 bytes share sectors (10^3, 16 B 10.4 to 12.6 -> 7.8); columns of at most a sector of larger blocks that
+    // do not fill sectors lie across two (32^2, 100 B 8 to 9.8 -> 8.6, allgather 9.1).  Single hops wait for memory
+    // once: 64 Ki (16^2 star, 3000 B (48 Ki) 8.0 -> 7.3, 6^4 star, 500 B (111 Ki, three less) 12.6 -> 10.8, 12^3 star,
+    // 400 B (131 Ki, two less) 10.4 to 12.9 -> 11.1).  A schedule of one launch gains nothing (4096, 16 B 6.5 -> 6.9).
     bool chain_launch(uint64_t launches) {
         if (c.mesh || !uniform || !size0 || launches < 2 || p > kChainThreads * kChainUnitsPerLane ||
             c.d > (int)kChainDims || (size0 >> min_log2) > 0xFFFF)
@@ -611,9 +612,11 @@ private:
         }
         ca.first[n_chains] = (uint8_t)at;
         l.grid = n_chains * ca.groups;
-        const uint64_t sectors = p * ((ca.column * width + 63) / 64);
-        const uint64_t own = sectors * longest, per_launch = own <= 1280 ? 48 * 1024 : 24 * 1024;
-        if (own > 6144 || own * l.grid > (launches - 1) * per_launch) return false;
+        const uint64_t piece = ca.column * width, own = p * ((piece + 63) / 64) * longest;
+        uint64_t all = own * l.grid;
+        if (size0 <= 32) all /= 2;
+        else if (longest > 1 && size0 % 64 && piece <= 64) all *= 2;
+        if (own > 6144 || all > (launches - 1) * (longest > 1 ? 32 : 64) * 1024) return false;
         l.threads = std::min<uint32_t>(kChainThreads, (ca.n_units + 63) & ~63u);
         pending.push_back(pd);
         return true;
