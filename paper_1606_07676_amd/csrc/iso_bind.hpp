@@ -862,8 +862,8 @@ private:
     //   293 -> 185 and 301 -> 214; 300^2, 24 neighbours, 25 B 82 -> 48 and 91 -> 63), and blocks up to 256 B that make
     //   two hops and more, so that much of what is written is read again (32^3, 100 B 123 -> 74 and 130 -> 107, 8^4, 80
     //   neighbours, 100 B 64 -> 44 and 76 -> 60; fewer hops: 300^2 star, 100 B 23 -> 20 and 28 -> 31, 200^2, 8
-    //   neighbours, 200 B 46 -> 36 and 49 -> 56; larger blocks: 16^3, 400 B 41 -> 33 and 45 -> 48; small collectives:
-    //   60^2, 24 neighbours, 200 B 15.6 -> 14 and 18.5 -> 20.7).  Other blocks take cached loads there (100^2, 24
+    //   neighbours, 200 B 46 -> 36 and 49 -> 56; larger blocks: 16^3, 400 B 41 -> 33 and 45 -> 48; under a sixteenth of
+    //   the cache, a twelfth on a mesh: 16^3 mesh, 200 B 27 -> 23 and 31.5 -> 34).  Other blocks take cached loads there (100^2, 24
     //   neighbours, 300 B 53 -> 46 and 57 -> 57, 30^3 star, 600 B 47 -> 37 and 49 -> 48).  Between half and 9/8 of the
     //   cache: streaming loads, plain stores under a sector and for two hops and more under 512 B (64^3, 36 B 495 -> 336
     //   and 507 -> 395, 32^3, 300 B 281 -> 219 and 285 -> 262; 300^2 star, 400 B 61 -> 57 and 63 -> 85), else cached
@@ -879,7 +879,7 @@ private:
     //   47 -> 64; 32^3, 200 B 70 -> 57 and 82 -> 92; box 40^3, 160 B 106 -> 89 and 118 -> 131; 300^2, 24 neighbours,
     //   56 B 51 -> 39 and 61 -> 71).
     //   The staged schedule's kernels, all-to-all, one set of buffers and many in turn.  From an eighth of the cache (a
-    //   sixteenth at 16 bytes) up to half of it cached loads in both; the rounds store plainly if blocks do not fill
+    //   sixteenth at 16 bytes, a sixth from 128 bytes on) up to half of it cached loads in both; the rounds store plainly if blocks do not fill
     //   sectors (64^3, 16 B 116 -> 97 and 118 -> 107 us, 44^3, 32 B 68 -> 58 and 70 -> 69, 9^4, 80 neighbours, 176 B
     //   131 -> 86 and 133 -> 111; 32^3, 32 B, under an eighth, 27 -> 27.5 and 29.5 -> 31) and stream at 64 B (40^3 89 ->
     //   81 and 90.5 -> 89; plain 75 and 93.5).  Up to 7/4 of it the rounds still gain from cached loads (64^3, 32 B 196
@@ -890,8 +890,9 @@ private:
     //   last launch with plain ones, one set of buffers and many in turn: 64^3, 16 B 45 -> 45 and 43 -> 49, 64^3 star,
     //   64 B 22 -> 23 and 23 -> 29, 300^2, 24 neighbours, 48 B 37 -> 34 and 33 -> 36).
     //   Unequal blocks: cached loads, and streaming ones in all-to-all rounds whose blocks all have the same number of
-    //   units (40^3, 1024 and 1023 B 1474 against 1487 us; 20^3, 256 and 255 B with plain stores 55 -> 44 and 57 ->
-    //   61).  Plain stores up to a quarter of the cache for rank-major blocks of less than two sectors and unequal or
+    //   units, outside a sixteenth to all of the cache (40^3, 1024 and 1023 B 1487 -> 1474 us, 16^3, 64 and 63 B 18.6 ->
+    //   17.7 with many sets; inside 32^3, 100 and 99 B cached 127 -> 101 and 131 -> 119, not in the staged schedule; 20^3,
+    //   256 and 255 B with plain stores 55 -> 44 and 57 -> 61).  Plain stores up to a quarter of the cache for rank-major blocks of less than two sectors and unequal or
     //   single units (stencils 64^3, 4 B 151 -> 119 and 173 -> 152, 48^3, 9 B 89 -> 83 and 116 -> 112; larger blocks
     //   gain only where one set is repeated: 24^3, 20 B 31 -> 28.5 and 40 -> 41, 20^3, 25 B 27 -> 25 and 34 -> 36.5;
     //   slot-major 24^3, 16 B 16 -> 17.5 and 22 -> 25).
@@ -901,13 +902,13 @@ private:
     int cache_policy(const Launch &l, const Round &r) const {
         const uint64_t bytes = inf.delivered_bytes;
         const uint64_t above = kLastLevelCacheBytes * 9 / 8;      // what still gains from the cache
-        const bool a2a = op == ISO_OP_ALLTOALL;
+        const bool a2a = op == ISO_OP_ALLTOALL, staged = pl.algorithm == ISO_ALG_COMBINED_STAGED;
         if (l.kernel == kStagedRoundKernel || l.kernel == kDeliverKernel) {
             const bool round = l.kernel == kStagedRoundKernel, whole = size0 % 64 == 0;
             if (!a2a) return 0;
             if (bytes > kLastLevelCacheBytes * 7 / 4 || (whole && size0 >= 128)) return kStreamLoads;
             if (bytes > kLastLevelCacheBytes / 2) return round ? 0 : kStreamLoads;
-            if (bytes <= kLastLevelCacheBytes / (size0 < 32 ? 16 : 8)) return kStreamLoads;
+            if (bytes <= kLastLevelCacheBytes / (size0 < 32 ? 16 : size0 < 128 ? 8 : 6)) return kStreamLoads;
             return round && !whole ? kPlainStores : 0;
         }
         if (l.kernel == kVectorKernel) {
@@ -918,9 +919,9 @@ private:
         if (l.kernel == kBlockKernel) {
             if (inf.block_bytes < 128 && l.block.equal_units <= 1 && !lay.slot_major && bytes <= kLastLevelCacheBytes / 4)
                 return kPlainStores;
-            return a2a && l.block.equal_units ? kStreamLoads : 0;
+            const bool cached = bytes > kLastLevelCacheBytes / 16 && bytes <= kLastLevelCacheBytes && !staged;
+            return a2a && l.block.equal_units && !cached ? kStreamLoads : 0;
         }
-        const bool staged = pl.algorithm == ISO_ALG_COMBINED_STAGED;
         if (!a2a)
             return size0 < 64 && c.d >= 3 && !c.mesh && !lay.slot_major && bytes <= kLastLevelCacheBytes &&
                            (!staged || bytes > kLastLevelCacheBytes / 8)
@@ -932,7 +933,8 @@ private:
             if (bytes > kLastLevelCacheBytes / 2 && (size0 < 64 || (size0 < 512 && read_again)))
                 return kStreamLoads | kPlainStores;
             if (size0 < 64) return kPlainStores;
-            if (size0 < (staged ? 128u : 256u) && read_again && bytes > kLastLevelCacheBytes / 12) return kPlainStores;
+            if (size0 < (staged ? 128u : 256u) && read_again && bytes > kLastLevelCacheBytes / (c.mesh || staged ? 12 : 16))
+                return kPlainStores;
             return bytes > kLastLevelCacheBytes / 8 && (!c.mesh || size0 < 512) ? 0 : kStreamLoads;
         }
         return bytes <= kLastLevelCacheBytes / 32 ? kPlainStores : kStreamLoads;

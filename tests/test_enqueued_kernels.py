@@ -109,7 +109,8 @@ def test_alltoall_rounds_of_whole_sectors_stream_beyond_8_MiB(stub_library, dims
     ((64, 64, 64), gen.moore(3, 1), 20, None, 3), ((64, 64, 64), gen.moore(3, 1), 16, None, 2),
     ((300, 300), gen.moore(2, 2), 25, None, 2), ((100, 100), gen.moore(2, 1), 48, (0, 0), 2),
     ((32, 32, 32), gen.moore(3, 1), 100, None, 2), ((45, 37, 29), gen.moore(3, 1), 100, (0, 0, 0), 2),
-    ((16, 16, 16), gen.moore(3, 1), 100, None, 1), ((16, 16, 16), gen.moore(3, 1), 100, (0, 0, 0), 1),
+    ((16, 16, 16), gen.moore(3, 1), 100, None, 1), ((16, 16, 16), gen.moore(3, 1), 200, (0, 0, 0), 1),
+    ((20, 20, 20), gen.moore(3, 1), 100, None, 2),
     ((60, 60), gen.moore(2, 2), 200, None, 1), ((300, 300), gen.von_neumann(2, 1), 100, None, 0),
     ((200, 200), gen.moore(2, 1), 200, None, 0), ((200, 200), gen.moore(2, 1), 100, (0, 0), 1),
     ((16, 16, 16), gen.moore(3, 1), 400, None, 0), ((100, 100), gen.moore(2, 2), 300, None, 0),
@@ -133,7 +134,8 @@ def test_staged_allgather_streams_its_stores(stub_library, dims, offsets, m):
 
 @pytest.mark.parametrize("dims,offsets,m,rounds,last", [
     ((64, 64, 64), gen.moore(3, 1), 16, 2, 0), ((20, 20, 20), gen.moore(3, 1), 64, 1, 1), ((32, 32, 32), gen.moore(3, 1), 32, 1, 1),
-    ((44, 44, 44), gen.moore(3, 1), 32, 2, 0), ((9, 9, 9, 9), gen.moore(4, 1), 176, 2, 0), ((40, 40, 40), gen.moore(3, 1), 64, 0, 0), ((64, 64, 64), gen.moore(3, 1), 32, 0, 1),
+    ((44, 44, 44), gen.moore(3, 1), 32, 2, 0), ((9, 9, 9, 9), gen.moore(4, 1), 176, 2, 0),
+    ((18, 18, 18), gen.moore(3, 1), 240, 1, 1), ((40, 40, 40), gen.moore(3, 1), 64, 0, 0), ((64, 64, 64), gen.moore(3, 1), 32, 0, 1),
     ((32, 32, 32), gen.moore(3, 1), 128, 1, 1), ((20, 20, 20), gen.moore(3, 1), 256, 1, 1), ((64, 64, 64), gen.moore(3, 1), 80, 1, 1)])
 def test_staged_alltoall_by_block_size_and_size(stub_library, dims, offsets, m, rounds, last):
     got = _policies(stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_STAGED, m))
@@ -155,7 +157,8 @@ def test_staged_schedule_on_the_general_kernels(stub_library, op, m, want):
 
 
 @pytest.mark.parametrize("dims,sizes,periodic,want", [
-    ((20, 20, 20), [256 - i % 2 for i in range(26)], None, 1), ((20, 20, 20), [256 - i % 2 for i in range(26)], (0, 0, 0), 1),
+    ((40, 40, 40), [256 - i % 2 for i in range(26)], None, 1), ((40, 40, 40), [256 - i % 2 for i in range(26)], (0, 0, 0), 1),
+    ((16, 16, 16), [64 - i % 2 for i in range(26)], None, 1), ((20, 20, 20), [256 - i % 2 for i in range(26)], None, 0),
     ((20, 20, 20), gen.stencil_block_sizes(gen.moore(3, 1), 25), None, 0),
     ((24, 24, 24), gen.stencil_block_sizes(gen.moore(3, 1), 20), None, 0),
     ((64, 64, 64), gen.stencil_block_sizes(gen.moore(3, 1), 4), None, 2),
