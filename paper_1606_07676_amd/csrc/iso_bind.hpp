@@ -9,6 +9,7 @@
 #include <cstring>
 #include <initializer_list>
 #include <map>
+#include <memory>
 #include <numeric>
 #include <type_traits>
 #include <vector>
@@ -57,7 +58,7 @@ struct Launch {
     DeliverArgs deliver;
     StagedRoundArgs staged;
     uint32_t tile_units;   // the staged schedule's kernels: kTileUnits or kSmallTileUnits
-    ChainArgs chain;
+    const ChainArgs *chain;    // BoundRequest::chain
     uint32_t threads;      // per workgroup, where not kThreads (chain kernel)
 };
 
@@ -257,7 +258,7 @@ KernelRef select_vector(const Launch &l) {
 
 template <typename V, bool LDS, bool TAIL>
 KernelRef select_regular(const Launch &l) {
-    if (l.kernel == kChainKernel) return {(const void *)&chain_kernel<V, TAIL>, &l.chain};
+    if (l.kernel == kChainKernel) return {(const void *)&chain_kernel<V, TAIL>, l.chain};
     if (l.kernel == kVectorKernel) {
         if constexpr (LDS) {
             if (l.vector_dims == 3) return select_vector<V, 3, TAIL>(l);
@@ -342,6 +343,7 @@ struct BoundRequest {
     void *dev_table = nullptr;         // owned (hipMalloc) unless the request was bound to a StaticArena
     std::vector<Launch> launches;          // what iso_start_range counts through
     std::vector<Launch> start_launches;    // what iso_start enqueues instead, where that differs (see merge_rounds)
+    std::unique_ptr<ChainArgs> chain;      // arguments of the chain kernel, if it is taken
 
     const std::vector<Launch> &start_list() const { return start_launches.empty() ? launches : start_launches; }
 };
@@ -406,27 +408,27 @@ inline std::vector<uint32_t> mesh_interior_tiles(const Comm &c, bool slot_major,
     }
     const uint64_t n_tiles = (total + kThreads - 1) / kThreads;
     std::vector<uint32_t> bits((size_t)((n_tiles + 31) / 32), 0u);
-    for (uint64_t tl = 0; has_interior && tl < n_tiles; ++tl) {
-        const uint64_t u0 = tl * kThreads, u1 = std::min<uint64_t>(u0 + kThreads, total) - 1;
-        const uint64_t t0 = u0 / chunks, t1 = u1 / chunks;
-        uint64_t R0, R1;
-        if (slot_major) {                      // (entry, rank, chunk): one entry per interior tile
-            if (t0 / p != t1 / p) continue;
-            R0 = t0 % p;
-            R1 = t1 % p;
-        } else {                               // (rank, entry, chunk)
-            R0 = t0 / k;
-            R1 = t1 / k;
-        }
-        uint64_t rem = R0;
+    if (!has_interior) return bits;
+    // line by line along the last dimension: its interior ranks' units are one run (per entry, slot-major), and the
+    // tiles inside that run are interior (tile by tile the same took 11 ms for the lists of a 64^3 box)
+    const int last = c.d - 1;
+    const uint64_t n_last = (uint64_t)c.dims[last], lines = p / n_last;
+    const uint64_t unit_per_rank = slot_major ? chunks : chunks * k, planes = slot_major ? k : 1;
+    std::vector<int64_t> at((size_t)c.d, 0);                   // coordinates of the line, last dimension excluded
+    for (uint64_t line = 0; line < lines; ++line) {
         bool inside = true;
-        for (int j = c.d - 1; j >= 0 && inside; --j) {
-            const int64_t r = (int64_t)(rem % (uint64_t)c.dims[j]);
-            rem /= (uint64_t)c.dims[j];
-            const int64_t last = j == c.d - 1 ? r + (int64_t)(R1 - R0) : r;
-            inside = r >= in_lo[(size_t)j] && last < in_hi[(size_t)j];
+        for (int j = 0; j < last && inside; ++j) inside = at[(size_t)j] >= in_lo[(size_t)j] && at[(size_t)j] < in_hi[(size_t)j];
+        for (uint64_t e = 0; inside && e < planes; ++e) {
+            const uint64_t first_rank = line * n_last + (uint64_t)in_lo[(size_t)last], end_rank = line * n_last + (uint64_t)in_hi[(size_t)last];
+            const uint64_t u0 = (e * p + first_rank) * unit_per_rank, u1 = (e * p + end_rank) * unit_per_rank;
+            const uint64_t t0 = (u0 + kThreads - 1) / kThreads, t1 = u1 == total ? n_tiles : u1 / kThreads;
+            for (uint64_t tl = t0; tl < t1;) {
+                const uint64_t n = std::min<uint64_t>(32 - (tl & 31), t1 - tl);
+                bits[(size_t)(tl >> 5)] |= (n == 32 ? ~0u : ((1u << n) - 1)) << (tl & 31);
+                tl += n;
+            }
         }
-        if (inside) bits[(size_t)(tl >> 5)] |= 1u << (tl & 31);
+        for (int j = last - 1; j >= 0 && ++at[(size_t)j] == c.dims[j]; --j) at[(size_t)j] = 0;
     }
     return bits;
 }
@@ -463,20 +465,22 @@ public:
         int st = describe_and_check();
         if (st != ISO_SUCCESS || inf.delivered_bytes == 0) return st;       // nothing to move: no launches
         rounds_as_launched();
+        if ((st = host_entries()) != ISO_SUCCESS) return st;
         const bool merges = pl.algorithm == ISO_ALG_COMBINED;
         const bool chains = merges || pl.algorithm == ISO_ALG_COMBINED_BYDIM || pl.algorithm == ISO_ALG_COMBINED_STAGED;
-        if (arena && chains && (st = host_entries()) == ISO_SUCCESS && chain_launch(launches_of_rounds(merges))) return upload();
-        if (!arena || !merges) {
+        const uint64_t launches = launches_of_rounds(merges);
+        if (!arena) {                                    // the list that iso_start_range and graphs take
             if ((st = bind_rounds()) != ISO_SUCCESS) return st;
             n_listed = pending.size();
         }
-        if (!arena && chains && chain_launch(launches_of_rounds(merges))) return upload();
-        if (merges) {
-            const size_t n_rounds = bound_rounds.size();
+        if (chains && chain_launch(launches)) return upload();
+        if (merges && launches < bound_rounds.size()) {
             merge_rounds();
-            if ((arena || bound_rounds.size() < n_rounds) && (st = bind_rounds()) != ISO_SUCCESS) return st;
+            st = bind_rounds();
+        } else if (arena) {
+            st = bind_rounds();
         }
-        return upload();
+        return st == ISO_SUCCESS ? upload() : st;
     }
 
 private:
@@ -494,8 +498,9 @@ private:
     iso_request_info_t &inf;
     const WorkLayout wl;
 
-    std::vector<Round> bound_rounds;              // the plan's rounds as launched
-    std::vector<int> round_of;                    // their index in the plan
+    struct BoundRound { int kind, dim, of; const Round *whole; };
+    std::vector<BoundRound> bound_rounds;         // the plan's rounds as launched (of: its index there; whole: all its
+                                                  // entries, else those along `dim`)
     std::vector<std::vector<HostEntry>> rounds;   // their entries that move something
     bool uniform = true;                          // all these entries have `size0` bytes
     uint64_t size0 = 0;
@@ -508,8 +513,7 @@ private:
     size_t n_listed = 0;                          // of these: rq.launches; the rest are rq.start_launches
 
     int bind_rounds() {
-        int st = host_entries();
-        if (st != ISO_SUCCESS) return st;
+        int st;
         for (size_t ri = 0; ri < bound_rounds.size(); ++ri)
             for (size_t done = 0; done < rounds[ri].size();)
                 if ((st = next_launch(ri, done)) != ISO_SUCCESS) return st;
@@ -541,12 +545,15 @@ private:
     // once: 64 Ki (16^2 star, 3000 B (48 Ki) 8.0 -> 7.3, 6^4 star, 500 B (111 Ki, three less) 12.6 -> 10.8, 12^3 star,
     // 400 B (131 Ki, two less) 10.4 to 12.9 -> 11.1).  A schedule of one launch gains nothing (4096, 16 B 6.5 -> 6.9).
     bool chain_launch(uint64_t launches) {
-        if (c.mesh || !uniform || !size0 || launches < 2 || p > kChainThreads * kChainUnitsPerLane ||
+        if (c.mesh || !uniform || !size0 || launches < 2 || p > kChainThreads * kChainUnitsPerLane || s > kChainHops ||
             c.d > (int)kChainDims || (size0 >> min_log2) > 0xFFFF)
             return false;
         std::vector<std::vector<const HostEntry *>> chains;
         size_t n_hops = 0;
         if (op == ISO_OP_ALLTOALL) {
+            for (const std::vector<HostEntry> &round : rounds) n_hops += round.size();
+            if (n_hops > kChainHops) return false;
+            n_hops = 0;
             chains.resize(s);
             for (const std::vector<HostEntry> &round : rounds)
                 for (const HostEntry &he : round) chains[(size_t)he.neighbor].push_back(&he);
@@ -568,12 +575,14 @@ private:
         }
         for (const auto &chain : chains) n_hops += chain.size();
         if (!n_hops || n_hops > kChainHops) return false;
-        Pending pd{};
+        Pending pd;
+        pd.first_entry = pd.first_prefix = 0;
         std::memset(&pd.l, 0, sizeof(pd.l));
         Launch &l = pd.l;
         l.kernel = kChainKernel;
         l.lds_table = true;
-        ChainArgs &ca = l.chain;
+        auto args = std::make_unique<ChainArgs>();
+        ChainArgs &ca = *args;
         const uint64_t width = uint64_t(1) << min_log2;
         l.tail = (size0 & (width - 1)) != 0;
         ca.last_offset = size0 - width;
@@ -618,6 +627,8 @@ private:
         else if (longest > 1 && size0 % 64 && piece <= 64) all *= 2;
         if (own > 6144 || all > (launches - 1) * (longest > 1 ? 32 : 64) * 1024) return false;
         l.threads = std::min<uint32_t>(kChainThreads, (ca.n_units + 63) & ~63u);
+        rq.chain = std::move(args);
+        l.chain = rq.chain.get();
         pending.push_back(pd);
         return true;
     }
@@ -628,27 +639,28 @@ private:
     // 8.7 us), and rounds that read the same blocks or share memory lines meet in the caches (allgather
     // 60 x 50 x 41, 200 B 372 -> 241 us).  iso_start_range still runs the rounds one by one.
     void merge_rounds() {
-        std::vector<Round> merged;
-        std::vector<int> first_round;
+        size_t n = 0;
         for (size_t ri = 0; ri < bound_rounds.size(); ++ri) {
-            Round &r = bound_rounds[ri];
-            const bool joins = !merged.empty() && r.kind == ISO_ROUND_SHIFT && merged.back().kind == ISO_ROUND_SHIFT &&
-                               merged.back().dim == r.dim;
-            if (!joins) {
-                first_round.push_back(round_of[ri]);
-                merged.push_back(std::move(r));
+            const BoundRound &r = bound_rounds[ri];
+            const bool joins = n && r.kind == ISO_ROUND_SHIFT && bound_rounds[n - 1].kind == ISO_ROUND_SHIFT &&
+                               bound_rounds[n - 1].dim == r.dim;
+            if (joins) {
+                rounds[n - 1].insert(rounds[n - 1].end(), rounds[ri].begin(), rounds[ri].end());
             } else {
-                merged.back().entries.insert(merged.back().entries.end(), r.entries.begin(), r.entries.end());
+                if (n != ri) {
+                    bound_rounds[n] = r;
+                    rounds[n] = std::move(rounds[ri]);
+                }
+                ++n;
             }
         }
-        for (Round &r : merged)                   // destination blocks in order
-            std::stable_sort(r.entries.begin(), r.entries.end(),
-                             [&](const iso_plan_entry_t &a, const iso_plan_entry_t &b) {
-                                 if (op == ISO_OP_ALLTOALL) return a.neighbor < b.neighbor;
-                                 return a.dst_buf != b.dst_buf ? a.dst_buf < b.dst_buf : a.dst_slot < b.dst_slot;
-                             });
-        bound_rounds = std::move(merged);
-        round_of = std::move(first_round);
+        bound_rounds.resize(n);
+        rounds.resize(n);
+        for (std::vector<HostEntry> &ents : rounds)                   // destination blocks in order
+            std::stable_sort(ents.begin(), ents.end(), [&](const HostEntry &a, const HostEntry &b) {
+                if (op == ISO_OP_ALLTOALL) return a.neighbor < b.neighbor;
+                return a.dst_buf != b.dst_buf ? a.dst_buf < b.dst_buf : a.dst_slot < b.dst_slot;
+            });
     }
 
     uint64_t entry_size(const iso_plan_entry_t &e) const {
@@ -734,20 +746,15 @@ private:
                     whole = lay.size[i] == m0 && lay.recv_displ[i] == i * m0 && r.entries[i].dst_slot == (int)i;
             }
             if (whole) {
-                bound_rounds.push_back(r);
-                round_of.push_back((int)ri);
+                bound_rounds.push_back({r.kind, r.dim, (int)ri, &r});
                 continue;
             }
-            for (int j = -1; j < c.d; ++j) {
-                Round part;
-                part.kind = j < 0 ? ISO_ROUND_SELF : ISO_ROUND_SHIFT;
-                part.dim = j;
+            for (int j = -1; j < c.d; ++j)
                 for (const iso_plan_entry_t &pe : r.entries)
-                    if (pe.dim == j) part.entries.push_back(pe);
-                if (part.entries.empty()) continue;
-                bound_rounds.push_back(std::move(part));
-                round_of.push_back((int)ri);
-            }
+                    if (pe.dim == j) {
+                        bound_rounds.push_back({j < 0 ? ISO_ROUND_SELF : ISO_ROUND_SHIFT, j, (int)ri, nullptr});
+                        break;
+                    }
         }
     }
 
@@ -756,8 +763,11 @@ private:
         rounds.assign(bound_rounds.size(), {});
         bool first = true;
         for (size_t ri = 0; ri < bound_rounds.size(); ++ri) {
-            const Round &r = bound_rounds[ri];
-            for (const iso_plan_entry_t &pe : r.entries) {
+            const BoundRound &r = bound_rounds[ri];
+            const std::vector<iso_plan_entry_t> &entries = pl.rounds[(size_t)r.of].entries;
+            rounds[ri].reserve(entries.size());
+            for (const iso_plan_entry_t &pe : entries) {
+                if (!r.whole && pe.dim != r.dim) continue;
                 HostEntry he{};
                 he.size = entry_size(pe);
                 he.dim = pe.dim;
@@ -802,14 +812,14 @@ private:
 
     // The next launch of round `ri`: as many of its entries from `done` on as one launch takes.
     int next_launch(size_t ri, size_t &done) {
-        const Round &r = bound_rounds[ri];
+        const BoundRound &r = bound_rounds[ri];
         const std::vector<HostEntry> &ents = rounds[ri];
-        Pending pd{};
+        Pending pd;
         pd.first_entry = table.size();
         pd.first_prefix = prefixes.size();
         Launch &l = pd.l;
         std::memset(&l, 0, sizeof(l));
-        l.round = round_of[ri];
+        l.round = r.of;
         uint32_t k = 0;
         uint64_t total = 0;
         // staged schedule, last launch: whole receive rows through LDS (left as one round only for
@@ -899,7 +909,7 @@ private:
     //   The s-exchange writes whole rows and is indifferent to the stores; streaming loads where the send buffer
     //   of an all-to-all exceeds the cache (805 MB -4.6 %, 5.4 GB -3.8 %; 218 MB +17 %, an allgather +60 %) and no
     //   two blocks of a rank-major row share a 128-byte line (64 B +9 %, 100 B +7 %, 300 B +9 %).
-    int cache_policy(const Launch &l, const Round &r) const {
+    int cache_policy(const Launch &l, const BoundRound &r) const {
         const uint64_t bytes = inf.delivered_bytes;
         const uint64_t above = kLastLevelCacheBytes * 9 / 8;      // what still gains from the cache
         const bool a2a = op == ISO_OP_ALLTOALL, staged = pl.algorithm == ISO_ALG_COMBINED_STAGED;
@@ -973,7 +983,7 @@ private:
     }
 
     // Staged schedule, a round of small equal blocks: re-tiled through LDS.
-    void staged_round_launch(Pending &pd, const Round &r, const std::vector<HostEntry> &ents, uint32_t &k,
+    void staged_round_launch(Pending &pd, const BoundRound &r, const std::vector<HostEntry> &ents, uint32_t &k,
                              uint64_t &total) {
         Launch &l = pd.l;
         l.kernel = kStagedRoundKernel;
@@ -1006,7 +1016,7 @@ private:
 
     // Regular blocks: every entry has `chunks` units of the request's common width (on a mesh: shift
     // rounds and same-rank copies; its s-exchange uses the block kernel).
-    int regular_launch(Pending &pd, const Round &r, const std::vector<HostEntry> &ents, size_t done,
+    int regular_launch(Pending &pd, const BoundRound &r, const std::vector<HostEntry> &ents, size_t done,
                        bool all_planes, uint32_t &k, uint64_t &total) {
         Launch &l = pd.l;
         const uint64_t width = uint64_t(1) << min_log2;
@@ -1035,8 +1045,8 @@ private:
             // several blocks of a rank-major row to a line, read by ranks that lie near each other: one eighth of the
             // ranks per XCD keeps the line in its L2 (64^3, 16 B 46.5 -> 38 us, 28 B 79 -> 73, 50^3 star, 20 B 10.2 ->
             // 5.9; 40 B 105 -> 112)
-            if (op == ISO_OP_ALLTOALL && !l.vec.entry_major && r.entries.size() > 1) l.eighths = size0 <= 32;
-            if (op == ISO_OP_ALLGATHER && r.entries.size() > 1) allgather_order(l, ents.data() + done, k);
+            if (op == ISO_OP_ALLTOALL && !l.vec.entry_major && ents.size() > 1) l.eighths = size0 <= 32;
+            if (op == ISO_OP_ALLGATHER && ents.size() > 1) allgather_order(l, ents.data() + done, k);
             if (l.vec.per) total = per_entry * ((k + l.vec.per - 1) / l.vec.per);
             if (l.vector_dims) return ISO_SUCCESS;
         } else if (l.kernel == kMeshShiftKernel) {
@@ -1216,7 +1226,7 @@ private:
     }
 
     // Irregular blocks, or a mesh's s-exchange: as many entries as fit the 32-bit unit index.
-    int block_launch(Pending &pd, const Round &r, const std::vector<HostEntry> &ents, size_t done, uint32_t &k,
+    int block_launch(Pending &pd, const BoundRound &r, const std::vector<HostEntry> &ents, size_t done, uint32_t &k,
                      uint64_t &total) {
         Launch &l = pd.l;
         l.kernel = kBlockKernel;
@@ -1298,12 +1308,13 @@ private:
             if ((st = store_table(*arena, entry_bytes, c.can.data(), off_used)) != ISO_SUCCESS) return st;
             if ((st = store_table(*arena, entry_bytes + off_bytes, prefixes.data(), pre_bytes)) != ISO_SUCCESS) return st;
         } else if (entry_bytes + off_bytes + pre_bytes) {
-            ISO_HIP_TRY(hipMalloc(&rq.dev_table, entry_bytes + off_bytes + pre_bytes));
+            std::vector<char> host(entry_bytes + off_bytes + pre_bytes);
+            if (entry_bytes) std::memcpy(host.data(), table.data(), entry_bytes);
+            if (off_used) std::memcpy(host.data() + entry_bytes, c.can.data(), off_used);
+            if (pre_bytes) std::memcpy(host.data() + entry_bytes + off_bytes, prefixes.data(), pre_bytes);
+            ISO_HIP_TRY(hipMalloc(&rq.dev_table, host.size()));
             dev = (char *)rq.dev_table;
-            if (entry_bytes) ISO_HIP_TRY(hipMemcpy(dev, table.data(), entry_bytes, hipMemcpyHostToDevice));
-            if (off_used) ISO_HIP_TRY(hipMemcpy(dev + entry_bytes, c.can.data(), off_used, hipMemcpyHostToDevice));
-            if (pre_bytes)
-                ISO_HIP_TRY(hipMemcpy(dev + entry_bytes + off_bytes, prefixes.data(), pre_bytes, hipMemcpyHostToDevice));
+            ISO_HIP_TRY(hipMemcpy(dev, host.data(), host.size(), hipMemcpyHostToDevice));
         }
         const DevEntry *dev_entries = (const DevEntry *)dev;
         const uint32_t *dev_offsets = (const uint32_t *)(dev + entry_bytes);

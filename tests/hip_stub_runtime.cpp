@@ -17,7 +17,7 @@
 namespace {
 std::mutex g_mu;
 std::map<uintptr_t, size_t> g_allocs;          // live hipMalloc ranges
-long g_graphs = 0, g_execs = 0, g_launches = 0, g_graph_launches = 0, g_nodes = 0;
+long g_copies = 0, g_graphs = 0, g_execs = 0, g_launches = 0, g_graph_launches = 0, g_nodes = 0;
 alignas(256) unsigned char g_symbol_memory[64u << 20];      // what hipGetSymbolAddress hands out
 std::map<const void *, std::string> &kernel_names() { static std::map<const void *, std::string> m; return m; }
 std::vector<std::string> g_log;                // kernels launched since stub_log_clear, and their workgroups
@@ -69,6 +69,7 @@ hipError_t hipFree(void *ptr) {
     return hipSuccess;
 }
 hipError_t hipMemcpy(void *dst, const void *src, size_t bytes, hipMemcpyKind) {
+    ++g_copies;
     std::memcpy(dst, src, bytes);
     return hipSuccess;
 }
@@ -121,6 +122,7 @@ long stub_live_graph_objects(void) { return g_graphs + g_execs; }
 long stub_kernel_launches(void) { return g_launches; }
 long stub_graph_launches(void) { return g_graph_launches; }
 long stub_graph_nodes(void) { return g_nodes; }
+long stub_copies(void) { return g_copies; }
 void stub_log_clear(void) { std::lock_guard<std::mutex> lock(g_mu); g_log.clear(); g_grids.clear(); }
 long stub_log_size(void) { std::lock_guard<std::mutex> lock(g_mu); return (long)g_log.size(); }
 long stub_log_grid(long i) { std::lock_guard<std::mutex> lock(g_mu); return (long)g_grids.at((size_t)i); }

@@ -15,24 +15,39 @@ PACKAGE = os.path.join(ROOT, "paper_1606_07676_amd")
 CLANGXX = "/opt/rocm/llvm/bin/clang++"
 
 
-def build(directory):
+def compile_host(directory, sources):
+    """(source, is HIP) -> object files for the host only"""
     objs = []
     inc = ["-I", os.path.join(ROOT, "include"), "-I", os.path.join(PACKAGE, "csrc")]
     common = ["-O1", "-std=c++17", "-fPIC"]
-    for src, hip in ((os.path.join(PACKAGE, "csrc", "iso_api.hip"), True),
-                     (os.path.join(PACKAGE, "csrc", "iso_plan.cpp"), False),
-                     (os.path.join(ROOT, "tests", "hip_stub_runtime.cpp"), False)):
+    for src, hip in sources:
         obj = os.path.join(directory, os.path.basename(src) + ".o")
         if hip:
-            cmd = ["hipcc", "--cuda-host-only", "-fuse-cuid=none", *common, *inc, "-c", src, "-o", obj]
+            cmd = ["hipcc", "-x", "hip", "--cuda-host-only", "-fuse-cuid=none", *common, *inc, "-c", src, "-o", obj]
         else:
             cmd = [CLANGXX, *common, *inc, "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-c", src, "-o", obj]
         proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         assert proc.returncode == 0, proc.stdout[-3000:]
         objs.append(obj)
+    return objs
+
+
+PLAN, RUNTIME = os.path.join(PACKAGE, "csrc", "iso_plan.cpp"), os.path.join(ROOT, "tests", "hip_stub_runtime.cpp")
+
+
+def build(directory):
+    objs = compile_host(directory, [(os.path.join(PACKAGE, "csrc", "iso_api.hip"), True), (PLAN, False), (RUNTIME, False)])
     lib = os.path.join(directory, "libiso_on_stub.so")
     subprocess.run([CLANGXX, "-shared", "-Wl,-Bsymbolic", *objs, "-o", lib], check=True)
     return lib
+
+
+def build_driver(directory, source):
+    """An executable from a test driver that includes the library's host code."""
+    objs = compile_host(directory, [(os.path.join(ROOT, "tests", source), True), (PLAN, False), (RUNTIME, False)])
+    exe = os.path.join(directory, os.path.splitext(source)[0])
+    subprocess.run([CLANGXX, *objs, "-o", exe], check=True)
+    return exe
 
 
 class StubLibrary:

@@ -1,4 +1,7 @@
 """Which kernels a call enqueues, on the CPU: the library's host code over a stand-in HIP runtime."""
+import subprocess
+import time
+
 import numpy as np
 import pytest
 
@@ -188,3 +191,28 @@ def test_fused_allgather_takes_eighths_where_a_run_does_not_hold_the_neighbourho
     assert got == ["vector_round_kernel"] or got == ["vector_round_uniform_kernel"]
     tiles = -(-int(np.prod(dims)) * len(offsets) * (-(-m // 16)) // 256)
     assert tiles % 1024 and stub_library.grids == [-(-tiles // 8) * 8 if eighths else -(-tiles // 1024) * 1024]
+
+
+def test_interior_tiles_of_mesh_launches(tmp_path):
+    import stub_library as sl
+    exe = sl.build_driver(str(tmp_path), "mesh_tiles_driver.cpp")
+    proc = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert proc.returncode == 0 and "mesh tiles ok" in proc.stdout, proc.stdout
+
+
+@pytest.mark.parametrize("alg", [iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM])
+def test_binding_a_large_box_is_no_walk_over_its_tiles(stub_library, alg):
+    """Init binds two launch lists (rounds one by one, and as iso_start takes them): one copy to the device for both,
+    and milliseconds less than a walk over the tiles of a 64^3 box takes (22 ms for both lists; here 0.4)."""
+    dims, offsets, m = (64, 64, 64), gen.moore(3, 1), 200
+    p, s, niso = 64 ** 3, len(offsets), stub_library.iso
+    comm = stub_library.comm(dims, offsets, (0, 0, 0))
+    with stub_library.buffers(p * s * m, p * s * m, niso.iso_workspace_bytes(comm, 0, alg, m)) as bufs:
+        best = 1.0
+        for _ in range(5):
+            copies, t0 = stub_library.lib.stub_copies(), time.perf_counter()
+            req = stub_library.request(comm, dims, s, 0, alg, m, 0, bufs)
+            best = min(best, time.perf_counter() - t0)
+            assert stub_library.lib.stub_copies() == copies + 1
+            niso.iso_request_free(req)
+    assert best < 4e-3, best
