@@ -177,9 +177,10 @@ typedef struct {
     int32_t op, algorithm;
     int32_t launches;            /* length of the launch list: what iso_start_range counts
                                   * through and a graph holds.  iso_start enqueues as many
-                                  * kernels, or fewer: ISO_ALG_COMBINED takes the rounds of a
-                                  * dimension together, small collectives of the three combined
-                                  * algorithms run all their rounds in one kernel             */
+                                  * kernels, or fewer (iso_request_start_info): ISO_ALG_COMBINED
+                                  * takes the rounds of a dimension together, small collectives
+                                  * of the three combined algorithms run all their rounds in one
+                                  * kernel                                                  */
     int32_t vector_bytes;        /* width of the loads/stores: the largest power of two that is
                                   * at most 16 and at most the smallest non-empty block; buffer
                                   * addresses need no alignment                               */
@@ -191,6 +192,14 @@ typedef struct {
     uint64_t delivered_bytes;    /* p*s*m                                                   */
     uint64_t workspace_bytes;    /* workspace the request uses                              */
 } iso_request_info_t;
+
+typedef struct {
+    int32_t kernels;             /* kernels                                                 */
+    int32_t reserved;
+    uint64_t bytes_read;         /* blocks they read, bytes: a block that several moves of one
+                                  * kernel read counts once for that kernel                 */
+    uint64_t bytes_written;      /* blocks they write, bytes                                */
+} iso_start_info_t;
 
 /* ---- neighbourhood set-up (Section 2, set-up listing) ----------------------
  * dims:       host, d ints, every p_j >= 1, 1 <= d <= ISO_MAX_DIMS, prod < 2^31.
@@ -382,6 +391,8 @@ int iso_request_set_graph(iso_request_t req, int enable);
  * on several streams synchronises the earlier streams itself. */
 int iso_wait(iso_request_t req);
 int iso_request_info(iso_request_t req, iso_request_info_t *info);
+/* What one iso_start of the request enqueues (with a graph: what the graph holds). */
+int iso_request_start_info(iso_request_t req, iso_start_info_t *info);
 /* Returns the plan the request executes (owned by the request; do not free). */
 int iso_request_plan(iso_request_t req, iso_plan_t *plan);
 /* Waits for the request's most recent start (as iso_wait does), then frees the

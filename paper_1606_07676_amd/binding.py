@@ -70,6 +70,11 @@ class iso_request_info_t(ctypes.Structure):
                 ("delivered_bytes", ctypes.c_uint64), ("workspace_bytes", ctypes.c_uint64)]
 
 
+class iso_start_info_t(ctypes.Structure):
+    _fields_ = [("kernels", ctypes.c_int32), ("reserved", ctypes.c_int32),
+                ("bytes_read", ctypes.c_uint64), ("bytes_written", ctypes.c_uint64)]
+
+
 def _struct_dict(st):
     out = {}
     for name, _ in st._fields_:
@@ -121,6 +126,7 @@ _PROTOTYPES = {
     "iso_request_set_graph": ([_VP, _I], _I),
     "iso_wait": ([_VP], _I),
     "iso_request_info": ([_VP, ctypes.POINTER(iso_request_info_t)], _I),
+    "iso_request_start_info": ([_VP, ctypes.POINTER(iso_start_info_t)], _I),
     "iso_request_plan": ([_VP, ctypes.POINTER(_VP)], _I),
     "iso_request_free": ([ctypes.POINTER(_VP)], _I),
     "iso_error_string": ([_I], ctypes.c_char_p),
@@ -497,6 +503,12 @@ def iso_wait(req):
 def iso_request_info(req):
     info = iso_request_info_t()
     _check(load_library().iso_request_info(req.handle, ctypes.byref(info)), "iso_request_info")
+    return _struct_dict(info)
+
+
+def iso_request_start_info(req):
+    info = iso_start_info_t()
+    _check(load_library().iso_request_start_info(req.handle, ctypes.byref(info)), "iso_request_start_info")
     return _struct_dict(info)
 
 

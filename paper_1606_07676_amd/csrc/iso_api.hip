@@ -640,6 +640,18 @@ int iso_request_info(iso_request_t req, iso_request_info_t *info) {
     return ISO_SUCCESS;
 }
 
+int iso_request_start_info(iso_request_t req, iso_start_info_t *info) {
+    if (!req || !info) return ISO_ERR_ARG;
+    const std::vector<iso::Launch> &list = req->use_graph ? req->b.launches : req->b.start_list();
+    *info = iso_start_info_t{};
+    info->kernels = (int32_t)list.size();
+    for (const iso::Launch &l : list) {
+        info->bytes_read += l.bytes_read;
+        info->bytes_written += l.bytes_written;
+    }
+    return ISO_SUCCESS;
+}
+
 int iso_request_plan(iso_request_t req, iso_plan_t *plan) {
     return guarded([&]() -> int {
         if (!req || !plan) return ISO_ERR_ARG;

@@ -59,6 +59,7 @@ struct Launch {
     StagedRoundArgs staged;
     uint32_t tile_units;   // the staged schedule's kernels: kTileUnits or kSmallTileUnits
     const ChainArgs *chain;    // BoundRequest::chain
+    uint64_t bytes_read, bytes_written;   // of blocks (see iso_start_info_t)
     uint32_t threads;      // per workgroup, where not kThreads (chain kernel)
 };
 
@@ -627,6 +628,18 @@ private:
         else if (longest > 1 && size0 % 64 && piece <= 64) all *= 2;
         if (own > 6144 || all > (launches - 1) * (longest > 1 ? 32 : 64) * 1024) return false;
         l.threads = std::min<uint32_t>(kChainThreads, (ca.n_units + 63) & ~63u);
+        std::vector<uint64_t> sources, targets;
+        for (const auto &chain : chains)
+            for (const HostEntry *he : chain) {
+                sources.push_back(he->de.src);
+                targets.push_back(he->de.dst);
+            }
+        for (std::vector<uint64_t> *v : {&sources, &targets}) {
+            std::sort(v->begin(), v->end());
+            v->erase(std::unique(v->begin(), v->end()), v->end());
+        }
+        l.bytes_read = p * size0 * sources.size();
+        l.bytes_written = p * size0 * targets.size();
         rq.chain = std::move(args);
         l.chain = rq.chain.get();
         pending.push_back(pd);
@@ -855,10 +868,22 @@ private:
             src_sides.push_back(Side{he.de.src, he.de.src_stride, he.size});
             dst_sides.push_back(Side{he.de.dst, he.de.dst_stride, he.size});
         }
+        describe_bytes(l, ents.data() + done, k);
         set_grid(l, (uint32_t)total, l.shift.k_all ? l.shift.k : k, l.eighths || page_resonant(src_sides) || page_resonant(dst_sides));
         pending.push_back(pd);
         done += k;
         return ISO_SUCCESS;
+    }
+
+    // Only an allgather's moves share sources.
+    void describe_bytes(Launch &l, const HostEntry *ents, uint32_t k) const {
+        for (uint32_t q = 0; q < k; ++q) l.bytes_written += p * ents[q].size;
+        l.bytes_read = l.bytes_written;
+        if (op == ISO_OP_ALLTOALL || !k) return;
+        std::vector<uint64_t> sources(k);
+        for (uint32_t q = 0; q < k; ++q) sources[q] = ents[q].de.src;
+        std::sort(sources.begin(), sources.end());
+        l.bytes_read = p * ents[0].size * (uint64_t)(std::unique(sources.begin(), sources.end()) - sources.begin());
     }
 
     // Cache policy of a launch whose kernel and arguments are set.  What decides is whether the blocks of the

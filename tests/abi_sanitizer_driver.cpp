@@ -77,6 +77,7 @@ int main() {
                 int ist = (op == 0 ? iso_neighbor_alltoall_init : iso_neighbor_allgather_init)(send_d, recv_d, m, work_d, wsb, comm, alg, &rq);
                 REQUIRE(ist == ISO_SUCCESS);
                 iso_request_info_t ri; REQUIRE(iso_request_info(rq, &ri) == ISO_SUCCESS);
+                iso_start_info_t si; REQUIRE(iso_request_start_info(rq, &si) == ISO_SUCCESS && si.kernels <= ri.launches);
                 iso_plan_t pl; REQUIRE(iso_request_plan(rq, &pl) == ISO_SUCCESS);
                 iso_plan_info_t pi; REQUIRE(iso_plan_info(pl, &pi) == ISO_SUCCESS);
                 for (int r = 0; r < pi.launches; ++r) { iso_round_info_t rinfo; REQUIRE(iso_plan_round(pl, r, &rinfo) == ISO_SUCCESS); std::vector<iso_plan_entry_t> ent(rinfo.n_entries + 1); REQUIRE(iso_plan_entries(pl, r, ent.data(), rinfo.n_entries) == ISO_SUCCESS); }

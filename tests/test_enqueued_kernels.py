@@ -216,3 +216,34 @@ def test_binding_a_large_box_is_no_walk_over_its_tiles(stub_library, alg):
             assert stub_library.lib.stub_copies() == copies + 1
             niso.iso_request_free(req)
     assert best < 4e-3, best
+
+
+@pytest.mark.parametrize("op", [iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER])
+@pytest.mark.parametrize("alg", [0, 1, 2, 3, 4, 5])
+@pytest.mark.parametrize("dims,offsets,m", [((8, 8), gen.moore(2, 1), 32), ((32, 32, 32), gen.moore(3, 1), 256), ((12, 13), gen.von_neumann(2, 2), 4000)])
+def test_start_info_says_what_a_start_enqueues(stub_library, dims, offsets, m, alg, op):
+    """The number of kernels, and the bytes of the plan's blocks: every move writes one; an allgather's moves out of one
+    block count it once per kernel."""
+    niso, p, s = stub_library.iso, int(np.prod(dims)), len(offsets)
+    comm = stub_library.comm(dims, offsets)
+    with stub_library.buffers(p * m * s, p * s * m, niso.iso_workspace_bytes(comm, op, alg, m)) as bufs:
+        req = stub_library.request(comm, dims, s, op, alg, m, 0, bufs)
+        info, plan = niso.iso_request_info(req), niso.iso_request_plan(req)
+        rounds = [niso.iso_plan_entries(plan, q) for q in range(niso.iso_plan_info(plan)["launches"])]
+        moves = [e for r in rounds for e in r]
+        for graph in (niso.ISO_GRAPH_OFF, niso.ISO_GRAPH_CHAIN):
+            niso.iso_request_set_graph(req, graph)
+            got = niso.iso_request_start_info(req)
+            if graph:
+                assert got["kernels"] == info["launches"]
+            else:
+                assert got["kernels"] == len(stub_library.launched(lambda: niso.iso_start(req, 0)))
+            if op == iso.ISO_OP_ALLTOALL:
+                assert got["bytes_read"] == info["bytes_read"]
+            else:
+                sources = len({(e["src_buf"], e["src_slot"]) for e in moves})
+                assert sources * p * m <= got["bytes_read"] <= info["bytes_read"]
+                if got["kernels"] == 1:
+                    assert got["bytes_read"] == sources * p * m
+            assert got["bytes_written"] == info["bytes_written"]
+        niso.iso_request_free(req)
