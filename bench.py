@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Benchmark of the hot path on one MI355X: persistent isomorphic all-to-all and
 allgather with the message-combining (torus-direct) schedule, one kernel per
-round, on synthetic workloads held entirely in HBM.
+dimension, on synthetic workloads held entirely in HBM.
 
 One step = one iso_start of every collective the workload names (e.g. config 5:
 all-to-all, then allgather), enqueued back to back on one stream.  Inputs are
@@ -167,28 +167,11 @@ def median(xs):
     return xs[n // 2] if n % 2 else 0.5 * (xs[n // 2 - 1] + xs[n // 2])
 
 
-def kernels_per_start(iso, req, graph=False):
-    """Kernels that one iso_start of `req` enqueues (workloads of bandwidth size): the request's launch list,
-    except that the message-combining schedule takes the rounds of one dimension together (a graph replays
-    the list).  Small collectives run in fewer."""
-    info = iso.iso_request_info(req)
-    n = info["launches"]
-    if info["algorithm"] != iso.ISO_ALG_COMBINED or graph:
-        return n
-    plan = iso.iso_request_plan(req)
-    if iso.iso_plan_info(plan)["launches"] != n:       # a round was split over several launches
-        return n
-    rounds = [iso.iso_plan_round(plan, q) for q in range(n)]
-    return sum(1 for q, r in enumerate(rounds)
-               if q == 0 or r["kind"] != iso.ISO_ROUND_SHIFT or (rounds[q - 1]["kind"], rounds[q - 1]["dim"])
-               != (r["kind"], r["dim"]))
-
-
 def small_sweep():
     """Section 4's setting carried over: Moore neighbourhoods on tori of about 500 processes,
     block sizes from a few bytes to 2 KiB.  Here every size is bound by the per-launch cost, the
-    GPU's counterpart of the message start-up latency, so the time follows the number of launches:
-    one per dimension for the message-combining schedules, s for the straightforward algorithm."""
+    GPU's counterpart of the message start-up latency, so the time follows the number of launches: one,
+    or one per dimension, for the message-combining schedules, s for the straightforward algorithm."""
     import numpy as np
     import torch
     import iso_inputs as gen
@@ -228,7 +211,7 @@ def small_sweep():
                         row[an]["graph_us"] = round(e0.elapsed_time(e1) / 200 * 1e3, 2)
                     else:
                         row[an] = {"us": round(e0.elapsed_time(e1) / 200 * 1e3, 2),
-                                   "launches": kernels_per_start(iso, req)}
+                                   "launches": iso.iso_request_start_info(req)["kernels"]}
                 iso.iso_request_free(req)
             log(row)
             rows.append(row)
@@ -382,11 +365,15 @@ class Bench:
             self.t_init.append(t)
         self.infos = [iso.iso_request_info(r) for r in self.reqs]
         self.delivered = sum(i["delivered_bytes"] for i in self.infos)
-        self.moved = sum(i["bytes_read"] + i["bytes_written"] for i in self.infos)
-        self.launches = sum(kernels_per_start(iso, r, args.graph) for r in self.reqs)
         if args.graph:
             for r in self.reqs:
                 iso.iso_request_set_graph(r, args.graph)
+        # the kernels of a step, and the blocks that they read and write: a block that an allgather's kernel
+        # sends on to several blocks counts as read once
+        starts = [iso.iso_request_start_info(r) for r in self.reqs]
+        self.moved = sum(i["bytes_read"] + i["bytes_written"] for i in starts)
+        self.launches = sum(i["kernels"] for i in starts)
+        self.requested = sum(i["bytes_read"] + i["bytes_written"] for i in self.infos)
 
     # -- requests ------------------------------------------------------------------
     def make_request(self, op, alg, timed_buffers=False):
@@ -501,6 +488,7 @@ class Bench:
             if n != n_rounds:          # a round was split over several launches: no per-round listing
                 continue
             ks = [iso.iso_plan_round(plan, q)["n_entries"] for q in range(n)]
+            sources = [len({(e["src_buf"], e["src_slot"]) for e in iso.iso_plan_entries(plan, q)}) for q in range(n)]
             dims_ = [iso.iso_plan_round(plan, q)["dim"] for q in range(n)]
             evs = [[(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
                     for _ in range(n)] for _ in range(ev_steps)]
@@ -518,12 +506,11 @@ class Bench:
                 row = {"op": self.op_name[inf["op"]], "round": q, "dim": dims_[q], "k": ks[q],
                        "us": round(t_ms * 1e3, 2)}
                 if uniform:
-                    row["moved_GBs"] = round(2 * ks[q] * p * m / (t_ms * 1e-3) / 1e9, 1)
+                    row["moved_GBs"] = round((sources[q] + ks[q]) * p * m / (t_ms * 1e-3) / 1e9, 1)
                 per_round.append(row)
 
-        # Every launch of the step is the same kernel, so its average launch duration over the
-        # timed region is region time / launches in the region (gaps between back-to-back
-        # launches included).
+        # The average launch duration over the timed region is region time / launches in the region
+        # (gaps between back-to-back launches included).
         alg_bytes_per_launch = self.moved / self.launches
         avg_launch_ms = ms_per_step / self.launches
         achieved = alg_bytes_per_launch / (avg_launch_ms * 1e-3) / 1e9
@@ -534,6 +521,8 @@ class Bench:
                   "mesh_shift_round_kernel" if args.mesh else
                   "shift_round_uniform_kernel" if m % 1024 == 0 and (self.slot or m <= 2048) else
                   "shift_round_kernel") + "<16B>"
+        if self.moved < self.requested and not args.algorithm.startswith("sx") and not args.mesh:
+            kernel += ", allgather: also shift_push_kernel<16B>"
         tag = self.tag()
         roofline = {
             "kernel": kernel, "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
@@ -626,14 +615,16 @@ class Bench:
         ksteps = max(5, K // 4)
 
         def rate(rs, ms, hbm_label=True):
-            """`moved_GBs` counts the bytes the algorithm asks for (read + written), which is
-            what HBM carries for the message-combining schedules (every block is read once and
-            written once per hop).  The s-exchange allgather reads each source block s times,
-            mostly from cache, so for it the figure is not HBM traffic and gets no fraction."""
-            mv = sum(iso.iso_request_info(r)["bytes_read"] * 2 for r in rs)
+            """`moved_GBs` counts the blocks that the kernels read and write (a block that a kernel sends
+            on to several blocks is read once), which is what HBM carries for the message-combining
+            schedules.  The s-exchange allgather is given by the bytes its moves ask for, every source block
+            s times: mostly from cache, so the figure is not HBM traffic and gets no fraction."""
+            starts = [iso.iso_request_start_info(r) for r in rs]
+            mv = (sum(i["bytes_read"] + i["bytes_written"] for i in starts) if hbm_label
+                  else sum(iso.iso_request_info(r)["bytes_read"] * 2 for r in rs))
             dl = sum(iso.iso_request_info(r)["delivered_bytes"] for r in rs)
             d = {"ms_per_step": round(ms, 5), "delivered_GBs": round(dl / ms / 1e6, 1),
-                 "launches": sum(kernels_per_start(iso, r) for r in rs)}
+                 "launches": sum(i["kernels"] for i in starts)}
             if hbm_label:
                 d["moved_GBs"] = round(mv / ms / 1e6, 1)
                 d["frac_of_peak"] = round(mv / ms / 1e6 / HBM_PEAK_GBS, 4)
@@ -849,7 +840,7 @@ def small_blocks(args, gen, iso):
     """Config 4 (64^3 torus, Moore radius 1, both collectives) at its small block sizes, where the
     paper's [p][s][m] rows make a round's writes sparse: the message-combining schedule as it is
     and regrouped for small blocks (--algorithm staged).  Both are priced on the same algorithmic
-    bytes, those of the message-combining schedule: 2 * (V + W) * p * m per step."""
+    bytes, those of the message-combining schedule: what its kernels read and write per step."""
     import copy
     cfg = gen.get_config(4)
     out = {}
