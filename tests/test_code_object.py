@@ -49,7 +49,8 @@ def test_no_kernel_uses_private_memory_or_spills(tmp_path):
             spill = re.search(r"\.vgpr_spill_count:\s+(\d+)", block)
             kernels[name] = (int(p.group(1)), int(spill.group(1)) if spill else 0)
     assert len(kernels) > 20, notes[:2000]
-    for want in ("shift_round_kernel", "shift_round_uniform_kernel", "vector_round_kernel", "block_round_kernel",
+    for want in ("shift_round_kernel", "shift_round_uniform_kernel", "shift_push_kernel", "vector_round_kernel",
+                 "vector_round_uniform_kernel", "push_round_kernel", "chain_kernel", "block_round_kernel",
                  "mesh_shift_round_kernel", "staged_round_kernel", "deliver_kernel", "copy_kernel", "table_store_kernel"):
         assert any(want in k for k in kernels), want
     bad = {k: v for k, v in kernels.items() if v != (0, 0)}

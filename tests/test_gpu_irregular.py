@@ -7,6 +7,7 @@ import torch
 
 import iso_inputs as gen
 import paper_1606_07676_amd as iso
+from launch_paths import start_both_ways
 from oracle import iso_oracle as orc
 
 pytestmark = pytest.mark.gpu
@@ -75,8 +76,7 @@ def test_alltoallv_every_byte(case, flavour, alg):
     work = torch.full((max(wsb, 16),), 0xDD, dtype=torch.uint8, device=DEV)
     req = iso.iso_neighbor_alltoallv_init(send, sizes, sd, sext, recv, sizes, rd, rext, work, comm, alg)
     info = iso.iso_request_info(req)
-    iso.iso_start(req)
-    iso.iso_wait(req)
+    start_both_ways(req, recv, work)
     assert np.array_equal(recv.cpu().numpy(), want), f"dims={dims} {flavour} alg={alg}"
     assert np.array_equal(send.cpu().numpy(), send_h)
     assert info["delivered_bytes"] == p * sum(sizes)
@@ -101,8 +101,7 @@ def test_allgatherv_every_byte(case, alg):
         wsb = iso.iso_workspace_bytes_v(comm, iso.ISO_OP_ALLGATHER, alg, [m] * s)
         work = torch.empty(max(wsb, 16), dtype=torch.uint8, device=DEV)
         req = iso.iso_neighbor_allgatherv_init(send, m, sext, recv, [m] * s, rd, rext, work, comm, alg)
-        iso.iso_start(req)
-        iso.iso_wait(req)
+        start_both_ways(req, recv, work)
         assert np.array_equal(recv.cpu().numpy(), want), f"dims={dims} m={m} alg={alg}"
         iso.iso_request_free(req)
 
@@ -191,8 +190,7 @@ def test_stencil_sized_alltoallv_at_scale(alg):
     wsb = iso.iso_workspace_bytes_v(comm, iso.ISO_OP_ALLTOALL, alg, sizes)
     work = torch.empty(max(wsb, 16), dtype=torch.uint8, device=DEV)
     req = iso.iso_neighbor_alltoallv_init(send, sizes, sd, sext, recv, sizes, rd, rext, work, comm, alg)
-    iso.iso_start(req)
-    iso.iso_wait(req)
+    start_both_ways(req, recv, work)
     src = torch.from_numpy(orc.source_ranks(dims, offsets)).to(DEV)
     covered = torch.zeros(rext, dtype=torch.bool, device=DEV)
     for i in range(s):
@@ -252,8 +250,7 @@ def test_random_sizes_with_ranks_in_groups(seed):
         wsb = iso.iso_workspace_bytes_v(comm, iso.ISO_OP_ALLTOALL, alg, sizes)
         work = torch.full((max(wsb, 16),), 0xDD, dtype=torch.uint8, device=DEV)
         req = iso.iso_neighbor_alltoallv_init(send, sizes, sd, sext, recv, sizes, rd, rext, work, comm, alg)
-        iso.iso_start(req)
-        iso.iso_wait(req)
+        start_both_ways(req, recv, work)
         assert np.array_equal(recv.cpu().numpy(), want), f"dims={dims} sizes={sizes} alg={ALG_NAMES[alg]}"
         iso.iso_request_free(req)
     assert np.array_equal(send.cpu().numpy(), send_h)

@@ -8,6 +8,7 @@ import torch
 
 import iso_inputs as gen
 import paper_1606_07676_amd as iso
+from launch_paths import start_both_ways
 from oracle import iso_oracle as orc
 
 pytestmark = pytest.mark.gpu
@@ -47,8 +48,7 @@ def _run(comm, op, alg, m, send, p, s, layout=SM):
         iso.iso_neighbor_allgather_init_layout
     req = init(send, recv, m, layout, work, comm, alg)
     info = iso.iso_request_info(req)
-    iso.iso_start(req)
-    iso.iso_wait(req)
+    start_both_ways(req, recv, work)
     iso.iso_request_free(req)
     return recv, info
 
@@ -191,8 +191,7 @@ def test_slot_major_irregular_every_byte(case, alg):
     wsb = iso.iso_workspace_bytes_v(comm, iso.ISO_OP_ALLTOALL, alg, sizes)
     work = torch.full((max(wsb, 16),), 0xDD, dtype=torch.uint8, device=DEV)
     req = iso.iso_neighbor_alltoallv_init_layout(send, sizes, sd, 0, recv, sizes, rd, 0, SM, work, comm, alg)
-    iso.iso_start(req)
-    iso.iso_wait(req)
+    start_both_ways(req, recv, work)
     iso.iso_request_free(req)
     assert np.array_equal(recv.cpu().numpy(), want), f"dims={dims} {flavour} alg={alg}"
     assert np.array_equal(send.cpu().numpy(), send_h)
@@ -210,8 +209,7 @@ def test_slot_major_irregular_every_byte(case, alg):
     gwork = torch.empty(max(wsb, 16), dtype=torch.uint8, device=DEV)
     req = iso.iso_neighbor_allgatherv_init_layout(torch.from_numpy(one).to(DEV), m, m + 3, grecv, [m] * s, gd, 0,
                                                   SM, gwork, comm, alg)
-    iso.iso_start(req)
-    iso.iso_wait(req)
+    start_both_ways(req, grecv, gwork)
     iso.iso_request_free(req)
     assert np.array_equal(grecv.cpu().numpy(), wantg), f"allgather dims={dims} alg={alg}"
 
@@ -258,7 +256,6 @@ def test_slot_major_irregular_on_a_mesh():
         wsb = iso.iso_workspace_bytes_v(comm, iso.ISO_OP_ALLTOALL, alg, sizes)
         work = torch.empty(max(wsb, 16), dtype=torch.uint8, device=DEV)
         req = iso.iso_neighbor_alltoallv_init_layout(send, sizes, sd, 0, recv, sizes, sd, 0, SM, work, comm, alg)
-        iso.iso_start(req)
-        iso.iso_wait(req)
+        start_both_ways(req, recv, work)
         iso.iso_request_free(req)
         assert np.array_equal(recv.cpu().numpy(), want), ALG_NAMES[alg]

@@ -6,6 +6,7 @@ import torch
 
 import iso_inputs as gen
 import paper_1606_07676_amd as iso
+from launch_paths import start_both_ways
 from oracle import iso_oracle as orc
 
 pytestmark = pytest.mark.gpu
@@ -36,8 +37,7 @@ def _run(dims, periodic, offsets, op, alg, m, send):
     work = torch.full((max(wsb, 16),), 0xDD, dtype=torch.uint8, device=DEV)
     init = iso.iso_neighbor_alltoall_init if op == iso.ISO_OP_ALLTOALL else iso.iso_neighbor_allgather_init
     req = init(send, recv, m, work, comm, alg)
-    iso.iso_start(req)
-    iso.iso_wait(req)
+    start_both_ways(req, recv, work)
     iso.iso_request_free(req)
     return recv
 
@@ -80,8 +80,7 @@ def test_mesh_irregular_blocks_and_refused_onehop(dims):
         wsb = iso.iso_workspace_bytes_v(comm, iso.ISO_OP_ALLTOALL, alg, sizes)
         work = torch.empty(max(wsb, 16), dtype=torch.uint8, device=DEV)
         req = iso.iso_neighbor_alltoallv_init(send, sizes, sd, ext, recv, sizes, sd, ext, work, comm, alg)
-        iso.iso_start(req)
-        iso.iso_wait(req)
+        start_both_ways(req, recv, work)
         assert np.array_equal(recv.cpu().numpy(), want), ALG_NAMES[alg]
         iso.iso_request_free(req)
     with pytest.raises(iso.IsoError) as e:

@@ -10,6 +10,7 @@ import torch
 
 import iso_inputs as gen
 import paper_1606_07676_amd as iso
+from launch_paths import start_both_ways
 from oracle import iso_oracle as orc
 from oracle import c_twin
 
@@ -55,9 +56,7 @@ def _run(dims, offsets, op, alg, m, send, misalign=0, stream=None, starts=1):
     init = iso.iso_neighbor_alltoall_init if op == iso.ISO_OP_ALLTOALL else iso.iso_neighbor_allgather_init
     req = init(send, recv, m, work, comm, alg)
     info = iso.iso_request_info(req)
-    for _ in range(starts):
-        iso.iso_start(req, stream)
-    iso.iso_wait(req)
+    start_both_ways(req, recv, work, stream, starts)
     iso.iso_request_free(req)
     return recv.view(p, s, m), info
 
@@ -151,8 +150,7 @@ def test_unaligned_buffers_keep_the_full_unit_width(send_off, recv_off, alg):
         work = torch.empty(max(wsb, 16), dtype=torch.uint8, device=DEV)
         req = iso.iso_neighbor_alltoall_init(send, recv, m, work, comm, alg)
         assert iso.iso_request_info(req)["vector_bytes"] == 16
-        iso.iso_start(req)
-        iso.iso_wait(req)
+        start_both_ways(req, recv, work)
         iso.iso_request_free(req)
         assert np.array_equal(recv.cpu().numpy().reshape(p, s, m), orc.alltoall(dims, offsets, send_h)), (m, alg)
         out = recv_store.cpu().numpy()

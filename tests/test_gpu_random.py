@@ -8,6 +8,7 @@ import torch
 
 import iso_inputs as gen
 import paper_1606_07676_amd as iso
+from launch_paths import start_both_ways
 from oracle import iso_oracle as orc
 
 pytestmark = pytest.mark.gpu
@@ -47,8 +48,7 @@ def _run(comm, op, alg, m, send, p, s):
     work = torch.full((max(wsb, 16),), 0xDD, dtype=torch.uint8, device=DEV)
     init = iso.iso_neighbor_alltoall_init if op == iso.ISO_OP_ALLTOALL else iso.iso_neighbor_allgather_init
     req = init(send, recv, m, work, comm, alg)
-    iso.iso_start(req)
-    iso.iso_wait(req)
+    start_both_ways(req, recv, work)
     iso.iso_request_free(req)
     return recv.cpu().numpy()
 
@@ -171,23 +171,20 @@ def _irregular_body(rng, mesh, dims, periodic, offsets):
         work = torch.full((max(wsb, 16),), 0xDD, dtype=torch.uint8, device=DEV)
         recv = torch.full((p, rext), 0xEE, dtype=torch.uint8, device=DEV)
         req = iso.iso_neighbor_alltoallv_init(send, sizes, sd, sext, recv, sizes, rd, rext, work, comm, alg)
-        iso.iso_start(req)
-        iso.iso_wait(req)
+        start_both_ways(req, recv, work)
         iso.iso_request_free(req)
         assert np.array_equal(recv.cpu().numpy(), want), ("rows", dims, periodic, offsets, sizes, alg)
         precv = torch.full((pext,), 0xEE, dtype=torch.uint8, device=DEV)
         req = iso.iso_neighbor_alltoallv_init_layout(psend, sizes, pd, 0, precv, sizes, pd, 0,
                                                      iso.ISO_LAYOUT_SLOT_MAJOR, work, comm, alg)
-        iso.iso_start(req)
-        iso.iso_wait(req)
+        start_both_ways(req, precv, work)
         iso.iso_request_free(req)
         assert np.array_equal(precv.cpu().numpy(), pwant), ("planes", dims, periodic, offsets, sizes, alg)
         wsb = iso.iso_workspace_bytes_v(comm, iso.ISO_OP_ALLGATHER, alg, [g] * s)
         work = torch.full((max(wsb, 16),), 0xDD, dtype=torch.uint8, device=DEV)
         grecv = torch.full((p, gext), 0xEE, dtype=torch.uint8, device=DEV)
         req = iso.iso_neighbor_allgatherv_init(one, g, g + 3, grecv, [g] * s, gd, gext, work, comm, alg)
-        iso.iso_start(req)
-        iso.iso_wait(req)
+        start_both_ways(req, grecv, work)
         iso.iso_request_free(req)
         assert np.array_equal(grecv.cpu().numpy(), gwant), ("allgatherv", dims, periodic, offsets, g, alg)
     assert np.array_equal(send.cpu().numpy(), send_h) and np.array_equal(psend.cpu().numpy(), psend_h)
@@ -229,8 +226,7 @@ def test_many_seeded_tori_regular_and_irregular():
                     init = (iso.iso_neighbor_alltoall_init if op == iso.ISO_OP_ALLTOALL
                             else iso.iso_neighbor_allgather_init)
                     req = init(source[op], recv, m, work, comm, alg)
-                    iso.iso_start(req)
-                    iso.iso_wait(req)
+                    start_both_ways(req, recv, work)
                     if not np.array_equal(recv.cpu().numpy(), expected[op]):
                         bad.append(("regular", seed, dims, s, m, alg, op))
                     iso.iso_request_free(req)
@@ -254,8 +250,7 @@ def test_many_seeded_tori_regular_and_irregular():
                 work = torch.empty(max(iso.iso_workspace_bytes_v(comm, iso.ISO_OP_ALLTOALL, alg, sizes), 16),
                                    dtype=torch.uint8, device=DEV)
                 req = iso.iso_neighbor_alltoallv_init(send, sizes, sd, sext, recv, sizes, rd, rext, work, comm, alg)
-                iso.iso_start(req)
-                iso.iso_wait(req)
+                start_both_ways(req, recv, work)
                 if not np.array_equal(recv.cpu().numpy(), want):
                     bad.append(("irregular", seed, dims, sizes, alg))
                 iso.iso_request_free(req)

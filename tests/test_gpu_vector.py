@@ -8,6 +8,7 @@ import torch
 
 import iso_inputs as gen
 import paper_1606_07676_amd as iso
+from launch_paths import start_both_ways
 from oracle import iso_oracle as orc
 
 pytestmark = pytest.mark.gpu
@@ -36,9 +37,7 @@ def check_exchange(dims, offsets, op, alg, m, layout, send_off=0, recv_off=0):
     work = torch.empty(max(1, iso.iso_workspace_bytes(comm, op, alg, m)), dtype=torch.uint8, device=DEV)
     init = iso.iso_neighbor_alltoall_init_layout if a2a else iso.iso_neighbor_allgather_init_layout
     req = init(send, recv, m, layout, work, comm, alg)
-    for _ in range(2):
-        iso.iso_start(req)
-    iso.iso_wait(req)
+    start_both_ways(req, recv, work, starts=2)
     iso.iso_request_free(req)
     src = torch.from_numpy(_source_ranks(dims, offsets).astype(np.int64)).to(DEV)
     for i in range(s):
