@@ -886,54 +886,55 @@ private:
         l.bytes_read = p * ents[0].size * (uint64_t)(std::unique(sources.begin(), sources.end()) - sources.begin());
     }
 
-    // Cache policy of a launch whose kernel and arguments are set.  What decides is whether the blocks of the
-    // whole collective (the receive buffer's size) stay in the last-level cache from one round to the next.
+    // Cache policy of a launch whose kernel and arguments are set.  What decides is whether the blocks of the whole
+    // collective (the receive buffer's size) stay in the last-level cache from one round to the next.  Figures in us,
+    // a -> b being streaming -> the other policy unless said otherwise, first with one set of buffers repeated, then
+    // with many sets in turn (1 GiB and more): a policy is taken where it gains in one and does not lose in the
+    // other.
     //   All-to-all rounds read every block once: streaming loads and stores, except for collectives of up to 8 MiB
-    //   (plain against streaming, one set of buffers and many in turn: 16^3, 64 B 13.1 -> 12.4 and 16.5 -> 15.3 us).
-    //   Plain stores gain further up only where one set is repeated (16^3, 128 B 17.3 -> 15.9 and 19.5 -> 24; 20^3,
-    //   128 B 26.5 -> 23.3 and 28 -> 33.4; 60^2, 24 neighbours, 128 B 11.6 -> 10.1 and 13.3 -> 15.9).
+    //   (plain stores, 16^3, 64 B 13.1 -> 12.4 and 16.5 -> 15.3).  Further up plain stores lose with many sets (16^3,
+    //   128 B 17.3 -> 15.9 and 19.5 -> 24; 20^3, 128 B 26.5 -> 23.3 and 28 -> 33.4; 60^2, 24 neighbours, 128 B 11.6
+    //   -> 10.1 and 13.3 -> 15.9).
     //   Blocks that do not fill whole 64-byte sectors of rank-major rows gain further up.  Up to half the cache plain
-    //   stores let neighbouring blocks meet there before a sector is written: blocks of less than a sector (64^3, 20 B
-    //   293 -> 185 and 301 -> 214; 300^2, 24 neighbours, 25 B 82 -> 48 and 91 -> 63), and blocks up to 256 B that make
-    //   two hops and more, so that much of what is written is read again (32^3, 100 B 123 -> 74 and 130 -> 107, 8^4, 80
-    //   neighbours, 100 B 64 -> 44 and 76 -> 60; fewer hops: 300^2 star, 100 B 23 -> 20 and 28 -> 31, 200^2, 8
-    //   neighbours, 200 B 46 -> 36 and 49 -> 56; larger blocks: 16^3, 400 B 41 -> 33 and 45 -> 48; under a sixteenth of
-    //   the cache, a twelfth on a mesh: 16^3 mesh, 200 B 27 -> 23 and 31.5 -> 34).  Other blocks take cached loads there (100^2, 24
-    //   neighbours, 300 B 53 -> 46 and 57 -> 57, 30^3 star, 600 B 47 -> 37 and 49 -> 48).  Between half and 9/8 of the
-    //   cache: streaming loads, plain stores under a sector and for two hops and more under 512 B (64^3, 36 B 495 -> 336
-    //   and 507 -> 395, 32^3, 300 B 281 -> 219 and 285 -> 262; 300^2 star, 400 B 61 -> 57 and 63 -> 85), else cached
-    //   loads (the same 61 -> 50 and 63 -> 61, 64^3 star, 140 B 174 -> 120 and 178 -> 158, 30^3 star, 1000 B 71 -> 55 and
-    //   72 -> 72; not on a mesh from 512 B on: 1 to 3 % slower with many sets).  In the staged schedule blocks of 128
-    //   bytes and more take the cached loads (20^3, 200 B with plain stores 55 -> 41 and 57 -> 61), and an allgather's
-    //   plain stores begin at an eighth of the cache (32^3, 20 B 24 -> 22 and 23.6 -> 25).
-    //   Allgather rounds may read a block several times: cached loads.  Streaming stores, except for blocks of less than
-    //   a sector in rank-major rows of three and more dimensions, of which several launches write parts, while all of it
-    //   fits (plain against streaming, one set of buffers and many in turn: 64^3, 32 B 120 -> 99 and 174 -> 160 us,
-    //   8^5, 40 random neighbours, 40 B 122 -> 76 and 136 -> 96, 64^3 star, 40 B 53 -> 32 and 54 -> 47).  Plain stores
-    //   of larger blocks and in two dimensions gain only where one set is repeated (30^3 star, 1000 B 47 -> 46 and
-    //   47 -> 64; 32^3, 200 B 70 -> 57 and 82 -> 92; box 40^3, 160 B 106 -> 89 and 118 -> 131; 300^2, 24 neighbours,
-    //   56 B 51 -> 39 and 61 -> 71).
-    //   The staged schedule's kernels, all-to-all, one set of buffers and many in turn.  From an eighth of the cache (a
-    //   sixteenth at 16 bytes, a sixth from 128 bytes on) up to half of it cached loads in both; the rounds store plainly if blocks do not fill
-    //   sectors (64^3, 16 B 116 -> 97 and 118 -> 107 us, 44^3, 32 B 68 -> 58 and 70 -> 69, 9^4, 80 neighbours, 176 B
-    //   131 -> 86 and 133 -> 111; 32^3, 32 B, under an eighth, 27 -> 27.5 and 29.5 -> 31) and stream at 64 B (40^3 89 ->
-    //   81 and 90.5 -> 89; plain 75 and 93.5).  Up to 7/4 of it the rounds still gain from cached loads (64^3, 32 B 196
-    //   -> 177 and 198 -> 186, 48^3, 80 B 195 -> 182 and 197 -> 188; 872 MB 617 -> 623).  Blocks of two and more whole
-    //   sectors stream throughout (32^3, 256 B 158 -> 148 and 159 -> 162, 9^4, 128 B 73 -> 61 and 75 -> 78).  Rounds
-    //   between planes of the workspace are dense on both sides whatever the block: as whole sectors.
-    //    Allgather: cached loads, streaming stores (the
-    //   last launch with plain ones, one set of buffers and many in turn: 64^3, 16 B 45 -> 45 and 43 -> 49, 64^3 star,
-    //   64 B 22 -> 23 and 23 -> 29, 300^2, 24 neighbours, 48 B 37 -> 34 and 33 -> 36).
-    //   Unequal blocks: cached loads, and streaming ones in all-to-all rounds whose blocks all have the same number of
-    //   units, outside a sixteenth to all of the cache (40^3, 1024 and 1023 B 1487 -> 1474 us, 16^3, 64 and 63 B 18.6 ->
-    //   17.7 with many sets; inside 32^3, 100 and 99 B cached 127 -> 101 and 131 -> 119, not in the staged schedule; 20^3,
-    //   256 and 255 B with plain stores 55 -> 44 and 57 -> 61).  Plain stores up to a quarter of the cache for rank-major blocks of less than two sectors and unequal or
-    //   single units (stencils 64^3, 4 B 151 -> 119 and 173 -> 152, 48^3, 9 B 89 -> 83 and 116 -> 112; larger blocks
-    //   gain only where one set is repeated: 24^3, 20 B 31 -> 28.5 and 40 -> 41, 20^3, 25 B 27 -> 25 and 34 -> 36.5;
-    //   slot-major 24^3, 16 B 16 -> 17.5 and 22 -> 25).
-    //   The s-exchange writes whole rows and is indifferent to the stores; streaming loads where the send buffer
-    //   of an all-to-all exceeds the cache (805 MB -4.6 %, 5.4 GB -3.8 %; 218 MB +17 %, an allgather +60 %) and no
-    //   two blocks of a rank-major row share a 128-byte line (64 B +9 %, 100 B +7 %, 300 B +9 %).
+    //   stores let neighbouring blocks meet there before a sector is written: blocks of less than a sector (64^3, 20
+    //   B 293 -> 185 and 301 -> 214; 300^2, 24 neighbours, 25 B 82 -> 48 and 91 -> 63), and blocks up to 256 B that
+    //   make two hops and more, so that much of what is written is read again (32^3, 100 B 123 -> 74 and 130 -> 107;
+    //   8^4, 80 neighbours, 100 B 64 -> 44 and 76 -> 60; fewer hops: 300^2 star, 100 B 23 -> 20 and 28 -> 31; larger
+    //   blocks: 16^3, 400 B 41 -> 33 and 45 -> 48; under a sixteenth of the cache, a twelfth on a mesh: 16^3 mesh,
+    //   200 B 27 -> 23 and 31.5 -> 34).  Other blocks take cached loads there (100^2, 24 neighbours, 300 B 53 -> 46
+    //   and 57 -> 57; 30^3 star, 600 B 47 -> 37 and 49 -> 48).  Between half and 9/8 of the cache: streaming loads,
+    //   plain stores under a sector, and for two hops and more under 512 B (64^3, 36 B 495 -> 336 and 507 -> 395;
+    //   32^3, 300 B 281 -> 219 and 285 -> 262; 300^2 star, 400 B 61 -> 57 and 63 -> 85), else cached loads (the same
+    //   61 -> 50 and 63 -> 61; 64^3 star, 140 B 174 -> 120 and 178 -> 158; 30^3 star, 1000 B 71 -> 55 and 72 -> 72;
+    //   not on a mesh from 512 B on: 1 to 3 % slower with many sets).  In the staged schedule blocks of 128 bytes and
+    //   more take the cached loads (20^3, 200 B with plain stores 55 -> 41 and 57 -> 61).
+    //   Allgather rounds may read a block several times: cached loads.  Streaming stores, except for blocks of less
+    //   than a sector in rank-major rows of three and more dimensions, of which several launches write parts, while
+    //   all of it fits (plain stores, 64^3, 32 B 120 -> 99 and 174 -> 160; 8^5, 40 random neighbours, 40 B 122 -> 76
+    //   and 136 -> 96; 64^3 star, 40 B 53 -> 32 and 54 -> 47; the staged schedule's from an eighth of the cache on:
+    //   32^3, 20 B 24 -> 22 and 23.6 -> 25).  Larger blocks and two dimensions: 30^3 star, 1000 B 47 -> 46 and 47 ->
+    //   64; 32^3, 200 B 70 -> 57 and 82 -> 92; box 40^3, 160 B 106 -> 89 and 118 -> 131; 300^2, 24 neighbours, 56 B
+    //   51 -> 39 and 61 -> 71.
+    //   The staged schedule's kernels, all-to-all.  From an eighth of the cache (a sixteenth at 16 bytes, a sixth
+    //   from 128 bytes on) up to half of it cached loads in both; the rounds store plainly if blocks do not fill
+    //   sectors (64^3, 16 B 116 -> 97 and 118 -> 107; 44^3, 32 B 68 -> 58 and 70 -> 69; 9^4, 80 neighbours, 176 B 131
+    //   -> 86 and 133 -> 111; under an eighth 32^3, 32 B 27 -> 27.5 and 29.5 -> 31) and stream at 64 B (40^3 89 -> 81
+    //   and 90.5 -> 89; plain 75 and 93.5).  Up to 7/4 of it the rounds still gain from cached loads (64^3, 32 B 196
+    //   -> 177 and 198 -> 186; 48^3, 80 B 195 -> 182 and 197 -> 188; 872 MB 617 -> 623).  Blocks of two and more
+    //   whole sectors stream throughout (cached loads 32^3, 256 B 158 -> 148 and 159 -> 162; 9^4, 128 B 73 -> 61 and
+    //   75 -> 78).  Rounds between planes of the workspace are dense on both sides whatever the block: as whole
+    //   sectors.  Allgather: cached loads, streaming stores (the last launch with plain ones 64^3, 16 B 45 -> 45 and
+    //   43 -> 49; 64^3 star, 64 B 22 -> 23 and 23 -> 29; 300^2, 24 neighbours, 48 B 37 -> 34 and 33 -> 36).
+    //   Unequal blocks: cached loads, streaming stores.  All-to-all rounds whose blocks all have the same number of
+    //   units stream their loads outside a sixteenth to all of the cache (against cached 40^3, 1024 and 1023 B 1474
+    //   and 1487; 16^3, 64 and 63 B with many sets 17.7 and 18.6; inside 32^3, 100 and 99 B 127 and 101, 131 and 119,
+    //   not in the staged schedule).  Plain stores up to a quarter of the cache for rank-major blocks of less than
+    //   two sectors and unequal or single units (stencils 64^3, 4 B 151 -> 119 and 173 -> 152; 48^3, 9 B 89 -> 83 and
+    //   116 -> 112; larger blocks: 24^3, 20 B 31 -> 28.5 and 40 -> 41; 20^3, 25 B 27 -> 25 and 34 -> 36.5; slot-major
+    //   24^3, 16 B 16 -> 17.5 and 22 -> 25).
+    //   The s-exchange writes whole rows and is indifferent to the stores; streaming loads where the send buffer of
+    //   an all-to-all exceeds the cache (805 MB -4.6 %, 5.4 GB -3.8 %; 218 MB +17 %, an allgather +60 %) and no two
+    //   blocks of a rank-major row share a 128-byte line (64 B +9 %, 100 B +7 %, 300 B +9 %).
     int cache_policy(const Launch &l, const BoundRound &r) const {
         const uint64_t bytes = inf.delivered_bytes;
         const uint64_t above = kLastLevelCacheBytes * 9 / 8;      // what still gains from the cache
@@ -1068,8 +1069,9 @@ private:
             l.vec.last_offset = size0 - width;
             vector_launch(l, ents.data() + done, k, chunks);
             // several blocks of a rank-major row to a line, read by ranks that lie near each other: one eighth of the
-            // ranks per XCD keeps the line in its L2 (64^3, 16 B 46.5 -> 38 us, 28 B 79 -> 73, 50^3 star, 20 B 10.2 ->
-            // 5.9; 40 B 105 -> 112)
+            // ranks per XCD keeps the line in its L2 (runs -> eighths, one set of buffers repeated and many in turn:
+            // 64^3, 20 B 65 -> 54 and 73 -> 78 us, 300^2, 24 neighbours, 16 B 13.6 -> 12.2 and 17.8 -> 17.8, 50^3 star,
+            // 20 B 10.3 -> 6.7 and 12 -> 11.5; 64^3, 40 B 103 -> 113 and 115 -> 123)
             if (op == ISO_OP_ALLTOALL && !l.vec.entry_major && ents.size() > 1) l.eighths = size0 <= 32;
             if (op == ISO_OP_ALLGATHER && ents.size() > 1) allgather_order(l, ents.data() + done, k);
             if (l.vec.per) total = per_entry * ((k + l.vec.per - 1) / l.vec.per);
