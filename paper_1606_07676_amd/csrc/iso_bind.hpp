@@ -532,19 +532,22 @@ private:
         return n;
     }
 
-    // iso_start of a small collective: all rounds in one launch (see chain_kernel), if its hops fit the arguments
-    // and a workgroup the ranks.  Against a launch per dimension: 8 x 8, 32 B 9.9 -> 7.2 us, 8^3, 26 neighbours, 64 B
-    // 13.4 -> 7.4, 5^4 star, 400 B 16.4 -> 7.4; allgather the same.  What it saves is 2.7 us of the host's time per
-    // launch less; what it costs is that a workgroup's accesses are a column of units per rank, at best a few sectors
-    // each, which most of the chip does not take part in.  The limits are 6144 sectors for one workgroup over all its
-    // hops (60^2, 64 B: 7200, 10.1 -> 12.7; 16^3, 16 B: 12288, 13.3 -> 16.4), and for all of them 32 Ki per launch that
-    // it saves, measured with buffers that the caches do not hold, on hosts that take 2 to 2.7 us per launch: one launch
-    // less: 16^2 radius 1, 400 B (32 Ki) 8 to 9.7 -> 7.9, 40^2, 64 B (50 Ki) 8 to 9.4 -> 9.0, 16^2, 1000 B (64 Ki) 8 to
-    // 10 -> 10.5; two less: 8^3, 64 B (39 Ki) 10.4 to 12.9 -> 7.9, 10^3, 64 B (76 Ki) 10.4 to 12.9 -> 13.2.  Blocks of
-    // up to 32 bytes share sectors (10^3, 16 B 10.4 to 12.6 -> 7.8); columns of at most a sector of larger blocks that
-    // do not fill sectors lie across two (32^2, 100 B 8 to 9.8 -> 8.6, allgather 9.1).  Single hops wait for memory
-    // once: 64 Ki (16^2 star, 3000 B (48 Ki) 8.0 -> 7.3, 6^4 star, 500 B (111 Ki, three less) 12.6 -> 10.8, 12^3 star,
-    // 400 B (131 Ki, two less) 10.4 to 12.9 -> 11.1).  A schedule of one launch gains nothing (4096, 16 B 6.5 -> 6.9).
+    // iso_start of a small collective: all rounds in one launch (see chain_kernel), if its hops fit the arguments and
+    // a workgroup the ranks.  Against a launch per dimension: 8 x 8, 32 B 9.9 -> 7.2 us, 8^3, 26 neighbours, 64 B
+    // 13.4 -> 7.4, 5^4 star, 400 B 16.4 -> 7.4; allgather the same.  What it saves is 2 to 2.7 us of the host's time
+    // per launch less; what it costs is that a workgroup's accesses are a column of units per rank, at best a few
+    // sectors each, which most of the chip does not take part in.  The limits are 6144 sectors for one workgroup over
+    // all its hops (60^2, 64 B: 7200, 10.1 -> 12.7; 16^3, 16 B: 12288, 13.3 -> 16.4), and for all of them 48 Ki per
+    // launch that it saves.  Measured with up to 25 sets of buffers in turn, which the caches hold, and with 1 GiB of
+    // them: one launch less, 16^2 radius 1, 400 B (32 Ki) 9.7 -> 7.8 and 9.7 -> 7.9, 16^2 star of two, 400 B (48 Ki)
+    // 9.5 -> 7.8 and 10 -> 8.5, 1000 B (96 Ki) 9.9 -> 8.9 and 9.8 -> 10.9, 24 x 20, 24 neighbours, 320 B (135 Ki) 9
+    // -> 8 and 9 -> 10.5; two less, 8^3, 64 B (39 Ki) 13.4 -> 7.4 and 12.9 -> 7.9, 10^3, 64 B (76 Ki) 12.1 -> 10.2
+    // and 12.5 -> 13.1, 10^3, 100 B (152 Ki) 12.4 -> 12.3 and 12.8 -> 16.8.  Blocks of up to 32 bytes share sectors
+    // (10^3, 16 B 12.4 -> 7 and 12.6 -> 7.8); columns of at most a sector of larger blocks that do not fill sectors
+    // lie across two (32^2, 100 B with many sets 9.8 -> 8.6, allgather 8 to 9.8 -> 9.1).  Single hops wait for memory
+    // once: 64 Ki (16^2 star, 3000 B (48 Ki) 8.0 -> 7.3, 6^4 star, 500 B (111 Ki, three less) 12.6 -> 10.8, 12^3
+    // star, 400 B (131 Ki, two less) 10.4 to 12.9 -> 11.1, many sets).  A schedule of one launch gains nothing (4096,
+    // 16 B 6.5 -> 6.9).
     bool chain_launch(uint64_t launches) {
         if (c.mesh || !uniform || !size0 || launches < 2 || p > kChainThreads * kChainUnitsPerLane || s > kChainHops ||
             c.d > (int)kChainDims || (size0 >> min_log2) > 0xFFFF)
@@ -626,7 +629,7 @@ private:
         uint64_t all = own * l.grid;
         if (size0 <= 32) all /= 2;
         else if (longest > 1 && size0 % 64 && piece <= 64) all *= 2;
-        if (own > 6144 || all > (launches - 1) * (longest > 1 ? 32 : 64) * 1024) return false;
+        if (own > 6144 || all > (launches - 1) * (longest > 1 ? 48 : 64) * 1024) return false;
         l.threads = std::min<uint32_t>(kChainThreads, (ca.n_units + 63) & ~63u);
         std::vector<uint64_t> sources, targets;
         for (const auto &chain : chains)
