@@ -58,7 +58,7 @@ def test_allocation_free_call_refuses_the_tables_it_always_refused(stub_library)
     ((16, 16), gen.von_neumann(2, 1), 3000, 1), ((16, 16), gen.von_neumann(2, 1), 5000, 2), ((16, 16), gen.moore(2, 1), 400, 1),
     ((32, 32), gen.moore(2, 1), 100, 2), ((10, 10, 10), gen.moore(3, 1), 16, 1), ((10, 10, 10), gen.moore(3, 1), 64, 1),
     ((16, 16), gen.von_neumann(2, 2), 400, 1), ((16, 16), gen.von_neumann(2, 2), 1000, 2),
-    ((12, 12, 12), gen.moore(3, 1), 16, 3), ((12, 12, 12), gen.von_neumann(3, 1), 400, 3),
+    ((12, 12, 12), gen.moore(3, 1), 16, 1), ((12, 12, 12), gen.von_neumann(3, 1), 400, 3),
     ((4096,), gen.von_neumann(1, 1), 16, 1), ((16, 16), gen.moore(2, 1), 1000, 2), ((32, 32), gen.von_neumann(2, 2), 300, 2),
     ((8, 8, 8), gen.moore(3, 1), 200, 3), ((10, 10, 10), gen.moore(3, 1), 100, 3)])
 def test_small_collectives_take_one_launch_where_it_saves_enough(stub_library, dims, offsets, m, kernels, op):
