@@ -19,7 +19,7 @@ def compile_host(directory, sources):
     """(source, is HIP) -> object files for the host only"""
     objs = []
     inc = ["-I", os.path.join(ROOT, "include"), "-I", os.path.join(PACKAGE, "csrc")]
-    common = ["-O1", "-std=c++17", "-fPIC"]
+    common = ["-O3", "-std=c++17", "-fPIC"]
     for src, hip in sources:
         obj = os.path.join(directory, os.path.basename(src) + ".o")
         if hip:

@@ -219,6 +219,28 @@ def test_binding_a_large_box_is_no_walk_over_its_tiles(stub_library, alg):
     assert best < 4e-3, best
 
 
+def test_merged_rounds_of_many_entries_bind_in_little_more_time(stub_library):
+    """16 806 neighbours: init that also merges the rounds of a dimension, against one whose plan has one round per
+    dimension from the start (1.1 times its time; 1.5 to 1.8 times under a comparison sort of the entries and a table
+    that grows and is copied).  As many tries as it takes to see the shortest of both."""
+    dims, offsets, m = (5, 4, 4, 3, 2), gen.moore(5, 3), 8
+    p, s = int(np.prod(dims)), len(offsets)
+    comm = stub_library.comm(dims, offsets)
+    algs = iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM
+    need = max(stub_library.iso.iso_workspace_bytes(comm, iso.ISO_OP_ALLTOALL, alg, m) for alg in algs)
+    best = {alg: 1.0 for alg in algs}
+    with stub_library.buffers(p * s * m, p * s * m, need) as bufs:
+        for _ in range(60):
+            for alg in algs:
+                t0 = time.perf_counter()
+                req = stub_library.request(comm, dims, s, iso.ISO_OP_ALLTOALL, alg, m, iso.ISO_LAYOUT_RANK_MAJOR, bufs)
+                best[alg] = min(best[alg], time.perf_counter() - t0)
+                stub_library.iso.iso_request_free(req)
+            if best[algs[0]] < 1.3 * best[algs[1]]:
+                break
+    assert best[algs[0]] < 1.3 * best[algs[1]], best
+
+
 @pytest.mark.parametrize("op", [iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER])
 @pytest.mark.parametrize("alg", [0, 1, 2, 3, 4, 5])
 @pytest.mark.parametrize("dims,offsets,m", [((8, 8), gen.moore(2, 1), 32), ((32, 32, 32), gen.moore(3, 1), 256), ((12, 13), gen.von_neumann(2, 2), 4000)])
