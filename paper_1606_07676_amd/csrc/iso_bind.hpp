@@ -479,8 +479,14 @@ public:
         }
         if (chains && chain_launch(launches)) return upload();
         if (merges && launches < bound_rounds.size()) {
+            const size_t n_entries = table.size(), n_prefixes = prefixes.size();
             merge_rounds();
             st = bind_rounds();
+            if (c.mesh && !arena && st == ISO_SUCCESS && rounds_move_faster()) {
+                pending.resize(n_listed);
+                table.resize(n_entries);
+                prefixes.resize(n_prefixes);
+            }
         } else if (arena) {
             st = bind_rounds();
         }
@@ -653,10 +659,12 @@ private:
     }
 
     // iso_start of ISO_ALG_COMBINED: the consecutive rounds of one dimension, which touch disjoint blocks, in one
-    // launch.  A launch costs about 4 us of ramp and drain on top of its traffic (32^3, 26 neighbours, 256 B:
-    // 6 launches 170 us, 3 launches 161; 256^2 star, 1 KiB: 8 launches 380, 2 launches 350; 8^2, 32 B: 13.5 and
-    // 8.7 us), and rounds that read the same blocks or share memory lines meet in the caches (allgather
-    // 60 x 50 x 41, 200 B 372 -> 241 us).  iso_start_range still runs the rounds one by one.
+    // launch.  A launch costs about 4 us of ramp and drain on top of its traffic, and rounds that read the same blocks
+    // or share memory lines meet in the caches (us, rounds -> together, one set of buffers repeated and 1 GiB of sets in
+    // turn: 32^3, 26 neighbours, 256 B 170 -> 158 and 170 -> 160; 64^3, 128 B 626 -> 615 and 627 -> 615; 256^2, 12
+    // neighbours, 1 KiB 451 -> 344 and 450 -> 345; 16^3, 400 B 48 -> 37 and 58 -> 46; 8^5, 40 random neighbours, 1
+    // KiB 2003 -> 1926; allgather 32^3, 256 B 70 -> 56 and 77 -> 56, 60 x 50 x 41, 200 B 370 -> 236 and 451 -> 292).
+    // iso_start_range still runs the rounds one by one.
     void merge_rounds() {
         size_t n = 0;
         for (size_t ri = 0; ri < bound_rounds.size(); ++ri) {
@@ -690,6 +698,30 @@ private:
             for (const HostEntry &he : ents) sorted[at[key(he)]++] = he;
             ents.swap(sorted);
         }
+    }
+
+    // On a mesh a launch's tiles are interior where all its entries have a source, which is less of the box for the
+    // rounds of a dimension together than for each by itself, and a tile that is not takes about twice its time.  Against
+    // that stand what a launch costs (4 us, here in bytes at the copy rate) and blocks that several rounds read.  Rounds
+    // one by one, all of a dimension together, us: 16^4, 40 random neighbours up to 3 away, 1 KiB 3040 and 3337; 32^3 the
+    // same 1240 and 1339; 48^3, 124 neighbours, 128 B 1510 and 1608; 8^5, 40 neighbours, 4 KiB 6504 and 6714; the other
+    // way 8^5, 256 B 531 and 517, 128^2, 48 neighbours, 2 KiB 1008 and 956, 10^4, 40 neighbours, 400 B 278 and 220,
+    // allgather 48^3, 128 B 611 and 551, 8^5, 4 KiB 5316 and 4995 (9^5, 512 B 1350 and 1427 is not told apart from these).
+    bool rounds_move_faster() const {
+        constexpr uint64_t kLaunchBytes = uint64_t(26) << 20;
+        uint64_t rounds_cost = 0, merged_cost = 0;
+        for (size_t i = 0; i < pending.size(); ++i) {
+            const Launch &l = pending[i].l;
+            uint64_t cost = kLaunchBytes + l.bytes_read;
+            if (l.kernel == kMeshShiftKernel) {
+                uint64_t outside = l.mesh_shift.map.n_tiles;
+                for (size_t q = 0; q < (l.mesh_shift.map.n_tiles + 31u) / 32; ++q)
+                    outside -= (uint64_t)__builtin_popcount(prefixes[pending[i].first_prefix + q]);
+                cost += outside * kThreads * 2 << min_log2;
+            }
+            (i < n_listed ? rounds_cost : merged_cost) += cost;
+        }
+        return rounds_cost < merged_cost;
     }
 
     uint64_t entry_size(const iso_plan_entry_t &e) const {

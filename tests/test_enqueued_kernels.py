@@ -241,6 +241,17 @@ def test_merged_rounds_of_many_entries_bind_in_little_more_time(stub_library):
     assert best[algs[0]] < 1.3 * best[algs[1]], best
 
 
+@pytest.mark.parametrize("dims,offsets,m,layout,op,kernels", [
+    ((16, 16, 16, 16), gen.random_distinct(4, -3, 3, 40, 5), 1024, 0, 0, 24), ((32, 32, 32), gen.random_distinct(3, -3, 3, 40, 5), 1024, 0, 0, 18),
+    ((8,) * 5, gen.random_distinct(5, -3, 3, 40, 5), 1024, 1, 0, 30), ((48, 48, 48), gen.moore(3, 2), 128, 0, 0, 12),
+    ((8,) * 5, gen.random_distinct(5, -3, 3, 40, 5), 256, 0, 0, 5), ((10,) * 4, gen.random_distinct(4, -3, 3, 40, 5), 400, 0, 0, 4),
+    ((64, 64, 64), gen.moore(3, 1), 128, 0, 0, 3), ((128, 128), gen.moore(2, 3), 2048, 0, 0, 2),
+    ((48, 48, 48), gen.moore(3, 2), 128, 0, 1, 3), ((8, 8), gen.moore(2, 1), 32, 0, 0, 2)])
+def test_mesh_rounds_go_together_where_that_does_not_cost_their_interior(stub_library, dims, offsets, m, layout, op, kernels):
+    names = _names(stub_library.start(dims, offsets, op, iso.ISO_ALG_COMBINED, m, layout, (0,) * len(dims)))
+    assert names == kernels * ["mesh_shift_round_kernel"]
+
+
 @pytest.mark.parametrize("op", [iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER])
 @pytest.mark.parametrize("alg", [0, 1, 2, 3, 4, 5])
 @pytest.mark.parametrize("dims,offsets,m", [((8, 8), gen.moore(2, 1), 32), ((32, 32, 32), gen.moore(3, 1), 256), ((12, 13), gen.von_neumann(2, 2), 4000)])
