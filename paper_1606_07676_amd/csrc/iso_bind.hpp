@@ -664,7 +664,8 @@ private:
     // turn: 32^3, 26 neighbours, 256 B 170 -> 158 and 170 -> 160; 64^3, 128 B 626 -> 615 and 627 -> 615; 256^2, 12
     // neighbours, 1 KiB 451 -> 344 and 450 -> 345; 16^3, 400 B 48 -> 37 and 58 -> 46; 8^5, 40 random neighbours, 1
     // KiB 2003 -> 1926; allgather 32^3, 256 B 70 -> 56 and 77 -> 56, 60 x 50 x 41, 200 B 370 -> 236 and 451 -> 292).
-    // iso_start_range still runs the rounds one by one.
+    // Some all-to-alls of several GB lose 1 to 3 %, with no rule in sight (100^3 star, 1 KiB 2016 -> 2073, 512 B 1114 ->
+    // 1045).  iso_start_range still runs the rounds one by one.
     void merge_rounds() {
         size_t n = 0;
         for (size_t ri = 0; ri < bound_rounds.size(); ++ri) {

@@ -59,7 +59,8 @@ struct alignas(16) DevEntry {
 // still sweep the same region of memory together.  kEighths instead gives XCD x
 // the x-th contiguous eighth of all tiles: the host picks it for launches whose
 // blocks sit at rank strides that are multiples of 4 KiB and cover only part of a
-// 4 KiB page (see page_resonant), where it is 4 - 26 % faster.
+// 4 KiB page (see page_resonant), where it is 4 - 26 % faster, and for fused
+// exchanges whose neighbouring ranks read the same lines (see allgather_order).
 struct TileMap {
     uint32_t n_tiles;      // tiles that carry work
     uint32_t run_log2;     // kEighths: XCD x works on the x-th contiguous eighth of the tiles
