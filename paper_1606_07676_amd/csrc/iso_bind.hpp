@@ -551,12 +551,14 @@ private:
     // them: one launch less, 16^2 radius 1, 400 B (32 Ki) 9.7 -> 7.8 and 9.7 -> 7.9, 16^2 star of two, 400 B (48 Ki)
     // 9.5 -> 7.8 and 10 -> 8.5, 1000 B (96 Ki) 9.9 -> 8.9 and 9.8 -> 10.9, 24 x 20, 24 neighbours, 320 B (135 Ki) 9
     // -> 8 and 9 -> 10.5; two less, 8^3, 64 B (39 Ki) 13.4 -> 7.4 and 12.9 -> 7.9, 10^3, 64 B (76 Ki) 12.1 -> 10.2
-    // and 12.5 -> 13.1, 10^3, 100 B (152 Ki) 12.4 -> 12.3 and 12.8 -> 16.8.  Blocks of up to 32 bytes share sectors
-    // (10^3, 16 B 12.4 -> 7 and 12.6 -> 7.8); columns of at most a sector of larger blocks that do not fill sectors
-    // lie across two (32^2, 100 B with many sets 9.8 -> 8.6, allgather 8 to 9.8 -> 9.1).  Single hops wait for memory
-    // once: 64 Ki (16^2 star, 3000 B (48 Ki) 8.0 -> 7.3, 6^4 star, 500 B (111 Ki, three less) 12.6 -> 10.8, 12^3
-    // star, 400 B (131 Ki, two less) 10.4 to 12.9 -> 11.1, many sets).  A schedule of one launch gains nothing (4096,
-    // 16 B 6.5 -> 6.9).
+    // and 12.5 -> 13.1, 100 B (152 Ki) 12.4 -> 12.3 and 12.8 -> 16.8; 10^3, 16 B (76 Ki) 10.4 -> 6.6 and 10.6 -> 9.2,
+    // 11^3, 16 B (101 Ki) 10.2 -> 8.9 and 10.3 -> 11.9, 12^3, 32 B (132 Ki) 10.2 -> 11.6 and 10.2 -> 16.  Columns of
+    // at most a sector of blocks of more than 32 bytes that do not fill sectors lie across two, which counts double
+    // (32^2, 100 B with many sets 9.8 -> 8.6, allgather 8 to 9.8 -> 9.1).  Single hops are no different (16^2 star, 3000
+    // B (48 Ki) 8.0 -> 7.3, 6^4 star, 500 B (111 Ki, three less) 12.6 -> 10.8, many sets; 45^2 star, 256 B (63 Ki) 9.3 ->
+    // 8.7 and 9.2 -> 12.3).  A schedule of one launch gains nothing (4096, 16 B 6.5 -> 6.9).  Near the limits many sets
+    // lose what repeated ones gain (45^2 radius 1, 32 B 9.3 -> 7.2 and 9.3 -> 11.3): a persistent request finds its
+    // blocks in the last-level cache again.
     bool chain_launch(uint64_t launches) {
         if (c.mesh || !uniform || !size0 || launches < 2 || p > kChainThreads * kChainUnitsPerLane || s > kChainHops ||
             c.d > (int)kChainDims || (size0 >> min_log2) > 0xFFFF)
@@ -636,9 +638,8 @@ private:
         l.grid = n_chains * ca.groups;
         const uint64_t piece = ca.column * width, own = p * ((piece + 63) / 64) * longest;
         uint64_t all = own * l.grid;
-        if (size0 <= 32) all /= 2;
-        else if (longest > 1 && size0 % 64 && piece <= 64) all *= 2;
-        if (own > 6144 || all > (launches - 1) * (longest > 1 ? 48 : 64) * 1024) return false;
+        if (longest > 1 && size0 > 32 && size0 % 64 && piece <= 64) all *= 2;
+        if (own > 6144 || all > (launches - 1) * 48 * 1024) return false;
         l.threads = std::min<uint32_t>(kChainThreads, (ca.n_units + 63) & ~63u);
         std::vector<uint64_t> sources, targets;
         for (const auto &chain : chains)

@@ -55,10 +55,10 @@ def test_allocation_free_call_refuses_the_tables_it_always_refused(stub_library)
     ((8, 8), gen.moore(2, 1), 64, 1), ((8, 8, 8), gen.moore(3, 1), 64, 1), ((32, 32), gen.von_neumann(2, 2), 64, 1),
     ((8, 8), [(1, 1), (0, 1), (2, 0)], 2056, 1), ((4, 3), [(1, 1), (1, 1), (0, 0), (0, 0), (5, -7), (2, 0)], 5464, 1),
     ((5, 5, 5, 5), gen.von_neumann(4, 1), 1000, 1), ((5, 5, 5, 5), gen.von_neumann(4, 1), 2000, 4),
-    ((16, 16), gen.von_neumann(2, 1), 3000, 1), ((16, 16), gen.von_neumann(2, 1), 5000, 2), ((16, 16), gen.moore(2, 1), 400, 1),
+    ((16, 16), gen.von_neumann(2, 1), 3000, 1), ((16, 16), gen.von_neumann(2, 1), 5000, 2), ((45, 45), gen.von_neumann(2, 1), 256, 2), ((16, 16), gen.moore(2, 1), 400, 1),
     ((32, 32), gen.moore(2, 1), 100, 2), ((10, 10, 10), gen.moore(3, 1), 16, 1), ((10, 10, 10), gen.moore(3, 1), 64, 1),
     ((16, 16), gen.von_neumann(2, 2), 400, 1), ((16, 16), gen.von_neumann(2, 2), 1000, 2),
-    ((12, 12, 12), gen.moore(3, 1), 16, 1), ((12, 12, 12), gen.von_neumann(3, 1), 400, 3),
+    ((11, 11, 11), gen.moore(3, 1), 16, 3), ((12, 12, 12), gen.moore(3, 1), 32, 3), ((12, 12, 12), gen.von_neumann(3, 1), 400, 3),
     ((4096,), gen.von_neumann(1, 1), 16, 1), ((16, 16), gen.moore(2, 1), 1000, 2), ((32, 32), gen.von_neumann(2, 2), 300, 2),
     ((8, 8, 8), gen.moore(3, 1), 200, 3), ((10, 10, 10), gen.moore(3, 1), 100, 3)])
 def test_small_collectives_take_one_launch_where_it_saves_enough(stub_library, dims, offsets, m, kernels, op):
