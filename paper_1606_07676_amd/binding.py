@@ -186,11 +186,21 @@ def _nbytes(x, given):
 
 def _stream_handle(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream or None
+        return _current_stream() or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None
+
+
+def _current_stream():
+    """Handle of torch's current stream.  Once torch has initialised the GPU it is asked for the handle
+    itself: building the Stream object takes 2.7 us, more than a whole start of a small collective spends
+    in the library (8 x 8, 8 neighbours, 32 B: 6.7 us a start with the object, 4.3 without)."""
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 class _Handle:

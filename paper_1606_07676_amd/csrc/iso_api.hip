@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -27,6 +28,9 @@ static __device__ __align__(256) unsigned char scratch[ISO_NOALLOC_SCRATCH_BYTES
 struct iso_comm_s {
     iso::Comm c;
     int64_t allgather_moves = -1;        // computed by the first iso_neighborhood_info
+    // all-to-all schedules for iso_neighbor_alltoall_noalloc, by algorithm: built by the first call that asks for one,
+    // since that call leaves nothing else behind to keep it in (see there)
+    std::unique_ptr<const iso::Plan> alltoall_plans[ISO_ALG_COMBINED_STAGED + 1];
 };
 
 struct iso_plan_s {
@@ -128,10 +132,24 @@ int make_request(int op, const iso::Layout &lay, const void *sendbuf, void *recv
     } guard{rq};
     int st = iso::build_plan(comm->c, op, algorithm, rq->b.plan);
     if (st != ISO_SUCCESS) return st;
-    st = iso::bind_request(rq->b, comm->c, lay, sendbuf, recvbuf, workspace, workspace_bytes);
+    st = iso::bind_request(rq->b, rq->b.plan, comm->c, lay, sendbuf, recvbuf, workspace, workspace_bytes);
     if (st != ISO_SUCCESS) return st;
     guard.r = nullptr;
     *out = rq;
+    return ISO_SUCCESS;
+}
+
+// The handle's all-to-all schedule of `algorithm`, for the call that binds it anew every time.
+int alltoall_plan(iso_comm_t comm, int algorithm, const iso::Plan **out) {
+    const bool known = algorithm >= 0 && algorithm < (int)(sizeof(comm->alltoall_plans) / sizeof(comm->alltoall_plans[0]));
+    if (!known || !comm->alltoall_plans[algorithm]) {
+        auto plan = std::make_unique<iso::Plan>();
+        const int st = iso::build_plan(comm->c, ISO_OP_ALLTOALL, algorithm, *plan);
+        if (st != ISO_SUCCESS) return st;
+        if (!known) return ISO_ERR_ARG;
+        comm->alltoall_plans[algorithm] = std::move(plan);
+    }
+    *out = comm->alltoall_plans[algorithm].get();
     return ISO_SUCCESS;
 }
 
@@ -513,10 +531,11 @@ int iso_neighbor_alltoall_noalloc(const void *sendbuf, void *recvbuf, size_t m, 
         int st = scratch_of_current_device(&ptr);
         if (st != ISO_SUCCESS) return st;
         hipStream_t stream = (hipStream_t)hip_stream;
+        const iso::Plan *plan = nullptr;
+        if ((st = alltoall_plan(comm, algorithm, &plan)) != ISO_SUCCESS) return st;
         iso::BoundRequest b;
-        if ((st = iso::build_plan(comm->c, ISO_OP_ALLTOALL, algorithm, b.plan)) != ISO_SUCCESS) return st;
         const iso::StaticArena arena{ptr, ISO_NOALLOC_TABLE_BYTES, stream};
-        st = iso::bind_request(b, comm->c, regular_layout(comm->c, ISO_OP_ALLTOALL, m), sendbuf, recvbuf,
+        st = iso::bind_request(b, *plan, comm->c, regular_layout(comm->c, ISO_OP_ALLTOALL, m), sendbuf, recvbuf,
                                ptr + ISO_NOALLOC_TABLE_BYTES, ISO_NOALLOC_SCRATCH_BYTES - ISO_NOALLOC_TABLE_BYTES,
                                &arena);
         if (st != ISO_SUCCESS) return st;

@@ -450,17 +450,17 @@ inline DeliverEntry make_deliver_entry(const Comm &c, const HostEntry &he) {
     return x;
 }
 
-// Binds a schedule (`rq.plan`) to buffers: checks the buffers, builds the device table and the launch
+// Binds a schedule to buffers: checks the buffers, builds the device table and the launch
 // list.  bind_request below runs the steps in order.
 // With `arena` the table is placed there instead of in an allocation of its own, and the workspace is
 // taken to be the library's own memory (no look-up of its allocation); ISO_ERR_SCRATCH if either does not fit.
 class Binder {
 public:
-    Binder(BoundRequest &request, const Comm &comm, const Layout &layout, const void *send, void *recv, void *work,
-           size_t work_bytes, const StaticArena *static_arena)
+    Binder(BoundRequest &request, const Plan &plan, const Comm &comm, const Layout &layout, const void *send, void *recv,
+           void *work, size_t work_bytes, const StaticArena *static_arena)
         : rq(request), c(comm), lay(layout), sendbuf(send), recvbuf(recv), workspace(work),
-          workspace_bytes(work_bytes), arena(static_arena), pl(request.plan), op(request.plan.op),
-          p((uint64_t)comm.p), s((size_t)comm.s), inf(request.info), wl(work_layout(request.plan, layout)) {}
+          workspace_bytes(work_bytes), arena(static_arena), pl(plan), op(plan.op),
+          p((uint64_t)comm.p), s((size_t)comm.s), inf(request.info), wl(work_layout(plan, layout)) {}
 
     int run() {
         int st = describe_and_check();
@@ -563,15 +563,20 @@ private:
         if (c.mesh || !uniform || !size0 || launches < 2 || p > kChainThreads * kChainUnitsPerLane || s > kChainHops ||
             c.d > (int)kChainDims || (size0 >> min_log2) > 0xFFFF)
             return false;
-        std::vector<std::vector<const HostEntry *>> chains;
-        size_t n_hops = 0;
+        std::vector<const HostEntry *> hops;             // chain after chain
+        std::vector<uint32_t> ends;                      // where each of them ends
         if (op == ISO_OP_ALLTOALL) {
+            size_t n_hops = 0;
             for (const std::vector<HostEntry> &round : rounds) n_hops += round.size();
             if (n_hops > kChainHops) return false;
-            n_hops = 0;
-            chains.resize(s);
+            hops.resize(n_hops);
+            ends.resize(s + 1);
             for (const std::vector<HostEntry> &round : rounds)
-                for (const HostEntry &he : round) chains[(size_t)he.neighbor].push_back(&he);
+                for (const HostEntry &he : round) ++ends[(size_t)he.neighbor + 1];
+            std::partial_sum(ends.begin(), ends.end(), ends.begin());
+            for (const std::vector<HostEntry> &round : rounds)
+                for (const HostEntry &he : round) hops[ends[(size_t)he.neighbor]++] = &he;
+            ends.pop_back();                             // (what was a chain's start has moved on to its end)
         } else {
             // Allgather: the way of every receive block from the send buffer down the trie.  Ways share moves, and
             // each makes them for itself; they write the same bytes, provided that no place is used twice.
@@ -581,15 +586,15 @@ private:
                     if (!written_by.emplace(he.de.dst, &he).second) return false;
             for (const auto &[dst, last] : written_by) {
                 if (last->dst_buf != ISO_BUF_RECV) continue;
-                std::vector<const HostEntry *> way{last};
+                const size_t start = hops.size();
+                hops.push_back(last);
                 for (auto at = written_by.find(last->de.src); at != written_by.end(); at = written_by.find(at->second->de.src))
-                    way.push_back(at->second);
-                std::reverse(way.begin(), way.end());
-                chains.push_back(std::move(way));
+                    hops.push_back(at->second);
+                std::reverse(hops.begin() + (ptrdiff_t)start, hops.end());
+                ends.push_back((uint32_t)hops.size());
             }
         }
-        for (const auto &chain : chains) n_hops += chain.size();
-        if (!n_hops || n_hops > kChainHops) return false;
+        if (hops.empty() || hops.size() > kChainHops) return false;
         Pending pd;
         pd.first_entry = pd.first_prefix = 0;
         std::memset(&pd.l, 0, sizeof(pd.l));
@@ -616,11 +621,12 @@ private:
             ca.d_pj[j] = make_fastdiv((uint32_t)c.dims[(size_t)j]);
         }
         uint32_t at = 0, n_chains = 0, longest = 0;
-        for (const auto &chain : chains) {
-            if (chain.empty()) continue;
-            longest = std::max(longest, (uint32_t)chain.size());
+        for (const uint32_t end : ends) {
+            if (end == at) continue;                             // no hops: an empty block
+            longest = std::max(longest, end - at);
             ca.first[n_chains++] = (uint8_t)at;
-            for (const HostEntry *he : chain) {
+            while (at < end) {
+                const HostEntry *he = hops[at];
                 const int dim = he->dim;
                 ChainHop &hop = ca.hops[at++];
                 hop.src = he->de.src;
@@ -641,22 +647,28 @@ private:
         if (longest > 1 && size0 > 32 && size0 % 64 && piece <= 64) all *= 2;
         if (own > 6144 || all > (launches - 1) * 48 * 1024) return false;
         l.threads = std::min<uint32_t>(kChainThreads, (ca.n_units + 63) & ~63u);
+        describe_chain_bytes(l, hops);
+        rq.chain = std::move(args);
+        l.chain = rq.chain.get();
+        pending.push_back(pd);
+        return true;
+    }
+
+    // An all-to-all's hops share no blocks; ways of an allgather's trie do.
+    void describe_chain_bytes(Launch &l, const std::vector<const HostEntry *> &hops) const {
+        l.bytes_read = l.bytes_written = p * size0 * hops.size();
+        if (op == ISO_OP_ALLTOALL) return;
         std::vector<uint64_t> sources, targets;
-        for (const auto &chain : chains)
-            for (const HostEntry *he : chain) {
-                sources.push_back(he->de.src);
-                targets.push_back(he->de.dst);
-            }
+        for (const HostEntry *he : hops) {
+            sources.push_back(he->de.src);
+            targets.push_back(he->de.dst);
+        }
         for (std::vector<uint64_t> *v : {&sources, &targets}) {
             std::sort(v->begin(), v->end());
             v->erase(std::unique(v->begin(), v->end()), v->end());
         }
         l.bytes_read = p * size0 * sources.size();
         l.bytes_written = p * size0 * targets.size();
-        rq.chain = std::move(args);
-        l.chain = rq.chain.get();
-        pending.push_back(pd);
-        return true;
     }
 
     // iso_start of ISO_ALG_COMBINED: the consecutive rounds of one dimension, which touch disjoint blocks, in one
@@ -1432,10 +1444,10 @@ private:
     }
 };
 
-inline int bind_request(BoundRequest &rq, const Comm &c, const Layout &lay, const void *sendbuf,
+inline int bind_request(BoundRequest &rq, const Plan &plan, const Comm &c, const Layout &lay, const void *sendbuf,
                         void *recvbuf, void *workspace, size_t workspace_bytes,
                         const StaticArena *arena = nullptr) {
-    return Binder(rq, c, lay, sendbuf, recvbuf, workspace, workspace_bytes, arena).run();
+    return Binder(rq, plan, c, lay, sendbuf, recvbuf, workspace, workspace_bytes, arena).run();
 }
 
 }  // namespace iso

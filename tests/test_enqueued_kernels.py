@@ -40,6 +40,22 @@ def test_allocation_free_call_stores_only_tables_that_its_kernels_read(stub_libr
         assert _noalloc(stub_library, dims, offsets, 64, alg, periodic) == want, dims
 
 
+def test_allocation_free_calls_on_one_handle_are_those_of_new_handles(stub_library):
+    """The handle keeps the schedules that these calls build: every algorithm its own, and what is refused stays refused."""
+    niso, dims, offsets, m = stub_library.iso, (9, 4, 7), gen.moore(3, 1), 48
+    p, s = int(np.prod(dims)), len(offsets)
+    comm = stub_library.comm(dims, offsets)
+    with stub_library.buffers(p * s * m, p * s * m) as (send, recv):
+        for alg in (0, 1, 2, 3, 4, 5, 0, 5, 3, -1, 6, 2, 1 << 30, 4):
+            if alg not in range(6):
+                with pytest.raises(niso.IsoError) as e:
+                    niso.iso_neighbor_alltoall_noalloc(send, recv, m, comm, alg, 0)
+                assert e.value.status == iso.ISO_ERR_ARG
+                continue
+            got = _names(stub_library.launched(lambda: niso.iso_neighbor_alltoall_noalloc(send, recv, m, comm, alg, 0)))
+            assert got == _noalloc(stub_library, dims, offsets, m, alg), alg
+
+
 def test_allocation_free_call_refuses_the_tables_it_always_refused(stub_library):
     """3900 neighbours in five dimensions: the entries alone would fit the table's 256 KiB, with the residues they do
     not, and the refusal does not depend on whether the kernels read them."""

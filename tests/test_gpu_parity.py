@@ -494,3 +494,13 @@ def test_large_blocks_are_taken_in_groups_of_ranks(dims, m, alg):
     one_h = gen.allgather_send(22, p, m)
     recv, info = _run(dims, offsets, iso.ISO_OP_ALLGATHER, alg, m, torch.from_numpy(one_h).to(DEV))
     assert np.array_equal(recv.cpu().numpy(), orc.allgather(dims, offsets, one_h))
+
+
+def test_calls_without_a_stream_take_torchs_current_one():
+    """The handle that the binding asks torch for is the current Stream object's, on the default stream and side streams."""
+    from paper_1606_07676_amd import binding
+    torch.zeros(1, device=DEV)
+    sides = [torch.cuda.Stream() for _ in range(2)]
+    for stream in (torch.cuda.default_stream(), *sides, torch.cuda.default_stream()):
+        with torch.cuda.stream(stream):
+            assert (binding._stream_handle(None) or 0) == torch.cuda.current_stream().cuda_stream == stream.cuda_stream
