@@ -20,10 +20,10 @@ thread_local int g_last_hip_error = 0;
 }
 
 // Device memory for iso_neighbor_alltoall_noalloc: the table of block index maps in the first
-// ISO_NOALLOC_TABLE_BYTES, the intermediate buffer of Algorithm 1 in the rest.  Every device the
+// ISO_NOALLOC_TABLE_BYTES (and kArenaTorusBytes), the intermediate buffer of Algorithm 1 in the rest.  Every device the
 // library's code is loaded on holds its own copy until the process ends.  In host code the name
 // only stands for the symbol: the address on the current device comes from hipGetSymbolAddress.
-static __device__ __align__(256) unsigned char scratch[ISO_NOALLOC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[ISO_NOALLOC_SCRATCH_BYTES + iso::kArenaTorusBytes];
 
 struct iso_comm_s {
     iso::Comm c;
@@ -536,7 +536,7 @@ int iso_neighbor_alltoall_noalloc(const void *sendbuf, void *recvbuf, size_t m, 
         iso::BoundRequest b;
         const iso::StaticArena arena{ptr, ISO_NOALLOC_TABLE_BYTES, stream};
         st = iso::bind_request(b, *plan, comm->c, regular_layout(comm->c, ISO_OP_ALLTOALL, m), sendbuf, recvbuf,
-                               ptr + ISO_NOALLOC_TABLE_BYTES, ISO_NOALLOC_SCRATCH_BYTES - ISO_NOALLOC_TABLE_BYTES,
+                               ptr + ISO_NOALLOC_TABLE_BYTES + iso::kArenaTorusBytes, ISO_NOALLOC_SCRATCH_BYTES - ISO_NOALLOC_TABLE_BYTES,
                                &arena);
         if (st != ISO_SUCCESS) return st;
         for (const iso::Launch &l : b.start_list())

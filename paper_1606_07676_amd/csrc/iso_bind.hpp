@@ -58,7 +58,11 @@ struct Launch {
     DeliverArgs deliver;
     StagedRoundArgs staged;
     uint32_t tile_units;   // the staged schedule's kernels: kTileUnits or kSmallTileUnits
-    const ChainArgs *chain;    // BoundRequest::chain
+    ChainTable chain;      // chain kernel: its arguments in the request's table
+    const ChainArgs *chain_by_value;      // or BoundRequest::chain, where there is no table
+    uint32_t n_tiles, run_log2;           // see TileMap
+    bool entry_major, vector_round;       // see launch_flags
+    uint32_t pull;
     uint64_t bytes_read, bytes_written;   // of blocks (see iso_start_info_t)
     uint32_t threads;      // per workgroup, where not kThreads (chain kernel)
 };
@@ -194,30 +198,17 @@ inline void set_grid(Launch &l, uint32_t total, uint32_t k, bool eighths) {
         run_log2 = kEighths;
         l.grid = per_xcd * 8;
     }
-    TileMap &tm = l.kernel == kVectorKernel  ? l.vec.map
-                  : l.kernel == kStagedRoundKernel ? l.staged.map
-                  : l.kernel == kDeliverKernel ? l.deliver.map
-                  : l.kernel == kBlockKernel ? l.block.map
-                  : l.kernel == kMeshShiftKernel ? l.mesh_shift.map
-                                                 : l.shift.map;
-    tm.n_tiles = n_tiles;
-    tm.run_log2 = run_log2;
-    tm.per_xcd = per_xcd;
+    l.n_tiles = n_tiles;
+    l.run_log2 = run_log2;
+    const uint32_t flags = launch_flags(run_log2, l.entry_major, l.pull, l.vector_round);
     l.lds_table = k <= kLdsEntries;
-    if (l.kernel == kStagedRoundKernel || l.kernel == kDeliverKernel) {
-        // one tile per workgroup: `total` counts tiles * kThreads here
-    } else if (l.kernel == kVectorKernel) {
-        l.vec.total = total;
-        l.vec.k = k;
-    } else if (l.kernel == kBlockKernel) {
-        l.block.total = total;
-        l.block.k = k;
-    } else if (l.kernel == kMeshShiftKernel) {
-        l.mesh_shift.total = total;
-        l.mesh_shift.k = k;
-    } else {
-        l.shift.total = total;
-        l.shift.k = k;
+    switch (l.kernel) {
+        case kStagedRoundKernel: l.staged.n_tiles = n_tiles; l.staged.more |= flags; break;
+        case kDeliverKernel: l.deliver.n_tiles = n_tiles; l.deliver.more |= flags; break;
+        case kVectorKernel: l.vec.total = total; l.vec.k = k; l.vec.more |= flags; break;
+        case kBlockKernel: l.block.total = total; l.block.k = k; l.block.more |= flags; break;
+        case kMeshShiftKernel: l.mesh_shift.total = total; l.mesh_shift.k = k; l.mesh_shift.more |= flags; break;
+        default: l.shift.total = total; l.shift.k = k; l.shift.more |= flags;
     }
 }
 
@@ -259,7 +250,10 @@ KernelRef select_vector(const Launch &l) {
 
 template <typename V, bool LDS, bool TAIL>
 KernelRef select_regular(const Launch &l) {
-    if (l.kernel == kChainKernel) return {(const void *)&chain_kernel<V, TAIL>, l.chain};
+    if (l.kernel == kChainKernel) {
+        if (l.chain_by_value) return {(const void *)&chain_kernel<V, TAIL, ChainArgs>, l.chain_by_value};
+        return {(const void *)&chain_kernel<V, TAIL, ChainTable>, &l.chain};
+    }
     if (l.kernel == kVectorKernel) {
         if constexpr (LDS) {
             if (l.vector_dims == 3) return select_vector<V, 3, TAIL>(l);
@@ -275,10 +269,10 @@ KernelRef select_regular(const Launch &l) {
     return with_policy<V>(l, [&](auto pol) -> KernelRef {
         if constexpr (sizeof(V) == 16) {
             if (l.uniform_waves) {
-                if (l.shift.group) return {(const void *)&shift_round_uniform_kernel<pol(), true>, &l.shift};
+                if (l.shift.grouped) return {(const void *)&shift_round_uniform_kernel<pol(), true>, &l.shift};
                 return {(const void *)&shift_round_uniform_kernel<pol()>, &l.shift};
             }
-            if (l.shift.group) return {(const void *)&shift_round_kernel<V, LDS, pol(), TAIL, true>, &l.shift};
+            if (l.shift.grouped) return {(const void *)&shift_round_kernel<V, LDS, pol(), TAIL, true>, &l.shift};
         }
         return {(const void *)&shift_round_kernel<V, LDS, pol(), TAIL>, &l.shift};
     });
@@ -344,7 +338,7 @@ struct BoundRequest {
     void *dev_table = nullptr;         // owned (hipMalloc) unless the request was bound to a StaticArena
     std::vector<Launch> launches;          // what iso_start_range counts through
     std::vector<Launch> start_launches;    // what iso_start enqueues instead, where that differs (see merge_rounds)
-    std::unique_ptr<ChainArgs> chain;      // arguments of the chain kernel, if it is taken
+    std::unique_ptr<ChainArgs> chain;      // arguments of the chain kernel, where it takes them by value
 
     const std::vector<Launch> &start_list() const { return start_launches.empty() ? launches : start_launches; }
 };
@@ -355,9 +349,12 @@ struct BoundRequest {
 // rest of the arena as the workspace.  Nothing is allocated, copied or freed.
 struct StaticArena {
     unsigned char *table;              // device address, 16-byte aligned
-    size_t table_bytes;
+    size_t table_bytes;                // for entries, residues and the rest; kArenaTorusBytes more are there
     hipStream_t stream;
 };
+
+constexpr size_t kArenaTorusBytes = 512;
+static_assert(sizeof(TorusDims) <= kArenaTorusBytes, "room behind the table");
 
 inline int store_table(const StaticArena &arena, size_t at, const void *host, size_t bytes) {
     // `at` and `bytes` are multiples of 4: every part of the table is an array of 32-bit words or of DevEntry
@@ -455,6 +452,13 @@ inline DeliverEntry make_deliver_entry(const Comm &c, const HostEntry &he) {
 // With `arena` the table is placed there instead of in an allocation of its own, and the workspace is
 // taken to be the library's own memory (no look-up of its allocation); ISO_ERR_SCRATCH if either does not fit.
 class Binder {
+    // one division among a launch's constants
+    static void put(uint32_t divisor, uint32_t &mul, uint32_t &shifts, uint32_t byte) {
+        const FastDiv f = make_fastdiv(divisor);
+        mul = f.mul;
+        shifts |= shift_byte(f) << (8 * byte);
+    }
+
 public:
     Binder(BoundRequest &request, const Plan &plan, const Comm &comm, const Layout &layout, const void *send, void *recv,
            void *work, size_t work_bytes, const StaticArena *static_arena)
@@ -648,8 +652,15 @@ private:
         if (own > 6144 || all > (launches - 1) * 48 * 1024) return false;
         l.threads = std::min<uint32_t>(kChainThreads, (ca.n_units + 63) & ~63u);
         describe_chain_bytes(l, hops);
-        rq.chain = std::move(args);
-        l.chain = rq.chain.get();
+        if (arena) {
+            rq.chain = std::move(args);
+            l.chain_by_value = rq.chain.get();
+        } else {
+            while (prefixes.size() % 4) prefixes.push_back(0);
+            pd.first_prefix = prefixes.size();
+            const uint32_t *words = (const uint32_t *)args.get();
+            prefixes.insert(prefixes.end(), words, words + sizeof(ChainArgs) / 4);
+        }
         pending.push_back(pd);
         return true;
     }
@@ -728,14 +739,21 @@ private:
             const Launch &l = pending[i].l;
             uint64_t cost = kLaunchBytes + l.bytes_read;
             if (l.kernel == kMeshShiftKernel) {
-                uint64_t outside = l.mesh_shift.map.n_tiles;
-                for (size_t q = 0; q < (l.mesh_shift.map.n_tiles + 31u) / 32; ++q)
+                uint64_t outside = l.n_tiles;
+                for (size_t q = 0; q < (l.n_tiles + 31u) / 32; ++q)
                     outside -= (uint64_t)__builtin_popcount(prefixes[pending[i].first_prefix + q]);
                 cost += outside * kThreads * 2 << min_log2;
             }
             (i < n_listed ? rounds_cost : merged_cost) += cost;
         }
         return rounds_cost < merged_cost;
+    }
+
+    uint32_t periodic_mask() const {
+        uint32_t mask = 0;
+        for (int j = 0; j < c.d; ++j)
+            if (c.periodic[(size_t)j]) mask |= 1u << j;
+        return mask;
     }
 
     uint64_t entry_size(const iso_plan_entry_t &e) const {
@@ -1027,7 +1045,7 @@ private:
                            (!staged || bytes > kLastLevelCacheBytes / 8)
                        ? kPlainStores
                        : 0;
-        const bool dense = lay.slot_major || (l.kernel == kShiftKernel && l.shift.entry_major);
+        const bool dense = lay.slot_major || (l.kernel == kShiftKernel && l.entry_major);
         if (size0 % 64 && !dense && bytes <= above) {
             const bool read_again = inf.entries >= 2 * (int64_t)s;          // two hops per block and more
             if (bytes > kLastLevelCacheBytes / 2 && (size0 < 64 || (size0 < 512 && read_again)))
@@ -1064,10 +1082,13 @@ private:
                 prefixes.insert(prefixes.end(), words, words + sizeof(x) / 4);
                 table.push_back(he.de);      // keeps the launch's entry count in step with the others
             }
-        da.d_upb = make_fastdiv(da.upb);
-        da.d_rows = make_fastdiv(std::max(1u, da.k_rows * da.upb));
-        da.d_plane = make_fastdiv(da.ranks * da.upb);
-        da.d_row = make_fastdiv((uint32_t)(s * upb));
+        da.rows = std::max(1u, da.k_rows * da.upb);
+        da.plane = da.ranks * da.upb;
+        da.row = (uint32_t)(s * upb);
+        put(da.upb, da.mul_upb, da.shifts, 0);
+        put(da.rows, da.mul_rows, da.shifts, 1);
+        put(da.plane, da.mul_plane, da.shifts, 2);
+        put(da.row, da.mul_row, da.shifts, 3);
         l.dyn_lds = (uint32_t)(s * ((uint64_t)da.ranks * da.upb + 1) * 16);
         total = ((p + da.ranks - 1) / da.ranks) * kThreads;      // set_grid: one workgroup per tile
     }
@@ -1095,11 +1116,13 @@ private:
         const bool shift = r.kind == ISO_ROUND_SHIFT;
         sa.inner = shift ? (uint32_t)c.inner[r.dim] : 1u;
         sa.pj = shift ? (uint32_t)c.dims[r.dim] : 1u;
-        sa.d_upb = make_fastdiv(sa.upb);
-        sa.d_row = make_fastdiv(std::max(1u, sa.k_rows * sa.upb));
-        sa.d_plane = make_fastdiv(sa.ranks * sa.upb);
-        sa.d_inner = make_fastdiv(sa.inner);
-        sa.d_pj = make_fastdiv(sa.pj);
+        sa.row = std::max(1u, sa.k_rows * sa.upb);
+        sa.plane = sa.ranks * sa.upb;
+        put(sa.upb, sa.mul_upb, sa.shifts, 0);
+        put(sa.row, sa.mul_row, sa.shifts, 1);
+        put(sa.plane, sa.mul_plane, sa.shifts, 2);
+        put(sa.inner, sa.mul_inner, sa.shifts, 3);
+        put(sa.pj, sa.mul_pj, sa.more, 0);
         l.dyn_lds = (uint32_t)(k * ((uint64_t)sa.ranks * sa.upb + 1) * 16);
         total = ((p + sa.ranks - 1) / sa.ranks) * kThreads;      // set_grid: one workgroup per tile
     }
@@ -1121,22 +1144,23 @@ private:
         // to 2 KiB (measured: no gain from 4 KiB on)
         l.uniform_waves = l.kernel == kShiftKernel && min_log2 == 4 && !l.tail && chunks % 64 == 0 &&
                           (lay.slot_major || chunks <= 128);
-        const FastDiv dch = make_fastdiv((uint32_t)chunks), dk = make_fastdiv(k);
-        const FastDiv dp = make_fastdiv((uint32_t)p);
+        l.pull = (uint32_t)(chunks * width - size0);
         const bool shift = r.kind == ISO_ROUND_SHIFT;
         if (l.kernel == kVectorKernel) {
-            l.vec.d = c.d;
-            l.vec.d_chunks = dch;
-            l.vec.d_k = dk;
-            l.vec.d_p = dp;
-            l.vec.entry_major = lay.slot_major || all_planes;
-            l.vec.last_offset = size0 - width;
+            VectorArgs &va = l.vec;
+            va.d = c.d;
+            va.chunks = (uint32_t)chunks;
+            va.p = (uint32_t)p;
+            put(va.chunks, va.mul_chunks, va.shifts, 0);
+            put(k, va.mul_k, va.shifts, 1);
+            put(va.p, va.mul_p, va.shifts, 2);
+            l.entry_major = lay.slot_major || all_planes;
             vector_launch(l, ents.data() + done, k, chunks);
             // several blocks of a rank-major row to a line, read by ranks that lie near each other: one eighth of the
             // ranks per XCD keeps the line in its L2 (runs -> eighths, one set of buffers repeated and many in turn:
             // 64^3, 20 B 65 -> 54 and 73 -> 78 us, 300^2, 24 neighbours, 16 B 13.6 -> 12.2 and 17.8 -> 17.8, 50^3 star,
             // 20 B 10.3 -> 6.7 and 12 -> 11.5; 64^3, 40 B 103 -> 113 and 115 -> 123)
-            if (op == ISO_OP_ALLTOALL && !l.vec.entry_major && ents.size() > 1) l.eighths = size0 <= 32;
+            if (op == ISO_OP_ALLTOALL && !l.entry_major && ents.size() > 1) l.eighths = size0 <= 32;
             if (op == ISO_OP_ALLGATHER && ents.size() > 1) allgather_order(l, ents.data() + done, k);
             if (l.vec.per) total = per_entry * ((k + l.vec.per - 1) / l.vec.per);
             if (l.vector_dims) return ISO_SUCCESS;
@@ -1144,43 +1168,35 @@ private:
             MeshArgs &ma = l.mesh_shift;
             ma.inner = shift ? (uint32_t)c.inner[r.dim] : 1u;
             ma.pj = shift ? (uint32_t)c.dims[r.dim] : 1u;
-            ma.shift_dim = shift ? r.dim : -1;
-            ma.d = c.d;
-            ma.d_chunks = dch;
-            ma.d_k = dk;
-            ma.d_p = dp;
-            ma.entry_major = lay.slot_major;
-            ma.last_offset = size0 - width;
-            ma.d_inner = make_fastdiv(ma.inner);
-            ma.d_pj = make_fastdiv(ma.pj);
-            for (int j = 0; j < c.d; ++j) {
-                if (c.periodic[(size_t)j]) ma.periodic_mask |= 1u << j;
-                ma.d_dims[j] = make_fastdiv((uint32_t)c.dims[j]);
-                ma.inner_of[j] = (uint32_t)c.inner[j];
-            }
+            ma.torus = torus_bits(c.d, shift ? r.dim : -1, periodic_mask());
+            ma.chunks = (uint32_t)chunks;
+            ma.p = (uint32_t)p;
+            l.entry_major = lay.slot_major;
+            put(ma.chunks, ma.mul_chunks, ma.shifts, 0);
+            put(k, ma.mul_k, ma.shifts, 1);
+            put(ma.inner, ma.mul_inner, ma.shifts, 2);
+            put(ma.pj, ma.mul_pj, ma.shifts, 3);
+            put(ma.p, ma.mul_p, ma.more, 0);
             const std::vector<uint32_t> bits =
                 mesh_interior_tiles(c, lay.slot_major, ents.data() + done, k, total, chunks, p);
             prefixes.insert(prefixes.end(), bits.begin(), bits.end());
         } else {
-            l.shift.inner = shift ? (uint32_t)c.inner[r.dim] : 1u;
-            l.shift.pj = shift ? (uint32_t)c.dims[r.dim] : 1u;
-            l.shift.d_chunks = dch;
-            l.shift.d_k = dk;
-            l.shift.d_p = dp;
-            l.shift.entry_major = lay.slot_major || all_planes;
+            ShiftArgs &sa = l.shift;
+            sa.inner = shift ? (uint32_t)c.inner[r.dim] : 1u;
+            sa.pj = shift ? (uint32_t)c.dims[r.dim] : 1u;
+            sa.chunks = (uint32_t)chunks;
+            sa.p = (uint32_t)p;
+            l.entry_major = lay.slot_major || all_planes;
             // blocks of 2 KiB and more on rank-major buffers: groups of 64 ranks (three tori: 2 KiB -1 to
             // -3 % of the step, 4 KiB 0 to -3 %, 8 KiB -5 %; at 1 KiB and below between -1.5 and +1 %:
             // left alone.  Groups of 32 to 256 ranks measure alike, smaller ones do nothing)
-            constexpr uint32_t kRankGroup = 64;
-            if (!l.shift.entry_major && size0 >= 2048 && p >= kRankGroup) {
-                l.shift.group = kRankGroup;
-                l.shift.grouped = (uint32_t)((p / kRankGroup) * kRankGroup * k);
-                l.shift.d_group_k = make_fastdiv(kRankGroup * k);
-                l.shift.d_group = make_fastdiv(kRankGroup);
-            }
-            l.shift.last_offset = size0 - width;
-            l.shift.d_inner = make_fastdiv(l.shift.inner);
-            l.shift.d_pj = make_fastdiv(l.shift.pj);
+            if (!l.entry_major && size0 >= 2048 && p >= kRankGroup) sa.grouped = (uint32_t)((p / kRankGroup) * kRankGroup * k);
+            put(sa.chunks, sa.mul_chunks, sa.shifts, 0);
+            put(k, sa.mul_k, sa.shifts, 1);
+            put(sa.inner, sa.mul_inner, sa.shifts, 2);
+            put(sa.pj, sa.mul_pj, sa.shifts, 3);
+            put(sa.p, sa.mul_p, sa.more, 0);
+            if (sa.grouped) put(k * kRankGroup, sa.mul_group_k, sa.more, 1);
             if (op == ISO_OP_ALLGATHER && push_launch(l, ents.data() + done, k, per_entry)) {
                 total = per_entry * l.shift.k;
                 return ISO_SUCCESS;
@@ -1228,10 +1244,11 @@ private:
         table.insert(table.end(), by_source.begin(), by_source.end());
         prefixes.insert(prefixes.end(), first.begin(), first.end());
         l.uniform_waves = false;
-        l.shift.group = 0;
+        l.shift.grouped = 0;
         l.shift.k_all = k;
         l.shift.k = n;
-        l.shift.d_k = make_fastdiv(n);
+        l.shift.shifts &= ~0xFF00u;
+        put(n, l.shift.mul_k, l.shift.shifts, 1);
         return true;
     }
 
@@ -1240,10 +1257,6 @@ private:
     // Other launches keep the general tables.
     void vector_launch(Launch &l, const HostEntry *ents, uint32_t k, uint64_t chunks) {
         VectorArgs &va = l.vec;
-        for (int j = 0; j < c.d; ++j) {
-            va.d_dims[j] = make_fastdiv((uint32_t)c.dims[j]);
-            va.inner[j] = (uint32_t)c.inner[j];
-        }
         bool packed = c.d <= kVectorDims && k <= kLdsEntries;
         for (uint32_t q = 0; packed && q < k; ++q)
             packed = ents[q].de.src_stride == ents[0].de.src_stride && ents[q].de.dst_stride == ents[0].de.dst_stride;
@@ -1254,8 +1267,9 @@ private:
         va.dst_stride = ents[0].de.dst_stride;
         for (int j = 0; j < kVectorDims; ++j) {                  // last dimension first, absent ones of size 1
             const int l_dim = c.d - 1 - j;
-            va.d_last[j] = make_fastdiv(l_dim < 0 ? 1u : (uint32_t)c.dims[(size_t)l_dim]);
-            va.wrap[j] = l_dim < 0 ? 0u : (uint32_t)((uint64_t)c.dims[(size_t)l_dim] * (uint64_t)c.inner[(size_t)l_dim]);
+            va.last[j] = l_dim < 0 ? 1u : (uint32_t)c.dims[(size_t)l_dim];
+            if (j + 1 < kVectorDims)
+                put(va.last[j], va.mul_last[j], j == 0 ? va.shifts : j < 3 ? va.more : va.shift_last3, j == 0 ? 3 : j < 3 ? j - 1 : 0);
         }
         for (uint32_t q = 0; q < k; ++q) {
             VectorEntry ve{};
@@ -1323,9 +1337,7 @@ private:
         l.kernel = kBlockKernel;
         l.mesh = c.mesh;
         BlockArgs &b = l.block;
-        b.shift_dim = r.kind == ISO_ROUND_SHIFT ? r.dim : -1;
-        for (int j = 0; j < c.d; ++j)
-            if (c.periodic[(size_t)j]) b.periodic_mask |= 1u << j;
+        b.torus = torus_bits(c.d, r.kind == ISO_ROUND_SHIFT ? r.dim : -1, periodic_mask());
         // per launch: k + 1 prefix values, then k multipliers of the divisions by the entries'
         // unit counts (the two shifts of each go into the entry's meta word)
         const bool entry_major = lay.slot_major;
@@ -1346,57 +1358,66 @@ private:
         if (k == 0) return ISO_ERR_TOO_LARGE;          // one block plane alone is too large
         for (uint32_t q = 0; q < k; ++q) prefixes.push_back(make_fastdiv(ents[done + q].de.units).mul);
         total = row_units * p;
-        b.entry_major = entry_major;
+        l.entry_major = entry_major;
+        l.vector_round = r.kind == ISO_ROUND_VECTOR;
         b.equal_units = ents[done].de.units;
         for (uint32_t q = 1; q < k; ++q)
             if (ents[done + q].de.units != b.equal_units) b.equal_units = 0;
-        b.d_units = make_fastdiv(b.equal_units ? b.equal_units : 1u);
-        b.d_plane = make_fastdiv(b.equal_units ? (uint32_t)(p * b.equal_units) : 1u);
-        b.vector_round = r.kind == ISO_ROUND_VECTOR;
-        b.d_row = make_fastdiv((uint32_t)row_units);
+        b.plane = b.equal_units ? (uint32_t)(p * b.equal_units) : 1u;
+        b.row = (uint32_t)row_units;
         // shift rounds on rank-major buffers: ranks in groups (not the staged schedule, whose tiny
         // blocks travel through dense planes: +1 % there; not the s-exchange: +1 to +4 %)
         if (!entry_major && r.kind != ISO_ROUND_VECTOR && pl.algorithm != ISO_ALG_COMBINED_STAGED &&
             p >= kBlockGroup) {
             l.block_groups = true;
             b.grouped = (uint32_t)((p / kBlockGroup) * kBlockGroup * row_units);
-            b.d_group_row = make_fastdiv((uint32_t)(row_units * kBlockGroup));
-            b.d_plane = make_fastdiv(b.equal_units ? kBlockGroup * b.equal_units : 1u);
+            b.plane = b.equal_units ? kBlockGroup * b.equal_units : 1u;
+            put((uint32_t)(row_units * kBlockGroup), b.mul_group_row, b.more, 1);
         }
         const bool shift = r.kind == ISO_ROUND_SHIFT;
         b.inner = shift ? (uint32_t)c.inner[r.dim] : 1u;
         b.pj = shift ? (uint32_t)c.dims[r.dim] : 1u;
-        b.d_inner = make_fastdiv(b.inner);
-        b.d_pj = make_fastdiv(b.pj);
-        b.d = c.d;
-        for (int j = 0; j < c.d; ++j) {
-            b.d_dims[j] = make_fastdiv((uint32_t)c.dims[j]);
-            b.inner_of[j] = (uint32_t)c.inner[j];
-        }
+        put(b.row, b.mul_row, b.shifts, 0);
+        put(b.inner, b.mul_inner, b.shifts, 1);
+        put(b.pj, b.mul_pj, b.shifts, 2);
+        put(b.equal_units ? b.equal_units : 1u, b.mul_units, b.shifts, 3);
+        put(b.plane, b.mul_plane, b.more, 0);
         return ISO_SUCCESS;
     }
 
-    // One device table: the entries, then the [s][d] residues, then what single launches read besides
+    // One device table: the entries, then the dimensions and the [s][d] residues, then what single launches read besides
     // (prefix arrays of irregular launches, the mesh's interior-tile bitmaps, the records of the staged
     // schedule's last launch); then the launches get their addresses in it.  The residues keep their place in it
     // but are written only where a kernel reads them (a launch of its own in the allocation-free call: 8^3, 26
     // neighbours, 64 B 13.5 -> 10.7 us).
     int upload() {
         const size_t entry_bytes = table.size() * sizeof(DevEntry);
-        const size_t off_bytes = (c.can.size() * sizeof(uint32_t) + 15) & ~size_t(15);   // what follows: 16-byte aligned
+        const size_t c_bytes = (c.can.size() * sizeof(uint32_t) + 15) & ~size_t(15);     // what follows: 16-byte aligned
+        const size_t off_bytes = sizeof(TorusDims) + c_bytes;
         bool reads_residues = false;
         for (const Pending &pd : pending)
             reads_residues = reads_residues || pd.l.kernel == kMeshShiftKernel || pd.l.kernel == kBlockKernel ||
                              (pd.l.kernel == kVectorKernel && !pd.l.vector_dims);
-        const size_t off_used = reads_residues ? c.can.size() * sizeof(uint32_t) : 0;
+        std::vector<uint32_t> torus;                     // TorusDims and the residues behind it
+        if (reads_residues) {
+            torus.resize(sizeof(TorusDims) / 4);
+            TorusDims &td = *(TorusDims *)torus.data();
+            for (int j = 0; j < c.d; ++j) {
+                td.d_dims[j] = make_fastdiv((uint32_t)c.dims[(size_t)j]);
+                td.inner[j] = (uint32_t)c.inner[(size_t)j];
+            }
+            torus.insert(torus.end(), c.can.begin(), c.can.end());
+        }
+        const size_t off_used = torus.size() * sizeof(uint32_t);
         const size_t pre_bytes = prefixes.size() * sizeof(uint32_t);
         char *dev = nullptr;
         int st;
         if (arena) {
-            if (entry_bytes + off_bytes + pre_bytes > arena->table_bytes) return ISO_ERR_SCRATCH;
+            // (TorusDims has room of its own behind table_bytes)
+            if (entry_bytes + c_bytes + pre_bytes > arena->table_bytes) return ISO_ERR_SCRATCH;
             dev = (char *)arena->table;
             if ((st = store_table(*arena, 0, table.data(), entry_bytes)) != ISO_SUCCESS) return st;
-            if ((st = store_table(*arena, entry_bytes, c.can.data(), off_used)) != ISO_SUCCESS) return st;
+            if ((st = store_table(*arena, entry_bytes, torus.data(), off_used)) != ISO_SUCCESS) return st;
             if ((st = store_table(*arena, entry_bytes + off_bytes, prefixes.data(), pre_bytes)) != ISO_SUCCESS) return st;
         } else if (entry_bytes + off_bytes + pre_bytes) {
             const size_t bytes = entry_bytes + off_bytes + pre_bytes;
@@ -1407,23 +1428,23 @@ private:
             } else {
                 std::vector<char> host(bytes);
                 if (entry_bytes) std::memcpy(host.data(), table.data(), entry_bytes);
-                if (off_used) std::memcpy(host.data() + entry_bytes, c.can.data(), off_used);
+                if (off_used) std::memcpy(host.data() + entry_bytes, torus.data(), off_used);
                 if (pre_bytes) std::memcpy(host.data() + entry_bytes + off_bytes, prefixes.data(), pre_bytes);
                 ISO_HIP_TRY(hipMemcpy(dev, host.data(), bytes, hipMemcpyHostToDevice));
             }
         }
         const DevEntry *dev_entries = (const DevEntry *)dev;
-        const uint32_t *dev_offsets = (const uint32_t *)(dev + entry_bytes);
+        const TorusDims *dev_dims = (const TorusDims *)(dev + entry_bytes);
         const uint32_t *dev_prefix = (const uint32_t *)(dev + entry_bytes + off_bytes);
         for (Pending &pd : pending) {
             if (pd.l.kernel == kChainKernel) {
-                // its hops are among its arguments
+                pd.l.chain.args = (const ChainArgs *)(dev_prefix + pd.first_prefix);
             } else if (pd.l.kernel == kVectorKernel) {
                 pd.l.vec.entries = dev_entries + pd.first_entry;
-                pd.l.vec.offsets = dev_offsets;
+                pd.l.vec.dims = dev_dims;
             } else if (pd.l.kernel == kMeshShiftKernel) {
                 pd.l.mesh_shift.entries = dev_entries + pd.first_entry;
-                pd.l.mesh_shift.offsets = dev_offsets;
+                pd.l.mesh_shift.dims = dev_dims;
                 pd.l.mesh_shift.interior = dev_prefix + pd.first_prefix;
             } else if (pd.l.kernel == kDeliverKernel) {
                 pd.l.deliver.entries = (const DeliverEntry *)(dev_prefix + pd.first_prefix);
@@ -1432,7 +1453,7 @@ private:
             } else if (pd.l.kernel == kBlockKernel) {
                 pd.l.block.entries = dev_entries + pd.first_entry;
                 pd.l.block.prefix = dev_prefix + pd.first_prefix;
-                pd.l.block.offsets = dev_offsets;
+                pd.l.block.dims = dev_dims;
             } else {
                 pd.l.shift.entries = dev_entries + pd.first_entry;
                 pd.l.shift.groups = dev_prefix + pd.first_prefix;

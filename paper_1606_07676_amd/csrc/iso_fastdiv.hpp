@@ -33,6 +33,19 @@ inline FastDiv make_fastdiv(uint32_t d) {
     return f;
 }
 
+// The two shifts in a byte, and a divisor again from its parts: launch constants carry the multiplier, the divisor
+// (often needed anyway) and this byte of each division.
+inline uint32_t shift_byte(const FastDiv &f) { return f.sh2 | (f.sh1 << 5); }
+
+ISO_HD FastDiv fastdiv_of(uint32_t mul, uint32_t div, uint32_t shifts, uint32_t byte) {
+    FastDiv f;
+    f.mul = mul;
+    f.sh2 = (shifts >> (8 * byte)) & 31u;
+    f.sh1 = (shifts >> (8 * byte + 5)) & 1u;
+    f.div = div;
+    return f;
+}
+
 ISO_HD uint32_t mulhi_u32(uint32_t a, uint32_t b) {
 #if defined(__HIP_DEVICE_COMPILE__)
     return __umulhi(a, b);

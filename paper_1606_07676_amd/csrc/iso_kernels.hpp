@@ -67,6 +67,7 @@ struct TileMap {
     uint32_t per_xcd;      // kEighths: tiles per XCD, ceil(n_tiles / 8)
 };
 constexpr uint32_t kEighths = 31;
+constexpr uint32_t kRankGroupLog2 = 6, kRankGroup = 1u << kRankGroupLog2;   // see ShiftArgs::grouped
 
 __device__ __forceinline__ bool tile_of_block(const TileMap &tm, uint32_t &tile) {
     const uint32_t bid = blockIdx.x, x = bid & 7u, y = bid >> 3;
@@ -75,26 +76,63 @@ __device__ __forceinline__ bool tile_of_block(const TileMap &tm, uint32_t &tile)
     return tile < tm.n_tiles;
 }
 
+// What a kernel is handed.  The runtime's cost of a launch on the host depends on the size of its arguments: 2.4 to
+// 2.7 us up to 112 bytes, 3.0 to 3.4 at 128 to 256, 3.5 to 3.9 from 512 on (starts of small collectives are nothing
+// but that, the shift kernel's 200 bytes of launch constants written out were a quarter of it).  So a division
+// travels as its multiplier and a byte of shifts next to the divisor, what follows from other constants is worked
+// out again in scalar registers, and arrays over the dimensions stay in the request's table.
+constexpr size_t kCheapArguments = 112;
+
 struct ShiftArgs {
     const DevEntry *entries;
-    TileMap map;
+    // Push form (k counts sources then): [k + 1] first entry of every source; entries in all (k_all).
+    const uint32_t *groups;
     uint32_t total;        // units in this launch = p * k * chunks
     uint32_t k;            // entries in this launch
     uint32_t inner;        // rank stride of the shifted dimension
     uint32_t pj;           // its size
-    uint32_t entry_major;  // unit order (entry, rank, chunk) instead of (rank, entry, chunk)
-    FastDiv d_chunks, d_k, d_inner, d_pj, d_p;
-    uint64_t last_offset;  // block size - unit width (read by the TAIL instantiations only)
-    // Large blocks on rank-major buffers: the ranks are taken in groups of `group`, and inside a group the
-    // order is (entry, rank, chunk), so that a plane of the workspace sees `group` consecutive blocks at a
-    // time instead of one (0: no groups).  `grouped` = the blocks of all whole groups, (p / group) * group * k;
+    uint32_t chunks, p;    // units of a block; ranks
+    uint32_t mul_chunks, mul_k, mul_inner, mul_pj, mul_p, mul_group_k;
+    uint32_t shifts;       // of the divisions by chunks, k, inner, pj
+    uint32_t more;         // shifts of p, group * k; launch_flags
+    // Large blocks on rank-major buffers: the ranks are taken in groups of kRankGroup, and inside a group the
+    // order is (entry, rank, chunk), so that a plane of the workspace sees that many consecutive blocks at a
+    // time instead of one.  `grouped` = the blocks of all whole groups, (p / kRankGroup) * kRankGroup * k;
     // the ranks after them keep the plain order.
-    uint32_t group, grouped;
-    FastDiv d_group_k, d_group;   // group * k; group
-    // Push form (k counts sources then): [k + 1] first entry of every source; entries in all.
-    const uint32_t *groups;
-    uint32_t k_all;
+    uint32_t grouped, k_all;
 };
+static_assert(sizeof(ShiftArgs) <= kCheapArguments, "launch cost");
+
+// The upper 16 bits of a word whose lower ones hold the shifts of two divisions.
+//   bits 16-20 TileMap::run_log2; 21 entry-major order (entry, rank, chunk) instead of (rank, entry, chunk);
+//   22-25 by how many bytes a block's last unit is pulled back (TAIL); 26 block kernel: full offset vectors
+inline uint32_t launch_flags(uint32_t run_log2, bool entry_major, uint32_t pull, bool vector_round = false) {
+    return (run_log2 << 16) | ((uint32_t)entry_major << 21) | (pull << 22) | ((uint32_t)vector_round << 26);
+}
+__device__ __forceinline__ uint32_t is_entry_major(uint32_t more) { return (more >> 21) & 1u; }
+__device__ __forceinline__ uint32_t is_vector_round(uint32_t more) { return (more >> 26) & 1u; }
+// block size - unit width
+template <typename V>
+__device__ __forceinline__ uint64_t last_offset_of(uint32_t chunks, uint32_t more) {
+    return (uint64_t)(chunks - 1u) * sizeof(V) - ((more >> 22) & 15u);
+}
+__device__ __forceinline__ TileMap map_of(uint32_t n_tiles, uint32_t more) {
+    return TileMap{n_tiles, (more >> 16) & 31u, (n_tiles + 7u) >> 3};
+}
+__device__ __forceinline__ uint32_t tiles_of(uint32_t total) { return (total + (uint32_t)kThreads - 1u) / (uint32_t)kThreads; }
+
+// The dimensions of the torus in the request's table, in front of the residues [s][d] of its offsets (kernels that
+// decode every coordinate with run-time indices, and meshes).  Read through the scalar cache.
+struct TorusDims {
+    FastDiv d_dims[ISO_MAX_DIMS];
+    uint32_t inner[ISO_MAX_DIMS];
+};
+typedef const TorusDims __attribute__((address_space(4))) *dims_ptr;
+__device__ __forceinline__ dims_ptr const_dims(const TorusDims *d) { return (dims_ptr)(uintptr_t)d; }
+__device__ __forceinline__ const uint32_t *offsets_after(const TorusDims *d) { return (const uint32_t *)(d + 1); }
+__device__ __forceinline__ FastDiv dim_of(dims_ptr d, int j) {
+    return FastDiv{d->d_dims[j].mul, d->d_dims[j].sh1, d->d_dims[j].sh2, d->d_dims[j].div};
+}
 
 // Entries of a launch that moves equal blocks by full offset vectors (the s-exchange) on a torus of at most
 // kVectorDims dimensions: all that a lane needs of its entry in 48 bytes, so that no second table is read.
@@ -110,21 +148,19 @@ static_assert(sizeof(VectorEntry) == sizeof(DevEntry), "staged by the same code"
 
 struct VectorArgs {
     const DevEntry *entries;   // VectorEntry records instead for the kernels of at most kVectorDims dimensions
-    const uint32_t *offsets;   // [s][d] residues
-    TileMap map;
-    uint32_t total;
-    uint32_t k;
+    const TorusDims *dims;     // the others: dimensions and residues
+    uint32_t total, k;
     int32_t d;
-    uint32_t entry_major;
     uint32_t per;                             // push kernel: entries a lane writes to
     uint32_t src_stride, dst_stride;          // the same for all entries (VectorEntry launches)
-    FastDiv d_chunks, d_k, d_p;
-    FastDiv d_last[kVectorDims];              // VectorEntry launches: the dimensions from the last to the first
-    uint32_t wrap[kVectorDims];               // p_j * inner_j of those
-    uint64_t last_offset;
-    FastDiv d_dims[ISO_MAX_DIMS];
-    uint32_t inner[ISO_MAX_DIMS];
+    uint32_t chunks, p;
+    uint32_t mul_chunks, mul_k, mul_p;
+    uint32_t shifts;                          // chunks, k, p; the last dimension
+    uint32_t more;                            // the second and third last dimension; launch_flags
+    uint32_t last[kVectorDims];               // VectorEntry launches: the dimensions from the last to the first
+    uint32_t mul_last[kVectorDims - 1], shift_last3;
 };
+static_assert(sizeof(VectorArgs) <= kCheapArguments, "launch cost");
 
 typedef uint32_t vec16_t __attribute__((ext_vector_type(4)));
 typedef uint32_t vec8_t __attribute__((ext_vector_type(2)));
@@ -242,9 +278,7 @@ constexpr int kUnrolledDims = 6;
 
 // Source rank of R for a move by the full offset vector c[0..d): R (-) c on the torus.
 template <int D>
-__device__ __forceinline__ uint32_t vector_source_rank_d(uint32_t R, const uint32_t *__restrict__ c,
-                                                         const FastDiv (&d_dims)[ISO_MAX_DIMS],
-                                                         const uint32_t (&inner)[ISO_MAX_DIMS]) {
+__device__ __forceinline__ uint32_t vector_source_rank_d(uint32_t R, const uint32_t *__restrict__ c, dims_ptr dims) {
     uint32_t cj[D];
 #pragma unroll
     for (int j = 0; j < D; ++j) cj[j] = c[j];
@@ -252,86 +286,85 @@ __device__ __forceinline__ uint32_t vector_source_rank_d(uint32_t R, const uint3
 #pragma unroll
     for (int j = D - 1; j >= 0; --j) {
         uint32_t q, rj;
-        fast_divmod(rem, d_dims[j], q, rj);
+        const FastDiv dj = dim_of(dims, j);
+        fast_divmod(rem, dj, q, rj);
         rem = q;
-        srcR -= cj[j] * inner[j];                                   // cj steps back ...
-        if (rj < cj[j]) srcR += d_dims[j].div * inner[j];           // ... around the ring
+        srcR -= cj[j] * dims->inner[j];                                   // cj steps back ...
+        if (rj < cj[j]) srcR += dj.div * dims->inner[j];           // ... around the ring
     }
     return srcR;
 }
 
-__device__ __forceinline__ uint32_t vector_source_rank(uint32_t R, const uint32_t *__restrict__ c, int32_t d,
-                                                       const FastDiv (&d_dims)[ISO_MAX_DIMS],
-                                                       const uint32_t (&inner)[ISO_MAX_DIMS]) {
+__device__ __forceinline__ uint32_t vector_source_rank(uint32_t R, const uint32_t *__restrict__ c, int32_t d, dims_ptr dims) {
     switch (d) {
-        case 1: return vector_source_rank_d<1>(R, c, d_dims, inner);
-        case 2: return vector_source_rank_d<2>(R, c, d_dims, inner);
-        case 3: return vector_source_rank_d<3>(R, c, d_dims, inner);
-        case 4: return vector_source_rank_d<4>(R, c, d_dims, inner);
-        case 5: return vector_source_rank_d<5>(R, c, d_dims, inner);
-        case 6: return vector_source_rank_d<6>(R, c, d_dims, inner);
+        case 1: return vector_source_rank_d<1>(R, c, dims);
+        case 2: return vector_source_rank_d<2>(R, c, dims);
+        case 3: return vector_source_rank_d<3>(R, c, dims);
+        case 4: return vector_source_rank_d<4>(R, c, dims);
+        case 5: return vector_source_rank_d<5>(R, c, dims);
+        case 6: return vector_source_rank_d<6>(R, c, dims);
         default: break;
     }
     uint32_t srcR = R, rem = R;
     for (int j = d - 1; j >= 0; --j) {
         uint32_t q, rj;
-        fast_divmod(rem, d_dims[j], q, rj);
+        const FastDiv dj = dim_of(dims, j);
+        fast_divmod(rem, dj, q, rj);
         rem = q;
-        srcR -= c[j] * inner[j];
-        if (rj < c[j]) srcR += d_dims[j].div * inner[j];
+        srcR -= c[j] * dims->inner[j];
+        if (rj < c[j]) srcR += dj.div * dims->inner[j];
     }
     return srcR;
 }
 
 // Makes the compiler fetch these launch constants here, in one batch of scalar loads, instead of
 // each in front of its first use behind some branch (every such fetch is a wait of its own).
-__device__ __forceinline__ void fetch_now(const FastDiv &f) { asm volatile("" ::"s"(f.mul), "s"(f.sh1), "s"(f.sh2), "s"(f.div)); }
-
 __device__ __forceinline__ void fetch_now(const ShiftArgs &a) {
-    asm volatile("" ::"s"(a.entries), "s"(a.map.n_tiles), "s"(a.map.run_log2), "s"(a.map.per_xcd), "s"(a.total),
-                 "s"(a.k), "s"(a.inner), "s"(a.pj), "s"(a.entry_major));
-    fetch_now(a.d_chunks);
-    fetch_now(a.d_k);
-    fetch_now(a.d_inner);
-    fetch_now(a.d_pj);
-    fetch_now(a.d_p);
+    asm volatile("" ::"s"(a.entries), "s"(a.total), "s"(a.k), "s"(a.inner), "s"(a.pj), "s"(a.chunks), "s"(a.p),
+                 "s"(a.mul_chunks), "s"(a.mul_k), "s"(a.mul_inner), "s"(a.mul_pj), "s"(a.mul_p), "s"(a.shifts), "s"(a.more));
 }
+
+// The divisions of a shift launch.
+struct ShiftDivs {
+    FastDiv chunks, k, inner, pj, p, group_k;
+    __device__ __forceinline__ explicit ShiftDivs(const ShiftArgs &a)
+        : chunks(fastdiv_of(a.mul_chunks, a.chunks, a.shifts, 0)), k(fastdiv_of(a.mul_k, a.k, a.shifts, 1)),
+          inner(fastdiv_of(a.mul_inner, a.inner, a.shifts, 2)), pj(fastdiv_of(a.mul_pj, a.pj, a.shifts, 3)),
+          p(fastdiv_of(a.mul_p, a.p, a.more, 0)), group_k(fastdiv_of(a.mul_group_k, a.k << kRankGroupLog2, a.more, 1)) {}
+};
 
 template <typename V, bool LDS, int POLICY, bool TAIL, bool GROUPS = false>
 __global__ __launch_bounds__(kThreads) void shift_round_kernel(const ShiftArgs a) {
     fetch_now(a);
-    if constexpr (GROUPS) {
-        asm volatile("" ::"s"(a.group), "s"(a.grouped));
-        fetch_now(a.d_group_k);
-        fetch_now(a.d_group);
-    }
+    if constexpr (GROUPS) asm volatile("" ::"s"(a.grouped), "s"(a.mul_group_k));
+    const ShiftDivs div(a);
     __shared__ DevEntry lds[LDS ? kLdsEntries : 1];
     uint32_t tile;
-    if (!tile_of_block(a.map, tile)) return;            // (the whole workgroup: no one is left at the barrier)
+    if (!tile_of_block(map_of(tiles_of(a.total), a.more), tile)) return;            // (the whole workgroup: no one is left at the barrier)
     // The table goes through LDS; its load is under way while the lanes work out their indices, which do
     // not depend on it.
     StagedEntries<LDS> staging;
     staging.issue(a.entries, a.k);
     const uint32_t u = tile * (uint32_t)kThreads + threadIdx.x;
     uint32_t t, ch, R, e;
-    fast_divmod(u, a.d_chunks, t, ch);
+    fast_divmod(u, div.chunks, t, ch);
     if constexpr (GROUPS) {                             // an instantiation of its own: the few scalar loads and
         if (t < a.grouped) {                            // the branch cost the plain one 2 - 3 % on small blocks
-            uint32_t g, in_group, rg;
-            fast_divmod(t, a.d_group_k, g, in_group);
-            fast_divmod(in_group, a.d_group, e, rg);
-            R = g * a.group + rg;
+            uint32_t g, in_group;
+            fast_divmod(t, div.group_k, g, in_group);
+            e = in_group >> kRankGroupLog2;
+            R = (g << kRankGroupLog2) + (in_group & (kRankGroup - 1u));
         } else {
-            fast_divmod(t - a.grouped, a.d_k, R, e);
-            R += fast_div(a.grouped, a.d_k);            // the ranks of the whole groups come first
+            fast_divmod(t - a.grouped, div.k, R, e);
+            R += fast_div(a.grouped, div.k);            // the ranks of the whole groups come first
         }
-    } else if (a.entry_major) {
-        fast_divmod(t, a.d_p, e, R);
+    } else if (is_entry_major(a.more)) {
+        fast_divmod(t, div.p, e, R);
     } else {
-        fast_divmod(t, a.d_k, R, e);
+        fast_divmod(t, div.k, R, e);
     }
-    const uint32_t q = fast_div(R, a.d_inner);
-    const uint32_t rj = q - fast_div(q, a.d_pj) * a.pj;       // coordinate of R in the shifted dimension
+    const uint32_t q = fast_div(R, div.inner);
+    const uint32_t rj = q - fast_div(q, div.pj) * a.pj;       // coordinate of R in the shifted dimension
     staging.commit(lds);
     if (u >= a.total) return;                                  // (indices beyond the launch are never used)
     const DevEntry en = LDS ? lds[e] : a.entries[e];
@@ -340,7 +373,7 @@ __global__ __launch_bounds__(kThreads) void shift_round_kernel(const ShiftArgs a
     uint32_t srcR = R - en.shift * a.inner;
     if (rj < en.shift) srcR += a.pj * a.inner;
     move_unit<V, POLICY>(block_address(en.dst, R, en.dst_stride), block_address(en.src, srcR, en.src_stride),
-                      unit_offset_if<V, TAIL>(ch, a.last_offset));
+                      unit_offset_if<V, TAIL>(ch, last_offset_of<V>(a.chunks, a.more)));
 }
 
 // The same round for blocks that are a multiple of 1 KiB (64 units of 16 bytes): the 64 units of a
@@ -351,30 +384,31 @@ __global__ __launch_bounds__(kThreads) void shift_round_kernel(const ShiftArgs a
 template <int POLICY, bool GROUPS = false>
 __global__ __launch_bounds__(kThreads) void shift_round_uniform_kernel(const ShiftArgs a) {
     fetch_now(a);
+    const ShiftDivs div(a);
     uint32_t tile;
-    if (!tile_of_block(a.map, tile)) return;
+    if (!tile_of_block(map_of(tiles_of(a.total), a.more), tile)) return;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t u0 = tile * (uint32_t)kThreads + wave * 64u;      // first unit of this wavefront
     if (u0 >= a.total) return;                                       // total is a multiple of 64
     uint32_t t, ch0, R, e;
-    fast_divmod(u0, a.d_chunks, t, ch0);
+    fast_divmod(u0, div.chunks, t, ch0);
     if constexpr (GROUPS) {
         if (t < a.grouped) {
-            uint32_t g, in_group, rg;
-            fast_divmod(t, a.d_group_k, g, in_group);
-            fast_divmod(in_group, a.d_group, e, rg);
-            R = g * a.group + rg;
+            uint32_t g, in_group;
+            fast_divmod(t, div.group_k, g, in_group);
+            e = in_group >> kRankGroupLog2;
+            R = (g << kRankGroupLog2) + (in_group & (kRankGroup - 1u));
         } else {
-            fast_divmod(t - a.grouped, a.d_k, R, e);
-            R += fast_div(a.grouped, a.d_k);
+            fast_divmod(t - a.grouped, div.k, R, e);
+            R += fast_div(a.grouped, div.k);
         }
-    } else if (a.entry_major) {
-        fast_divmod(t, a.d_p, e, R);
+    } else if (is_entry_major(a.more)) {
+        fast_divmod(t, div.p, e, R);
     } else {
-        fast_divmod(t, a.d_k, R, e);
+        fast_divmod(t, div.k, R, e);
     }
-    const uint32_t q = fast_div(R, a.d_inner);
-    const uint32_t rj = q - fast_div(q, a.d_pj) * a.pj;
+    const uint32_t q = fast_div(R, div.inner);
+    const uint32_t rj = q - fast_div(q, div.pj) * a.pj;
     // the table is never written while a collective runs: read it as constant memory, through the scalar cache
     typedef const DevEntry __attribute__((address_space(4))) *const_entry_ptr;
     const const_entry_ptr en = (const_entry_ptr)(uintptr_t)(a.entries + e);
@@ -393,10 +427,11 @@ template <typename V, bool TAIL>
 __global__ __launch_bounds__(kThreads) void shift_push_kernel(const ShiftArgs a) {
     fetch_now(a);
     asm volatile("" ::"s"(a.groups), "s"(a.k_all));
+    const ShiftDivs div(a);
     __shared__ DevEntry lds[kLdsEntries];
     __shared__ uint32_t lds_first[kLdsEntries + 1];
     uint32_t tile;
-    if (!tile_of_block(a.map, tile)) return;
+    if (!tile_of_block(map_of(tiles_of(a.total), a.more), tile)) return;
     StagedEntries<true> staging;
     staging.issue(a.entries, a.k_all);
     const uint32_t q = kThreads - 1 - threadIdx.x;       // the workgroup's last lanes, as in the block kernel
@@ -404,12 +439,12 @@ __global__ __launch_bounds__(kThreads) void shift_push_kernel(const ShiftArgs a)
     const uint32_t first = stages ? a.groups[q] : 0u;
     const uint32_t u = tile * (uint32_t)kThreads + threadIdx.x;
     uint32_t t, ch, S, g;
-    fast_divmod(u, a.d_chunks, t, ch);
-    if (a.entry_major) fast_divmod(t, a.d_p, g, S);
-    else fast_divmod(t, a.d_k, S, g);
-    const uint32_t qq = fast_div(S, a.d_inner);
-    const uint32_t sj = qq - fast_div(qq, a.d_pj) * a.pj;
-    const uint64_t off = unit_offset_if<V, TAIL>(ch, a.last_offset);
+    fast_divmod(u, div.chunks, t, ch);
+    if (is_entry_major(a.more)) fast_divmod(t, div.p, g, S);
+    else fast_divmod(t, div.k, S, g);
+    const uint32_t qq = fast_div(S, div.inner);
+    const uint32_t sj = qq - fast_div(qq, div.pj) * a.pj;
+    const uint64_t off = unit_offset_if<V, TAIL>(ch, last_offset_of<V>(a.chunks, a.more));
     if (stages) lds_first[q] = first;
     staging.commit(lds);
     if (u >= a.total) return;
@@ -434,34 +469,40 @@ __global__ __launch_bounds__(kThreads) void shift_push_kernel(const ShiftArgs a)
 // decoded into (3 or kVectorDims, absent ones of size 1 in front); D = 0: any torus, from the general tables.
 template <int D>
 __device__ __forceinline__ void fetch_now(const VectorArgs &a) {
-    asm volatile("" ::"s"(a.entries), "s"(a.map.n_tiles), "s"(a.map.run_log2), "s"(a.map.per_xcd), "s"(a.total),
-                 "s"(a.k), "s"(a.entry_major));
-    fetch_now(a.d_chunks);
-    fetch_now(a.d_k);
-    fetch_now(a.d_p);
+    asm volatile("" ::"s"(a.entries), "s"(a.total), "s"(a.k), "s"(a.chunks), "s"(a.p), "s"(a.mul_chunks), "s"(a.mul_k),
+                 "s"(a.mul_p), "s"(a.shifts), "s"(a.more));
     if constexpr (D == 0) {
-        asm volatile("" ::"s"(a.offsets), "s"(a.d));
+        asm volatile("" ::"s"(a.dims), "s"(a.d));
     } else {
         asm volatile("" ::"s"(a.src_stride), "s"(a.dst_stride));
 #pragma unroll
-        for (int j = 0; j < D; ++j) {
-            asm volatile("" ::"s"(a.wrap[j]));
-            if (j + 1 < D) fetch_now(a.d_last[j]);
-        }
+        for (int j = 0; j + 1 < D; ++j) asm volatile("" ::"s"(a.last[j]), "s"(a.mul_last[j]));
+        if constexpr (D > 4) asm volatile("" ::"s"(a.shift_last3));
     }
 }
 
-// Coordinates of R, last dimension first.
+struct VectorDivs {
+    FastDiv chunks, k, p;
+    __device__ __forceinline__ explicit VectorDivs(const VectorArgs &a)
+        : chunks(fastdiv_of(a.mul_chunks, a.chunks, a.shifts, 0)), k(fastdiv_of(a.mul_k, a.k, a.shifts, 1)),
+          p(fastdiv_of(a.mul_p, a.p, a.shifts, 2)) {}
+};
+
+// Coordinates of R, last dimension first, and the ranks once around each dimension.
 template <int D>
-__device__ __forceinline__ void last_coordinates(uint32_t R, const VectorArgs &a, uint32_t (&r)[D]) {
-    uint32_t rem = R;
+__device__ __forceinline__ void last_coordinates(uint32_t R, const VectorArgs &a, uint32_t (&r)[D], uint32_t (&wrap)[D]) {
+    uint32_t rem = R, once = 1;
 #pragma unroll
     for (int j = 0; j + 1 < D; ++j) {
         uint32_t q;
-        fast_divmod(rem, a.d_last[j], q, r[j]);
+        fast_divmod(rem, fastdiv_of(a.mul_last[j], a.last[j], j == 0 ? a.shifts : j < 3 ? a.more : a.shift_last3, j == 0 ? 3 : j < 3 ? j - 1 : 0),
+                    q, r[j]);
         rem = q;
+        once *= a.last[j];
+        wrap[j] = once;
     }
     r[D - 1] = rem;
+    wrap[D - 1] = a.p;
 }
 
 // What bounds this kernel is the time a wavefront holds its slot before its one load is under way.  Two things
@@ -473,33 +514,34 @@ __device__ __forceinline__ void last_coordinates(uint32_t R, const VectorArgs &a
 template <typename V, int D, bool LDS, int POLICY, bool TAIL>
 __global__ __launch_bounds__(kThreads) void vector_round_kernel(const VectorArgs a) {
     fetch_now<D>(a);
+    const VectorDivs div(a);
     __shared__ DevEntry lds[LDS ? kLdsEntries : 1];
     uint32_t tile;
-    if (!tile_of_block(a.map, tile)) return;
+    if (!tile_of_block(map_of(tiles_of(a.total), a.more), tile)) return;
     StagedEntries<LDS> staging;
     staging.issue(a.entries, a.k);
     const uint32_t u = tile * (uint32_t)kThreads + threadIdx.x;
     uint32_t t, ch, R, e;
-    fast_divmod(u, a.d_chunks, t, ch);
-    if (a.entry_major) fast_divmod(t, a.d_p, e, R);
-    else fast_divmod(t, a.d_k, R, e);
-    const uint64_t off = unit_offset_if<V, TAIL>(ch, a.last_offset);
+    fast_divmod(u, div.chunks, t, ch);
+    if (is_entry_major(a.more)) fast_divmod(t, div.p, e, R);
+    else fast_divmod(t, div.k, R, e);
+    const uint64_t off = unit_offset_if<V, TAIL>(ch, last_offset_of<V>(a.chunks, a.more));
     if constexpr (D == 0) {
         staging.commit(lds);
         if (u >= a.total) return;
         const DevEntry en = LDS ? lds[e] : a.entries[e];
-        const uint32_t srcR = vector_source_rank(R, a.offsets + (size_t)en.shift * a.d, a.d, a.d_dims, a.inner);
+        const uint32_t srcR = vector_source_rank(R, offsets_after(a.dims) + (size_t)en.shift * a.d, a.d, const_dims(a.dims));
         move_unit<V, POLICY>(block_address(en.dst, R, en.dst_stride), block_address(en.src, srcR, en.src_stride), off);
     } else {
-        uint32_t r[D];
-        last_coordinates<D>(R, a, r);
+        uint32_t r[D], wrap[D];
+        last_coordinates<D>(R, a, r, wrap);
         staging.commit(lds);
         if (u >= a.total) return;
         const VectorEntry &en = ((const VectorEntry *)(LDS ? lds : a.entries))[e];
         uint32_t srcR = R - en.back;                    // modulo 2^32, see vector_source_rank
 #pragma unroll
         for (int j = 0; j < D; ++j)
-            if (r[j] < en.c[j]) srcR += a.wrap[j];
+            if (r[j] < en.c[j]) srcR += wrap[j];
         move_unit<V, POLICY>(block_address(en.dst, R, a.dst_stride), block_address(en.src, srcR, a.src_stride), off);
     }
 }
@@ -510,23 +552,24 @@ __global__ __launch_bounds__(kThreads) void vector_round_kernel(const VectorArgs
 template <int D, int POLICY>
 __global__ __launch_bounds__(kThreads) void vector_round_uniform_kernel(const VectorArgs a) {
     fetch_now<D>(a);
+    const VectorDivs div(a);
     uint32_t tile;
-    if (!tile_of_block(a.map, tile)) return;
+    if (!tile_of_block(map_of(tiles_of(a.total), a.more), tile)) return;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t u0 = tile * (uint32_t)kThreads + wave * 64u;      // first unit of this wavefront
     if (u0 >= a.total) return;                                       // total is a multiple of 64
     uint32_t t, ch0, R, e;
-    fast_divmod(u0, a.d_chunks, t, ch0);
-    if (a.entry_major) fast_divmod(t, a.d_p, e, R);
-    else fast_divmod(t, a.d_k, R, e);
+    fast_divmod(u0, div.chunks, t, ch0);
+    if (is_entry_major(a.more)) fast_divmod(t, div.p, e, R);
+    else fast_divmod(t, div.k, R, e);
     typedef const VectorEntry __attribute__((address_space(4))) *const_entry_ptr;
     const const_entry_ptr en = (const_entry_ptr)(uintptr_t)((const VectorEntry *)a.entries + e);
-    uint32_t r[D];
-    last_coordinates<D>(R, a, r);
+    uint32_t r[D], wrap[D];
+    last_coordinates<D>(R, a, r, wrap);
     uint32_t srcR = R - en->back;
 #pragma unroll
     for (int j = 0; j < D; ++j)
-        if (r[j] < en->c[j]) srcR += a.wrap[j];
+        if (r[j] < en->c[j]) srcR += wrap[j];
     move_unit<vec16_t, POLICY>(block_address(en->dst, R, a.dst_stride), block_address(en->src, srcR, a.src_stride),
                             (uint64_t)(ch0 + (threadIdx.x & 63u)) * sizeof(vec16_t));
 }
@@ -538,19 +581,20 @@ __global__ __launch_bounds__(kThreads) void vector_round_uniform_kernel(const Ve
 template <typename V, int D, bool TAIL>
 __global__ __launch_bounds__(kThreads) void push_round_kernel(const VectorArgs a) {
     fetch_now<D>(a);
+    const VectorDivs div(a);
     asm volatile("" ::"s"(a.per));
     __shared__ DevEntry lds[kLdsEntries];
     uint32_t tile;
-    if (!tile_of_block(a.map, tile)) return;
+    if (!tile_of_block(map_of(tiles_of(a.total), a.more), tile)) return;
     StagedEntries<true> staging;
     staging.issue(a.entries, a.k);
     const uint32_t u = tile * (uint32_t)kThreads + threadIdx.x;
     uint32_t t, ch, S, g;
-    fast_divmod(u, a.d_chunks, t, ch);
-    fast_divmod(t, a.d_p, g, S);                         // (entry group, rank, chunk)
-    const uint64_t off = unit_offset_if<V, TAIL>(ch, a.last_offset);
-    uint32_t r[D];
-    last_coordinates<D>(S, a, r);
+    fast_divmod(u, div.chunks, t, ch);
+    fast_divmod(t, div.p, g, S);                         // (entry group, rank, chunk)
+    const uint64_t off = unit_offset_if<V, TAIL>(ch, last_offset_of<V>(a.chunks, a.more));
+    uint32_t r[D], wrap[D];
+    last_coordinates<D>(S, a, r, wrap);
     staging.commit(lds);
     if (u >= a.total) return;
     typedef typename Unaligned<V>::type UV;
@@ -565,7 +609,7 @@ __global__ __launch_bounds__(kThreads) void push_round_kernel(const VectorArgs a
         uint32_t R = S + en.back;                        // modulo 2^32, see vector_source_rank
 #pragma unroll
         for (int j = 0; j < D; ++j)
-            if (r[j] + en.c[j] >= a.d_last[j].div) R -= a.wrap[j];
+            if (r[j] + en.c[j] >= a.last[j]) R -= wrap[j];
         const dst_ptr dp = (dst_ptr)(block_address(en.dst, R, a.dst_stride) + off);
         if constexpr (sizeof(V) == 16) __builtin_nontemporal_store(v, dp);
         else *dp = v;
@@ -598,30 +642,43 @@ __global__ __launch_bounds__(kThreads) void push_round_kernel(const VectorArgs a
 struct BlockArgs {
     const DevEntry *entries;
     const uint32_t *prefix;    // [k + 1] first unit of every entry, then [k] multipliers (entry-major order)
-    const uint32_t *offsets;   // [s][d] effective coordinates (residues; signed where non-periodic)
-    TileMap map;
+    const TorusDims *dims;     // and after it the [s][d] effective coordinates (residues; signed where non-periodic)
     uint32_t total;            // p * row_units
     uint32_t k;
-    uint32_t vector_round;     // 0: shift along one dimension, 1: full offset vector
     uint32_t inner, pj;        // shift rounds
-    int32_t shift_dim;         // shift rounds: the dimension (-1: same-rank copy)
-    uint32_t periodic_mask;    // bit j set: dimension j wraps
-    int32_t d;
     uint32_t equal_units;      // != 0: every entry of the launch has this many units (no search)
-    uint32_t entry_major;      // slot-major buffers: units ordered (entry, rank, unit) and prefix[e] counts
-                               // the units of all ranks before entry e; else (rank, entry, unit)
     uint32_t grouped;          // GROUPS: units of the ranks that form whole groups (the first ones)
-    FastDiv d_row, d_inner, d_pj, d_units, d_plane;   // d_plane: p * equal_units (GROUPS: group * equal_units)
-    FastDiv d_group_row;       // GROUPS: units of a group's rows
-    FastDiv d_dims[ISO_MAX_DIMS];
-    uint32_t inner_of[ISO_MAX_DIMS];
+    uint32_t row, plane;       // units of a row; p * equal_units (GROUPS: group * equal_units)
+    uint32_t mul_row, mul_inner, mul_pj, mul_units, mul_plane, mul_group_row;
+    uint32_t shifts;           // row, inner, pj, units
+    uint32_t more;             // plane, units of a group's rows; launch_flags.  Entry-major (slot-major buffers): units
+                               // ordered (entry, rank, unit) and prefix[e] counts the units of all ranks before
+                               // entry e; else (rank, entry, unit)
+    uint32_t torus;            // torus_bits
+};
+static_assert(sizeof(BlockArgs) <= kCheapArguments, "launch cost");
+
+// Dimensions (bits 0-4), the shifted one plus 1 (5-9; 0: same-rank copy or full vectors), which of them wrap (16-31).
+inline uint32_t torus_bits(int32_t d, int32_t shift_dim, uint32_t periodic_mask) {
+    return (uint32_t)d | ((uint32_t)(shift_dim + 1) << 5) | (periodic_mask << 16);
+}
+
+// What mesh_source_rank reads.
+struct MeshView {
+    const uint32_t *offsets;
+    dims_ptr dims;
+    uint32_t inner, pj, vector_round, periodic_mask;
+    int32_t d, shift_dim;
+    __device__ __forceinline__ MeshView(const TorusDims *t, uint32_t torus, uint32_t inner_, uint32_t pj_, uint32_t vector)
+        : offsets(offsets_after(t)), dims(const_dims(t)), inner(inner_), pj(pj_), vector_round(vector),
+          periodic_mask(torus >> 16), d((int32_t)(torus & 31u)), shift_dim((int32_t)((torus >> 5) & 31u) - 1) {}
 };
 
 // Mesh: does the move of entry `en` happen at rank R (R - C^ref inside the mesh in every masked
 // dimension), and from which rank?  Offsets of non-periodic dimensions are signed values stored
 // as two's complement, so one unsigned comparison tests both ends of the dimension.
-template <int D, typename Args>
-__device__ __forceinline__ bool mesh_source_rank_d(const Args &a, const DevEntry &en, uint32_t R,
+template <int D>
+__device__ __forceinline__ bool mesh_source_rank_d(const MeshView &a, const DevEntry &en, uint32_t R,
                                                    uint32_t &srcR) {
     const uint32_t mask = (en.meta >> 8) & 0xFFFFu;
     const uint32_t *cref = a.offsets + (size_t)en.ref * a.d;
@@ -632,13 +689,13 @@ __device__ __forceinline__ bool mesh_source_rank_d(const Args &a, const DevEntry
 #pragma unroll
     for (int j = D - 1; j >= 0; --j) {
         uint32_t q;
-        fast_divmod(rem, a.d_dims[j], q, r[j]);
+        fast_divmod(rem, dim_of(a.dims, j), q, r[j]);
         rem = q;
     }
     uint32_t outside = 0;
 #pragma unroll
     for (int j = 0; j < D; ++j)
-        outside |= ((mask >> j) & 1u) & (uint32_t)((uint32_t)(r[j] - cr[j]) >= a.d_dims[j].div);
+        outside |= ((mask >> j) & 1u) & (uint32_t)((uint32_t)(r[j] - cr[j]) >= a.dims->d_dims[j].div);
     if (outside) return false;
     srcR = R;
     if (a.vector_round) {                                  // en.shift: the neighbour whose offsets move the block
@@ -648,8 +705,8 @@ __device__ __forceinline__ bool mesh_source_rank_d(const Args &a, const DevEntry
         for (int j = 0; j < D; ++j) cv[j] = cvec[j];
 #pragma unroll
         for (int j = 0; j < D; ++j) {
-            srcR -= cv[j] * a.inner_of[j];                 // signed where the dimension does not wrap
-            if (((a.periodic_mask >> j) & 1u) && r[j] < cv[j]) srcR += a.d_dims[j].div * a.inner_of[j];
+            srcR -= cv[j] * a.dims->inner[j];                 // signed where the dimension does not wrap
+            if (((a.periodic_mask >> j) & 1u) && r[j] < cv[j]) srcR += a.dims->d_dims[j].div * a.dims->inner[j];
         }
     } else if (a.shift_dim >= 0) {                         // en.shift: the distance along the one moving dimension
         uint32_t rj = 0;
@@ -662,8 +719,7 @@ __device__ __forceinline__ bool mesh_source_rank_d(const Args &a, const DevEntry
     return true;
 }
 
-template <typename Args>
-__device__ __forceinline__ bool mesh_source_rank(const Args &a, const DevEntry &en, uint32_t R,
+__device__ __forceinline__ bool mesh_source_rank(const MeshView &a, const DevEntry &en, uint32_t R,
                                                  uint32_t &srcR) {
     switch (a.d) {
         case 1: return mesh_source_rank_d<1>(a, en, R, srcR);
@@ -684,14 +740,14 @@ __device__ __forceinline__ bool mesh_source_rank(const Args &a, const DevEntry &
     srcR = R;
     for (int j = a.d - 1; j >= 0; --j) {
         uint32_t q, rj;
-        fast_divmod(rem, a.d_dims[j], q, rj);
+        fast_divmod(rem, dim_of(a.dims, j), q, rj);
         rem = q;
-        const uint32_t pj = a.d_dims[j].div;
+        const uint32_t pj = a.dims->d_dims[j].div;
         if (((mask >> j) & 1u) && (uint32_t)(rj - cref[j]) >= pj) has_source = false;
         if (a.vector_round || j == a.shift_dim) {
             const uint32_t cj = a.vector_round ? cvec[j] : en.shift;
-            srcR -= cj * a.inner_of[j];
-            if (((a.periodic_mask >> j) & 1u) && rj < cj) srcR += pj * a.inner_of[j];
+            srcR -= cj * a.dims->inner[j];
+            if (((a.periodic_mask >> j) & 1u) && rj < cj) srcR += pj * a.dims->inner[j];
         }
     }
     return has_source;
@@ -706,20 +762,20 @@ __device__ __forceinline__ bool mesh_source_rank(const Args &a, const DevEntry &
 constexpr uint32_t kBlockGroupLog2 = 7, kBlockGroup = 1u << kBlockGroupLog2;
 
 __device__ __forceinline__ void fetch_now(const BlockArgs &a) {
-    asm volatile("" ::"s"(a.entries), "s"(a.prefix), "s"(a.map.n_tiles), "s"(a.map.run_log2), "s"(a.map.per_xcd),
-                 "s"(a.total), "s"(a.k), "s"(a.vector_round), "s"(a.inner), "s"(a.pj), "s"(a.equal_units),
-                 "s"(a.entry_major), "s"(a.grouped));
-    fetch_now(a.d_row);
-    fetch_now(a.d_inner);
-    fetch_now(a.d_pj);
-    fetch_now(a.d_units);
-    fetch_now(a.d_plane);
-    fetch_now(a.d_group_row);
+    asm volatile("" ::"s"(a.entries), "s"(a.prefix), "s"(a.total), "s"(a.k), "s"(a.inner), "s"(a.pj), "s"(a.equal_units),
+                 "s"(a.grouped), "s"(a.row), "s"(a.plane), "s"(a.mul_row), "s"(a.mul_inner), "s"(a.mul_pj), "s"(a.mul_units),
+                 "s"(a.mul_plane), "s"(a.mul_group_row), "s"(a.shifts), "s"(a.more));
 }
 
 template <bool LDS, bool MESH, int POLICY, bool GROUPS = false>
 __global__ __launch_bounds__(kThreads) void block_round_kernel(const BlockArgs a) {
     if constexpr (!MESH) fetch_now(a);
+    const FastDiv d_row = fastdiv_of(a.mul_row, a.row, a.shifts, 0), d_inner = fastdiv_of(a.mul_inner, a.inner, a.shifts, 1),
+                  d_pj = fastdiv_of(a.mul_pj, a.pj, a.shifts, 2),
+                  d_units = fastdiv_of(a.mul_units, a.equal_units ? a.equal_units : 1u, a.shifts, 3),
+                  d_plane = fastdiv_of(a.mul_plane, a.plane, a.more, 0),
+                  d_group_row = fastdiv_of(a.mul_group_row, a.row << kBlockGroupLog2, a.more, 1);
+    const bool entry_major = is_entry_major(a.more);
     __shared__ DevEntry lds[LDS ? kLdsEntries : 1];
     __shared__ uint32_t lds_prefix[LDS ? 2 * kLdsEntries + 1 : 1];
     const uint32_t *prefix = a.prefix;
@@ -733,31 +789,31 @@ __global__ __launch_bounds__(kThreads) void block_round_kernel(const BlockArgs a
     // (the two-step staging of the other kernels, with the first division between the steps, is 0.5 to 1 %
     // slower here)
     uint32_t tile;
-    if (!tile_of_block(a.map, tile)) return;
+    if (!tile_of_block(map_of(tiles_of(a.total), a.more), tile)) return;
     const uint32_t u = tile * (uint32_t)kThreads + threadIdx.x;
     if (u >= a.total) return;
     // flat index -> rank R, entry lo, unit ch of that entry's block
     uint32_t R = 0, lo = 0, ch = 0, w = u;
     uint32_t span_log2 = 0;                                // GROUPS: w counts through 2^span_log2 rows, entry by entry
-    bool planes = a.entry_major;                           // w (then ch) counts through several ranks' blocks
+    bool planes = entry_major;                           // w (then ch) counts through several ranks' blocks
     if constexpr (GROUPS) {
         planes = u < a.grouped;
         if (planes) {
-            fast_divmod(u, a.d_group_row, R, w);          // R: the group, below its first rank
+            fast_divmod(u, d_group_row, R, w);          // R: the group, below its first rank
             R <<= kBlockGroupLog2;
             span_log2 = kBlockGroupLog2;
         } else {
-            fast_divmod(u - a.grouped, a.d_row, R, w);
-            R += fast_div(a.grouped, a.d_row);
+            fast_divmod(u - a.grouped, d_row, R, w);
+            R += fast_div(a.grouped, d_row);
         }
-    } else if (!a.entry_major) {
-        fast_divmod(u, a.d_row, R, w);                     // w: unit inside the rank's row
+    } else if (!entry_major) {
+        fast_divmod(u, d_row, R, w);                     // w: unit inside the rank's row
     }
     // entry-major: w counts through the entries one after another, each with the units of all p ranks
     if (a.k == 1) {
         ch = w;
     } else if (a.equal_units) {                            // equal blocks: plain division, no search
-        fast_divmod(w, planes ? a.d_plane : a.d_units, lo, ch);
+        fast_divmod(w, planes ? d_plane : d_units, lo, ch);
     } else {
         const uint32_t key = w >> span_log2;               // prefix[e] * 2^n <= w  <=>  prefix[e] <= w >> n
         uint32_t hi = a.k;                                 // largest e with prefix[e] <= key
@@ -771,7 +827,7 @@ __global__ __launch_bounds__(kThreads) void block_round_kernel(const BlockArgs a
     const DevEntry en = table[lo];
     if (planes) {                                          // ch still counts (rank, unit) inside the plane
         const FastDiv by_units = a.equal_units
-                                     ? a.d_units
+                                     ? d_units
                                      : FastDiv{prefix[a.k + 1 + lo], (en.meta >> 24) & 1u, (en.meta >> 25) & 31u, en.units};
         const uint32_t in_plane = ch;
         uint32_t rank_in_span;
@@ -780,12 +836,12 @@ __global__ __launch_bounds__(kThreads) void block_round_kernel(const BlockArgs a
     }
     uint32_t srcR = R;                                    // modulo 2^32, see vector_source_rank
     if constexpr (MESH) {
-        if (!mesh_source_rank(a, en, R, srcR)) return;    // no source: leave the destination as it is
-    } else if (a.vector_round) {
-        srcR = vector_source_rank(R, a.offsets + (size_t)en.shift * a.d, a.d, a.d_dims, a.inner_of);
+        if (!mesh_source_rank(MeshView(a.dims, a.torus, a.inner, a.pj, is_vector_round(a.more)), en, R, srcR)) return;    // no source: leave the destination as it is
+    } else if (is_vector_round(a.more)) {
+        srcR = vector_source_rank(R, offsets_after(a.dims) + (size_t)en.shift * (a.torus & 31u), (int32_t)(a.torus & 31u), const_dims(a.dims));
     } else {
-        const uint32_t q = fast_div(R, a.d_inner);
-        const uint32_t rj = q - fast_div(q, a.d_pj) * a.pj;
+        const uint32_t q = fast_div(R, d_inner);
+        const uint32_t rj = q - fast_div(q, d_pj) * a.pj;
         srcR -= en.shift * a.inner;
         if (rj < en.shift) srcR += a.pj * a.inner;
     }
@@ -811,53 +867,50 @@ __global__ __launch_bounds__(kThreads) void block_round_kernel(const BlockArgs a
 // kernels is how long a wavefront holds its slot before its one load is under way.)
 struct MeshArgs {
     const DevEntry *entries;
-    const uint32_t *offsets;   // [s][d] effective coordinates
+    const TorusDims *dims;     // and after it the [s][d] effective coordinates
     const uint32_t *interior;  // bit t: every rank of tile t has a source for every entry of the launch
-    TileMap map;
     uint32_t total, k;
     uint32_t inner, pj;        // rank stride and size of the moving dimension (1, 1 for a same-rank copy)
-    uint32_t entry_major;
-    int32_t shift_dim;         // -1: same-rank copy
-    int32_t d;
-    uint32_t periodic_mask;
-    static constexpr uint32_t vector_round = 0;
-    FastDiv d_chunks, d_k, d_p, d_inner, d_pj;
-    FastDiv d_dims[ISO_MAX_DIMS];
-    uint32_t inner_of[ISO_MAX_DIMS];
-    uint64_t last_offset;
+    uint32_t chunks, p;
+    uint32_t mul_chunks, mul_k, mul_inner, mul_pj, mul_p;
+    uint32_t shifts;           // chunks, k, inner, pj
+    uint32_t more;             // p; launch_flags
+    uint32_t torus;            // torus_bits
 };
+static_assert(sizeof(MeshArgs) <= kCheapArguments, "launch cost");
 
 template <typename V, bool LDS, int POLICY, bool TAIL>
 __global__ __launch_bounds__(kThreads) void mesh_shift_round_kernel(const MeshArgs a) {
     __shared__ DevEntry lds[LDS ? kLdsEntries : 1];
     uint32_t tile;
-    if (!tile_of_block(a.map, tile)) return;
+    if (!tile_of_block(map_of(tiles_of(a.total), a.more), tile)) return;
     StagedEntries<LDS> staging;
     staging.issue(a.entries, a.k);
     const bool interior = (a.interior[tile >> 5] >> (tile & 31u)) & 1u;      // uniform: one scalar load
     const uint32_t u = tile * (uint32_t)kThreads + threadIdx.x;
     uint32_t t, ch, R, e;
-    fast_divmod(u, a.d_chunks, t, ch);
-    if (a.entry_major) fast_divmod(t, a.d_p, e, R);
-    else fast_divmod(t, a.d_k, R, e);
+    fast_divmod(u, fastdiv_of(a.mul_chunks, a.chunks, a.shifts, 0), t, ch);
+    if (is_entry_major(a.more)) fast_divmod(t, fastdiv_of(a.mul_p, a.p, a.more, 0), e, R);
+    else fast_divmod(t, fastdiv_of(a.mul_k, a.k, a.shifts, 1), R, e);
     staging.commit(lds);
     if (u >= a.total) return;
     const DevEntry en = LDS ? lds[e] : a.entries[e];
     uint32_t srcR = R;
     if (interior) {                                       // every move has its source: the torus kernel's path
-        if (a.shift_dim >= 0) {
+        const uint32_t shift_dim = (a.torus >> 5) & 31u;  // plus 1
+        if (shift_dim) {
             srcR -= en.shift * a.inner;
-            if ((a.periodic_mask >> a.shift_dim) & 1u) {  // the moving dimension wraps
-                const uint32_t q = fast_div(R, a.d_inner);
-                const uint32_t rj = q - fast_div(q, a.d_pj) * a.pj;
+            if ((a.torus >> (15u + shift_dim)) & 1u) {    // the moving dimension wraps
+                const uint32_t q = fast_div(R, fastdiv_of(a.mul_inner, a.inner, a.shifts, 2));
+                const uint32_t rj = q - fast_div(q, fastdiv_of(a.mul_pj, a.pj, a.shifts, 3)) * a.pj;
                 if (rj < en.shift) srcR += a.pj * a.inner;
             }
         }
-    } else if (!mesh_source_rank(a, en, R, srcR)) {
+    } else if (!mesh_source_rank(MeshView(a.dims, a.torus, a.inner, a.pj, 0u), en, R, srcR)) {
         return;                                           // no source: leave the destination as it is
     }
     move_unit<V, POLICY>(block_address(en.dst, R, en.dst_stride), block_address(en.src, srcR, en.src_stride),
-                      unit_offset_if<V, TAIL>(ch, a.last_offset));
+                      unit_offset_if<V, TAIL>(ch, last_offset_of<V>(a.chunks, a.more)));
 }
 
 // ---- small blocks re-tiled through LDS (the staged schedule) ----------------------------------
@@ -878,27 +931,30 @@ constexpr uint32_t kSmallTileUnits = 1024;             // used where the blocks 
 struct StagedRoundArgs {
     const DevEntry *entries;   // the first k_rows entries read a rank-major buffer, the others a slot-major one;
                                // every destination is a slot-major plane of the workspace
-    TileMap map;
+    uint32_t n_tiles;
     uint32_t p, k, k_rows;
     uint32_t ranks;            // ranks per tile: k * ranks * upb <= kTileUnits
     uint32_t upb;              // units per block
     uint32_t inner, pj;        // the moving dimension (1, 1: same-rank copies)
-    FastDiv d_upb, d_row, d_plane, d_inner, d_pj;   // upb; k_rows * upb; ranks * upb
+    uint32_t row, plane;       // k_rows * upb (at least 1); ranks * upb
+    uint32_t mul_upb, mul_row, mul_plane, mul_inner, mul_pj;
+    uint32_t shifts;           // upb, row, plane, inner
+    uint32_t more;             // pj; launch_flags
 };
+static_assert(sizeof(StagedRoundArgs) <= kCheapArguments, "launch cost");
 
 __device__ __forceinline__ void fetch_now(const StagedRoundArgs &a) {
-    asm volatile("" ::"s"(a.entries), "s"(a.map.n_tiles), "s"(a.map.run_log2), "s"(a.map.per_xcd), "s"(a.p), "s"(a.k),
-                 "s"(a.k_rows), "s"(a.ranks), "s"(a.upb), "s"(a.inner), "s"(a.pj));
-    fetch_now(a.d_upb);
-    fetch_now(a.d_row);
-    fetch_now(a.d_plane);
-    fetch_now(a.d_inner);
-    fetch_now(a.d_pj);
+    asm volatile("" ::"s"(a.entries), "s"(a.n_tiles), "s"(a.p), "s"(a.k), "s"(a.k_rows), "s"(a.ranks), "s"(a.upb),
+                 "s"(a.inner), "s"(a.pj), "s"(a.row), "s"(a.plane), "s"(a.mul_upb), "s"(a.mul_row), "s"(a.mul_plane),
+                 "s"(a.mul_inner), "s"(a.mul_pj), "s"(a.shifts), "s"(a.more));
 }
 
 template <typename V, int POLICY, uint32_t UPL>
 __global__ __launch_bounds__(kThreads) void staged_round_kernel(const StagedRoundArgs a) {
     fetch_now(a);
+    const FastDiv d_upb = fastdiv_of(a.mul_upb, a.upb, a.shifts, 0), d_row = fastdiv_of(a.mul_row, a.row, a.shifts, 1),
+                  d_plane = fastdiv_of(a.mul_plane, a.plane, a.shifts, 2), d_inner = fastdiv_of(a.mul_inner, a.inner, a.shifts, 3),
+                  d_pj = fastdiv_of(a.mul_pj, a.pj, a.more, 0);
     __shared__ DevEntry lds[kLdsEntries];
     extern __shared__ __align__(16) unsigned char tile_bytes[];
     V *tile = (V *)tile_bytes;
@@ -906,11 +962,11 @@ __global__ __launch_bounds__(kThreads) void staged_round_kernel(const StagedRoun
     typedef const UV __attribute__((address_space(1))) *src_ptr;
     typedef UV __attribute__((address_space(1))) *dst_ptr;
     uint32_t tile_id;
-    if (!tile_of_block(a.map, tile_id)) return;          // (before anything is loaded: the grid is padded)
+    if (!tile_of_block(map_of(a.n_tiles, a.more), tile_id)) return;          // (before anything is loaded: the grid is padded)
     const EntryTable<true> table(a.entries, a.k, lds);
     const uint32_t R0 = tile_id * a.ranks;
     const uint32_t n = a.p - R0 < a.ranks ? a.p - R0 : a.ranks;
-    const uint32_t plane = a.ranks * a.upb, pitch = plane + 1u;      // padded planes: the strided LDS writes spread over the banks
+    const uint32_t plane = a.plane, pitch = plane + 1u;      // padded planes: the strided LDS writes spread over the banks
     const uint32_t n_rows = a.k_rows * plane, n_all = a.k * plane;
     V regs[UPL];
     uint32_t at[UPL];                          // where in the tile the unit goes; ~0: no unit
@@ -919,11 +975,11 @@ __global__ __launch_bounds__(kThreads) void staged_round_kernel(const StagedRoun
         const uint32_t q = threadIdx.x + it * (uint32_t)kThreads;
         uint32_t e, r, c, rem;
         if (q < n_rows) {                                // (rank, entry, unit) over the rank-major sources
-            fast_divmod(q, a.d_row, r, rem);
-            fast_divmod(rem, a.d_upb, e, c);
+            fast_divmod(q, d_row, r, rem);
+            fast_divmod(rem, d_upb, e, c);
         } else {                                         // (entry, rank, unit) over the slot-major sources
-            fast_divmod(q - n_rows, a.d_plane, e, rem);
-            fast_divmod(rem, a.d_upb, r, c);
+            fast_divmod(q - n_rows, d_plane, e, rem);
+            fast_divmod(rem, d_upb, r, c);
             e += a.k_rows;
         }
         // a lane with no unit loads the tile's first unit instead and drops it: the eight loads stay
@@ -946,14 +1002,14 @@ __global__ __launch_bounds__(kThreads) void staged_round_kernel(const StagedRoun
     for (uint32_t it = 0; it < UPL; ++it) {    // (entry, rank, unit): dense runs of every plane
         const uint32_t q = threadIdx.x + it * (uint32_t)kThreads;
         uint32_t e, r, c, rem;
-        fast_divmod(q, a.d_plane, e, rem);
-        fast_divmod(rem, a.d_upb, r, c);
+        fast_divmod(q, d_plane, e, rem);
+        fast_divmod(rem, d_upb, r, c);
         if (q < n_all && r < n) {
             const DevEntry en = table[e];
             // the tile's ranks are source ranks S: the block goes to the rank `shift` steps on
             const uint32_t S = R0 + r;
-            const uint32_t qq = fast_div(S, a.d_inner);
-            const uint32_t sj = qq - fast_div(qq, a.d_pj) * a.pj;
+            const uint32_t qq = fast_div(S, d_inner);
+            const uint32_t sj = qq - fast_div(qq, d_pj) * a.pj;
             uint32_t R = S + en.shift * a.inner;
             R -= sj + en.shift >= a.pj ? a.pj * a.inner : 0u;
             const dst_ptr dp = (dst_ptr)(block_address(en.dst, R, en.dst_stride) + (uint64_t)c * sizeof(V));
@@ -982,25 +1038,28 @@ static_assert(sizeof(DeliverEntry) == 64, "four 16-byte words per entry");
 struct DeliverArgs {
     const DeliverEntry *entries;   // the first k_rows entries read a rank-major buffer
     uint64_t dst;                  // rank 0's receive row; rows of s blocks, back to back
-    TileMap map;
+    uint32_t n_tiles;
     uint32_t p, s, k_rows;
     uint32_t ranks;                // ranks per workgroup: s * ranks * upb <= UPL * kThreads
     uint32_t upb;                  // units per block
-    FastDiv d_upb, d_rows, d_plane, d_row;    // upb; k_rows * upb; ranks * upb; s * upb
+    uint32_t rows, plane, row;     // k_rows * upb (at least 1); ranks * upb; s * upb
+    uint32_t mul_upb, mul_rows, mul_plane, mul_row;
+    uint32_t shifts;               // upb, rows, plane, row
+    uint32_t more;                 // launch_flags
 };
+static_assert(sizeof(DeliverArgs) <= kCheapArguments, "launch cost");
 
 __device__ __forceinline__ void fetch_now(const DeliverArgs &a) {
-    asm volatile("" ::"s"(a.entries), "s"(a.dst), "s"(a.map.n_tiles), "s"(a.map.run_log2), "s"(a.map.per_xcd), "s"(a.p),
-                 "s"(a.s), "s"(a.k_rows), "s"(a.ranks), "s"(a.upb));
-    fetch_now(a.d_upb);
-    fetch_now(a.d_rows);
-    fetch_now(a.d_plane);
-    fetch_now(a.d_row);
+    asm volatile("" ::"s"(a.entries), "s"(a.dst), "s"(a.n_tiles), "s"(a.p), "s"(a.s), "s"(a.k_rows), "s"(a.ranks), "s"(a.upb),
+                 "s"(a.rows), "s"(a.plane), "s"(a.row), "s"(a.mul_upb), "s"(a.mul_rows), "s"(a.mul_plane), "s"(a.mul_row),
+                 "s"(a.shifts), "s"(a.more));
 }
 
 template <typename V, int POLICY, uint32_t UPL>
 __global__ __launch_bounds__(kThreads) void deliver_kernel(const DeliverArgs a) {
     fetch_now(a);
+    const FastDiv d_upb = fastdiv_of(a.mul_upb, a.upb, a.shifts, 0), d_rows = fastdiv_of(a.mul_rows, a.rows, a.shifts, 1),
+                  d_plane = fastdiv_of(a.mul_plane, a.plane, a.shifts, 2), d_row = fastdiv_of(a.mul_row, a.row, a.shifts, 3);
     __shared__ DeliverEntry lds[kLdsEntries];
     extern __shared__ __align__(16) unsigned char tile_bytes[];
     V *tile = (V *)tile_bytes;
@@ -1008,12 +1067,12 @@ __global__ __launch_bounds__(kThreads) void deliver_kernel(const DeliverArgs a) 
     typedef const UV __attribute__((address_space(1))) *src_ptr;
     typedef UV __attribute__((address_space(1))) *dst_ptr;
     uint32_t tile_id;
-    if (!tile_of_block(a.map, tile_id)) return;          // (before anything is loaded: the grid is padded)
+    if (!tile_of_block(map_of(a.n_tiles, a.more), tile_id)) return;          // (before anything is loaded: the grid is padded)
     for (uint32_t w = threadIdx.x; w < a.s * 4u; w += kThreads) ((vec16_t *)lds)[w] = ((const vec16_t *)a.entries)[w];
     __syncthreads();
     const uint32_t R0 = tile_id * a.ranks;
     const uint32_t n = a.p - R0 < a.ranks ? a.p - R0 : a.ranks;
-    const uint32_t plane = a.ranks * a.upb, pitch = plane + 1u;
+    const uint32_t plane = a.plane, pitch = plane + 1u;
     const uint32_t n_rows = a.k_rows * plane, n_all = a.s * plane;
     V regs[UPL];
     uint32_t at[UPL];                                    // where in the tile the unit goes; ~0: no unit
@@ -1022,11 +1081,11 @@ __global__ __launch_bounds__(kThreads) void deliver_kernel(const DeliverArgs a) 
         const uint32_t q = threadIdx.x + it * (uint32_t)kThreads;
         uint32_t e, r, c, rem;
         if (q < n_rows) {                                // (rank, entry, unit) over the rank-major sources
-            fast_divmod(q, a.d_rows, r, rem);
-            fast_divmod(rem, a.d_upb, e, c);
+            fast_divmod(q, d_rows, r, rem);
+            fast_divmod(rem, d_upb, e, c);
         } else {                                         // (entry, rank, unit) over the planes
-            fast_divmod(q - n_rows, a.d_plane, e, rem);
-            fast_divmod(rem, a.d_upb, r, c);
+            fast_divmod(q - n_rows, d_plane, e, rem);
+            fast_divmod(rem, d_upb, r, c);
             e += a.k_rows;
         }
         // a lane with no unit loads the tile's first unit instead and drops it
@@ -1053,8 +1112,8 @@ __global__ __launch_bounds__(kThreads) void deliver_kernel(const DeliverArgs a) 
     for (uint32_t it = 0; it < UPL; ++it) {              // (rank, block, unit): the receive rows, back to back
         const uint32_t q = threadIdx.x + it * (uint32_t)kThreads;
         uint32_t i, r, c, rem;
-        fast_divmod(q, a.d_row, r, rem);
-        fast_divmod(rem, a.d_upb, i, c);
+        fast_divmod(q, d_row, r, rem);
+        fast_divmod(rem, d_upb, i, c);
         if (r < n) {
             const dst_ptr dp = (dst_ptr)(out + (uint64_t)q * sizeof(V));
             if constexpr (sizeof(V) == 16 && !(POLICY & kPlainStores)) __builtin_nontemporal_store(tile[i * pitch + r * a.upb + c], dp);
@@ -1087,10 +1146,18 @@ struct ChainArgs {
     ChainHop hops[kChainHops];         // chain after chain
     uint8_t first[kChainHops + 4];     // first hop of every chain
 };
-static_assert(sizeof(ChainArgs) <= 4096, "kernel arguments");
+static_assert(sizeof(ChainArgs) <= 4096 && sizeof(ChainArgs) % 4 == 0, "kernel arguments");
 
-template <typename V, bool TAIL>
-__global__ __launch_bounds__(kChainThreads) void chain_kernel(const ChainArgs a) {
+// A request's launches take them from the request's table instead (ChainTable), which costs less to launch.
+struct ChainTable {
+    const ChainArgs *args;
+};
+__device__ __forceinline__ const ChainArgs &chain_args(const ChainArgs &a) { return a; }
+__device__ __forceinline__ const ChainArgs &chain_args(const ChainTable &t) { return *t.args; }
+
+template <typename V, bool TAIL, typename ARGS>
+__global__ __launch_bounds__(kChainThreads) void chain_kernel(const ARGS from) {
+    const ChainArgs &a = chain_args(from);
     typedef typename Unaligned<V>::type UV;
     typedef const UV __attribute__((address_space(1))) *src_ptr;
     typedef UV __attribute__((address_space(1))) *dst_ptr;
