@@ -58,8 +58,9 @@ struct Launch {
     DeliverArgs deliver;
     StagedRoundArgs staged;
     uint32_t tile_units;   // the staged schedule's kernels: kTileUnits or kSmallTileUnits
-    ChainTable chain;      // chain kernel: its arguments in the request's table
+    ChainHead chain;       // chain kernel: its hops in the request's table
     const ChainArgs *chain_by_value;      // or BoundRequest::chain, where there is no table
+    uint32_t chain_width;  // its unit width, where not the request's
     uint32_t n_tiles, run_log2;           // see TileMap
     bool entry_major, vector_round;       // see launch_flags
     uint32_t pull;
@@ -251,8 +252,13 @@ KernelRef select_vector(const Launch &l) {
 template <typename V, bool LDS, bool TAIL>
 KernelRef select_regular(const Launch &l) {
     if (l.kernel == kChainKernel) {
-        if (l.chain_by_value) return {(const void *)&chain_kernel<V, TAIL, ChainArgs>, l.chain_by_value};
-        return {(const void *)&chain_kernel<V, TAIL, ChainTable>, &l.chain};
+        const bool one = l.chain.n_units <= kChainThreads;         // a unit per lane
+        if (l.chain_by_value) {
+            if (one) return {(const void *)&chain_kernel<V, TAIL, 1, ChainArgs>, l.chain_by_value};
+            return {(const void *)&chain_kernel<V, TAIL, kChainUnitsPerLane, ChainArgs>, l.chain_by_value};
+        }
+        if (one) return {(const void *)&chain_kernel<V, TAIL, 1, ChainHead>, &l.chain};
+        return {(const void *)&chain_kernel<V, TAIL, kChainUnitsPerLane, ChainHead>, &l.chain};
     }
     if (l.kernel == kVectorKernel) {
         if constexpr (LDS) {
@@ -316,7 +322,7 @@ inline KernelRef select_kernel(int vector_bytes, const Launch &l) {
         if (l.mesh) return l.lds_table ? select_block<true, true>(l) : select_block<false, true>(l);
         return l.lds_table ? select_block<true, false>(l) : select_block<false, false>(l);
     }
-    switch (vector_bytes) {
+    switch (l.chain_width ? (int)l.chain_width : vector_bytes) {
         case 16: return select_width<vec16_t>(l);
         case 8:  return select_width<vec8_t>(l);
         case 4:  return select_width<uint32_t>(l);
@@ -565,7 +571,7 @@ private:
     // blocks in the last-level cache again.
     bool chain_launch(uint64_t launches) {
         if (c.mesh || !uniform || !size0 || launches < 2 || p > kChainThreads * kChainUnitsPerLane || s > kChainHops ||
-            c.d > (int)kChainDims || (size0 >> min_log2) > 0xFFFF)
+            (size0 >> min_log2) > 0xFFFF)
             return false;
         std::vector<const HostEntry *> hops;             // chain after chain
         std::vector<uint32_t> ends;                      // where each of them ends
@@ -606,60 +612,76 @@ private:
         l.kernel = kChainKernel;
         l.lds_table = true;
         auto args = std::make_unique<ChainArgs>();
-        ChainArgs &ca = *args;
-        const uint64_t width = uint64_t(1) << min_log2;
-        l.tail = (size0 & (width - 1)) != 0;
-        ca.last_offset = size0 - width;
-        ca.chunks = (uint32_t)((size0 + width - 1) >> min_log2);
-        ca.column = std::min<uint32_t>(ca.chunks, kChainThreads * kChainUnitsPerLane / (uint32_t)p);
+        ChainHead &ca = args->head;
+        uint64_t width = uint64_t(1) << min_log2;
+        const auto cut = [&] {
+            l.tail = (size0 & (width - 1)) != 0;
+            ca.chunks = (uint32_t)((size0 + width - 1) / width);
+            ca.column = std::min<uint32_t>(ca.chunks, kChainThreads * kChainUnitsPerLane / (uint32_t)p);
+        };
+        cut();
         // A last unit that overlaps the one before it goes into the same column: two workgroups are not at the
         // same hop, and one would read bytes that the other has already replaced.
         while (l.tail && ca.column > 1 && ca.column < ca.chunks && (ca.chunks - 1) % ca.column == 0) --ca.column;
-        if (l.tail && ca.chunks > 1 && ca.column == 1) return false;
+        if (l.tail && ca.chunks > 1 && ca.column == 1) {
+            // one unit of every rank is all that a workgroup holds: units that divide the block (5 x 4 x 7 x 6 x 4
+            // star, 6 B: 14.7 us in five launches, 4.3 in this one)
+            width = size0 & (~size0 + 1);
+            l.chain_width = (uint32_t)width;
+            cut();
+        }
         ca.groups = (ca.chunks + ca.column - 1) / ca.column;
         ca.n_units = (uint32_t)p * ca.column;
-        ca.d_column = make_fastdiv(ca.column);
-        ca.d_groups = make_fastdiv(ca.groups);
-        for (int j = 0; j < c.d; ++j) {
-            ca.d_inner[j] = make_fastdiv((uint32_t)c.inner[(size_t)j]);
-            ca.d_pj[j] = make_fastdiv((uint32_t)c.dims[(size_t)j]);
-        }
-        uint32_t at = 0, n_chains = 0, longest = 0;
+        put(ca.column, ca.mul_column, ca.more, 0);
+        put(ca.groups, ca.mul_groups, ca.more, 1);
+        ca.more |= launch_flags(0, false, (uint32_t)(ca.chunks * width - size0));
+        ChainHops &ch = args->hops;
+        uint32_t begin = 0, n_chains = 0, longest = 0;
         for (const uint32_t end : ends) {
-            if (end == at) continue;                             // no hops: an empty block
-            longest = std::max(longest, end - at);
-            ca.first[n_chains++] = (uint8_t)at;
-            while (at < end) {
+            n_chains += end != begin;
+            begin = end;
+        }
+        begin = 0;
+        uint32_t chain = 0, later = n_chains;
+        for (const uint32_t end : ends) {
+            if (end == begin) continue;                          // no hops: an empty block
+            longest = std::max(longest, end - begin);
+            ch.later[chain] = later - n_chains;
+            for (uint32_t at = begin; at < end; ++at) {
                 const HostEntry *he = hops[at];
-                const int dim = he->dim;
-                ChainHop &hop = ca.hops[at++];
+                ChainHop &hop = ch.hops[at == begin ? chain : later++];
                 hop.src = he->de.src;
                 hop.dst = he->de.dst;
                 hop.src_stride = he->de.src_stride;
                 hop.dst_stride = he->de.dst_stride;
-                if (dim < 0) continue;                            // same-rank copy: shift 0
-                hop.dim = (uint32_t)dim;
-                hop.shift = he->de.shift;
-                hop.back = hop.shift * (uint32_t)c.inner[(size_t)dim];
-                hop.wrap = (uint32_t)c.dims[(size_t)dim] * (uint32_t)c.inner[(size_t)dim];
+                hop.shift = he->dim < 0 ? 0u : he->de.shift;     // (a same-rank copy)
+                hop.inner = he->dim < 0 ? 1u : (uint32_t)c.inner[(size_t)he->dim];
+                hop.pj = he->dim < 0 ? 1u : (uint32_t)c.dims[(size_t)he->dim];
+                put(hop.inner, hop.mul_inner, hop.shifts, 0);
+                put(hop.pj, hop.mul_pj, hop.shifts, 1);
             }
+            ++chain;
+            begin = end;
         }
-        ca.first[n_chains] = (uint8_t)at;
+        ch.later[n_chains] = later - n_chains;
+        ca.n_chains = n_chains;
         l.grid = n_chains * ca.groups;
         const uint64_t piece = ca.column * width, own = p * ((piece + 63) / 64) * longest;
         uint64_t all = own * l.grid;
         if (longest > 1 && size0 > 32 && size0 % 64 && piece <= 64) all *= 2;
         if (own > 6144 || all > (launches - 1) * 48 * 1024) return false;
         l.threads = std::min<uint32_t>(kChainThreads, (ca.n_units + 63) & ~63u);
+        l.dyn_lds = longest > 1 ? ca.n_units * (uint32_t)width : 0;
         describe_chain_bytes(l, hops);
+        l.chain = ca;
         if (arena) {
             rq.chain = std::move(args);
             l.chain_by_value = rq.chain.get();
         } else {
             while (prefixes.size() % 4) prefixes.push_back(0);
             pd.first_prefix = prefixes.size();
-            const uint32_t *words = (const uint32_t *)args.get();
-            prefixes.insert(prefixes.end(), words, words + sizeof(ChainArgs) / 4);
+            const uint32_t *words = (const uint32_t *)&ch;
+            prefixes.insert(prefixes.end(), words, words + sizeof(ChainHops) / 4);
         }
         pending.push_back(pd);
         return true;
@@ -1438,7 +1460,7 @@ private:
         const uint32_t *dev_prefix = (const uint32_t *)(dev + entry_bytes + off_bytes);
         for (Pending &pd : pending) {
             if (pd.l.kernel == kChainKernel) {
-                pd.l.chain.args = (const ChainArgs *)(dev_prefix + pd.first_prefix);
+                pd.l.chain.table = (const ChainHops *)(dev_prefix + pd.first_prefix);
             } else if (pd.l.kernel == kVectorKernel) {
                 pd.l.vec.entries = dev_entries + pd.first_entry;
                 pd.l.vec.dims = dev_dims;

@@ -1122,74 +1122,143 @@ __global__ __launch_bounds__(kThreads) void deliver_kernel(const DeliverArgs a) 
     }
 }
 
-// ---- small all-to-alls in one launch ------------------------------------------------------------
+// ---- small collectives in one launch -------------------------------------------------------------
 // Block i of an all-to-all only ever moves between its own places (send slot, workspace slots, receive slot),
 // and so does every column of its units: a workgroup takes one block's column of all p ranks through all its
-// hops, one hop after the other with a barrier between, through the same buffers as the rounds.  What bounds
-// these collectives is the cost of a launch per dimension.  The hops travel in the kernel's arguments, so the
-// launch needs no table in device memory (8 x 8 x 8, 26 neighbours, 64 B, allocation-free call: the table took
-// launches of its own).
+// hops, one hop after the other with a barrier between, making every stop in the same buffers as the rounds.  What
+// bounds these collectives is first the cost of a launch per dimension, then the latency of the one launch: every
+// dependent access is 0.5 to 2 us.  So the hops travel in the request's table, the first one of each chain at the
+// chain's own index (no look-up in front of it), and a hop takes what the hop before it has stored from LDS
+// instead of waiting for the store and loading it again.
 constexpr uint32_t kChainThreads = 1024, kChainUnitsPerLane = 4;
-constexpr uint32_t kChainHops = 72, kChainDims = 8;
+constexpr uint32_t kChainHops = 72;
 struct ChainHop {
     uint64_t src, dst;                 // addresses of rank 0's blocks
     uint32_t src_stride, dst_stride;
-    uint32_t shift, back, wrap;        // residue v along the hop's dimension; v * inner_j; p_j * inner_j
-    uint32_t dim;
+    uint32_t shift, inner, pj;         // residue v along the hop's dimension, its rank stride and size (0, 1, 1: same rank)
+    uint32_t mul_inner, mul_pj, shifts;
 };
-struct ChainArgs {
+static_assert(sizeof(ChainHop) == 48, "three 16-byte words");
+struct ChainHops {
+    ChainHop hops[kChainHops];         // the chains' first hops, then their others, chain after chain
+    uint32_t later[kChainHops + 4];    // [chains + 1] where those of each chain begin, counted behind the first ones
+};
+struct ChainHead {
+    const ChainHops *table;
     uint32_t n_units;                  // p * column
     uint32_t chunks, column, groups;   // units of a block, of a workgroup's column; columns of a block
-    FastDiv d_column, d_groups;
-    uint64_t last_offset;
-    FastDiv d_inner[kChainDims], d_pj[kChainDims];
-    ChainHop hops[kChainHops];         // chain after chain
-    uint8_t first[kChainHops + 4];     // first hop of every chain
+    uint32_t n_chains;
+    uint32_t mul_column, mul_groups;
+    uint32_t more;                     // shifts of column, groups; launch_flags
 };
-static_assert(sizeof(ChainArgs) <= 4096 && sizeof(ChainArgs) % 4 == 0, "kernel arguments");
-
-// A request's launches take them from the request's table instead (ChainTable), which costs less to launch.
-struct ChainTable {
-    const ChainArgs *args;
+static_assert(sizeof(ChainHead) <= kCheapArguments, "launch cost");
+// The allocation-free call has no table and passes the hops with the launch (3.5 KiB; a launch that writes a table
+// first costs more: 8 x 8 x 8, 26 neighbours, 64 B 13 -> 11 us).
+struct ChainArgs {
+    ChainHead head;
+    ChainHops hops;
 };
-__device__ __forceinline__ const ChainArgs &chain_args(const ChainArgs &a) { return a; }
-__device__ __forceinline__ const ChainArgs &chain_args(const ChainTable &t) { return *t.args; }
+static_assert(sizeof(ChainArgs) <= 4096 && sizeof(ChainHops) % 4 == 0, "kernel arguments, table words");
 
-template <typename V, bool TAIL, typename ARGS>
+typedef const ChainHops __attribute__((address_space(4))) *chain_hops_ptr;
+__device__ __forceinline__ const ChainHead &chain_head(const ChainHead &a) { return a; }
+__device__ __forceinline__ const ChainHead &chain_head(const ChainArgs &a) { return a.head; }
+__device__ __forceinline__ chain_hops_ptr chain_hops(const ChainHead &a) { return (chain_hops_ptr)(uintptr_t)a.table; }
+__device__ __forceinline__ chain_hops_ptr chain_hops(const ChainArgs &) {
+    typedef const char __attribute__((address_space(4))) *bytes_ptr;
+    return (chain_hops_ptr)((bytes_ptr)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(ChainArgs, hops));
+}
+
+// Synchronises the workgroup on LDS only: stores to global memory stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// One hop in scalar registers; the constructor makes the compiler fetch it there and then.
+struct HopNow {
+    uint64_t src, dst;
+    uint32_t src_stride, dst_stride, shift, back, wrap;
+    FastDiv d_inner, d_pj;
+    __device__ __forceinline__ HopNow(chain_hops_ptr table, uint32_t h)
+        : src(table->hops[h].src), dst(table->hops[h].dst), src_stride(table->hops[h].src_stride),
+          dst_stride(table->hops[h].dst_stride), shift(table->hops[h].shift),
+          d_inner(fastdiv_of(table->hops[h].mul_inner, table->hops[h].inner, table->hops[h].shifts, 0)),
+          d_pj(fastdiv_of(table->hops[h].mul_pj, table->hops[h].pj, table->hops[h].shifts, 1)) {
+        asm volatile("" ::"s"(src), "s"(dst), "s"(src_stride), "s"(dst_stride), "s"(shift), "s"(d_inner.div), "s"(d_inner.mul),
+                     "s"(d_pj.div), "s"(d_pj.mul));
+        back = shift * d_inner.div;
+        wrap = d_inner.div * d_pj.div;
+    }
+    __device__ __forceinline__ uint32_t source_rank(uint32_t R) const {
+        const uint32_t q = fast_div(R, d_inner);
+        const uint32_t rj = q - fast_div(q, d_pj) * d_pj.div;
+        return R - back + (rj < shift ? wrap : 0u);
+    }
+};
+
+// A place that a chain writes twice (Algorithm 1 alternates between two) is written twice by the same lane, in
+// order.  Only the bytes that a last unit shares with its predecessor are written by two lanes (TAIL): there the
+// stores of a hop are waited for.
+// Hops through memory, arguments by value -> as here: 8 x 8, 8 neighbours, 32 B 4.1 -> 3.6 us a start, 8^3, 26
+// neighbours, 64 B 6.4 -> 4.5, 10^3, 64 B 9.3 -> 6.2 (allgather 9.0 -> 5.3), 45^2, 32 B 6.6 -> 4.7.
+template <typename V, bool TAIL, uint32_t UPL, typename ARGS>
 __global__ __launch_bounds__(kChainThreads) void chain_kernel(const ARGS from) {
-    const ChainArgs &a = chain_args(from);
     typedef typename Unaligned<V>::type UV;
     typedef const UV __attribute__((address_space(1))) *src_ptr;
     typedef UV __attribute__((address_space(1))) *dst_ptr;
+    extern __shared__ __align__(16) unsigned char tile_bytes[];
+    V *tile = (V *)tile_bytes;
+    const ChainHead &a = chain_head(from);
+    const chain_hops_ptr table = chain_hops(from);
     uint32_t chain, group;
-    fast_divmod(blockIdx.x, a.d_groups, chain, group);
-    const uint32_t n_threads = blockDim.x;
-    const uint32_t h1 = a.first[chain + 1];
-    for (uint32_t h = a.first[chain]; h < h1; ++h) {
-        const ChainHop hop = a.hops[h];
-        const FastDiv d_inner = a.d_inner[hop.dim], d_pj = a.d_pj[hop.dim];
-        V v[kChainUnitsPerLane];
-        uint64_t to[kChainUnitsPerLane];
+    fast_divmod(blockIdx.x, fastdiv_of(a.mul_groups, a.groups, a.more, 1), chain, group);
+    const uint32_t n_threads = UPL > 1 ? kChainThreads : 0u;          // (one unit per lane: no stride)
+    const FastDiv d_column = fastdiv_of(a.mul_column, a.column, a.more, 0);
+    HopNow hop(table, chain);
+    uint32_t unit[UPL], rank[UPL];
+    uint64_t off[UPL];
+    bool has[UPL];
+    V v[UPL];
 #pragma unroll
-        for (uint32_t it = 0; it < kChainUnitsPerLane; ++it) {
-            const uint32_t u = threadIdx.x + it * n_threads;
-            uint32_t R, c;
-            fast_divmod(u, a.d_column, R, c);
-            const uint32_t ch = group * a.column + c;
-            to[it] = 0;
-            if (u < a.n_units && ch < a.chunks) {
-                const uint32_t q = fast_div(R, d_inner);
-                const uint32_t rj = q - fast_div(q, d_pj) * d_pj.div;
-                const uint32_t srcR = R - hop.back + (rj < hop.shift ? hop.wrap : 0u);
-                const uint64_t off = unit_offset_if<V, TAIL>(ch, a.last_offset);
-                v[it] = *(src_ptr)(block_address(hop.src, srcR, hop.src_stride) + off);
-                to[it] = block_address(hop.dst, R, hop.dst_stride) + off;
-            }
-        }
+    for (uint32_t it = 0; it < UPL; ++it) {
+        unit[it] = threadIdx.x + it * n_threads;
+        uint32_t c;
+        fast_divmod(unit[it], d_column, rank[it], c);
+        const uint32_t ch = group * a.column + c;
+        has[it] = unit[it] < a.n_units && ch < a.chunks;
+        unit[it] = has[it] ? unit[it] : 0u;              // a lane without a unit reads rank 0's first one
+        rank[it] = has[it] ? rank[it] : 0u;
+        off[it] = has[it] ? unit_offset_if<V, TAIL>(ch, last_offset_of<V>(a.chunks, a.more)) : 0u;
+        v[it] = *(src_ptr)(block_address(hop.src, hop.source_rank(rank[it]), hop.src_stride) + off[it]);
+    }
+    const auto stop = [&](const HopNow &h) {
 #pragma unroll
-        for (uint32_t it = 0; it < kChainUnitsPerLane; ++it)
-            if (to[it]) *(dst_ptr)to[it] = v[it];
-        __syncthreads();                                 // the next hop reads what other wavefronts wrote
+        for (uint32_t it = 0; it < UPL; ++it)
+            if (has[it]) *(dst_ptr)(block_address(h.dst, rank[it], h.dst_stride) + off[it]) = v[it];
+    };
+    // on their way while the blocks are
+    uint32_t at = a.n_chains + table->later[chain];
+    const uint32_t end = a.n_chains + table->later[chain + 1];
+    HopNow next(table, at < end ? at : chain);
+    // (waited for here, not behind the first stop: that wait would be for its stores as well)
+    __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0)
+    stop(hop);
+    while (at < end) {
+#pragma unroll
+        for (uint32_t it = 0; it < UPL; ++it)
+            if (has[it]) tile[unit[it]] = v[it];
+        if constexpr (TAIL) __syncthreads();
+        else lds_barrier();
+        hop = next;
+        ++at;
+        next = HopNow(table, at < end ? at : chain);
+#pragma unroll
+        for (uint32_t it = 0; it < UPL; ++it)            // the same unit of the rank that the hop comes from
+            v[it] = tile[unit[it] + (hop.source_rank(rank[it]) - rank[it]) * a.column];
+        stop(hop);
+        if (at < end) lds_barrier();                     // what this hop has read may now be replaced
     }
 }
 

@@ -85,6 +85,16 @@ def test_small_collectives_take_one_launch_where_it_saves_enough(stub_library, d
         assert names == ["chain_kernel"] if chained else (len(names) == kernels and "chain_kernel" not in names), (alg, names)
 
 
+@pytest.mark.parametrize("dims,offsets,m,width", [((5, 4, 7, 6, 4), gen.von_neumann(5, 1), 6, "unsigned short, false"),
+                                                  ((13, 14, 15), gen.von_neumann(3, 1), 5, "unsigned char, false"),
+                                                  ((46, 47), gen.von_neumann(2, 1), 3, "unsigned char, false"),
+                                                  ((45, 45), gen.von_neumann(2, 1), 6, "unsigned int, true")])
+def test_columns_of_one_unit_take_units_that_divide_the_block(stub_library, dims, offsets, m, width):
+    for op in (iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER):
+        (kernel,) = stub_library.start(dims, offsets, op, iso.ISO_ALG_COMBINED, m)
+        assert kernel.startswith(f"chain_kernel<{width}"), kernel
+
+
 # cache policies: 0 cached loads, streaming stores; 1 streaming both; 2 cached, plain stores; 3 streaming loads, plain stores
 POLICY_ARGUMENT = {"shift_round_kernel": 2, "mesh_shift_round_kernel": 2, "shift_round_uniform_kernel": 0,
                    "staged_round_kernel": 1, "deliver_kernel": 1, "block_round_kernel": 2, "vector_round_kernel": 3,

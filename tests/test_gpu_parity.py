@@ -496,6 +496,23 @@ def test_large_blocks_are_taken_in_groups_of_ranks(dims, m, alg):
     assert np.array_equal(recv.cpu().numpy(), orc.allgather(dims, offsets, one_h))
 
 
+@pytest.mark.parametrize("dims,offsets,m", [
+    ((5, 4, 7, 6, 4), gen.von_neumann(5, 1), 6), ((13, 14, 15), gen.von_neumann(3, 1), 5), ((46, 47), gen.von_neumann(2, 1), 3),
+    ((4096, 1), [(1, 0), (-1, 0), (2, 0)], 3), ((16, 8, 8, 4), [(1, 1, 1, 1), (3, 2, 1, 0), (0, 0, 0, 0)], 20),
+    ((32, 32), gen.moore(2, 1), 16), ((5, 5, 41), gen.von_neumann(3, 1), 16), ((8, 8, 16), [(1, 1, 1), (2, 3, 5), (1, 1, 1)], 17),
+    ((9, 9, 9), gen.moore(3, 1), 37), ((2,) * 10, [tuple(int(b) for b in f"{v:010b}") for v in (1, 3, 7, 1023, 512, 682)], 24)])
+def test_stops_of_a_collective_in_one_launch(dims, offsets, m):
+    """Chains of up to ten hops (stops written twice) on both sides of one unit per lane, last units that overlap, a
+    single unit of every rank to a workgroup, and more starts than one over the same buffers."""
+    p, s = int(np.prod(dims)), len(offsets)
+    for op in (iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER):
+        send_h = gen.alltoall_send(7, p, s, m) if op == iso.ISO_OP_ALLTOALL else gen.allgather_send(7, p, m)
+        want = (orc.alltoall if op == iso.ISO_OP_ALLTOALL else orc.allgather)(dims, offsets, send_h)
+        for alg in (iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM, iso.ISO_ALG_COMBINED_STAGED):
+            recv, _ = _run(dims, offsets, op, alg, m, torch.from_numpy(send_h).to(DEV), starts=3)
+            assert np.array_equal(recv.cpu().numpy(), want), (dims, m, op, alg)
+
+
 def test_calls_without_a_stream_take_torchs_current_one():
     """The handle that the binding asks torch for is the current Stream object's, on the default stream and side streams."""
     from paper_1606_07676_amd import binding

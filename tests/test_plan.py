@@ -353,6 +353,32 @@ def test_fastdiv_is_exact_on_the_host():
         assert int(out[0]) > 1_000_000 and int(out[1]) == 0
 
 
+PACKED_FASTDIV_TEST = r"""
+#include <cstdint>
+#include "iso_fastdiv.hpp"
+int main() {
+    long bad = 0;
+    for (uint64_t d = 1; d < (uint64_t(1) << 32); d = d < 5000 ? d + 1 : d + d / 3) {
+        const iso::FastDiv f = iso::make_fastdiv((uint32_t)d);
+        for (uint32_t byte = 0; byte < 4; ++byte) {
+            const uint32_t others = 0x5A3CC3A5u & ~(255u << (8 * byte));
+            const iso::FastDiv g = iso::fastdiv_of(f.mul, f.div, others | (iso::shift_byte(f) << (8 * byte)), byte);
+            bad += iso::shift_byte(f) > 255 || f.mul != g.mul || f.sh1 != g.sh1 || f.sh2 != g.sh2 || f.div != g.div;
+        }
+    }
+    return bad != 0;
+}
+"""
+
+
+def test_a_division_survives_its_packing(tmp_path):
+    """Shifts in any byte of a word whose other bytes are in use, for divisors up to 2^32."""
+    (tmp_path / "t.cpp").write_text(PACKED_FASTDIV_TEST)
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_1606_07676_amd", "csrc"),
+                           str(tmp_path / "t.cpp"), "-o", str(tmp_path / "t")])
+    assert subprocess.run([str(tmp_path / "t")]).returncode == 0
+
+
 def test_schedule_builder_under_address_and_ub_sanitizers():
     """The host-side schedule builder (pure C++) compiled with -fsanitize=address,undefined
     and driven with seeded random tori, meshes and neighbourhoods through every algorithm."""
