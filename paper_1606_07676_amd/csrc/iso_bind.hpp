@@ -209,7 +209,7 @@ inline void set_grid(Launch &l, uint32_t total, uint32_t k, bool eighths) {
         case kVectorKernel: l.vec.total = total; l.vec.k = k; l.vec.more |= flags; break;
         case kBlockKernel: l.block.total = total; l.block.k = k; l.block.more |= flags; break;
         case kMeshShiftKernel: l.mesh_shift.total = total; l.mesh_shift.k = k; l.mesh_shift.more |= flags; break;
-        default: l.shift.total = total; l.shift.k = k; l.shift.more |= flags;
+        default: l.shift.total = total; l.shift.k = k; l.shift.more |= flags; l.shift.map = TileMap{n_tiles, run_log2, per_xcd};
     }
 }
 
@@ -1213,10 +1213,10 @@ private:
             // -3 % of the step, 4 KiB 0 to -3 %, 8 KiB -5 %; at 1 KiB and below between -1.5 and +1 %:
             // left alone.  Groups of 32 to 256 ranks measure alike, smaller ones do nothing)
             if (!l.entry_major && size0 >= 2048 && p >= kRankGroup) sa.grouped = (uint32_t)((p / kRankGroup) * kRankGroup * k);
-            put(sa.chunks, sa.mul_chunks, sa.shifts, 0);
-            put(k, sa.mul_k, sa.shifts, 1);
-            put(sa.inner, sa.mul_inner, sa.shifts, 2);
-            put(sa.pj, sa.mul_pj, sa.shifts, 3);
+            put(sa.chunks, sa.mul_chunks, sa.sh_chunks, 0);
+            put(k, sa.mul_k, sa.sh_k, 0);
+            put(sa.inner, sa.mul_inner, sa.sh_inner, 0);
+            put(sa.pj, sa.mul_pj, sa.sh_pj, 0);
             put(sa.p, sa.mul_p, sa.more, 0);
             if (sa.grouped) put(k * kRankGroup, sa.mul_group_k, sa.more, 1);
             if (op == ISO_OP_ALLGATHER && push_launch(l, ents.data() + done, k, per_entry)) {
@@ -1269,8 +1269,8 @@ private:
         l.shift.grouped = 0;
         l.shift.k_all = k;
         l.shift.k = n;
-        l.shift.shifts &= ~0xFF00u;
-        put(n, l.shift.mul_k, l.shift.shifts, 1);
+        l.shift.sh_k = 0;
+        put(n, l.shift.mul_k, l.shift.sh_k, 0);
         return true;
     }
 

@@ -93,7 +93,10 @@ struct ShiftArgs {
     uint32_t pj;           // its size
     uint32_t chunks, p;    // units of a block; ranks
     uint32_t mul_chunks, mul_k, mul_inner, mul_pj, mul_p, mul_group_k;
-    uint32_t shifts;       // of the divisions by chunks, k, inner, pj
+    // What every wavefront needs stays a word of its own as far as there is room (all of it packed: 0.4 % of a
+    // 32^3, 256 B all-to-all).
+    uint32_t sh_chunks, sh_k, sh_inner, sh_pj;    // shift_byte of these divisions
+    TileMap map;
     uint32_t more;         // shifts of p, group * k; launch_flags
     // Large blocks on rank-major buffers: the ranks are taken in groups of kRankGroup, and inside a group the
     // order is (entry, rank, chunk), so that a plane of the workspace sees that many consecutive blocks at a
@@ -321,15 +324,16 @@ __device__ __forceinline__ uint32_t vector_source_rank(uint32_t R, const uint32_
 // each in front of its first use behind some branch (every such fetch is a wait of its own).
 __device__ __forceinline__ void fetch_now(const ShiftArgs &a) {
     asm volatile("" ::"s"(a.entries), "s"(a.total), "s"(a.k), "s"(a.inner), "s"(a.pj), "s"(a.chunks), "s"(a.p),
-                 "s"(a.mul_chunks), "s"(a.mul_k), "s"(a.mul_inner), "s"(a.mul_pj), "s"(a.mul_p), "s"(a.shifts), "s"(a.more));
+                 "s"(a.mul_chunks), "s"(a.mul_k), "s"(a.mul_inner), "s"(a.mul_pj), "s"(a.mul_p), "s"(a.sh_chunks), "s"(a.sh_k),
+                 "s"(a.sh_inner), "s"(a.sh_pj), "s"(a.map.n_tiles), "s"(a.map.run_log2), "s"(a.map.per_xcd), "s"(a.more));
 }
 
 // The divisions of a shift launch.
 struct ShiftDivs {
     FastDiv chunks, k, inner, pj, p, group_k;
     __device__ __forceinline__ explicit ShiftDivs(const ShiftArgs &a)
-        : chunks(fastdiv_of(a.mul_chunks, a.chunks, a.shifts, 0)), k(fastdiv_of(a.mul_k, a.k, a.shifts, 1)),
-          inner(fastdiv_of(a.mul_inner, a.inner, a.shifts, 2)), pj(fastdiv_of(a.mul_pj, a.pj, a.shifts, 3)),
+        : chunks(fastdiv_of(a.mul_chunks, a.chunks, a.sh_chunks, 0)), k(fastdiv_of(a.mul_k, a.k, a.sh_k, 0)),
+          inner(fastdiv_of(a.mul_inner, a.inner, a.sh_inner, 0)), pj(fastdiv_of(a.mul_pj, a.pj, a.sh_pj, 0)),
           p(fastdiv_of(a.mul_p, a.p, a.more, 0)), group_k(fastdiv_of(a.mul_group_k, a.k << kRankGroupLog2, a.more, 1)) {}
 };
 
@@ -340,7 +344,7 @@ __global__ __launch_bounds__(kThreads) void shift_round_kernel(const ShiftArgs a
     const ShiftDivs div(a);
     __shared__ DevEntry lds[LDS ? kLdsEntries : 1];
     uint32_t tile;
-    if (!tile_of_block(map_of(tiles_of(a.total), a.more), tile)) return;            // (the whole workgroup: no one is left at the barrier)
+    if (!tile_of_block(a.map, tile)) return;            // (the whole workgroup: no one is left at the barrier)
     // The table goes through LDS; its load is under way while the lanes work out their indices, which do
     // not depend on it.
     StagedEntries<LDS> staging;
@@ -386,7 +390,7 @@ __global__ __launch_bounds__(kThreads) void shift_round_uniform_kernel(const Shi
     fetch_now(a);
     const ShiftDivs div(a);
     uint32_t tile;
-    if (!tile_of_block(map_of(tiles_of(a.total), a.more), tile)) return;
+    if (!tile_of_block(a.map, tile)) return;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t u0 = tile * (uint32_t)kThreads + wave * 64u;      // first unit of this wavefront
     if (u0 >= a.total) return;                                       // total is a multiple of 64
@@ -431,7 +435,7 @@ __global__ __launch_bounds__(kThreads) void shift_push_kernel(const ShiftArgs a)
     __shared__ DevEntry lds[kLdsEntries];
     __shared__ uint32_t lds_first[kLdsEntries + 1];
     uint32_t tile;
-    if (!tile_of_block(map_of(tiles_of(a.total), a.more), tile)) return;
+    if (!tile_of_block(a.map, tile)) return;
     StagedEntries<true> staging;
     staging.issue(a.entries, a.k_all);
     const uint32_t q = kThreads - 1 - threadIdx.x;       // the workgroup's last lanes, as in the block kernel
