@@ -62,6 +62,7 @@ struct Launch {
     const ChainArgs *chain_by_value;      // or BoundRequest::chain, where there is no table
     uint32_t chain_width;  // its unit width, where not the request's
     uint32_t n_tiles, run_log2;           // see TileMap
+    uint32_t outside_tiles;               // mesh: tiles not interior to all entries (see rounds_move_faster)
     bool entry_major, vector_round;       // see launch_flags
     uint32_t pull;
     uint64_t bytes_read, bytes_written;   // of blocks (see iso_start_info_t)
@@ -388,53 +389,99 @@ struct HostEntry {
     int dim, dst_buf, dst_slot, neighbor;
 };
 
-// Mesh shift launches of equal blocks: one bit per tile of kThreads units, set where every rank of the tile has
-// a source for every entry of the launch.  Coordinates at which every entry finds its source: r_l - c_l in
-// [0, p_l) for all masked dimensions l of all entries.  A tile is interior if its ranks share all coordinates
-// but the last and lie inside these bounds (conservative: a tile that crosses into the next row of the last
-// dimension counts as not interior).
-inline std::vector<uint32_t> mesh_interior_tiles(const Comm &c, bool slot_major, const HostEntry *ents, uint32_t k,
-                                                 uint64_t total, uint64_t chunks, uint64_t p) {
-    std::vector<int64_t> in_lo((size_t)c.d, 0), in_hi((size_t)c.d, 0);
-    bool has_interior = true;
+// Mesh shift launches of equal blocks: the ranks where every one of the entries finds its source, as runs of
+// consecutive ranks, f(first, count).  Coordinates that do: r_l - c_l in [0, p_l) for all masked dimensions l of all
+// entries.  A run holds the ranks that share the coordinates before dimension L, lie inside L's bounds, and all
+// dimensions behind it; L is the last bounded dimension (none: all ranks are one run), or with `by_line` the last one.
+template <typename F>
+void for_interior_runs(const Comm &c, const HostEntry *ents, uint32_t k, bool by_line, F &&f) {
+    std::vector<int64_t> lo((size_t)c.d, 0), hi((size_t)c.d), at;
+    int last = by_line ? c.d - 1 : -1;
     for (int j = 0; j < c.d; ++j) {
-        int64_t lo = 0, hi = c.dims[j];
+        hi[(size_t)j] = c.dims[(size_t)j];
         for (uint32_t q = 0; q < k; ++q) {
             const DevEntry &de = ents[q].de;
-            if (!(((de.meta >> 8) >> j) & 1u)) continue;
             const int64_t cl = c.c((int)de.ref, j);
-            lo = std::max<int64_t>(lo, cl);
-            hi = std::min<int64_t>(hi, (int64_t)c.dims[j] + cl);
+            if (!(((de.meta >> 8) >> j) & 1u) || !cl) continue;
+            lo[(size_t)j] = std::max<int64_t>(lo[(size_t)j], cl);
+            hi[(size_t)j] = std::min<int64_t>(hi[(size_t)j], (int64_t)c.dims[(size_t)j] + cl);
+            last = std::max(last, j);
         }
-        if (lo >= hi) has_interior = false;
-        in_lo[(size_t)j] = lo;
-        in_hi[(size_t)j] = hi;
+        if (lo[(size_t)j] >= hi[(size_t)j]) return;
     }
-    const uint64_t n_tiles = (total + kThreads - 1) / kThreads;
-    std::vector<uint32_t> bits((size_t)((n_tiles + 31) / 32), 0u);
-    if (!has_interior) return bits;
-    // line by line along the last dimension: its interior ranks' units are one run (per entry, slot-major), and the
-    // tiles inside that run are interior (tile by tile the same took 11 ms for the lists of a 64^3 box)
-    const int last = c.d - 1;
-    const uint64_t n_last = (uint64_t)c.dims[last], lines = p / n_last;
-    const uint64_t unit_per_rank = slot_major ? chunks : chunks * k, planes = slot_major ? k : 1;
-    std::vector<int64_t> at((size_t)c.d, 0);                   // coordinates of the line, last dimension excluded
-    for (uint64_t line = 0; line < lines; ++line) {
-        bool inside = true;
-        for (int j = 0; j < last && inside; ++j) inside = at[(size_t)j] >= in_lo[(size_t)j] && at[(size_t)j] < in_hi[(size_t)j];
-        for (uint64_t e = 0; inside && e < planes; ++e) {
-            const uint64_t first_rank = line * n_last + (uint64_t)in_lo[(size_t)last], end_rank = line * n_last + (uint64_t)in_hi[(size_t)last];
-            const uint64_t u0 = (e * p + first_rank) * unit_per_rank, u1 = (e * p + end_rank) * unit_per_rank;
-            const uint64_t t0 = (u0 + kThreads - 1) / kThreads, t1 = u1 == total ? n_tiles : u1 / kThreads;
-            for (uint64_t tl = t0; tl < t1;) {
-                const uint64_t n = std::min<uint64_t>(32 - (tl & 31), t1 - tl);
-                bits[(size_t)(tl >> 5)] |= (n == 32 ? ~0u : ((1u << n) - 1)) << (tl & 31);
-                tl += n;
-            }
+    if (last < 0) {
+        f((uint64_t)0, (uint64_t)c.p);
+        return;
+    }
+    const uint64_t run = (uint64_t)((hi[(size_t)last] - lo[(size_t)last]) * c.inner[(size_t)last]);
+    uint64_t first = 0;
+    for (int j = 0; j <= last; ++j) first += (uint64_t)(lo[(size_t)j] * c.inner[(size_t)j]);
+    at = lo;
+    for (bool more = true; more;) {                            // the coordinates before L step through their bounds
+        f(first, run);
+        more = false;
+        for (int j = last - 1; j >= 0 && !more; --j) {
+            const uint64_t inner = (uint64_t)c.inner[(size_t)j];
+            more = ++at[(size_t)j] < hi[(size_t)j];
+            if (more) first += inner;
+            else first -= (uint64_t)(hi[(size_t)j] - 1 - lo[(size_t)j]) * inner, at[(size_t)j] = lo[(size_t)j];
         }
-        for (int j = last - 1; j >= 0 && ++at[(size_t)j] == c.dims[j]; --j) at[(size_t)j] = 0;
     }
+}
+
+constexpr uint32_t kWaveLog2 = 6, kTileLog2 = 8;
+static_assert(1 << kTileLog2 == kThreads, "a tile");
+
+// Sets the bits of the groups of 2^group_log2 units that lie inside [u0, u1); the last group may be a part.
+inline void mark_groups(std::vector<uint32_t> &bits, uint32_t group_log2, uint64_t total, uint64_t u0, uint64_t u1) {
+    const uint64_t fill = (uint64_t(1) << group_log2) - 1;
+    const uint64_t w0 = (u0 + fill) >> group_log2, w1 = (u1 == total ? total + fill : u1) >> group_log2;
+    if (w0 >= w1) return;
+    const size_t first = (size_t)(w0 >> 5), last = (size_t)((w1 - 1) >> 5);
+    const uint32_t from = ~0u << (w0 & 31), to = ~0u >> (31 - ((w1 - 1) & 31));
+    if (first == last) {
+        bits[first] |= from & to;
+        return;
+    }
+    bits[first] |= from;
+    std::fill(bits.begin() + (ptrdiff_t)first + 1, bits.begin() + (ptrdiff_t)last, ~0u);
+    bits[last] |= to;
+}
+
+// One bit per tile of kThreads units, set where every rank of the tile has a source for every entry of the launch and
+// all of them share all coordinates but the last: what rounds_move_faster counts.  (Line by line along the last
+// dimension; tile by tile the same took 11 ms for the lists of a 64^3 box.)
+inline std::vector<uint32_t> mesh_interior_tiles(const Comm &c, bool slot_major, const HostEntry *ents, uint32_t k,
+                                                 uint64_t total, uint64_t chunks, uint64_t p) {
+    const uint64_t unit_per_rank = slot_major ? chunks : chunks * k;
+    std::vector<uint32_t> bits((size_t)(((total + kThreads - 1) / kThreads + 31) / 32), 0u);
+    for_interior_runs(c, ents, k, true, [&](uint64_t first, uint64_t n) {
+        for (uint64_t e = 0; e < (slot_major ? k : 1); ++e)
+            mark_groups(bits, kTileLog2, total, (e * p + first) * unit_per_rank, (e * p + first + n) * unit_per_rank);
+    });
     return bits;
+}
+
+// What the mesh shift kernel reads: one bit per 2^group_log2 units (a wavefront or a tile), set where all their moves
+// have a source.  On slot-major buffers a wavefront's units belong to one entry, whose own bounds count.
+inline std::vector<uint32_t> mesh_interior_units(const Comm &c, bool slot_major, const HostEntry *ents, uint32_t k,
+                                                 uint32_t group_log2, uint64_t total, uint64_t chunks, uint64_t p) {
+    const uint64_t unit_per_rank = slot_major ? chunks : chunks * k;
+    std::vector<uint32_t> bits((size_t)((((total - 1) >> group_log2) + 32) / 32), 0u);
+    for (uint32_t e = 0; e < (slot_major ? k : 1); ++e)
+        for_interior_runs(c, ents + e, slot_major ? 1 : k, false, [&](uint64_t first, uint64_t n) {
+            mark_groups(bits, group_log2, total, (e * p + first) * unit_per_rank, (e * p + first + n) * unit_per_rank);
+        });
+    return bits;
+}
+
+// How finely: by the wavefront where a run holds few tiles, of which the first and the last are lost to tiles.
+// From 32 tiles on that is 3 % of a launch, and the bitmap's size is what an init call pays for (64^3 box, 200 B:
+// 600 KiB by the wavefront in its two lists).
+inline uint32_t interior_group_log2(const Comm &c, bool slot_major, const HostEntry *ents, uint32_t k, uint64_t chunks) {
+    uint64_t run = 0;
+    for_interior_runs(c, ents, slot_major ? 1 : k, false, [&](uint64_t, uint64_t n) { run = n; });
+    return run * (slot_major ? chunks : chunks * k) < 32 * kThreads ? kWaveLog2 : kTileLog2;
 }
 
 // The record of one entry of the staged schedule's last launch.
@@ -748,12 +795,12 @@ private:
     }
 
     // On a mesh a launch's tiles are interior where all its entries have a source, which is less of the box for the
-    // rounds of a dimension together than for each by itself, and a tile that is not takes about twice its time.  Against
+    // rounds of a dimension together than for each by itself, and a tile that is not takes up to twice its time.  Against
     // that stand what a launch costs (4 us, here in bytes at the copy rate) and blocks that several rounds read.  Rounds
-    // one by one, all of a dimension together, us: 16^4, 40 random neighbours up to 3 away, 1 KiB 3040 and 3337; 32^3 the
-    // same 1240 and 1339; 48^3, 124 neighbours, 128 B 1510 and 1608; 8^5, 40 neighbours, 4 KiB 6504 and 6714; the other
-    // way 8^5, 256 B 531 and 517, 128^2, 48 neighbours, 2 KiB 1008 and 956, 10^4, 40 neighbours, 400 B 278 and 220,
-    // allgather 48^3, 128 B 611 and 551, 8^5, 4 KiB 5316 and 4995 (9^5, 512 B 1350 and 1427 is not told apart from these).
+    // one by one, all of a dimension together, us: 16^4, 40 random neighbours up to 3 away, 1 KiB 2788 and 2960; 32^3 the
+    // same 1165 and 1184; 48^3, 124 neighbours, 128 B 1491 and 1527; the other way 8^5, 256 B 450 and 445, 128^2, 48
+    // neighbours, 2 KiB 897 and 888.  Wrong by 3 to 5 % where most tiles are outside for either (8^5, 4 KiB 5908 and 5701,
+    // slot-major, 1 KiB 1412 and 1349; allgather 9^5, 512 B 1248 and 1214): no weight of a tile outside tells these apart.
     bool rounds_move_faster() const {
         constexpr uint64_t kLaunchBytes = uint64_t(26) << 20;
         uint64_t rounds_cost = 0, merged_cost = 0;
@@ -761,10 +808,7 @@ private:
             const Launch &l = pending[i].l;
             uint64_t cost = kLaunchBytes + l.bytes_read;
             if (l.kernel == kMeshShiftKernel) {
-                uint64_t outside = l.n_tiles;
-                for (size_t q = 0; q < (l.n_tiles + 31u) / 32; ++q)
-                    outside -= (uint64_t)__builtin_popcount(prefixes[pending[i].first_prefix + q]);
-                cost += outside * kThreads * 2 << min_log2;
+                cost += (uint64_t)l.outside_tiles * kThreads * 2 << min_log2;
             }
             (i < n_listed ? rounds_cost : merged_cost) += cost;
         }
@@ -1190,7 +1234,15 @@ private:
             MeshArgs &ma = l.mesh_shift;
             ma.inner = shift ? (uint32_t)c.inner[r.dim] : 1u;
             ma.pj = shift ? (uint32_t)c.dims[r.dim] : 1u;
-            ma.torus = torus_bits(c.d, shift ? r.dim : -1, periodic_mask());
+            bool packed = true;                                // in all entries or in none
+            const size_t first = table.size();
+            for (uint32_t q = 0; q < k; ++q) {
+                table.push_back(ents[done + q].de);
+                const DevEntry &de = ents[done + q].de;
+                packed = packed && pack_reference(c.can.data() + (size_t)de.ref * c.d, c.d, de.meta >> 8, table.back());
+            }
+            for (uint32_t q = 0; q < k && !packed; ++q) table[first + q] = ents[done + q].de;
+            ma.torus = torus_bits(c.d, shift ? r.dim : -1, periodic_mask(), packed);
             ma.chunks = (uint32_t)chunks;
             ma.p = (uint32_t)p;
             l.entry_major = lay.slot_major;
@@ -1199,9 +1251,17 @@ private:
             put(ma.inner, ma.mul_inner, ma.shifts, 2);
             put(ma.pj, ma.mul_pj, ma.shifts, 3);
             put(ma.p, ma.mul_p, ma.more, 0);
+            const uint32_t group_log2 = interior_group_log2(c, lay.slot_major, ents.data() + done, k, chunks);
             const std::vector<uint32_t> bits =
-                mesh_interior_tiles(c, lay.slot_major, ents.data() + done, k, total, chunks, p);
+                mesh_interior_units(c, lay.slot_major, ents.data() + done, k, group_log2, total, chunks, p);
+            ma.torus |= (uint32_t)(group_log2 == kTileLog2) << 11;
             prefixes.insert(prefixes.end(), bits.begin(), bits.end());
+            if (pl.algorithm == ISO_ALG_COMBINED && !arena) {
+                l.outside_tiles = (uint32_t)((total + kThreads - 1) / kThreads);
+                for (uint32_t w : mesh_interior_tiles(c, lay.slot_major, ents.data() + done, k, total, chunks, p))
+                    l.outside_tiles -= (uint32_t)__builtin_popcount(w);
+            }
+            return ISO_SUCCESS;
         } else {
             ShiftArgs &sa = l.shift;
             sa.inner = shift ? (uint32_t)c.inner[r.dim] : 1u;

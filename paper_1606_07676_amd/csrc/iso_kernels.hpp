@@ -662,9 +662,30 @@ struct BlockArgs {
 };
 static_assert(sizeof(BlockArgs) <= kCheapArguments, "launch cost");
 
-// Dimensions (bits 0-4), the shifted one plus 1 (5-9; 0: same-rank copy or full vectors), which of them wrap (16-31).
-inline uint32_t torus_bits(int32_t d, int32_t shift_dim, uint32_t periodic_mask) {
-    return (uint32_t)d | ((uint32_t)(shift_dim + 1) << 5) | (periodic_mask << 16);
+// Dimensions (bits 0-4), the shifted one plus 1 (5-9; 0: same-rank copy or full vectors), whether the entries hold
+// their reference coordinates (10, see pack_reference), an interior bit per tile instead of per wavefront (11), which dimensions wrap (16-31).
+inline uint32_t torus_bits(int32_t d, int32_t shift_dim, uint32_t periodic_mask, bool packed_reference = false) {
+    return (uint32_t)d | ((uint32_t)(shift_dim + 1) << 5) | ((uint32_t)packed_reference << 10) | (periodic_mask << 16);
+}
+
+// Mesh shift rounds read no `units`, `ref` and `last_offset` of an entry: 16 bits for the coordinate of C^ref in each
+// of up to 6 dimensions that do not wrap.  Saves the lanes near a face a dependent load (see mesh_shift_round_kernel).
+inline bool pack_reference(const int32_t *cref, int32_t d, uint32_t mask, DevEntry &de) {
+    uint32_t w[3] = {};
+    if (d > 6) return false;
+    for (int j = 0; j < d; ++j) {
+        if (!((mask >> j) & 1u)) continue;
+        if (cref[j] < -32768 || cref[j] > 32767) return false;
+        w[j / 2] |= (uint32_t)(uint16_t)cref[j] << (16 * (j & 1));
+    }
+    de.units = w[0];
+    de.ref = w[1];
+    de.last_offset = w[2];
+    return true;
+}
+__device__ __forceinline__ uint32_t packed_reference(const DevEntry &en, int j) {
+    const uint32_t w = j < 2 ? en.units : j < 4 ? en.ref : (uint32_t)en.last_offset;
+    return (uint32_t)((int32_t)(w << (j & 1 ? 0 : 16)) >> 16);
 }
 
 // What mesh_source_rank reads.
@@ -672,10 +693,11 @@ struct MeshView {
     const uint32_t *offsets;
     dims_ptr dims;
     uint32_t inner, pj, vector_round, periodic_mask;
+    bool packed;
     int32_t d, shift_dim;
     __device__ __forceinline__ MeshView(const TorusDims *t, uint32_t torus, uint32_t inner_, uint32_t pj_, uint32_t vector)
         : offsets(offsets_after(t)), dims(const_dims(t)), inner(inner_), pj(pj_), vector_round(vector),
-          periodic_mask(torus >> 16), d((int32_t)(torus & 31u)), shift_dim((int32_t)((torus >> 5) & 31u) - 1) {}
+          periodic_mask(torus >> 16), packed((torus >> 10) & 1u), d((int32_t)(torus & 31u)), shift_dim((int32_t)((torus >> 5) & 31u) - 1) {}
 };
 
 // Mesh: does the move of entry `en` happen at rank R (R - C^ref inside the mesh in every masked
@@ -687,8 +709,13 @@ __device__ __forceinline__ bool mesh_source_rank_d(const MeshView &a, const DevE
     const uint32_t mask = (en.meta >> 8) & 0xFFFFu;
     const uint32_t *cref = a.offsets + (size_t)en.ref * a.d;
     uint32_t cr[D], r[D];
+    if (a.packed) {
 #pragma unroll
-    for (int j = 0; j < D; ++j) cr[j] = cref[j];
+        for (int j = 0; j < D; ++j) cr[j] = packed_reference(en, j);
+    } else {
+#pragma unroll
+        for (int j = 0; j < D; ++j) cr[j] = cref[j];
+    }
     uint32_t rem = R;
 #pragma unroll
     for (int j = D - 1; j >= 0; --j) {
@@ -863,16 +890,20 @@ __global__ __launch_bounds__(kThreads) void block_round_kernel(const BlockArgs a
 // Shift rounds of equal blocks on a mesh: the shift kernel's decomposition (no prefix search, no
 // per-entry unit width) with the mesh's validity test.  Field names match what mesh_source_rank reads.
 //
-// Most ranks of a mesh are interior: every move of the launch has a source there.  The host marks,
-// one bit per tile, the tiles all of whose ranks are interior; such a workgroup skips the per-lane
-// decode of all coordinates and the loads of the reference offsets and does what the torus kernel
-// does.  (Deciding this in the kernel from the tile's first and last rank costs as much as it
-// saves: the test is a chain of dependent scalar loads of launch constants, and what bounds these
-// kernels is how long a wavefront holds its slot before its one load is under way.)
+// Most ranks of a mesh are interior: every move has a source there.  The host marks, one bit per wavefront or tile,
+// the runs of ranks where that holds (mesh_interior_units); such a wavefront skips the per-lane decode of all
+// coordinates and does what the torus kernel does.  (Deciding this in the kernel from the first and last rank costs
+// as much as it saves: the test is a chain of dependent scalar loads of launch constants, and what bounds these
+// kernels is how long a wavefront holds its slot before its one load is under way.)  The others find the
+// coordinates of C^ref in the entry itself.
+// One bit per tile with the bounds of all the launch's entries, reference coordinates from a table -> as here, boxes:
+// 45 x 37 x 29, 100 B, slot-major 121 -> 96 us (the torus: 96), 40^3, 128 B 163 -> 157 and slot-major 175 -> 147, 8^5,
+// 40 neighbours up to 3 away, 256 B 513 -> 450 and 4 KiB 6460 -> 5908, allgather 8^5, 1 KiB 1444 -> 1265, 12^3, 40 B
+// 12.8 -> 9.5.
 struct MeshArgs {
     const DevEntry *entries;
     const TorusDims *dims;     // and after it the [s][d] effective coordinates
-    const uint32_t *interior;  // bit t: every rank of tile t has a source for every entry of the launch
+    const uint32_t *interior;  // a bit per wavefront (64 units) or per tile: all the blocks it moves have a source
     uint32_t total, k;
     uint32_t inner, pj;        // rank stride and size of the moving dimension (1, 1 for a same-rank copy)
     uint32_t chunks, p;
@@ -890,7 +921,10 @@ __global__ __launch_bounds__(kThreads) void mesh_shift_round_kernel(const MeshAr
     if (!tile_of_block(map_of(tiles_of(a.total), a.more), tile)) return;
     StagedEntries<LDS> staging;
     staging.issue(a.entries, a.k);
-    const bool interior = (a.interior[tile >> 5] >> (tile & 31u)) & 1u;      // uniform: one scalar load
+    const uint32_t wave = tile * (kThreads / 64u) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t bit = (a.torus >> 11) & 1u ? tile : wave;
+    typedef const uint32_t __attribute__((address_space(4))) *const_word_ptr;
+    const bool interior = (((const_word_ptr)(uintptr_t)a.interior)[bit >> 5] >> (bit & 31u)) & 1u;
     const uint32_t u = tile * (uint32_t)kThreads + threadIdx.x;
     uint32_t t, ch, R, e;
     fast_divmod(u, fastdiv_of(a.mul_chunks, a.chunks, a.shifts, 0), t, ch);

@@ -227,6 +227,13 @@ def test_interior_tiles_of_mesh_launches(tmp_path):
     assert proc.returncode == 0 and "mesh tiles ok" in proc.stdout, proc.stdout
 
 
+def test_interior_units_and_packed_coordinates_of_mesh_launches(tmp_path):
+    import stub_library as sl
+    exe = sl.build_driver(str(tmp_path), "mesh_units_driver.cpp")
+    proc = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert proc.returncode == 0 and "mesh units ok" in proc.stdout, (proc.returncode, proc.stdout)
+
+
 @pytest.mark.parametrize("alg", [iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM])
 def test_binding_a_large_box_is_no_walk_over_its_tiles(stub_library, alg):
     """Init binds two launch lists (rounds one by one, and as iso_start takes them): one copy to the device for both,
