@@ -55,8 +55,10 @@ enum iso_algorithm {
     /* Message-combining, torus-direct schedule (Section 5): one round per
      * dimension j and distinct non-zero coordinate value v.  The request's launch
      * list has one entry per round (iso_start_range, graphs); iso_start itself
-     * takes the rounds of one dimension, which touch disjoint blocks, in one
-     * kernel launch.  All-to-all uses the alternating receive/intermediate buffer
+     * takes moves that touch disjoint blocks together in one kernel launch: the
+     * rounds of one dimension; where every block makes one move, all rounds; in
+     * all-to-alls of small or odd blocks the last move of every block, so that
+     * receive rows are written whole.  All-to-all uses the alternating receive/intermediate buffer
      * rule of Algorithm 1; allgather routes along the prefix trie of
      * Section 3.2. */
     ISO_ALG_COMBINED       = 0,
@@ -89,8 +91,9 @@ enum iso_algorithm {
      * overwritten later: allgather trie nodes) goes to an extra workspace slot and is
      * copied from there by the last launch; the workspace grows by one plane of
      * p*m bytes per such block.  Rounds left empty disappear.  The row-writing
-     * launch takes equal blocks that are multiples of 16 bytes in dense rank-major
-     * rows with s <= 128 and s*m <= 32 KiB; any other request runs the same plan on
+     * launch takes equal blocks in dense rank-major rows with s <= 128 and
+     * s*m <= 32 KiB (a little less for blocks that are no multiple of 16 bytes,
+     * which are moved in overlapping units); any other request runs the same plan on
      * the general kernels, the last launch as one launch per dimension (so the
      * request's launches can exceed the plan's rounds).  Not available on a mesh
      * (ISO_ERR_ARG). */

@@ -57,6 +57,7 @@ struct Launch {
     MeshArgs mesh_shift;
     DeliverArgs deliver;
     StagedRoundArgs staged;
+    bool by_bytes;         // deliver kernel: blocks of any size (deliver_bytes_kernel)
     uint32_t tile_units;   // the staged schedule's kernels: kTileUnits or kSmallTileUnits
     ChainHead chain;       // chain kernel: its hops in the request's table
     const ChainArgs *chain_by_value;      // or BoundRequest::chain, where there is no table
@@ -308,16 +309,50 @@ KernelRef select_block(const Launch &l) {
     return form(std::integral_constant<int, 0>());
 }
 
+template <typename V>
+KernelRef select_deliver_bytes(const Launch &l) {
+    return with_policy<V>(l, [&](auto pol) -> KernelRef {
+        constexpr uint32_t kSmall = kSmallTileUnits / kThreads, kLarge = kTileUnits / kThreads;
+        if (l.tile_units == kSmallTileUnits) return {(const void *)&deliver_bytes_kernel<V, pol(), kSmall>, &l.deliver};
+        return {(const void *)&deliver_bytes_kernel<V, pol(), kLarge>, &l.deliver};
+    });
+}
+
+template <typename V>
+KernelRef select_staged_round(const Launch &l) {
+    return with_policy<V>(l, [&](auto pol) -> KernelRef {
+        constexpr uint32_t kSmall = kSmallTileUnits / kThreads, kLarge = kTileUnits / kThreads;
+        const bool small = l.tile_units == kSmallTileUnits;
+        if constexpr (sizeof(V) > 1) {
+            if (l.tail)
+                return small ? KernelRef{(const void *)&staged_round_kernel<V, pol(), kSmall, true>, &l.staged}
+                             : KernelRef{(const void *)&staged_round_kernel<V, pol(), kLarge, true>, &l.staged};
+        }
+        return small ? KernelRef{(const void *)&staged_round_kernel<V, pol(), kSmall, false>, &l.staged}
+                     : KernelRef{(const void *)&staged_round_kernel<V, pol(), kLarge, false>, &l.staged};
+    });
+}
+
+template <typename V>
+KernelRef select_tile(const Launch &l) {
+    return l.kernel == kStagedRoundKernel ? select_staged_round<V>(l) : select_deliver_bytes<V>(l);
+}
+
 inline KernelRef select_kernel(int vector_bytes, const Launch &l) {
-    if (l.kernel == kStagedRoundKernel || l.kernel == kDeliverKernel)       // blocks of whole 16-byte units only
+    if (l.kernel == kStagedRoundKernel || (l.kernel == kDeliverKernel && l.by_bytes)) {
+        switch (vector_bytes) {
+            case 16: return select_tile<vec16_t>(l);
+            case 8:  return select_tile<vec8_t>(l);
+            case 4:  return select_tile<uint32_t>(l);
+            case 2:  return select_tile<uint16_t>(l);
+            default: return select_tile<uint8_t>(l);
+        }
+    }
+    if (l.kernel == kDeliverKernel)                      // blocks of whole 16-byte units
         return with_policy<vec16_t>(l, [&](auto pol) -> KernelRef {
             constexpr uint32_t kSmall = kSmallTileUnits / kThreads, kLarge = kTileUnits / kThreads;
-            const bool small = l.tile_units == kSmallTileUnits;
-            if (l.kernel == kDeliverKernel)
-                return small ? KernelRef{(const void *)&deliver_kernel<vec16_t, pol(), kSmall>, &l.deliver}
-                             : KernelRef{(const void *)&deliver_kernel<vec16_t, pol(), kLarge>, &l.deliver};
-            return small ? KernelRef{(const void *)&staged_round_kernel<vec16_t, pol(), kSmall>, &l.staged}
-                         : KernelRef{(const void *)&staged_round_kernel<vec16_t, pol(), kLarge>, &l.staged};
+            return l.tile_units == kSmallTileUnits ? KernelRef{(const void *)&deliver_kernel<vec16_t, pol(), kSmall>, &l.deliver}
+                                                   : KernelRef{(const void *)&deliver_kernel<vec16_t, pol(), kLarge>, &l.deliver};
         });
     if (l.kernel == kBlockKernel) {
         if (l.mesh) return l.lds_table ? select_block<true, true>(l) : select_block<false, true>(l);
@@ -535,8 +570,11 @@ public:
             n_listed = pending.size();
         }
         if (chains && chain_launch(launches)) return upload();
-        if (merges && launches < bound_rounds.size()) {
+        const bool star = star_in_one_launch(launches), rows = !star && rows_in_one_launch();
+        if (rows || star || (merges && launches < bound_rounds.size())) {
             const size_t n_entries = table.size(), n_prefixes = prefixes.size();
+            if (star) join_star();
+            else if (rows) defer_last_hops();
             merge_rounds();
             st = bind_rounds();
             if (c.mesh && !arena && st == ISO_SUCCESS && rounds_move_faster()) {
@@ -794,6 +832,77 @@ private:
         }
     }
 
+    // iso_start of an all-to-all whose rows fit a workgroup (rows_fit_a_tile): the last hop of every block taken out of
+    // its round, and all of them in one launch that writes whole receive rows (deliver_launch), after the rounds of the
+    // other hops, which read rows and write planes (staged_round_launch).  Every block makes the moves of its schedule;
+    // what goes are rounds that write parts of memory sectors, which cost up to 2.7 times what the blocks hold.  For
+    // blocks that do not fill 64-byte sectors, and 64 bytes, half a line (us, one launch per dimension -> rows, a
+    // gigabyte of buffer sets in turn: 64^3, 26 neighbours, 20 B 222 -> 171, 100 B 1119 -> 800, 400 B 2721 -> 2606; 662
+    // x 503, 10 neighbours, 100 B 351 -> 223, 64 B 158 -> 135; 24^3, 100 B 50 -> 41; 16^3, 200 B 31 -> 26; 8^5, 40
+    // neighbours, 40 B 135 -> 119).  Not: other whole sectors (64^3, 192 B 965 -> 1024, 320 B 1525 -> 1682), 512 B and
+    // more (64^3, 500 B 3269 -> 3279), up to 8 MiB (64^2, 24 neighbours, 40 B 5.9 -> 8.5; 16^3, 40 B 10 -> 13.6), up to
+    // 48 MiB under 32 bytes and for 64 (24^3, 20 B 15.1 -> 17.7).  ISO_ALG_COMBINED_BYDIM starts its launch list up to 7/4
+    // of the last-level cache (above: 64^3, 100 B 1119 -> 800; 8^5, 40 neighbours, 400 B 1045 -> 1063).
+    bool rows_in_one_launch() const {
+        const uint64_t llc = kLastLevelCacheBytes, bytes = inf.delivered_bytes;
+        if (op != ISO_OP_ALLTOALL || arena || !rows_fit_a_tile() || (size0 % 64 == 0 && size0 != 64) || size0 >= 512) return false;
+        if (pl.algorithm == ISO_ALG_COMBINED_BYDIM) return bytes > llc * 7 / 4;
+        return pl.algorithm == ISO_ALG_COMBINED && bytes > (size0 < 32 || size0 == 64 ? llc * 3 / 16 : llc / 32);
+    }
+
+    // iso_start of ISO_ALG_COMBINED where every block makes its one move out of the send buffer (a star): the moves of
+    // all dimensions touch different receive blocks and go together, as one launch of the kernel that knows the
+    // neighbours' full vectors (us, a launch per dimension -> one, a gigabyte of buffer sets in turn: 64^3, 6 neighbours,
+    // 16 B 34 -> 15.5, 72 B 100 -> 48, 128 B 75 -> 65, 2 KiB 1083 -> 1025; 24^3, 100 B 13.1 -> 7.0; 12^4, 200 B 31.5 ->
+    // 15.3; 300^2, 4000 B 483 -> 467; slot-major 64^3, 128 B 69.9 -> 65.7).  From 256 bytes on above a 24th of the
+    // cache; an allgather below 256 bytes.  Nothing to gain in one dimension (262144, 256 B 44.1 -> 45.1).
+    bool star_in_one_launch(uint64_t launches) const {
+        if (pl.algorithm != ISO_ALG_COMBINED || c.mesh || !uniform || inf.entries != (int64_t)s || launches < 2 ||
+            c.d > kVectorDims || s > kLdsEntries)
+            return false;
+        for (const Round &r : pl.rounds)
+            for (const iso_plan_entry_t &e : r.entries)
+                if (e.src_buf != ISO_BUF_SEND) return false;
+        return size0 < 256 || (op == ISO_OP_ALLTOALL && inf.delivered_bytes > kLastLevelCacheBytes / 24);
+    }
+
+    void join_star() {
+        std::vector<HostEntry> all;
+        all.reserve(s);
+        for (const std::vector<HostEntry> &ents : rounds) all.insert(all.end(), ents.begin(), ents.end());
+        for (HostEntry &he : all) he.de.shift = (uint32_t)he.neighbor;
+        bound_rounds.assign(1, {ISO_ROUND_VECTOR, -1, bound_rounds[0].of, nullptr});
+        rounds.assign(1, std::move(all));
+    }
+
+    void defer_last_hops() {
+        std::vector<HostEntry> last(s);
+        std::vector<bool> taken(s, false);
+        for (size_t ri = rounds.size(); ri-- > 0;) {
+            std::vector<HostEntry> &ents = rounds[ri], kept;
+            for (const HostEntry &he : ents) {
+                const size_t i = (size_t)he.neighbor;
+                if (taken[i]) kept.push_back(he);
+                else last[i] = he, taken[i] = true;
+            }
+            ents.swap(kept);
+        }
+        size_t n = 0;
+        for (size_t ri = 0; ri < rounds.size(); ++ri) {
+            if (rounds[ri].empty()) continue;
+            if (n != ri) {
+                bound_rounds[n] = bound_rounds[ri];
+                rounds[n] = std::move(rounds[ri]);
+            }
+            ++n;
+        }
+        const int of = (int)pl.rounds.size() - 1;
+        bound_rounds.resize(n);
+        rounds.resize(n);
+        bound_rounds.push_back({ISO_ROUND_DELIVER, -1, of, nullptr});
+        rounds.push_back(std::move(last));
+    }
+
     // On a mesh a launch's tiles are interior where all its entries have a source, which is less of the box for the
     // rounds of a dimension together than for each by itself, and a tile that is not takes up to twice its time.  Against
     // that stand what a launch costs (4 us, here in bytes at the copy rate) and blocks that several rounds read.  Rounds
@@ -891,18 +1000,26 @@ private:
         return ISO_SUCCESS;
     }
 
-    // The last launch of the staged schedule has a kernel of its own for equal blocks in dense
-    // [p][s][m] receive rows; anywhere else it runs as one launch per dimension on the general kernels.
+    // Equal blocks in dense [p][s][m] receive rows that a workgroup can hold whole (deliver_launch).
+    bool rows_fit_a_tile() const {
+        const uint64_t m0 = s ? lay.size[0] : 0;
+        if (!m0 || lay.slot_major || c.mesh || s > kLdsEntries || lay.recv_extent != s * m0) return false;
+        const uint64_t width = uint64_t(1) << unit_log2_of(m0);
+        if (m0 > kTileUnits * 16 || s * ((m0 + width - 1) / width) > kTileUnits || (m0 % 16 && s * m0 + 15 > kTileUnits * 16)) return false;
+        for (size_t i = 0; i < s; ++i)
+            if (lay.size[i] != m0 || lay.recv_displ[i] != i * m0) return false;
+        return true;
+    }
+
+    // The last launch of the staged schedule has a kernel of its own for rows_fit_a_tile; anywhere else it runs as
+    // one launch per dimension on the general kernels.
     void rounds_as_launched() {
         for (size_t ri = 0; ri < pl.rounds.size(); ++ri) {
             const Round &r = pl.rounds[ri];
             bool whole = r.kind != ISO_ROUND_DELIVER;
             if (!whole) {
-                const uint64_t m0 = s ? lay.size[0] : 0;              // blocks of whole 16-byte units
-                whole = m0 > 0 && m0 % 16 == 0 && !lay.slot_major && !c.mesh && r.entries.size() == s &&
-                        s <= kLdsEntries && s * (m0 / 16) <= kTileUnits && lay.recv_extent == s * m0;
-                for (size_t i = 0; whole && i < s; ++i)
-                    whole = lay.size[i] == m0 && lay.recv_displ[i] == i * m0 && r.entries[i].dst_slot == (int)i;
+                whole = rows_fit_a_tile() && r.entries.size() == s;
+                for (size_t i = 0; whole && i < s; ++i) whole = r.entries[i].dst_slot == (int)i;
             }
             if (whole) {
                 bound_rounds.push_back({r.kind, r.dim, (int)ri, &r});
@@ -986,16 +1103,16 @@ private:
         const bool deliver = r.kind == ISO_ROUND_DELIVER;
         // staged schedule, the rounds: all destinations are planes of the workspace; small equal blocks
         // are re-tiled through LDS (any round of that schedule whose blocks of one rank fit a tile)
-        const uint64_t st_upb = size0 / 16;
         // (a round between planes only is dense on both sides as it is: the plain kernel, plane after plane)
-        bool all_planes = pl.algorithm == ISO_ALG_COMBINED_STAGED && !deliver && uniform && !c.mesh;
+        const bool rows_later = pl.algorithm == ISO_ALG_COMBINED_STAGED || bound_rounds.back().kind == ISO_ROUND_DELIVER;
+        bool all_planes = rows_later && !deliver && uniform && !c.mesh;
         for (const HostEntry &he : ents)
             all_planes = all_planes && he.de.src_stride == size0 && he.de.dst_stride == size0;
-        const bool staged_round = pl.algorithm == ISO_ALG_COMBINED_STAGED && !deliver && !all_planes && uniform &&
-                                  size0 % 16 == 0 &&
-                                  !lay.slot_major && !c.mesh && r.kind != ISO_ROUND_VECTOR && done == 0 &&
-                                  ents.size() <= kLdsEntries && ents.size() * st_upb <= kTileUnits &&
-                                  p * st_upb <= kMaxUnits;
+        const uint64_t st_upb = (size0 + (uint64_t(1) << min_log2) - 1) >> min_log2;
+        const bool staged_round = rows_later && !deliver && !all_planes && uniform &&
+                                  (pl.algorithm != ISO_ALG_COMBINED_STAGED || retiled()) && !lay.slot_major && !c.mesh &&
+                                  r.kind != ISO_ROUND_VECTOR && done == 0 && ents.size() <= kLdsEntries &&
+                                  ents.size() * st_upb <= kTileUnits && p * st_upb <= kMaxUnits;
         if (deliver) {
             deliver_launch(pd, ents, k, total);
         } else if (staged_round) {
@@ -1022,6 +1139,11 @@ private:
         done += k;
         return ISO_SUCCESS;
     }
+
+    // Blocks that the staged schedule's rounds re-tile on their way from rows to planes: whole units at any size, others
+    // from 48 MiB on (a launch of the plain kernel -> re-tiled: 32^3, 200 B 188 -> 137 us, 64^3, 100 B 745 -> 584; 24^3,
+    // 100 B 33 -> 34).
+    bool retiled() const { return size0 % 16 == 0 || inf.delivered_bytes > kLastLevelCacheBytes * 3 / 16; }
 
     // Only an allgather's moves share sources.
     void describe_bytes(Launch &l, const HostEntry *ents, uint32_t k) const {
@@ -1090,6 +1212,13 @@ private:
         if (l.kernel == kStagedRoundKernel || l.kernel == kDeliverKernel) {
             const bool round = l.kernel == kStagedRoundKernel, whole = size0 % 64 == 0;
             if (!a2a) return 0;
+            // Blocks that are no whole units, and rows in one launch of the other schedules: 32^3, 100 B with streaming
+            // stores in the rounds 92 -> 78 us, 64^3, 72 B 585 -> 548; cached loads in them 24^3, 150 B 54 -> 48, 64^3,
+            // 40 B 305 -> 363; cached loads in the last launch 32^3, 100 B 85 -> 78, 64^3, 100 B 748 -> 824.
+            if (!staged || size0 % 16) {
+                if (round) return bytes <= kLastLevelCacheBytes / 4 ? kPlainStores : kStreamLoads | kPlainStores;
+                return bytes <= kLastLevelCacheBytes / 2 ? 0 : kStreamLoads;
+            }
             if (bytes > kLastLevelCacheBytes * 7 / 4 || (whole && size0 >= 128)) return kStreamLoads;
             if (bytes > kLastLevelCacheBytes / 2) return round ? 0 : kStreamLoads;
             if (bytes <= kLastLevelCacheBytes / (size0 < 32 ? 16 : size0 < 128 ? 8 : 6)) return kStreamLoads;
@@ -1124,18 +1253,31 @@ private:
         return bytes <= kLastLevelCacheBytes / 32 ? kPlainStores : kStreamLoads;
     }
 
-    // Staged schedule, last launch: every rank's receive row written in one piece.
+    // Every rank's receive row written in one piece.  Blocks of whole 16-byte units of the staged schedule keep the kernel
+    // that moves units (64^3, 16 B 107 us against 109 by bytes; from 32 B on the two are within 1 %).
     void deliver_launch(Pending &pd, const std::vector<HostEntry> &ents, uint32_t &k, uint64_t &total) {
         Launch &l = pd.l;
         l.kernel = kDeliverKernel;
         DeliverArgs &da = l.deliver;
-        const uint64_t upb = size0 / 16;
+        l.by_bytes = size0 % 16 != 0 || pl.algorithm != ISO_ALG_COMBINED_STAGED;
+        const uint64_t width = uint64_t(1) << min_log2, upb = (size0 + width - 1) / width;
         k = (uint32_t)s;
         da.p = (uint32_t)p;
         da.s = (uint32_t)s;
         da.upb = (uint32_t)upb;
         l.tile_units = s * upb <= kSmallTileUnits ? kSmallTileUnits : kTileUnits;
         da.ranks = (uint32_t)std::min<uint64_t>(p, l.tile_units / (s * upb));
+        if (l.by_bytes) {
+            const uint64_t row = s * size0;
+            while (da.ranks * row + 15 > l.tile_units * 16) --da.ranks;
+            // tiles that begin and end with whole sectors, as far as the rows allow it
+            for (uint32_t part = 64; part >= 16; part /= 2) {
+                const uint32_t whole = part / (uint32_t)std::gcd<uint64_t>(part, row);
+                if (da.ranks < whole || da.ranks == p) continue;
+                da.ranks -= da.ranks % whole;
+                break;
+            }
+        }
         da.dst = (uint64_t)(uintptr_t)recvbuf;
         while (prefixes.size() % 4) prefixes.push_back(0);            // 16-byte aligned entries
         pd.first_prefix = prefixes.size();
@@ -1150,12 +1292,13 @@ private:
             }
         da.rows = std::max(1u, da.k_rows * da.upb);
         da.plane = da.ranks * da.upb;
-        da.row = (uint32_t)(s * upb);
+        da.row = l.by_bytes ? (uint32_t)size0 : (uint32_t)(s * upb);
         put(da.upb, da.mul_upb, da.shifts, 0);
         put(da.rows, da.mul_rows, da.shifts, 1);
         put(da.plane, da.mul_plane, da.shifts, 2);
         put(da.row, da.mul_row, da.shifts, 3);
-        l.dyn_lds = (uint32_t)(s * ((uint64_t)da.ranks * da.upb + 1) * 16);
+        l.dyn_lds = l.by_bytes ? (uint32_t)((da.ranks * s * size0 + 31) & ~uint64_t(15))
+                               : (uint32_t)(s * ((uint64_t)da.ranks * da.upb + 1) * 16);
         total = ((p + da.ranks - 1) / da.ranks) * kThreads;      // set_grid: one workgroup per tile
     }
 
@@ -1166,7 +1309,9 @@ private:
         l.kernel = kStagedRoundKernel;
         k = (uint32_t)ents.size();
         StagedRoundArgs &sa = l.staged;
-        const uint64_t upb = size0 / 16;
+        const uint64_t width = uint64_t(1) << min_log2, upb = (size0 + width - 1) / width;
+        l.pull = (uint32_t)(upb * width - size0);
+        l.tail = l.pull != 0;
         // entries that read a rank-major buffer (rank stride larger than the block) first
         for (int rows = 1; rows >= 0; --rows)
             for (const HostEntry &he : ents)
@@ -1189,7 +1334,7 @@ private:
         put(sa.plane, sa.mul_plane, sa.shifts, 2);
         put(sa.inner, sa.mul_inner, sa.shifts, 3);
         put(sa.pj, sa.mul_pj, sa.more, 0);
-        l.dyn_lds = (uint32_t)(k * ((uint64_t)sa.ranks * sa.upb + 1) * 16);
+        l.dyn_lds = (uint32_t)(k * ((uint64_t)sa.ranks * sa.upb + 1) * width);
         total = ((p + sa.ranks - 1) / sa.ranks) * kThreads;      // set_grid: one workgroup per tile
     }
 

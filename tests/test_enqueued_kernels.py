@@ -178,6 +178,20 @@ def test_staged_rounds_between_planes_stream(stub_library):
     assert ("shift", 1) in got and all(policy == 1 for _, policy in got)
 
 
+@pytest.mark.parametrize("dims,offsets,m,alg,want", [
+    ((24, 24, 24), gen.moore(3, 1), 100, 0, ["staged_round_kernel"] * 2 + ["deliver_bytes_kernel"]), ((24, 24, 24), gen.moore(3, 1), 20, 0, ["shift_round_kernel"] * 3),
+    ((64, 64, 64), gen.moore(3, 1), 20, 0, ["staged_round_kernel"] * 2 + ["deliver_bytes_kernel"]), ((64, 64, 64), gen.moore(3, 1), 192, 0, ["shift_round_kernel"] * 3),
+    ((64, 64, 64), gen.moore(3, 1), 100, 1, ["staged_round_kernel"] * 2 + ["deliver_bytes_kernel"]), ((32, 32, 32), gen.moore(3, 1), 200, 1, ["shift_round_kernel"] * 3),
+    ((20, 20, 20), gen.moore(3, 2), 264, 0, ["shift_round_kernel"] * 3), ((100, 100), gen.moore(2, 1), 500, 0, ["staged_round_kernel", "deliver_bytes_kernel"]),
+    ((24, 24, 24), gen.von_neumann(3, 1), 100, 0, ["vector_round_kernel"]), ((24, 24, 24), gen.von_neumann(3, 1), 100, 1, ["shift_round_kernel"] * 3),
+    ((24, 24, 24), gen.von_neumann(3, 1), 300, 0, ["vector_round_kernel"]), ((250000,), gen.von_neumann(1, 1), 256, 0, ["shift_round_kernel"])])
+def test_alltoalls_that_write_rows_whole_or_all_at_once(stub_library, dims, offsets, m, alg, want):
+    names = _names(stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, alg, m))
+    assert names == want
+    listed = _names(stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, alg, m, by_rounds=True))
+    assert "deliver_bytes_kernel" not in listed and "vector_round_kernel" not in listed
+
+
 @pytest.mark.parametrize("op,m,want", [(iso.ISO_OP_ALLTOALL, 200, 0), (iso.ISO_OP_ALLTOALL, 100, 1), (iso.ISO_OP_ALLTOALL, 40, 2),
                                        (iso.ISO_OP_ALLGATHER, 40, 0)])
 def test_staged_schedule_on_the_general_kernels(stub_library, op, m, want):
