@@ -8,7 +8,6 @@
 #include <algorithm>
 #include <cstring>
 #include <initializer_list>
-#include <map>
 #include <memory>
 #include <numeric>
 #include <type_traits>
@@ -654,8 +653,16 @@ private:
     // 8.7 and 9.2 -> 12.3).  A schedule of one launch gains nothing (4096, 16 B 6.5 -> 6.9).  Near the limits many sets
     // lose what repeated ones gain (45^2 radius 1, 32 B 9.3 -> 7.2 and 9.3 -> 11.3): a persistent request finds its
     // blocks in the last-level cache again.
+    // Chains of several hops that fill 64 workgroups and more are spread over the chip, and the launches that they save
+    // are the longer ones: 12288 sectors for one workgroup, 192 Ki per launch saved (a launch per dimension -> chain, a
+    // few sets of buffers and 60 of them: 8^3, 124 neighbours, 64 B 10.1 -> 5.9 and 11.6 -> 7.0; 5^4, 80 neighbours, 64 B
+    // 10.7 -> 6.7 and 13 -> 9.2; 4^4, 80 neighbours, 200 B 14 -> 7.5 and 14.6 -> 9.8; 5 x 4 x 5 x 4 x 5, 31
+    // neighbours, 64 B 14.5 -> 13.2 and 16.6 -> 15.3; beyond it 8^4, 30 neighbours, 16 B 13.6 -> 15.2 and 14.8 -> 16.9; with fewer workgroups 32^2, 24 neighbours, 100 B 7.2 -> 9.3, 45^2,
+    // 32 B 6.5 -> 7.3 with many sets).
+    static constexpr size_t kChainHops = 1024;
     bool chain_launch(uint64_t launches) {
-        if (c.mesh || !uniform || !size0 || launches < 2 || p > kChainThreads * kChainUnitsPerLane || s > kChainHops ||
+        const size_t most_hops = arena ? kChainHopsByValue : kChainHops;
+        if (c.mesh || !uniform || !size0 || launches < 2 || p > kChainThreads * kChainUnitsPerLane || s > most_hops ||
             (size0 >> min_log2) > 0xFFFF)
             return false;
         std::vector<const HostEntry *> hops;             // chain after chain
@@ -663,7 +670,7 @@ private:
         if (op == ISO_OP_ALLTOALL) {
             size_t n_hops = 0;
             for (const std::vector<HostEntry> &round : rounds) n_hops += round.size();
-            if (n_hops > kChainHops) return false;
+            if (n_hops > most_hops) return false;
             hops.resize(n_hops);
             ends.resize(s + 1);
             for (const std::vector<HostEntry> &round : rounds)
@@ -675,21 +682,26 @@ private:
         } else {
             // Allgather: the way of every receive block from the send buffer down the trie.  Ways share moves, and
             // each makes them for itself; they write the same bytes, provided that no place is used twice.
-            std::map<uint64_t, const HostEntry *> written_by;
+            std::vector<std::pair<uint64_t, const HostEntry *>> written_by;      // in order of the places
             for (const std::vector<HostEntry> &round : rounds)
-                for (const HostEntry &he : round)
-                    if (!written_by.emplace(he.de.dst, &he).second) return false;
+                for (const HostEntry &he : round) written_by.emplace_back(he.de.dst, &he);
+            std::sort(written_by.begin(), written_by.end());
+            for (size_t q = 1; q < written_by.size(); ++q)
+                if (written_by[q].first == written_by[q - 1].first) return false;
+            const auto writer = [&](uint64_t place) -> const HostEntry * {
+                const auto at = std::lower_bound(written_by.begin(), written_by.end(), std::make_pair(place, (const HostEntry *)nullptr));
+                return at != written_by.end() && at->first == place ? at->second : nullptr;
+            };
             for (const auto &[dst, last] : written_by) {
                 if (last->dst_buf != ISO_BUF_RECV) continue;
                 const size_t start = hops.size();
-                hops.push_back(last);
-                for (auto at = written_by.find(last->de.src); at != written_by.end(); at = written_by.find(at->second->de.src))
-                    hops.push_back(at->second);
+                for (const HostEntry *at = last; at; at = writer(at->de.src)) hops.push_back(at);
+                if (hops.size() > most_hops) return false;
                 std::reverse(hops.begin() + (ptrdiff_t)start, hops.end());
                 ends.push_back((uint32_t)hops.size());
             }
         }
-        if (hops.empty() || hops.size() > kChainHops) return false;
+        if (hops.empty() || hops.size() > most_hops) return false;
         Pending pd;
         pd.first_entry = pd.first_prefix = 0;
         std::memset(&pd.l, 0, sizeof(pd.l));
@@ -720,21 +732,22 @@ private:
         put(ca.column, ca.mul_column, ca.more, 0);
         put(ca.groups, ca.mul_groups, ca.more, 1);
         ca.more |= launch_flags(0, false, (uint32_t)(ca.chunks * width - size0));
-        ChainHops &ch = args->hops;
+        std::vector<ChainHop> table_hops(hops.size());
         uint32_t begin = 0, n_chains = 0, longest = 0;
         for (const uint32_t end : ends) {
             n_chains += end != begin;
             begin = end;
         }
         begin = 0;
+        std::vector<uint32_t> begins(n_chains + 1);
         uint32_t chain = 0, later = n_chains;
         for (const uint32_t end : ends) {
             if (end == begin) continue;                          // no hops: an empty block
             longest = std::max(longest, end - begin);
-            ch.later[chain] = later - n_chains;
+            begins[chain] = later - n_chains;
             for (uint32_t at = begin; at < end; ++at) {
                 const HostEntry *he = hops[at];
-                ChainHop &hop = ch.hops[at == begin ? chain : later++];
+                ChainHop &hop = table_hops[at == begin ? chain : later++];
                 hop.src = he->de.src;
                 hop.dst = he->de.dst;
                 hop.src_stride = he->de.src_stride;
@@ -748,25 +761,30 @@ private:
             ++chain;
             begin = end;
         }
-        ch.later[n_chains] = later - n_chains;
+        begins[n_chains] = later - n_chains;
         ca.n_chains = n_chains;
+        ca.n_hops = (uint32_t)hops.size();
         l.grid = n_chains * ca.groups;
         const uint64_t piece = ca.column * width, own = p * ((piece + 63) / 64) * longest;
         uint64_t all = own * l.grid;
         if (longest > 1 && size0 > 32 && size0 % 64 && piece <= 64) all *= 2;
-        if (own > 6144 || all > (launches - 1) * 48 * 1024) return false;
+        const bool wide = l.grid >= 64 && longest > 1;
+        if (own > (wide ? 12288 : 6144) || all > (launches - 1) * (wide ? 192 : 48) * 1024) return false;
         l.threads = std::min<uint32_t>(kChainThreads, (ca.n_units + 63) & ~63u);
         l.dyn_lds = longest > 1 ? ca.n_units * (uint32_t)width : 0;
         describe_chain_bytes(l, hops);
         l.chain = ca;
+        const uint32_t *words = (const uint32_t *)table_hops.data();
+        const size_t n_words = table_hops.size() * sizeof(ChainHop) / 4;
         if (arena) {
+            std::copy(begins.begin(), begins.end(), std::copy(words, words + n_words, args->table));
             rq.chain = std::move(args);
             l.chain_by_value = rq.chain.get();
         } else {
             while (prefixes.size() % 4) prefixes.push_back(0);
             pd.first_prefix = prefixes.size();
-            const uint32_t *words = (const uint32_t *)&ch;
-            prefixes.insert(prefixes.end(), words, words + sizeof(ChainHops) / 4);
+            prefixes.insert(prefixes.end(), words, words + n_words);
+            prefixes.insert(prefixes.end(), begins.begin(), begins.end());
         }
         pending.push_back(pd);
         return true;
@@ -847,7 +865,7 @@ private:
         const uint64_t llc = kLastLevelCacheBytes, bytes = inf.delivered_bytes;
         if (op != ISO_OP_ALLTOALL || arena || !rows_fit_a_tile() || (size0 % 64 == 0 && size0 != 64) || size0 >= 512) return false;
         if (pl.algorithm == ISO_ALG_COMBINED_BYDIM) return bytes > llc * 7 / 4;
-        return pl.algorithm == ISO_ALG_COMBINED && bytes > (size0 < 32 || size0 == 64 ? llc * 3 / 16 : llc / 32);
+        return pl.algorithm == ISO_ALG_COMBINED && bytes > (size0 < 32 || size0 == 64 ? llc * 3 / 16 : inf.entries >= 3 * (int64_t)s ? llc / 16 : llc / 32);
     }
 
     // iso_start of ISO_ALG_COMBINED where every block makes its one move out of the send buffer (a star): the moves of
@@ -1665,7 +1683,7 @@ private:
         const uint32_t *dev_prefix = (const uint32_t *)(dev + entry_bytes + off_bytes);
         for (Pending &pd : pending) {
             if (pd.l.kernel == kChainKernel) {
-                pd.l.chain.table = (const ChainHops *)(dev_prefix + pd.first_prefix);
+                pd.l.chain.table = (const ChainHop *)(dev_prefix + pd.first_prefix);
             } else if (pd.l.kernel == kVectorKernel) {
                 pd.l.vec.entries = dev_entries + pd.first_entry;
                 pd.l.vec.dims = dev_dims;

@@ -1249,7 +1249,6 @@ __global__ __launch_bounds__(kThreads) void deliver_bytes_kernel(const DeliverAr
 // chain's own index (no look-up in front of it), and a hop takes what the hop before it has stored from LDS
 // instead of waiting for the store and loading it again.
 constexpr uint32_t kChainThreads = 1024, kChainUnitsPerLane = 4;
-constexpr uint32_t kChainHops = 72;
 struct ChainHop {
     uint64_t src, dst;                 // addresses of rank 0's blocks
     uint32_t src_stride, dst_stride;
@@ -1257,34 +1256,33 @@ struct ChainHop {
     uint32_t mul_inner, mul_pj, shifts;
 };
 static_assert(sizeof(ChainHop) == 48, "three 16-byte words");
-struct ChainHops {
-    ChainHop hops[kChainHops];         // the chains' first hops, then their others, chain after chain
-    uint32_t later[kChainHops + 4];    // [chains + 1] where those of each chain begin, counted behind the first ones
-};
+// In the table: the chains' first hops, then their others, chain after chain; then [chains + 1] words, where the others
+// of each chain begin, counted behind the first ones.
 struct ChainHead {
-    const ChainHops *table;
+    const ChainHop *table;
     uint32_t n_units;                  // p * column
     uint32_t chunks, column, groups;   // units of a block, of a workgroup's column; columns of a block
-    uint32_t n_chains;
+    uint32_t n_chains, n_hops;
     uint32_t mul_column, mul_groups;
     uint32_t more;                     // shifts of column, groups; launch_flags
 };
 static_assert(sizeof(ChainHead) <= kCheapArguments, "launch cost");
 // The allocation-free call has no table and passes the hops with the launch (3.5 KiB; a launch that writes a table
 // first costs more: 8 x 8 x 8, 26 neighbours, 64 B 13 -> 11 us).
+constexpr uint32_t kChainHopsByValue = 72;
 struct ChainArgs {
     ChainHead head;
-    ChainHops hops;
+    uint32_t table[kChainHopsByValue * sizeof(ChainHop) / 4 + kChainHopsByValue + 1];
 };
-static_assert(sizeof(ChainArgs) <= 4096 && sizeof(ChainHops) % 4 == 0, "kernel arguments, table words");
+static_assert(sizeof(ChainArgs) <= 4096 && offsetof(ChainArgs, table) % 16 == 0, "kernel arguments");
 
-typedef const ChainHops __attribute__((address_space(4))) *chain_hops_ptr;
+typedef const ChainHop __attribute__((address_space(4))) *chain_hops_ptr;
 __device__ __forceinline__ const ChainHead &chain_head(const ChainHead &a) { return a; }
 __device__ __forceinline__ const ChainHead &chain_head(const ChainArgs &a) { return a.head; }
 __device__ __forceinline__ chain_hops_ptr chain_hops(const ChainHead &a) { return (chain_hops_ptr)(uintptr_t)a.table; }
 __device__ __forceinline__ chain_hops_ptr chain_hops(const ChainArgs &) {
     typedef const char __attribute__((address_space(4))) *bytes_ptr;
-    return (chain_hops_ptr)((bytes_ptr)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(ChainArgs, hops));
+    return (chain_hops_ptr)((bytes_ptr)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(ChainArgs, table));
 }
 
 // Synchronises the workgroup on LDS only: stores to global memory stay in flight.
@@ -1300,10 +1298,10 @@ struct HopNow {
     uint32_t src_stride, dst_stride, shift, back, wrap;
     FastDiv d_inner, d_pj;
     __device__ __forceinline__ HopNow(chain_hops_ptr table, uint32_t h)
-        : src(table->hops[h].src), dst(table->hops[h].dst), src_stride(table->hops[h].src_stride),
-          dst_stride(table->hops[h].dst_stride), shift(table->hops[h].shift),
-          d_inner(fastdiv_of(table->hops[h].mul_inner, table->hops[h].inner, table->hops[h].shifts, 0)),
-          d_pj(fastdiv_of(table->hops[h].mul_pj, table->hops[h].pj, table->hops[h].shifts, 1)) {
+        : src(table[h].src), dst(table[h].dst), src_stride(table[h].src_stride),
+          dst_stride(table[h].dst_stride), shift(table[h].shift),
+          d_inner(fastdiv_of(table[h].mul_inner, table[h].inner, table[h].shifts, 0)),
+          d_pj(fastdiv_of(table[h].mul_pj, table[h].pj, table[h].shifts, 1)) {
         asm volatile("" ::"s"(src), "s"(dst), "s"(src_stride), "s"(dst_stride), "s"(shift), "s"(d_inner.div), "s"(d_inner.mul),
                      "s"(d_pj.div), "s"(d_pj.mul));
         back = shift * d_inner.div;
@@ -1357,8 +1355,10 @@ __global__ __launch_bounds__(kChainThreads) void chain_kernel(const ARGS from) {
             if (has[it]) *(dst_ptr)(block_address(h.dst, rank[it], h.dst_stride) + off[it]) = v[it];
     };
     // on their way while the blocks are
-    uint32_t at = a.n_chains + table->later[chain];
-    const uint32_t end = a.n_chains + table->later[chain + 1];
+    typedef const uint32_t __attribute__((address_space(4))) *const_word_ptr;
+    const const_word_ptr later = (const_word_ptr)(table + a.n_hops);
+    uint32_t at = a.n_chains + later[chain];
+    const uint32_t end = a.n_chains + later[chain + 1];
     HopNow next(table, at < end ? at : chain);
     // (waited for here, not behind the first stop: that wait would be for its stores as well)
     __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0)

@@ -85,6 +85,17 @@ def test_small_collectives_take_one_launch_where_it_saves_enough(stub_library, d
         assert names == ["chain_kernel"] if chained else (len(names) == kernels and "chain_kernel" not in names), (alg, names)
 
 
+@pytest.mark.parametrize("dims,offsets,m,kernels", [
+    ((8, 8, 8), gen.moore(3, 2), 64, 1), ((11, 11, 11), gen.moore(3, 2), 64, 3), ((4, 4, 4, 4), gen.moore(4, 1), 200, 1), ((4, 4, 4, 4), gen.moore(4, 1), 600, 4),
+    ((7, 7, 7, 7), gen.random_distinct(4, -3, 3, 30, 5), 16, 4), ((8, 8, 8, 8), gen.random_distinct(4, -3, 3, 30, 5), 16, 4), ((2, 2, 2, 2, 2), gen.moore(5, 2), 16, 6)])
+def test_many_chains_fill_the_chip_with_more(stub_library, dims, offsets, m, kernels):
+    """Chains of several hops in 64 workgroups and more go further; the allocation-free call carries 72 hops at most."""
+    names = _names(stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED, m))
+    assert len(names) == kernels and ("chain_kernel" in names) == (kernels == 1), names
+    if kernels == 1:
+        assert "chain_kernel" not in _noalloc(stub_library, dims, offsets, m, iso.ISO_ALG_COMBINED)
+
+
 @pytest.mark.parametrize("dims,offsets,m,width", [((5, 4, 7, 6, 4), gen.von_neumann(5, 1), 6, "unsigned short, false"),
                                                   ((13, 14, 15), gen.von_neumann(3, 1), 5, "unsigned char, false"),
                                                   ((46, 47), gen.von_neumann(2, 1), 3, "unsigned char, false"),

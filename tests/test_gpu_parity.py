@@ -500,7 +500,8 @@ def test_large_blocks_are_taken_in_groups_of_ranks(dims, m, alg):
     ((5, 4, 7, 6, 4), gen.von_neumann(5, 1), 6), ((13, 14, 15), gen.von_neumann(3, 1), 5), ((46, 47), gen.von_neumann(2, 1), 3),
     ((4096, 1), [(1, 0), (-1, 0), (2, 0)], 3), ((16, 8, 8, 4), [(1, 1, 1, 1), (3, 2, 1, 0), (0, 0, 0, 0)], 20),
     ((32, 32), gen.moore(2, 1), 16), ((5, 5, 41), gen.von_neumann(3, 1), 16), ((8, 8, 16), [(1, 1, 1), (2, 3, 5), (1, 1, 1)], 17),
-    ((9, 9, 9), gen.moore(3, 1), 37), ((2,) * 10, [tuple(int(b) for b in f"{v:010b}") for v in (1, 3, 7, 1023, 512, 682)], 24)])
+    ((8, 8, 8), gen.moore(3, 2), 16), ((4, 4, 4, 4), gen.moore(4, 1), 100), ((5, 4, 5, 4, 5), gen.positive_octant(5, 1), 33),
+    ((4, 4, 4, 4, 4), gen.random_distinct(5, -3, 3, 40, 5), 24), ((9, 9, 9), gen.moore(3, 1), 37), ((2,) * 10, [tuple(int(b) for b in f"{v:010b}") for v in (1, 3, 7, 1023, 512, 682)], 24)])
 def test_stops_of_a_collective_in_one_launch(dims, offsets, m):
     """Chains of up to ten hops (stops written twice) on both sides of one unit per lane, last units that overlap, a
     single unit of every rank to a workgroup, and more starts than one over the same buffers."""
