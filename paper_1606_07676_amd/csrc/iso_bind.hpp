@@ -863,7 +863,9 @@ private:
     // of the last-level cache (above: 64^3, 100 B 1119 -> 800; 8^5, 40 neighbours, 400 B 1045 -> 1063).
     bool rows_in_one_launch() const {
         const uint64_t llc = kLastLevelCacheBytes, bytes = inf.delivered_bytes;
-        if (op != ISO_OP_ALLTOALL || arena || !rows_fit_a_tile() || (size0 % 64 == 0 && size0 != 64) || size0 >= 512) return false;
+        if (op != ISO_OP_ALLTOALL || arena || !rows_fit_a_tile() || (size0 % 64 == 0 && size0 != 64) || size0 >= 512 ||
+            s * size0 + 15 > kTileUnits * 16)
+            return false;
         if (pl.algorithm == ISO_ALG_COMBINED_BYDIM) return bytes > llc * 7 / 4;
         return pl.algorithm == ISO_ALG_COMBINED && bytes > (size0 < 32 || size0 == 64 ? llc * 3 / 16 : inf.entries >= 3 * (int64_t)s ? llc / 16 : llc / 32);
     }
@@ -1283,10 +1285,11 @@ private:
         da.p = (uint32_t)p;
         da.s = (uint32_t)s;
         da.upb = (uint32_t)upb;
-        l.tile_units = s * upb <= kSmallTileUnits ? kSmallTileUnits : kTileUnits;
+        // at least one row has to fit, by bytes at any alignment of the receive buffer (rows_fit_a_tile)
+        const uint64_t row = s * size0, row_units = std::max<uint64_t>(s * upb, l.by_bytes ? (row + 30) / 16 : 0);
+        l.tile_units = row_units <= kSmallTileUnits ? kSmallTileUnits : kTileUnits;
         da.ranks = (uint32_t)std::min<uint64_t>(p, l.tile_units / (s * upb));
         if (l.by_bytes) {
-            const uint64_t row = s * size0;
             while (da.ranks * row + 15 > l.tile_units * 16) --da.ranks;
             // tiles that begin and end with whole sectors, as far as the rows allow it
             for (uint32_t part = 64; part >= 16; part /= 2) {

@@ -203,6 +203,15 @@ def test_alltoalls_that_write_rows_whole_or_all_at_once(stub_library, dims, offs
     assert "deliver_bytes_kernel" not in listed and "vector_round_kernel" not in listed
 
 
+@pytest.mark.parametrize("s,m,small", [(4, 4095, False), (8, 2047, False), (1, 16383, False), (1, 16369, True), (4, 4092, True), (16, 1023, True)])
+def test_rows_next_to_a_small_tile(stub_library, s, m, small):
+    """A tile by bytes holds up to 15 bytes more than the rows: the alignment of the receive buffer."""
+    for op in (iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER):
+        kernels = stub_library.start((64, 65), [(i + 1, 1) for i in range(s)], op, iso.ISO_ALG_COMBINED_STAGED, m)
+        (last,) = [k for k in kernels if k.startswith("deliver_bytes_kernel")]
+        assert last.endswith("4u>" if small else "8u>"), kernels
+
+
 @pytest.mark.parametrize("op,m,want", [(iso.ISO_OP_ALLTOALL, 200, 0), (iso.ISO_OP_ALLTOALL, 100, 1), (iso.ISO_OP_ALLTOALL, 40, 2),
                                        (iso.ISO_OP_ALLGATHER, 40, 0)])
 def test_staged_schedule_on_the_general_kernels(stub_library, op, m, want):

@@ -35,11 +35,11 @@ def _received(dims, offsets, op, alg, m, send, shift=0, layout=iso.ISO_LAYOUT_RA
 @pytest.mark.parametrize("dims,offsets", [((5, 4, 7), gen.moore(3, 1)), ((37, 11), gen.von_neumann(2, 2)), ((13, 11, 6), gen.random_distinct(3, -3, 3, 20, 5)),
                                           ((2, 3), [(0, 0), (1, 1), (1, 1), (0, 2)]), ((1,), [(0,)]), ((259,), gen.von_neumann(1, 1))])
 def test_rows_of_any_block_size(dims, offsets, op):
-    """Blocks shorter than a unit, one byte either side of whole units, rows up to the tile's 32 KiB and just beyond it,
-    fewer ranks than a tile takes, and receive buffers at odd addresses."""
+    """Blocks shorter than a unit, one byte either side of whole units, rows up to the small tile's 16 KiB, up to the
+    large one's 32 KiB and just beyond it, fewer ranks than a tile takes, and receive buffers at odd addresses."""
     p, s = int(np.prod(dims)), len(offsets)
-    fits = (2048 * 16 - 15) // s
-    for m in (1, 2, 3, 7, 9, 15, 17, 31, 33, 100, 257, fits - 1, fits, fits + 1):
+    small, fits = (1024 * 16 - 1) // s, (2048 * 16 - 15) // s
+    for m in (1, 2, 3, 7, 9, 15, 17, 31, 33, 100, 257, small, fits - 1, fits, fits + 1):
         send_h = gen.alltoall_send(5, p, s, m) if op == iso.ISO_OP_ALLTOALL else gen.allgather_send(5, p, m)
         want = (orc.alltoall if op == iso.ISO_OP_ALLTOALL else orc.allgather)(dims, offsets, send_h).reshape(-1)
         send = torch.from_numpy(send_h).to(DEV)
