@@ -31,6 +31,7 @@ struct iso_comm_s {
     // all-to-all schedules for iso_neighbor_alltoall_noalloc, by algorithm: built by the first call that asks for one,
     // since that call leaves nothing else behind to keep it in (see there)
     std::unique_ptr<const iso::Plan> alltoall_plans[ISO_ALG_COMBINED_STAGED + 1];
+    std::mutex alltoall_plans_mutex;     // threads that drive a GPU each may share a neighbourhood
 };
 
 struct iso_plan_s {
@@ -142,6 +143,7 @@ int make_request(int op, const iso::Layout &lay, const void *sendbuf, void *recv
 // The handle's all-to-all schedule of `algorithm`, for the call that binds it anew every time.
 int alltoall_plan(iso_comm_t comm, int algorithm, const iso::Plan **out) {
     const bool known = algorithm >= 0 && algorithm < (int)(sizeof(comm->alltoall_plans) / sizeof(comm->alltoall_plans[0]));
+    std::lock_guard<std::mutex> lock(comm->alltoall_plans_mutex);
     if (!known || !comm->alltoall_plans[algorithm]) {
         auto plan = std::make_unique<iso::Plan>();
         const int st = iso::build_plan(comm->c, ISO_OP_ALLTOALL, algorithm, *plan);
