@@ -41,11 +41,12 @@ struct Launch {
     uint32_t grid;
     bool lds_table;
     bool mesh;
-    int policy;            // kStreamLoads, kPlainStores (see cache_policy)
+    int policy;            // kStreamLoads, kPlainStores, kBySize (see cache_policy)
     bool tail;             // regular kernels: the last unit of a block overlaps the one before it
     bool uniform_waves;    // shift kernel, 16-byte units, blocks a multiple of 64 units: one block per wavefront
     bool eighths;          // one contiguous eighth of the tiles per XCD, whatever page_resonant says
     int vector_dims;       // vector kernel: dimensions its VectorEntry records hold (0: the general tables)
+    bool small_and_large;  // block kernel: blocks on both sides of kSmallUnits in the launch
     bool block_groups;     // block kernel: ranks taken in groups of kBlockGroup
     int round;             // the plan's round this launch belongs to (a large round is split over several launches)
     uint32_t dyn_lds;      // bytes of dynamic LDS (the kernels of the staged schedule: their tile)
@@ -303,6 +304,9 @@ KernelRef select_block(const Launch &l) {
         if (l.block_groups) return {(const void *)&block_round_kernel<LDS, MESH, pol(), true>, &l.block};
         return {(const void *)&block_round_kernel<LDS, MESH, pol()>, &l.block};
     };
+    if constexpr (!MESH) {
+        if (l.policy == kBySize) return form(std::integral_constant<int, kBySize>());
+    }
     if (l.policy == kStreamLoads) return form(std::integral_constant<int, kStreamLoads>());
     if (l.policy == kPlainStores) return form(std::integral_constant<int, kPlainStores>());
     return form(std::integral_constant<int, 0>());
@@ -1221,7 +1225,11 @@ private:
     //   not in the staged schedule).  Plain stores up to a quarter of the cache for rank-major blocks of less than
     //   two sectors and unequal or single units (stencils 64^3, 4 B 151 -> 119 and 173 -> 152; 48^3, 9 B 89 -> 83 and
     //   116 -> 112; larger blocks: 24^3, 20 B 31 -> 28.5 and 40 -> 41; 20^3, 25 B 27 -> 25 and 34 -> 36.5; slot-major
-    //   24^3, 16 B 16 -> 17.5 and 22 -> 25).
+    //   24^3, 16 B 16 -> 17.5 and 22 -> 25).  Blocks up to 128 bytes and larger ones in one launch, from a quarter of the
+    //   cache on: by size (cached loads, streaming stores for all -> by size, stencils: 32^3, 64 B 351 -> 337 and 351 ->
+    //   337; 64^3, 16 B 418 -> 374; 60 x 50 x 41, 25 B 323 -> 308; 16^4, 4 B 176 -> 167; 7^5, 4 B 286 -> 261; 16^3, 64 B
+    //   56.4 -> 55.8 and 56.4 -> 55.6; under it 24^3, 25 B 45.2 -> 46.8 and 47.6 -> 47.3, 16^3, 16 B 13.4 -> 14.8 and
+    //   16.2 -> 15.9; the staged schedule 32^3, 64 B 348 -> 354).
     //   The s-exchange writes whole rows and is indifferent to the stores; streaming loads where the send buffer of
     //   an all-to-all exceeds the cache (805 MB -4.6 %, 5.4 GB -3.8 %; 218 MB +17 %, an allgather +60 %) and no two
     //   blocks of a rank-major row share a 128-byte line (64 B +9 %, 100 B +7 %, 300 B +9 %).
@@ -1252,6 +1260,7 @@ private:
         if (l.kernel == kBlockKernel) {
             if (inf.block_bytes < 128 && l.block.equal_units <= 1 && !lay.slot_major && bytes <= kLastLevelCacheBytes / 4)
                 return kPlainStores;
+            if (a2a && !staged && !c.mesh && !lay.slot_major && l.small_and_large && bytes > kLastLevelCacheBytes / 4) return kBySize;
             const bool cached = bytes > kLastLevelCacheBytes / 16 && bytes <= kLastLevelCacheBytes && !staged;
             return a2a && l.block.equal_units && !cached ? kStreamLoads : 0;
         }
@@ -1611,6 +1620,9 @@ private:
         b.equal_units = ents[done].de.units;
         for (uint32_t q = 1; q < k; ++q)
             if (ents[done + q].de.units != b.equal_units) b.equal_units = 0;
+        const auto is_small = [](const HostEntry &he) { return he.de.units <= kSmallUnits; };
+        const auto n_small = std::count_if(ents.begin() + (ptrdiff_t)done, ents.begin() + (ptrdiff_t)(done + k), is_small);
+        l.small_and_large = n_small > 0 && n_small < (ptrdiff_t)k;
         b.plane = b.equal_units ? (uint32_t)(p * b.equal_units) : 1u;
         b.row = (uint32_t)row_units;
         // shift rounds on rank-major buffers: ranks in groups (not the staged schedule, whose tiny

@@ -181,6 +181,10 @@ struct Unaligned {
 
 // Cache policy of the accesses of a launch (see cache_policy in iso_bind.hpp for when each is taken).
 constexpr int kStreamLoads = 1, kPlainStores = 2;
+// Block kernel: every block by its own size.  Blocks of up to kSmallUnits units share sectors and lines with others of
+// their row: cached loads, plain stores that meet in the L2.  The larger ones stream both.
+constexpr int kBySize = 4;
+constexpr uint32_t kSmallUnits = 8;
 
 // The unit at byte offset `off` of the block at byte address `src` to the same offset of the
 // block at `dst`, both in global memory (the address space is spelled out so that the accesses
@@ -879,7 +883,22 @@ __global__ __launch_bounds__(kThreads) void block_round_kernel(const BlockArgs a
     const uint64_t src = block_address(en.src, srcR, en.src_stride);
     const uint64_t dst = block_address(en.dst, R, en.dst_stride);
     switch (en.meta & 0xFFu) {
-        case 4: move_unit<vec16_t, POLICY>(dst, src, unit_offset<vec16_t>(ch, en.last_offset)); break;
+        case 4:
+            if constexpr (POLICY & kBySize) {
+                const uint64_t off = unit_offset<vec16_t>(ch, en.last_offset);
+                // (the compiler joins two moves that differ in their cache policy only, and drops the policy: 32^3
+                // stencil, 64 B 407 us; what is between these two lines stays as it is)
+                if (en.units > kSmallUnits) {
+                    asm volatile("; large block" ::: "memory");
+                    move_unit<vec16_t, kStreamLoads>(dst, src, off);
+                    asm volatile("; large block done" ::: "memory");
+                } else {
+                    move_unit<vec16_t, kPlainStores>(dst, src, off);
+                }
+            } else {
+                move_unit<vec16_t, POLICY>(dst, src, unit_offset<vec16_t>(ch, en.last_offset));
+            }
+            break;
         case 3: move_unit<vec8_t, 0>(dst, src, unit_offset<vec8_t>(ch, en.last_offset)); break;
         case 2: move_unit<uint32_t, 0>(dst, src, unit_offset<uint32_t>(ch, en.last_offset)); break;
         case 1: move_unit<uint16_t, 0>(dst, src, unit_offset<uint16_t>(ch, en.last_offset)); break;

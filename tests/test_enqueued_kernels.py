@@ -106,7 +106,8 @@ def test_columns_of_one_unit_take_units_that_divide_the_block(stub_library, dims
         assert kernel.startswith(f"chain_kernel<{width}"), kernel
 
 
-# cache policies: 0 cached loads, streaming stores; 1 streaming both; 2 cached, plain stores; 3 streaming loads, plain stores
+# cache policies: 0 cached loads, streaming stores; 1 streaming both; 2 cached, plain stores; 3 streaming loads, plain stores;
+# 4 by the block's size
 POLICY_ARGUMENT = {"shift_round_kernel": 2, "mesh_shift_round_kernel": 2, "shift_round_uniform_kernel": 0,
                    "staged_round_kernel": 1, "deliver_kernel": 1, "block_round_kernel": 2, "vector_round_kernel": 3,
                    "vector_round_uniform_kernel": 1}
@@ -232,6 +233,16 @@ def test_rounds_of_unequal_blocks(stub_library, dims, sizes, periodic, want):
     """Streaming loads where all blocks have the same number of units, plain stores for small blocks near the cache."""
     got = _policies(stub_library.start_unequal(dims, gen.moore(3, 1), iso.ISO_ALG_COMBINED_BYDIM, list(sizes), periodic))
     assert got == {("block", want)}
+
+
+@pytest.mark.parametrize("dims,edge,periodic,alg,want", [
+    ((32, 32, 32), 64, None, 0, True), ((32, 32, 32), 64, None, 1, True), ((32, 32, 32), 64, None, 5, False), ((32, 32, 32), 64, (0, 0, 0), 0, False),
+    ((24, 24, 24), 25, None, 0, False), ((32, 32, 32), 25, None, 0, True), ((64, 64, 64), 11, None, 0, False), ((64, 64, 64), 12, None, 0, True)])
+def test_small_and_large_blocks_by_their_size(stub_library, dims, edge, periodic, alg, want):
+    """Blocks of up to 128 bytes and larger ones in one launch, a quarter of the cache and more; 11 x 11 is not larger."""
+    sizes = list(gen.stencil_block_sizes(gen.moore(3, 1), edge))
+    got = _policies(stub_library.start_unequal(dims, gen.moore(3, 1), alg, sizes, periodic))
+    assert (("block", 4) in got) == want, got
 
 
 @pytest.mark.parametrize("dims,offsets,m,layout,push", [

@@ -159,3 +159,25 @@ def test_small_collective_in_one_launch(case, op, layout, alg):
 def test_staged_schedule_by_what_the_last_level_cache_holds(dims, m, op):
     """17, 162, 270 and 496 MB of blocks."""
     check_exchange(dims, gen.moore(3, 1), op, iso.ISO_ALG_COMBINED_STAGED, m, iso.ISO_LAYOUT_RANK_MAJOR, recv_off=16)
+
+
+@pytest.mark.parametrize("dims,edge,align", [((32, 32, 32), 25, 16), ((21, 20, 19), 51, 1), ((64, 63, 65), 12, 1), ((16, 17, 16, 17), 6, 4)])
+def test_small_and_large_blocks_by_their_size(dims, edge, align):
+    """Blocks of up to 128 bytes and larger ones together in rounds of 64 MiB and more, against the straightforward exchange."""
+    offsets = gen.moore(len(dims), 1)
+    p, sizes = int(np.prod(dims)), list(gen.stencil_block_sizes(offsets, edge))
+    displs, row = gen.packed_displacements(sizes, align)
+    assert p * sum(sizes) > 64 << 20
+    comm = iso.iso_neighborhood_create(dims, offsets)
+    send = torch.randint(0, 256, (p * row,), dtype=torch.uint8, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(8))
+    got = []
+    for alg in (iso.ISO_ALG_SX_FUSED, iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM):
+        recv = torch.full((p * row,), 0xEE, dtype=torch.uint8, device="cuda:0")
+        work = torch.empty(max(1, iso.iso_workspace_bytes_v(comm, iso.ISO_OP_ALLTOALL, alg, sizes)), dtype=torch.uint8, device="cuda:0")
+        req = iso.iso_neighbor_alltoallv_init(send, sizes, displs, row, recv, sizes, displs, row, work, comm, alg)
+        for _ in range(2):
+            iso.iso_start(req)
+        iso.iso_wait(req)
+        iso.iso_request_free(req)
+        got.append(recv)
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
