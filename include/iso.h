@@ -415,8 +415,10 @@ int iso_request_free(iso_request_t *req);
  * by small kernels that carry it in their arguments, ordered on the stream
  * before the rounds.  No hipMalloc, hipFree, host-to-device copy or other
  * allocating routine is called.
- * Limits: the table (48 bytes per block-move per rank, plus 4*s*d) must fit
- * ISO_NOALLOC_TABLE_BYTES and iso_workspace_bytes() the rest of the array,
+ * Limits: the table must fit ISO_NOALLOC_TABLE_BYTES (48 bytes per block-move
+ * per rank, plus 4*s*d; on a mesh also a bit per 256 units of at most 16 bytes
+ * that a launch moves, in whole words, or 8 bytes per block-move of the
+ * straightforward exchange) and iso_workspace_bytes() the rest of the array,
  * else ISO_ERR_SCRATCH and nothing is enqueued.
  * All calls on one GPU share that GPU's array, which keeps the previous call's
  * contents (nothing in it needs to start at zero: every block of the

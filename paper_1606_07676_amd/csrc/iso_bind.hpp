@@ -562,6 +562,7 @@ public:
         if (st != ISO_SUCCESS || inf.delivered_bytes == 0) return st;       // nothing to move: no launches
         rounds_as_launched();
         if ((st = host_entries()) != ISO_SUCCESS) return st;
+        bits_by_wave = !arena || wave_bits_cost_no_launch();
         const bool merges = pl.algorithm == ISO_ALG_COMBINED;
         const bool chains = merges || pl.algorithm == ISO_ALG_COMBINED_BYDIM || pl.algorithm == ISO_ALG_COMBINED_STAGED;
         const uint64_t launches = launches_of_rounds(merges);
@@ -613,6 +614,7 @@ private:
     bool uniform = true;                          // all these entries have `size0` bytes
     uint64_t size0 = 0;
     uint32_t min_log2 = 4;                        // the narrowest unit width among them
+    bool bits_by_wave = true;                     // mesh: interior bits by the wavefront where that is the better one
 
     std::vector<DevEntry> table;
     std::vector<uint32_t> prefixes;               // what launches read besides their entries (see upload)
@@ -947,6 +949,23 @@ private:
         }
         return rounds_cost < merged_cost;
     }
+
+    // In the allocation-free call the bitmaps of a mesh lie in its table and reach it 3 KiB a launch.  By the wavefront
+    // they are four times as large: only where all of them go in the one launch that bits by the tile take as well, and
+    // fit behind the entries (64^3, 6 neighbours, 256 B would be 10 of these launches instead of 6, and 400^3 refused).
+    bool wave_bits_cost_no_launch() const {
+        const uint64_t chunks = (size0 + (uint64_t(1) << min_log2) - 1) >> min_log2;
+        uint64_t words = 0, entries = 0;
+        for (const std::vector<HostEntry> &ents : rounds) {
+            words += (p * chunks * ents.size() >> (kWaveLog2 + 5)) + 1;
+            entries += ents.size();
+        }
+        return words <= kStoreWords &&
+               entries * sizeof(DevEntry) + residue_bytes() + words * sizeof(uint32_t) <= arena->table_bytes;
+    }
+
+    // the [s][d] residues in the table; what follows them is 16-byte aligned
+    size_t residue_bytes() const { return (c.can.size() * sizeof(uint32_t) + 15) & ~size_t(15); }
 
     uint32_t periodic_mask() const {
         uint32_t mask = 0;
@@ -1426,7 +1445,8 @@ private:
             put(ma.inner, ma.mul_inner, ma.shifts, 2);
             put(ma.pj, ma.mul_pj, ma.shifts, 3);
             put(ma.p, ma.mul_p, ma.more, 0);
-            const uint32_t group_log2 = interior_group_log2(c, lay.slot_major, ents.data() + done, k, chunks);
+            const uint32_t group_log2 =
+                bits_by_wave ? interior_group_log2(c, lay.slot_major, ents.data() + done, k, chunks) : kTileLog2;
             const std::vector<uint32_t> bits =
                 mesh_interior_units(c, lay.slot_major, ents.data() + done, k, group_log2, total, chunks, p);
             ma.torus |= (uint32_t)(group_log2 == kTileLog2) << 11;
@@ -1652,7 +1672,7 @@ private:
     // neighbours, 64 B 13.5 -> 10.7 us).
     int upload() {
         const size_t entry_bytes = table.size() * sizeof(DevEntry);
-        const size_t c_bytes = (c.can.size() * sizeof(uint32_t) + 15) & ~size_t(15);     // what follows: 16-byte aligned
+        const size_t c_bytes = residue_bytes();
         const size_t off_bytes = sizeof(TorusDims) + c_bytes;
         bool reads_residues = false;
         for (const Pending &pd : pending)

@@ -66,6 +66,18 @@ def test_allocation_free_call_refuses_the_tables_it_always_refused(stub_library)
     assert e.value.status == iso.ISO_ERR_SCRATCH
 
 
+@pytest.mark.parametrize("dims,offsets,m,stores,rounds", [
+    ((1200000, 64), [(0, 1), (0, -1)], 1, 27, 1), ((400, 400, 400), gen.von_neumann(3, 1), 1, 64, 3),
+    ((64, 64, 64), gen.von_neumann(3, 1), 256, 6, 3), ((64, 64, 64), gen.von_neumann(3, 1), 64, 3, 3),
+    ((262144, 16), gen.von_neumann(2, 1), 16, 5, 2), ((12, 12, 12), gen.moore(3, 1), 40, 3, 3)])
+def test_allocation_free_call_on_boxes_stores_bitmaps_by_the_tile(stub_library, dims, offsets, m, stores, rounds):
+    """The bitmaps of a mesh share the table with the entries and the residues, and every 3 KiB of it is a launch: as many
+    as with a bit per tile of 256 units, and none refused that fits so."""
+    for alg in (iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM):
+        names = _noalloc(stub_library, dims, offsets, m, alg, (0,) * len(dims))
+        assert names == stores * ["table_store_kernel"] + rounds * ["mesh_shift_round_kernel"], (alg, len(names))
+
+
 @pytest.mark.parametrize("op", [iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER])
 @pytest.mark.parametrize("dims,offsets,m,kernels", [
     ((8, 8), gen.moore(2, 1), 64, 1), ((8, 8, 8), gen.moore(3, 1), 64, 1), ((32, 32), gen.von_neumann(2, 2), 64, 1),

@@ -113,3 +113,19 @@ def test_noalloc_limits_and_errors():
     assert e.value.status == iso.ISO_ERR_OVERLAP
     # empty collectives are a successful no-op
     iso.iso_neighbor_alltoall_noalloc(send, recv, 0, big, iso.ISO_ALG_COMBINED)
+
+
+@pytest.mark.parametrize("dims,offsets,m", [((12, 11, 10), gen.moore(3, 1), 40), ((64, 65, 63), gen.von_neumann(3, 1), 256),
+                                            ((4097, 16), [(0, 1), (1, 0), (-1, -2)], 300), ((700,), [(3,), (-2,), (0,)], 9)])
+def test_noalloc_on_boxes(dims, offsets, m):
+    """Interior bits by the wavefront and, where that would be a launch more, by the tile: as the persistent request, and
+    receive blocks without a source keep their content."""
+    p, s = int(np.prod(dims)), len(offsets)
+    send = torch.randint(0, 256, (p, s, m), dtype=torch.uint8, device=DEV, generator=torch.Generator(DEV).manual_seed(6))
+    for periodic in ((False,) * len(dims), (True,) + (False,) * (len(dims) - 1)):
+        comm = iso.iso_neighborhood_create_mesh(dims, periodic, offsets)
+        for alg in (iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM):
+            want = _persistent(comm, send, p, s, m, alg)
+            recv = torch.full((p, s, m), 0xEE, dtype=torch.uint8, device=DEV)
+            iso.iso_neighbor_alltoall_noalloc(send, recv, m, comm, alg)
+            assert torch.equal(recv, want), (dims, periodic, alg)
