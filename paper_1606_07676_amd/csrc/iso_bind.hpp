@@ -63,7 +63,7 @@ struct Launch {
     const ChainArgs *chain_by_value;      // or BoundRequest::chain, where there is no table
     uint32_t chain_width;  // its unit width, where not the request's
     uint32_t n_tiles, run_log2;           // see TileMap
-    uint32_t outside_tiles;               // mesh: tiles not interior to all entries (see rounds_move_faster)
+    uint64_t outside_units;               // mesh: units of wavefronts or tiles not marked interior (see rounds_move_faster)
     bool entry_major, vector_round;       // see launch_flags
     uint32_t pull;
     uint64_t bytes_read, bytes_written;   // of blocks (see iso_start_info_t)
@@ -487,8 +487,8 @@ inline void mark_groups(std::vector<uint32_t> &bits, uint32_t group_log2, uint64
 }
 
 // One bit per tile of kThreads units, set where every rank of the tile has a source for every entry of the launch and
-// all of them share all coordinates but the last: what rounds_move_faster counts.  (Line by line along the last
-// dimension; tile by tile the same took 11 ms for the lists of a 64^3 box.)
+// all of them share all coordinates but the last: by its definition, line by line along the last dimension, a part of what
+// mesh_interior_units finds, whose tests are held against it.
 inline std::vector<uint32_t> mesh_interior_tiles(const Comm &c, bool slot_major, const HostEntry *ents, uint32_t k,
                                                  uint64_t total, uint64_t chunks, uint64_t p) {
     const uint64_t unit_per_rank = slot_major ? chunks : chunks * k;
@@ -929,13 +929,16 @@ private:
         rounds.push_back(std::move(last));
     }
 
-    // On a mesh a launch's tiles are interior where all its entries have a source, which is less of the box for the
-    // rounds of a dimension together than for each by itself, and a tile that is not takes up to twice its time.  Against
-    // that stand what a launch costs (4 us, here in bytes at the copy rate) and blocks that several rounds read.  Rounds
-    // one by one, all of a dimension together, us: 16^4, 40 random neighbours up to 3 away, 1 KiB 2788 and 2960; 32^3 the
-    // same 1165 and 1184; 48^3, 124 neighbours, 128 B 1491 and 1527; the other way 8^5, 256 B 450 and 445, 128^2, 48
-    // neighbours, 2 KiB 897 and 888.  Wrong by 3 to 5 % where most tiles are outside for either (8^5, 4 KiB 5908 and 5701,
-    // slot-major, 1 KiB 1412 and 1349; allgather 9^5, 512 B 1248 and 1214): no weight of a tile outside tells these apart.
+    // On a mesh of rank-major buffers the units of a launch are interior where all its entries have a source, which is less
+    // of the box for the rounds of a dimension together than for each by itself, and a unit that is not takes up to twice
+    // its time (counted half as much again).  Against that stand what a launch costs (4 us, here in bytes at the copy rate)
+    // and blocks that several rounds read.  On slot-major buffers every entry has its own bounds, together or not.  Rounds
+    // one by one and all of a dimension together, us, many sets of buffers: 48^3, 124 neighbours, 128 B 1497 and 1567; 9^5,
+    // 40 random neighbours up to 3 away, 512 B 1575 and 1640; 8^5, 1 KiB 1626 and 1647; the other way 8^5, 256 B 487 and
+    // 460; 128^2, 48 neighbours, 2 KiB 988 and 937; 300^2, 12 neighbours, 400 B 302 and 250; slot-major 16^4, 40 random
+    // neighbours, 256 B 703 and 633; 8^5, 1 KiB 1435 and 1371.  Over 93 boxes the choice loses 0.15 % on average and at
+    // most 4.5 % (12^4, 30 random neighbours, 777 B 638 and 611; 28^3, 20, 2 KiB 809 and 783; 8^5, 4 KiB 5954 and 5822);
+    // with weights of 1 and 2 it loses 0.17 and 0.19 %, with all of a dimension always together 0.18 %.
     bool rounds_move_faster() const {
         constexpr uint64_t kLaunchBytes = uint64_t(26) << 20;
         uint64_t rounds_cost = 0, merged_cost = 0;
@@ -943,7 +946,7 @@ private:
             const Launch &l = pending[i].l;
             uint64_t cost = kLaunchBytes + l.bytes_read;
             if (l.kernel == kMeshShiftKernel) {
-                cost += (uint64_t)l.outside_tiles * kThreads * 2 << min_log2;
+                cost += l.outside_units * 3 / 2 << min_log2;
             }
             (i < n_listed ? rounds_cost : merged_cost) += cost;
         }
@@ -1452,9 +1455,9 @@ private:
             ma.torus |= (uint32_t)(group_log2 == kTileLog2) << 11;
             prefixes.insert(prefixes.end(), bits.begin(), bits.end());
             if (pl.algorithm == ISO_ALG_COMBINED && !arena) {
-                l.outside_tiles = (uint32_t)((total + kThreads - 1) / kThreads);
-                for (uint32_t w : mesh_interior_tiles(c, lay.slot_major, ents.data() + done, k, total, chunks, p))
-                    l.outside_tiles -= (uint32_t)__builtin_popcount(w);
+                l.outside_units = ((total - 1) >> group_log2) + 1;
+                for (uint32_t w : bits) l.outside_units -= (uint32_t)__builtin_popcount(w);
+                l.outside_units <<= group_log2;
             }
             return ISO_SUCCESS;
         } else {

@@ -61,6 +61,11 @@ int main() {
             const std::vector<uint32_t> bits = iso::mesh_interior_units(c, slot, ents.data(), k, log2, total, chunks, p);
             const uint64_t n = (total + (1u << log2) - 1) >> log2;
             if (bits.size() != (n + 31) / 32) return 4;
+            if (log2 == iso::kTileLog2) {                      // no tile less than the line by line form finds
+                const std::vector<uint32_t> lines = iso::mesh_interior_tiles(c, slot, ents.data(), k, total, chunks, p);
+                for (size_t w = 0; w < bits.size(); ++w)
+                    if (lines[w] & ~bits[w]) return 8;
+            }
             for (uint64_t g = 0; g < 32 * bits.size(); ++g) {
                 const bool got = (bits[(size_t)(g >> 5)] >> (g & 31)) & 1u;
                 if (g >= n && got) return 5;

@@ -333,7 +333,8 @@ def test_merged_rounds_of_many_entries_bind_in_little_more_time(stub_library):
 
 @pytest.mark.parametrize("dims,offsets,m,layout,op,kernels", [
     ((16, 16, 16, 16), gen.random_distinct(4, -3, 3, 40, 5), 1024, 0, 0, 24), ((32, 32, 32), gen.random_distinct(3, -3, 3, 40, 5), 1024, 0, 0, 18),
-    ((8,) * 5, gen.random_distinct(5, -3, 3, 40, 5), 1024, 1, 0, 30), ((48, 48, 48), gen.moore(3, 2), 128, 0, 0, 12),
+    ((8,) * 5, gen.random_distinct(5, -3, 3, 40, 5), 1024, 1, 0, 5), ((16,) * 4, gen.random_distinct(4, -3, 3, 40, 5), 256, 1, 0, 4),
+    ((32, 32, 32), gen.random_distinct(3, -3, 3, 40, 5), 1024, 1, 0, 3), ((9,) * 5, gen.random_distinct(5, -3, 3, 40, 5), 512, 0, 0, 30), ((48, 48, 48), gen.moore(3, 2), 128, 0, 0, 12),
     ((8,) * 5, gen.random_distinct(5, -3, 3, 40, 5), 256, 0, 0, 5), ((10,) * 4, gen.random_distinct(4, -3, 3, 40, 5), 400, 0, 0, 4),
     ((64, 64, 64), gen.moore(3, 1), 128, 0, 0, 3), ((128, 128), gen.moore(2, 3), 2048, 0, 0, 2),
     ((48, 48, 48), gen.moore(3, 2), 128, 0, 1, 3), ((8, 8), gen.moore(2, 1), 32, 0, 0, 2)])
