@@ -659,12 +659,17 @@ private:
     // 8.7 and 9.2 -> 12.3).  A schedule of one launch gains nothing (4096, 16 B 6.5 -> 6.9).  Near the limits many sets
     // lose what repeated ones gain (45^2 radius 1, 32 B 9.3 -> 7.2 and 9.3 -> 11.3): a persistent request finds its
     // blocks in the last-level cache again.
-    // Chains of several hops that fill 64 workgroups and more are spread over the chip, and the launches that they save
-    // are the longer ones: 12288 sectors for one workgroup, 192 Ki per launch saved (a launch per dimension -> chain, a
-    // few sets of buffers and 60 of them: 8^3, 124 neighbours, 64 B 10.1 -> 5.9 and 11.6 -> 7.0; 5^4, 80 neighbours, 64 B
-    // 10.7 -> 6.7 and 13 -> 9.2; 4^4, 80 neighbours, 200 B 14 -> 7.5 and 14.6 -> 9.8; 5 x 4 x 5 x 4 x 5, 31
-    // neighbours, 64 B 14.5 -> 13.2 and 16.6 -> 15.3; beyond it 8^4, 30 neighbours, 16 B 13.6 -> 15.2 and 14.8 -> 16.9; with fewer workgroups 32^2, 24 neighbours, 100 B 7.2 -> 9.3, 45^2,
-    // 32 B 6.5 -> 7.3 with many sets).
+    // Chains of several hops that fill 64 workgroups and more are spread over the chip, and where they save two launches
+    // and more, these are the longer ones: 12288 sectors for one workgroup, 192 Ki per launch saved (a launch per dimension
+    // -> chain, one set of buffers and a gigabyte of them: 8^3, 124 neighbours, 64 B 10.1 -> 5.9 and 11.6 -> 7.0; 5^4, 80
+    // neighbours, 64 B 10.7 -> 6.7 and 13 -> 9.2; 4^4, 80 neighbours, 200 B 14 -> 7.5 and 14.6 -> 9.8; 5 x 4 x 5 x 4 x 5,
+    // 31 neighbours, 64 B 14.5 -> 13.2 and 16.6 -> 15.3; near it 5 x 7 x 5, 20 neighbours, 2144 B 11.9 -> 7.3 and 11.5 ->
+    // 10.0, 6 x 5 x 7 x 4, 30, 144 B 14.2 -> 9.5 and 15.5 -> 11.7, 12 x 9 x 7, 24, 367 B 10.7 -> 9.8 and 12.2 -> 13.2;
+    // beyond it 8^4, 30 neighbours, 16 B 13.6 -> 15.2 and 14.8 -> 16.9).  Not for one launch saved (20 x 16, 24 neighbours,
+    // 586 B 7.9 -> 8.2 and 8.1 -> 10.1; 13 x 16, 24, 796 B 6.1 -> 5.2 and 6.9 -> 8.3; 13^2, 12, 2784 B 6.7 -> 4.9 and
+    // 7.1 -> 8.0), nor with fewer workgroups (32^2, 24 neighbours, 100 B 7.2 -> 9.3, 45^2, 32 B 6.5 -> 7.3 with many sets).
+    // The allocation-free call always saves two and more, with the one that stores its table (20 x 16, 586 B 10.9 -> 8.2
+    // and 11.0 -> 10.0; 13^2, 2784 B 10.6 -> 5.4 and 10.6 -> 7.8).
     static constexpr size_t kChainHops = 1024;
     bool chain_launch(uint64_t launches) {
         const size_t most_hops = arena ? kChainHopsByValue : kChainHops;
@@ -774,7 +779,7 @@ private:
         const uint64_t piece = ca.column * width, own = p * ((piece + 63) / 64) * longest;
         uint64_t all = own * l.grid;
         if (longest > 1 && size0 > 32 && size0 % 64 && piece <= 64) all *= 2;
-        const bool wide = l.grid >= 64 && longest > 1;
+        const bool wide = l.grid >= 64 && longest > 1 && (launches > 2 || arena);
         if (own > (wide ? 12288 : 6144) || all > (launches - 1) * (wide ? 192 : 48) * 1024) return false;
         l.threads = std::min<uint32_t>(kChainThreads, (ca.n_units + 63) & ~63u);
         l.dyn_lds = longest > 1 ? ca.n_units * (uint32_t)width : 0;

@@ -108,6 +108,18 @@ def test_many_chains_fill_the_chip_with_more(stub_library, dims, offsets, m, ker
         assert "chain_kernel" not in _noalloc(stub_library, dims, offsets, m, iso.ISO_ALG_COMBINED)
 
 
+@pytest.mark.parametrize("dims,offsets,m,kernels", [
+    ((20, 16), gen.moore(2, 2), 586, 2), ((13, 13), gen.von_neumann(2, 2), 2784, 2), ((13, 16), gen.moore(2, 2), 796, 2), ((13, 16), gen.moore(2, 2), 64, 1),
+    ((5, 5, 5), gen.moore(3, 2), 240, 1)])
+def test_more_sectors_only_where_two_launches_are_saved(stub_library, dims, offsets, m, kernels):
+    """A chain that replaces two launches keeps 48 Ki sectors, however many workgroups share them; the allocation-free call
+    saves the launch of its table as well (up to 72 hops)."""
+    for alg in (iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM):
+        names = _names(stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, alg, m))
+        assert len(names) == kernels and ("chain_kernel" in names) == (kernels == 1), (alg, names)
+        assert _noalloc(stub_library, dims, offsets, m, alg)[-1] == ("chain_kernel" if len(dims) == 2 else "shift_round_kernel")
+
+
 @pytest.mark.parametrize("dims,offsets,m,width", [((5, 4, 7, 6, 4), gen.von_neumann(5, 1), 6, "unsigned short, false"),
                                                   ((13, 14, 15), gen.von_neumann(3, 1), 5, "unsigned char, false"),
                                                   ((46, 47), gen.von_neumann(2, 1), 3, "unsigned char, false"),
