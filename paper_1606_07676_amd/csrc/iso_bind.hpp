@@ -865,20 +865,33 @@ private:
     // its round, and all of them in one launch that writes whole receive rows (deliver_launch), after the rounds of the
     // other hops, which read rows and write planes (staged_round_launch).  Every block makes the moves of its schedule;
     // what goes are rounds that write parts of memory sectors, which cost up to 2.7 times what the blocks hold.  For
-    // blocks that do not fill 64-byte sectors, and 64 bytes, half a line (us, one launch per dimension -> rows, a
-    // gigabyte of buffer sets in turn: 64^3, 26 neighbours, 20 B 222 -> 171, 100 B 1119 -> 800, 400 B 2721 -> 2606; 662
-    // x 503, 10 neighbours, 100 B 351 -> 223, 64 B 158 -> 135; 24^3, 100 B 50 -> 41; 16^3, 200 B 31 -> 26; 8^5, 40
-    // neighbours, 40 B 135 -> 119).  Not: other whole sectors (64^3, 192 B 965 -> 1024, 320 B 1525 -> 1682), 512 B and
-    // more (64^3, 500 B 3269 -> 3279), up to 8 MiB (64^2, 24 neighbours, 40 B 5.9 -> 8.5; 16^3, 40 B 10 -> 13.6), up to
-    // 48 MiB under 32 bytes and for 64 (24^3, 20 B 15.1 -> 17.7).  ISO_ALG_COMBINED_BYDIM starts its launch list up to 7/4
-    // of the last-level cache (above: 64^3, 100 B 1119 -> 800; 8^5, 40 neighbours, 400 B 1045 -> 1063).
+    // blocks that do not fill 64-byte sectors (us, one launch per dimension -> rows, a gigabyte of buffer sets in turn:
+    // 64^3, 26 neighbours, 20 B 222 -> 171, 100 B 1119 -> 800, 400 B 2721 -> 2606; 662 x 503, 10 neighbours, 100 B 351 ->
+    // 223; 20^4, 80 neighbours, 100 B 3195 -> 2413; 24^3, 100 B 50 -> 41; 16^3, 200 B 31 -> 26; 8^5, 40 neighbours, 40 B
+    // 135 -> 119; one set of buffers repeated gains less and in part loses what the cache holds of it between the rounds:
+    // 16^3, 168 B 27.8 -> 24.4 and 19.3 -> 21.7; 23 x 32 x 26, 124 neighbours, 32 B 111 -> 87 and 70 -> 82).
+    // Not: 512 B and more (64^3, 500 B 3269 -> 3279), up to 8 MiB (64^2, 24 neighbours, 40 B 5.9 -> 8.5; 16^3, 40 B 10 ->
+    // 13.6), up to 16 MiB where blocks make three hops and more (6^4, 30 neighbours, 348 B 30.7 -> 31.9; 3^7, 132 B 39.6 ->
+    // 42.4; 7^4, 168 B 31.4 -> 31.0; though 5^5, 40 neighbours, 84 B 43.6 -> 39.1), up to 48 MiB under 32 bytes (24^3, 20 B
+    // 15.1 -> 17.7).  ISO_ALG_COMBINED_BYDIM starts its launch list up to 7/4 of the last-level cache (above: 64^3, 100 B
+    // 1119 -> 800; 8^5, 40 neighbours, 400 B 1045 -> 1063).
+    // Whole sectors gain at 64 bytes, half a line, from 48 MiB on (662 x 503, 10 neighbours 147 -> 134; 64^3, 26 neighbours
+    // 409 -> 388; 80^3, 20 811 -> 758; 14^4, 80 254 -> 215; 8^5, 40 177 -> 149), except in two dimensions for fewer than
+    // eight hops to five blocks (600^2, 8 neighbours, 12 hops 112 -> 117, 420^2, 12, 16 75 -> 78; 600^2, 8, 13 132 -> 117,
+    // 24, 40 349 -> 331) and in four and more above 3/2 of the cache, where a tile's ranks are few and far apart in every
+    // plane (20^4, 80 neighbours 984 -> 1146; 12^5, 40 1276 -> 1417; 30^4, 10 770 -> 842; 11^5, 40, 412 MB 868 -> 859).
+    // Larger ones do not but in two dimensions (128 B 64^3 618 -> 618, 192 B 951 -> 1061, 14^4 571 -> 636, 662 x 503 391
+    // -> 364; 320 B 64^3 1529 -> 1640).
     bool rows_in_one_launch() const {
         const uint64_t llc = kLastLevelCacheBytes, bytes = inf.delivered_bytes;
-        if (op != ISO_OP_ALLTOALL || arena || !rows_fit_a_tile() || (size0 % 64 == 0 && size0 != 64) || size0 >= 512 ||
-            s * size0 + 15 > kTileUnits * 16)
-            return false;
+        const int64_t blocks = (int64_t)s;
+        if (op != ISO_OP_ALLTOALL || arena || !rows_fit_a_tile() || size0 >= 512 || s * size0 + 15 > kTileUnits * 16) return false;
+        if (size0 % 64 == 0) {
+            if (size0 > 64 || bytes <= llc * 3 / 16) return false;
+            if (c.d <= 2 ? 5 * inf.entries < 8 * blocks : c.d > 3 && bytes > llc * 3 / 2) return false;
+        }
         if (pl.algorithm == ISO_ALG_COMBINED_BYDIM) return bytes > llc * 7 / 4;
-        return pl.algorithm == ISO_ALG_COMBINED && bytes > (size0 < 32 || size0 == 64 ? llc * 3 / 16 : inf.entries >= 3 * (int64_t)s ? llc / 16 : llc / 32);
+        return pl.algorithm == ISO_ALG_COMBINED && bytes > (size0 < 32 ? llc * 3 / 16 : inf.entries >= 3 * blocks ? llc / 16 : llc / 32);
     }
 
     // iso_start of ISO_ALG_COMBINED where every block makes its one move out of the send buffer (a star): the moves of

@@ -228,6 +228,17 @@ def test_alltoalls_that_write_rows_whole_or_all_at_once(stub_library, dims, offs
     assert "deliver_bytes_kernel" not in listed and "vector_round_kernel" not in listed
 
 
+@pytest.mark.parametrize("dims,offsets,alg,rows", [
+    ((600, 600), gen.moore(2, 1), 0, False), ((420, 420), gen.von_neumann(2, 2), 0, False), ((300, 300), gen.moore(2, 2), 0, True),
+    ((662, 503), gen.random_distinct(2, -3, 3, 10, 5), 0, True), ((600, 600), gen.random_distinct(2, -3, 3, 8, 5), 0, True), ((64, 64, 64), gen.moore(3, 1), 0, True), ((24, 24, 24), gen.moore(3, 1), 0, False),
+    ((80, 80, 80), gen.von_neumann(3, 2), 1, True), ((16, 16, 16, 16), gen.moore(4, 1), 0, True), ((20, 20, 20, 20), gen.moore(4, 1), 0, False),
+    ((20, 20, 20, 20), gen.moore(4, 1), 1, False), ((12,) * 5, gen.random_distinct(5, -3, 3, 40, 5), 0, False)])
+def test_rows_of_64_byte_blocks(stub_library, dims, offsets, alg, rows):
+    """Half a line: from 48 MiB on, in two dimensions from eight hops to five blocks, in four and more up to 384 MiB."""
+    names = _names(stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, alg, 64))
+    assert names == (["staged_round_kernel"] * (len(dims) - 1) + ["deliver_bytes_kernel"] if rows else ["shift_round_kernel"] * len(dims))
+
+
 @pytest.mark.parametrize("s,m,small", [(4, 4095, False), (8, 2047, False), (1, 16383, False), (1, 16369, True), (4, 4092, True), (16, 1023, True)])
 def test_rows_next_to_a_small_tile(stub_library, s, m, small):
     """A tile by bytes holds up to 15 bytes more than the rows: the alignment of the receive buffer."""
