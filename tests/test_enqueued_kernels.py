@@ -78,6 +78,19 @@ def test_allocation_free_call_on_boxes_stores_bitmaps_by_the_tile(stub_library, 
         assert names == stores * ["table_store_kernel"] + rounds * ["mesh_shift_round_kernel"], (alg, len(names))
 
 
+@pytest.mark.parametrize("dims,offsets,m,kernels", [
+    ((8, 8, 8), gen.von_neumann(3, 1), 60, "chain"), ((16, 16), gen.von_neumann(2, 1), 100, "chain"), ((6, 6, 4, 6), gen.von_neumann(4, 2), 93, "chain"),
+    ((700,), [(1,), (-1,), (3,)], 11, "store deliver_bytes"), ((50,), [(0,), (2,), (-1,)], 1, "chain"), ((1, 1), gen.moore(2, 1), 35, "store deliver_bytes"),
+    ((15, 19, 16), [(-2, 0, -3), (3, 0, 2)], 3, "store shift_round deliver_bytes"),
+    ((9, 6, 12), gen.moore(3, 2), 86, "store store store store store store shift_round shift_round deliver_bytes"),
+    ((8, 8, 8), gen.von_neumann(3, 1), 64, "store deliver"), ((32, 32, 32), gen.von_neumann(3, 1), 100, "store deliver_bytes")])
+def test_allocation_free_call_of_the_staged_schedule(stub_library, dims, offsets, m, kernels):
+    """Rows of any block size cost a launch for their records there: the chain stands against a launch per dimension, and
+    nothing is stored that no kernel reads."""
+    names = _noalloc(stub_library, dims, offsets, m, iso.ISO_ALG_COMBINED_STAGED)
+    assert " ".join(n.replace("_kernel", "").replace("table_", "") for n in names) == kernels
+
+
 @pytest.mark.parametrize("op", [iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER])
 @pytest.mark.parametrize("dims,offsets,m,kernels", [
     ((8, 8), gen.moore(2, 1), 64, 1), ((8, 8, 8), gen.moore(3, 1), 64, 1), ((32, 32), gen.von_neumann(2, 2), 64, 1),

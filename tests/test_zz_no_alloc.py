@@ -129,3 +129,17 @@ def test_noalloc_on_boxes(dims, offsets, m):
             recv = torch.full((p, s, m), 0xEE, dtype=torch.uint8, device=DEV)
             iso.iso_neighbor_alltoall_noalloc(send, recv, m, comm, alg)
             assert torch.equal(recv, want), (dims, periodic, alg)
+
+
+@pytest.mark.parametrize("dims,offsets,m", [((8, 8, 8), gen.von_neumann(3, 1), 60), ((15, 19, 16), [(-2, 0, -3), (3, 0, 2)], 3),
+                                            ((32, 32, 32), gen.von_neumann(3, 1), 100), ((9, 6, 12), gen.moore(3, 2), 86),
+                                            ((700,), [(1,), (-1,), (3,)], 11), ((8, 8, 8), gen.von_neumann(3, 1), 64)])
+def test_noalloc_rows_of_any_block_size(dims, offsets, m):
+    """The staged schedule's last launch with its records next to the entries, and the chain in its place."""
+    p, s = int(np.prod(dims)), len(offsets)
+    send_h = gen.alltoall_send(8, p, s, m)
+    send, recv = torch.from_numpy(send_h).to(DEV), torch.full((p, s, m), 0xEE, dtype=torch.uint8, device=DEV)
+    comm = iso.iso_neighborhood_create(dims, offsets)
+    for _ in range(2):
+        iso.iso_neighbor_alltoall_noalloc(send, recv, m, comm, iso.ISO_ALG_COMBINED_STAGED)
+    assert np.array_equal(recv.cpu().numpy(), orc.alltoall(dims, offsets, send_h))
