@@ -1334,8 +1334,9 @@ struct HopNow {
 };
 
 // A place that a chain writes twice (Algorithm 1 alternates between two) is written twice by the same lane, in
-// order.  Only the bytes that a last unit shares with its predecessor are written by two lanes (TAIL): there the
-// stores of a hop are waited for.
+// order.  The bytes that a last unit shares with its predecessor are written by two lanes (TAIL), by both at every
+// stop: whichever of their last stores lands last carries the last stop's bytes.  No stop is read back from memory, so
+// that no store is waited for.
 // Hops through memory, arguments by value -> as here: 8 x 8, 8 neighbours, 32 B 4.1 -> 3.6 us a start, 8^3, 26
 // neighbours, 64 B 6.4 -> 4.5, 10^3, 64 B 9.3 -> 6.2 (allgather 9.0 -> 5.3), 45^2, 32 B 6.6 -> 4.7.
 template <typename V, bool TAIL, uint32_t UPL, typename ARGS>
@@ -1386,8 +1387,7 @@ __global__ __launch_bounds__(kChainThreads) void chain_kernel(const ARGS from) {
 #pragma unroll
         for (uint32_t it = 0; it < UPL; ++it)
             if (has[it]) tile[unit[it]] = v[it];
-        if constexpr (TAIL) __syncthreads();
-        else lds_barrier();
+        lds_barrier();
         hop = next;
         ++at;
         next = HopNow(table, at < end ? at : chain);

@@ -13,6 +13,7 @@ import pytest
 import paper_1606_07676_amd as iso
 
 READELF = "/opt/rocm/llvm/bin/llvm-readelf"
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 
 
@@ -51,7 +52,28 @@ def test_no_kernel_uses_private_memory_or_spills(tmp_path):
     assert len(kernels) > 20, notes[:2000]
     for want in ("shift_round_kernel", "shift_round_uniform_kernel", "shift_push_kernel", "vector_round_kernel",
                  "vector_round_uniform_kernel", "push_round_kernel", "chain_kernel", "block_round_kernel",
-                 "mesh_shift_round_kernel", "staged_round_kernel", "deliver_kernel", "copy_kernel", "table_store_kernel"):
+                 "mesh_shift_round_kernel", "staged_round_kernel", "deliver_kernel", "deliver_bytes_kernel", "copy_kernel", "table_store_kernel"):
         assert any(want in k for k in kernels), want
     bad = {k: v for k, v in kernels.items() if v != (0, 0)}
     assert not bad, f"kernels with private memory or register spills: {bad}"
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="llvm-objdump of the ROCm toolchain not found")
+def test_blocks_by_size_keep_both_cache_policies(tmp_path):
+    """block_round_kernel with the policy by size: 16-byte units once streamed and once plain, on both sides.  The compiler
+    joins the two moves, and drops the streaming, unless something keeps them apart; results are the same either way."""
+    elf = tmp_path / "libiso_gfx950.co"
+    elf.write_bytes(_device_code_object(os.path.join(os.path.dirname(iso.__file__), "libiso.so")))
+    symbols = subprocess.run([READELF, "-sW", str(elf)], stdout=subprocess.PIPE, text=True, check=True).stdout
+    kernels = sorted(set(re.findall(r"\bFUNC\b.*\s(\S*block_round_kernelILb[01]ELb0ELi4E\S*)", symbols)))
+    assert len(kernels) == 4, kernels                        # entries in LDS or not, ranks in groups or not
+    for kernel in kernels:
+        code = subprocess.run([OBJDUMP, "-d", f"--disassemble-symbols={kernel}", str(elf)], stdout=subprocess.PIPE, text=True,
+                              check=True).stdout
+        moves = [line.split("//")[0].split() for line in code.split("\n") if re.search(r"global_(load|store)_dwordx4", line)]
+        stores = [m for m in moves if m[0].startswith("global_store")]
+        assert sorted("nt" in m for m in stores) == [False, True], (kernel, stores)
+        for store in stores:                                 # the load of the units that it writes: streamed or not as well
+            unit = store[2]
+            loads = [m for m in moves[:moves.index(store)] if m[0].startswith("global_load") and m[1] == unit]
+            assert loads and ("nt" in loads[-1]) == ("nt" in store), (kernel, store, loads)
