@@ -62,7 +62,6 @@ struct Launch {
     ChainHead chain;       // chain kernel: its hops in the request's table
     const ChainArgs *chain_by_value;      // or BoundRequest::chain, where there is no table
     uint32_t chain_width;  // its unit width, where not the request's
-    uint32_t n_tiles, run_log2;           // see TileMap
     uint64_t outside_units;               // mesh: units of wavefronts or tiles not marked interior (see rounds_move_faster)
     bool entry_major, vector_round;       // see launch_flags
     uint32_t pull;
@@ -201,8 +200,6 @@ inline void set_grid(Launch &l, uint32_t total, uint32_t k, bool eighths) {
         run_log2 = kEighths;
         l.grid = per_xcd * 8;
     }
-    l.n_tiles = n_tiles;
-    l.run_log2 = run_log2;
     const uint32_t flags = launch_flags(run_log2, l.entry_major, l.pull, l.vector_round);
     l.lds_table = k <= kLdsEntries;
     switch (l.kernel) {

@@ -147,14 +147,15 @@ def test_columns_of_one_unit_take_units_that_divide_the_block(stub_library, dims
 # 4 by the block's size
 POLICY_ARGUMENT = {"shift_round_kernel": 2, "mesh_shift_round_kernel": 2, "shift_round_uniform_kernel": 0,
                    "staged_round_kernel": 1, "deliver_kernel": 1, "block_round_kernel": 2, "vector_round_kernel": 3,
-                   "vector_round_uniform_kernel": 1}
+                   "vector_round_uniform_kernel": 1, "deliver_bytes_kernel": 1}
+NO_POLICY = {"chain_kernel", "shift_push_kernel", "push_round_kernel"}
 
 
 def _policies(kernels):
     out = set()
     for k in kernels:
         name, args = k.rstrip(">").split("<")
-        if name in POLICY_ARGUMENT:
+        if name not in NO_POLICY:
             out.add((name.replace("_kernel", "").replace("_round", ""), int(args.split(", ")[POLICY_ARGUMENT[name]])))
     return out
 
@@ -239,6 +240,17 @@ def test_alltoalls_that_write_rows_whole_or_all_at_once(stub_library, dims, offs
     assert names == want
     listed = _names(stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, alg, m, by_rounds=True))
     assert "deliver_bytes_kernel" not in listed and "vector_round_kernel" not in listed
+
+
+@pytest.mark.parametrize("dims,m,rounds,last", [
+    ((24, 24, 24), 100, 2, 0), ((29, 29, 29), 105, 2, 0), ((29, 29, 29), 106, 3, 0), ((40, 40, 40), 79, 3, 0), ((40, 40, 40), 81, 3, 1), ((64, 64, 64), 100, 3, 1), ((64, 64, 64), 15, 0, 0)])
+def test_cache_policy_of_rows_of_any_block_size(stub_library, dims, m, rounds, last):
+    """26 neighbours.  The rounds in front of the rows stream their loads above a quarter of the cache, the rows both above
+    half of it; narrower units have one form."""
+    for alg in (iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_STAGED):
+        got = _policies(stub_library.start(dims, gen.moore(3, 1), iso.ISO_OP_ALLTOALL, alg, m))
+        got.discard(("shift", rounds))                       # the staged schedule's small blocks keep the plain kernel
+        assert got <= {("staged", rounds), ("deliver_bytes", last)} and ("deliver_bytes", last) in got, (alg, got)
 
 
 @pytest.mark.parametrize("dims,offsets,alg,rows", [

@@ -64,10 +64,11 @@ def test_large_collectives_against_the_straightforward_exchange(dims, offsets, m
         assert n == kernels and torch.equal(got, want), (dims, m, shift, n)
 
 
+@pytest.mark.parametrize("layout", [iso.ISO_LAYOUT_RANK_MAJOR, iso.ISO_LAYOUT_SLOT_MAJOR])
 @pytest.mark.parametrize("dims,m", [((40, 41, 39), 20), ((9, 8, 7, 6, 5), 100), ((300, 301), 255)])
-def test_star_allgather_in_one_launch(dims, m):
+def test_star_allgather_in_one_launch(dims, m, layout):
     p, offsets = int(np.prod(dims)), gen.von_neumann(len(dims), 1)
     send = torch.randint(0, 256, (p * m,), dtype=torch.uint8, device=DEV, generator=torch.Generator(DEV).manual_seed(4))
-    want, _ = _received(dims, offsets, iso.ISO_OP_ALLGATHER, iso.ISO_ALG_SX_ROUNDS, m, send)
-    got, n = _received(dims, offsets, iso.ISO_OP_ALLGATHER, iso.ISO_ALG_COMBINED, m, send)
+    want, _ = _received(dims, offsets, iso.ISO_OP_ALLGATHER, iso.ISO_ALG_SX_ROUNDS, m, send, 0, layout)
+    got, n = _received(dims, offsets, iso.ISO_OP_ALLGATHER, iso.ISO_ALG_COMBINED, m, send, 0, layout)
     assert n == 1 and torch.equal(got, want)

@@ -15,23 +15,23 @@ CSRC = os.path.join(ROOT, "paper_1606_07676_amd", "csrc")
 CLANGXX = "/opt/rocm/llvm/bin/clang++"
 
 
-def _build(td, tag, extra):
+def _build(td, tag, extra, driver="request_lifecycle_driver.cpp", sanitizer="address"):
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
-    common = ["-O1", "-g", "-std=c++17", "-fsanitize=address", "-fno-omit-frame-pointer"]
+    common = ["-O1", "-g", "-std=c++17", "-fno-omit-frame-pointer"]
     objs = []
     for src, hip in ((os.path.join(CSRC, "iso_api.hip"), True), (os.path.join(ROOT, "tests", "hip_stub_runtime.cpp"), False),
                      (os.path.join(CSRC, "iso_plan.cpp"), False),
-                     (os.path.join(ROOT, "tests", "request_lifecycle_driver.cpp"), False)):
+                     (os.path.join(ROOT, "tests", driver), False)):
         obj = os.path.join(td, f"{tag}_{os.path.basename(src)}.o")
         if hip:      # the host pass of the HIP compiler: kernels become launch stubs, no device code
-            cmd = ["hipcc", "--cuda-host-only", "-fuse-cuid=none", *common, *inc, *extra, "-c", src, "-o", obj]
+            cmd = ["hipcc", "--cuda-host-only", "-fuse-cuid=none", "-Xarch_host", f"-fsanitize={sanitizer}", *common, *inc, *extra, "-c", src, "-o", obj]
         else:
-            cmd = [CLANGXX, *common, *inc, "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-c", src, "-o", obj]
+            cmd = [CLANGXX, f"-fsanitize={sanitizer}", *common, *inc, "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-c", src, "-o", obj]
         proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         assert proc.returncode == 0, proc.stdout[-3000:]
         objs.append(obj)
     exe = os.path.join(td, f"lifecycle_{tag}")
-    proc = subprocess.run([CLANGXX, "-fsanitize=address", *objs, "-o", exe], stdout=subprocess.PIPE,
+    proc = subprocess.run([CLANGXX, f"-fsanitize={sanitizer}", "-pthread", *objs, "-o", exe], stdout=subprocess.PIPE,
                           stderr=subprocess.STDOUT, text=True)
     assert proc.returncode == 0, proc.stdout[-3000:]
     return exe
@@ -54,3 +54,10 @@ def test_request_life_cycle_leaves_nothing_behind_and_a_planted_leak_is_caught()
         assert bad.returncode != 0
         assert "left behind" in bad.stdout and "device allocations" in bad.stdout
         assert "LeakSanitizer: detected memory leaks" in bad.stdout
+
+
+@pytest.mark.skipif(not os.path.exists(CLANGXX), reason="needs the ROCm clang++")
+def test_threads_share_a_neighbourhood_in_the_allocation_free_call():
+    with tempfile.TemporaryDirectory() as td:
+        run = _run(_build(td, "threads", [], "shared_handle_driver.cpp", "thread"))
+        assert run.returncode == 0 and "shared handle ok" in run.stdout and "ThreadSanitizer" not in run.stdout, run.stdout[-3000:]
