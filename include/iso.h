@@ -18,7 +18,8 @@
  *     every buffer it passes; the library owns only its handles and, per
  *     request, one small device table of block index maps (allocated in the
  *     init call, freed in iso_request_free).
- *   - A handle may be used from one host thread at a time.
+ *   - A handle may be used from one host thread at a time; a neighbourhood may be
+ *     shared by threads in iso_neighbor_alltoall_noalloc.
  */
 #ifndef ISO_H
 #define ISO_H
@@ -64,7 +65,9 @@ enum iso_algorithm {
     ISO_ALG_COMBINED       = 0,
     /* Same schedule, all rounds of one dimension as a single round of the plan and
      * of the launch list (they touch disjoint blocks; the k-ported remark of
-     * Section 3). */
+     * Section 3).  iso_start takes the launch list, but for all-to-alls of small or
+     * odd blocks well above the last-level cache, whose receive rows it writes whole
+     * as above. */
     ISO_ALG_COMBINED_BYDIM = 1,
     /* Straightforward algorithm (first listing of Section 3): one exchange,
      * here one launch, per neighbour; s launches. */
@@ -181,9 +184,11 @@ typedef struct {
     int32_t launches;            /* length of the launch list: what iso_start_range counts
                                   * through and a graph holds.  iso_start enqueues as many
                                   * kernels, or fewer (iso_request_start_info): ISO_ALG_COMBINED
-                                  * takes the rounds of a dimension together, small collectives
-                                  * of the three combined algorithms run all their rounds in one
-                                  * kernel                                                  */
+                                  * takes the rounds of a dimension together and single moves
+                                  * out of the send buffer all at once, it and
+                                  * ISO_ALG_COMBINED_BYDIM the last moves into small or odd
+                                  * blocks; small collectives of the three combined algorithms
+                                  * run all their rounds in one kernel                      */
     int32_t vector_bytes;        /* width of the loads/stores: the largest power of two that is
                                   * at most 16 and at most the smallest non-empty block; buffer
                                   * addresses need no alignment                               */
@@ -406,7 +411,9 @@ int iso_request_free(iso_request_t *req);
  * Code under HIP graph capture, tight serving loops and harnesses that forbid
  * hipMalloc cannot use the init calls (they allocate the request's device
  * table) and may have no workspace to pass.  This call is
- * iso_neighbor_alltoall_init + iso_start in one, with no request left behind:
+ * iso_neighbor_alltoall_init + iso_start in one, with no request left behind
+ * (the neighbourhood keeps the schedule in host memory, one for each algorithm
+ * that was asked for, until it is freed; threads may share it):
  * it enqueues one all-to-all (same arguments, layout [p][s][m], same result,
  * same algorithms) on `hip_stream` and returns without waiting.  The table of
  * block index maps and the intermediate buffer live in a static device array
@@ -416,7 +423,7 @@ int iso_request_free(iso_request_t *req);
  * before the rounds.  No hipMalloc, hipFree, host-to-device copy or other
  * allocating routine is called.
  * Limits: the table must fit ISO_NOALLOC_TABLE_BYTES (48 bytes per block-move
- * per rank, plus 4*s*d; on a mesh also a bit per 256 units of at most 16 bytes
+ * per rank, 64 in the last launch of ISO_ALG_COMBINED_STAGED, plus 4*s*d; on a mesh also a bit per 256 units of at most 16 bytes
  * that a launch moves, in whole words, or 8 bytes per block-move of the
  * straightforward exchange) and iso_workspace_bytes() the rest of the array,
  * else ISO_ERR_SCRATCH and nothing is enqueued.

@@ -906,7 +906,11 @@ private:
     // neighbours' full vectors (us, a launch per dimension -> one, a gigabyte of buffer sets in turn: 64^3, 6 neighbours,
     // 16 B 34 -> 15.5, 72 B 100 -> 48, 128 B 75 -> 65, 2 KiB 1083 -> 1025; 24^3, 100 B 13.1 -> 7.0; 12^4, 200 B 31.5 ->
     // 15.3; 300^2, 4000 B 483 -> 467; slot-major 64^3, 128 B 69.9 -> 65.7).  From 256 bytes on above a 24th of the
-    // cache; an allgather below 256 bytes.  Nothing to gain in one dimension (262144, 256 B 44.1 -> 45.1).
+    // cache.  An allgather below 256 bytes (64^3 128 B 47 -> 37, 200 B 130 -> 58; 24^3, 128 B 9.0 -> 4.4; 16^4, 128 B 18.2 ->
+    // 14.2; 500^2, 128 B 28.9 -> 24.1; in two dimensions single sizes of whole sectors lose with many sets of buffers what
+    // they gain with one: 300^2, 128 B 11.8 -> 14.3 and 10.7 -> 8.7, 700^2, 192 B 92 -> 121 and 92 -> 71); from there on
+    // whole lines lose more of that (300^2, 1 KiB 81 -> 102 and 79 -> 63, 2 KiB 170 -> 229; 64^3, 1 KiB 366 -> 408), though
+    // other sizes would gain (64^3, 300 B 179 -> 89).  Nothing to gain in one dimension (262144, 256 B 44.1 -> 45.1).
     bool star_in_one_launch(uint64_t launches) const {
         if (pl.algorithm != ISO_ALG_COMBINED || c.mesh || !uniform || inf.entries != (int64_t)s || launches < 2 ||
             c.d > kVectorDims || s > kLdsEntries)
@@ -1083,7 +1087,10 @@ private:
     }
 
     // The last launch of the staged schedule has a kernel of its own for rows_fit_a_tile; anywhere else it runs as
-    // one launch per dimension on the general kernels.
+    // one launch per dimension on the general kernels.  Blocks that are no multiple of 16, a launch per dimension -> rows, us,
+    // many sets of buffers: 64^3, 6 neighbours, 100 B 123 -> 74, 1000 B 658 -> 576; 300^2, 8, 2500 B 974 -> 941; 24^3, 26,
+    // 33 B 34 -> 24; allgather 48^3, 26, 700 B 915 -> 749.  A few single hops of kilobytes lose (152 x 186, 4 neighbours,
+    // 2485 B, allgather 81 -> 99; one dimension, 36651, 500 B 14.8 -> 16.0).
     void rounds_as_launched() {
         for (size_t ri = 0; ri < pl.rounds.size(); ++ri) {
             const Round &r = pl.rounds[ri];
