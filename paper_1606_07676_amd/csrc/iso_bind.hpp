@@ -871,9 +871,9 @@ private:
     // iso_start of an all-to-all whose rows fit a workgroup (rows_fit_a_tile): the last hop of every block taken out of
     // its round, and all of them in one launch that writes whole receive rows (deliver_launch), after the rounds of the
     // other hops, which read rows and write planes (staged_round_launch).  Every block makes the moves of its schedule;
-    // what goes are rounds that write parts of memory sectors, which cost up to 2.7 times what the blocks hold.  For
-    // blocks that do not fill 64-byte sectors (us, one launch per dimension -> rows, a gigabyte of buffer sets in turn:
-    // 64^3, 26 neighbours, 20 B 222 -> 171, 100 B 1119 -> 800, 400 B 2721 -> 2606; 662 x 503, 10 neighbours, 100 B 351 ->
+    // what goes are writes of parts of memory sectors (64^3, 100 B: 26 % of the rounds' write requests, 9 % here), with which
+    // the rounds take up to 2.6 times as long as their blocks at the copy rate.  For blocks that do not fill 64-byte
+    // sectors (us, one launch per dimension -> rows, a gigabyte of buffer sets in turn: 64^3, 26 neighbours, 20 B 222 -> 171, 100 B 1119 -> 800, 400 B 2721 -> 2606; 662 x 503, 10 neighbours, 100 B 351 ->
     // 223; 20^4, 80 neighbours, 100 B 3195 -> 2413; 24^3, 100 B 50 -> 41; 16^3, 200 B 31 -> 26; 8^5, 40 neighbours, 40 B
     // 135 -> 119; one set of buffers repeated gains less and in part loses what the cache holds of it between the rounds:
     // 16^3, 168 B 27.8 -> 24.4 and 19.3 -> 21.7; 23 x 32 x 26, 124 neighbours, 32 B 111 -> 87 and 70 -> 82).
@@ -886,7 +886,8 @@ private:
     // 409 -> 388; 80^3, 20 811 -> 758; 14^4, 80 254 -> 215; 8^5, 40 177 -> 149), except in two dimensions for fewer than
     // eight hops to five blocks (600^2, 8 neighbours, 12 hops 112 -> 117, 420^2, 12, 16 75 -> 78; 600^2, 8, 13 132 -> 117,
     // 24, 40 349 -> 331) and in four and more above 3/2 of the cache, where a tile's ranks are few and far apart in every
-    // plane (20^4, 80 neighbours 984 -> 1146; 12^5, 40 1276 -> 1417; 30^4, 10 770 -> 842; 11^5, 40, 412 MB 868 -> 859).
+    // plane (20^4, 80 neighbours 984 -> 1146; 12^5, 40 1276 -> 1417; 30^4, 10 770 -> 842; 11^5, 40, 412 MB 868 -> 859;
+    // in three 74^3, 26 634 -> 649).
     // Larger ones do not but in two dimensions (128 B 64^3 618 -> 618, 192 B 951 -> 1061, 14^4 571 -> 636, 662 x 503 391
     // -> 364; 320 B 64^3 1529 -> 1640).
     bool rows_in_one_launch() const {
@@ -1700,7 +1701,7 @@ private:
     }
 
     // One device table: the entries, then the dimensions and the [s][d] residues, then what single launches read besides
-    // (prefix arrays of irregular launches, the mesh's interior-tile bitmaps, the records of the staged
+    // (prefix arrays of irregular launches, the mesh's interior bitmaps, the records of the staged
     // schedule's last launch); then the launches get their addresses in it.  The residues keep their place in it
     // but are written only where a kernel reads them (a launch of its own in the allocation-free call: 8^3, 26
     // neighbours, 64 B 13.5 -> 10.7 us).
