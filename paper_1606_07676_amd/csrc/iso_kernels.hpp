@@ -1006,6 +1006,30 @@ __device__ __forceinline__ void fetch_now(const StagedRoundArgs &a) {
                  "s"(a.mul_inner), "s"(a.mul_pj), "s"(a.shifts), "s"(a.more));
 }
 
+// Unit q of a tile in the order of its sources: (rank, entry, unit) over the entries that read a rank-major buffer, which
+// come first, then (entry, rank, unit) over the others.  A lane with no unit takes the tile's first one and drops it: its
+// loads stay straight-line code, all in flight together.
+struct TileUnit {
+    uint32_t e, r, c;
+    bool any;
+    __device__ __forceinline__ TileUnit(uint32_t q, uint32_t n_rows, uint32_t n_all, uint32_t k_rows, uint32_t n_ranks,
+                                        const FastDiv &d_row, const FastDiv &d_plane, const FastDiv &d_upb) {
+        uint32_t rem;
+        if (q < n_rows) {
+            fast_divmod(q, d_row, r, rem);
+            fast_divmod(rem, d_upb, e, c);
+        } else {
+            fast_divmod(q - n_rows, d_plane, e, rem);
+            fast_divmod(rem, d_upb, r, c);
+            e += k_rows;
+        }
+        any = q < n_all && r < n_ranks;
+        e = any ? e : 0u;
+        r = any ? r : 0u;
+        c = any ? c : 0u;
+    }
+};
+
 template <typename V, int POLICY, uint32_t UPL, bool TAIL>
 __global__ __launch_bounds__(kThreads) void staged_round_kernel(const StagedRoundArgs a) {
     fetch_now(a);
@@ -1030,27 +1054,12 @@ __global__ __launch_bounds__(kThreads) void staged_round_kernel(const StagedRoun
     uint32_t at[UPL];                          // where in the tile the unit goes; ~0: no unit
 #pragma unroll
     for (uint32_t it = 0; it < UPL; ++it) {
-        const uint32_t q = threadIdx.x + it * (uint32_t)kThreads;
-        uint32_t e, r, c, rem;
-        if (q < n_rows) {                                // (rank, entry, unit) over the rank-major sources
-            fast_divmod(q, d_row, r, rem);
-            fast_divmod(rem, d_upb, e, c);
-        } else {                                         // (entry, rank, unit) over the slot-major sources
-            fast_divmod(q - n_rows, d_plane, e, rem);
-            fast_divmod(rem, d_upb, r, c);
-            e += a.k_rows;
-        }
-        // a lane with no unit loads the tile's first unit instead and drops it: the eight loads stay
-        // straight-line code, all in flight together
-        const bool has_unit = q < n_all && r < n;
-        e = has_unit ? e : 0u;
-        r = has_unit ? r : 0u;
-        c = has_unit ? c : 0u;
-        const DevEntry en = table[e];
-        const src_ptr sp = (src_ptr)(block_address(en.src, R0 + r, en.src_stride) + unit_offset_if<V, TAIL>(c, last_offset));
+        const TileUnit u(threadIdx.x + it * (uint32_t)kThreads, n_rows, n_all, a.k_rows, n, d_row, d_plane, d_upb);
+        const DevEntry en = table[u.e];
+        const src_ptr sp = (src_ptr)(block_address(en.src, R0 + u.r, en.src_stride) + unit_offset_if<V, TAIL>(u.c, last_offset));
         if constexpr ((POLICY & kStreamLoads) && sizeof(V) == 16) regs[it] = __builtin_nontemporal_load(sp);
         else regs[it] = *sp;
-        at[it] = has_unit ? e * pitch + r * a.upb + c : ~0u;
+        at[it] = u.any ? u.e * pitch + u.r * a.upb + u.c : ~0u;
     }
 #pragma unroll
     for (uint32_t it = 0; it < UPL; ++it)
@@ -1090,6 +1099,11 @@ struct alignas(16) DeliverEntry {
     uint32_t shift, pj;    // residue v along the entry's dimension (0: same rank); that dimension's size
     uint32_t back, wrap;   // v * inner_j; p_j * inner_j
     FastDiv d_inner, d_pj;
+    __device__ __forceinline__ uint64_t source_of(uint32_t R) const {
+        const uint32_t q = fast_div(R, d_inner);
+        const uint32_t rj = q - fast_div(q, d_pj) * pj;
+        return block_address(src, R - back + (rj < shift ? wrap : 0u), src_stride);
+    }
 };
 static_assert(sizeof(DeliverEntry) == 64, "four 16-byte words per entry");
 
@@ -1136,30 +1150,12 @@ __global__ __launch_bounds__(kThreads) void deliver_kernel(const DeliverArgs a) 
     uint32_t at[UPL];                                    // where in the tile the unit goes; ~0: no unit
 #pragma unroll
     for (uint32_t it = 0; it < UPL; ++it) {
-        const uint32_t q = threadIdx.x + it * (uint32_t)kThreads;
-        uint32_t e, r, c, rem;
-        if (q < n_rows) {                                // (rank, entry, unit) over the rank-major sources
-            fast_divmod(q, d_rows, r, rem);
-            fast_divmod(rem, d_upb, e, c);
-        } else {                                         // (entry, rank, unit) over the planes
-            fast_divmod(q - n_rows, d_plane, e, rem);
-            fast_divmod(rem, d_upb, r, c);
-            e += a.k_rows;
-        }
-        // a lane with no unit loads the tile's first unit instead and drops it
-        const bool has_unit = q < n_all && r < n;
-        e = has_unit ? e : 0u;
-        r = has_unit ? r : 0u;
-        c = has_unit ? c : 0u;
-        const DeliverEntry &en = lds[e];
-        const uint32_t R = R0 + r;
-        const uint32_t qq = fast_div(R, en.d_inner);
-        const uint32_t rj = qq - fast_div(qq, en.d_pj) * en.pj;
-        const uint32_t srcR = R - en.back + (rj < en.shift ? en.wrap : 0u);
-        const src_ptr sp = (src_ptr)(block_address(en.src, srcR, en.src_stride) + (uint64_t)c * sizeof(V));
+        const TileUnit u(threadIdx.x + it * (uint32_t)kThreads, n_rows, n_all, a.k_rows, n, d_rows, d_plane, d_upb);
+        const DeliverEntry &en = lds[u.e];
+        const src_ptr sp = (src_ptr)(en.source_of(R0 + u.r) + (uint64_t)u.c * sizeof(V));
         if constexpr ((POLICY & kStreamLoads) && sizeof(V) == 16) regs[it] = __builtin_nontemporal_load(sp);
         else regs[it] = *sp;
-        at[it] = has_unit ? en.slot * pitch + r * a.upb + c : ~0u;
+        at[it] = u.any ? en.slot * pitch + u.r * a.upb + u.c : ~0u;
     }
 #pragma unroll
     for (uint32_t it = 0; it < UPL; ++it)
@@ -1213,30 +1209,13 @@ __global__ __launch_bounds__(kThreads) void deliver_bytes_kernel(const DeliverAr
     uint32_t at[UPL];                                    // where in the tile the unit goes; ~0: no unit
 #pragma unroll
     for (uint32_t it = 0; it < UPL; ++it) {
-        const uint32_t q = threadIdx.x + it * (uint32_t)kThreads;
-        uint32_t e, r, c, rem;
-        if (q < n_rows) {                                // (rank, entry, unit) over the rank-major sources
-            fast_divmod(q, d_rows, r, rem);
-            fast_divmod(rem, d_upb, e, c);
-        } else {                                         // (entry, rank, unit) over the planes
-            fast_divmod(q - n_rows, d_plane, e, rem);
-            fast_divmod(rem, d_upb, r, c);
-            e += a.k_rows;
-        }
-        const bool has_unit = q < n_all && r < n;
-        e = has_unit ? e : 0u;
-        r = has_unit ? r : 0u;
-        c = has_unit ? c : 0u;
-        const DeliverEntry &en = lds[e];
-        const uint32_t R = R0 + r;
-        const uint32_t qq = fast_div(R, en.d_inner);
-        const uint32_t rj = qq - fast_div(qq, en.d_pj) * en.pj;
-        const uint32_t srcR = R - en.back + (rj < en.shift ? en.wrap : 0u);
-        const uint32_t unpulled = c * (uint32_t)sizeof(V), off = unpulled < m - (uint32_t)sizeof(V) ? unpulled : m - (uint32_t)sizeof(V);
-        const src_ptr sp = (src_ptr)(block_address(en.src, srcR, en.src_stride) + off);
+        const TileUnit u(threadIdx.x + it * (uint32_t)kThreads, n_rows, n_all, a.k_rows, n, d_rows, d_plane, d_upb);
+        const DeliverEntry &en = lds[u.e];
+        const uint32_t unpulled = u.c * (uint32_t)sizeof(V), off = unpulled < m - (uint32_t)sizeof(V) ? unpulled : m - (uint32_t)sizeof(V);
+        const src_ptr sp = (src_ptr)(en.source_of(R0 + u.r) + off);
         if constexpr ((POLICY & kStreamLoads) && sizeof(V) == 16) regs[it] = __builtin_nontemporal_load(sp);
         else regs[it] = *sp;
-        at[it] = has_unit ? skew + r * row_bytes + en.slot * m + off : ~0u;
+        at[it] = u.any ? skew + u.r * row_bytes + en.slot * m + off : ~0u;
     }
 #pragma unroll
     for (uint32_t it = 0; it < UPL; ++it)
