@@ -59,15 +59,17 @@ enum iso_algorithm {
      * takes moves that touch disjoint blocks together in one kernel launch: the
      * rounds of one dimension; where every block makes one move, all rounds; in
      * all-to-alls of small or odd blocks the last move of every block, so that
-     * receive rows are written whole.  All-to-all uses the alternating receive/intermediate buffer
+     * receive rows are written whole; in all-to-alls beyond a few MiB all moves, every
+     * block handed on from hop to hop inside the kernel and stored at every stop, for
+     * which its place in the workspace serves.  All-to-all uses the alternating receive/intermediate buffer
      * rule of Algorithm 1; allgather routes along the prefix trie of
      * Section 3.2. */
     ISO_ALG_COMBINED       = 0,
     /* Same schedule, all rounds of one dimension as a single round of the plan and
      * of the launch list (they touch disjoint blocks; the k-ported remark of
-     * Section 3).  iso_start takes the launch list, but for all-to-alls of small or
-     * odd blocks well above the last-level cache, whose receive rows it writes whole
-     * as above. */
+     * Section 3).  iso_start takes the launch list, but well above the last-level
+     * cache: there all moves of an all-to-all go together, or its receive rows are
+     * written whole, as above. */
     ISO_ALG_COMBINED_BYDIM = 1,
     /* Straightforward algorithm (first listing of Section 3): one exchange,
      * here one launch, per neighbour; s launches. */
@@ -186,8 +188,8 @@ typedef struct {
                                   * kernels, or fewer (iso_request_start_info): ISO_ALG_COMBINED
                                   * takes the rounds of a dimension together and single moves
                                   * out of the send buffer all at once, it and
-                                  * ISO_ALG_COMBINED_BYDIM the last moves into small or odd
-                                  * blocks; small collectives of the three combined algorithms
+                                  * ISO_ALG_COMBINED_BYDIM all moves of an all-to-all, or the
+                                  * last ones into small or odd blocks; small collectives of the three combined algorithms
                                   * run all their rounds in one kernel                      */
     int32_t vector_bytes;        /* width of the loads/stores: the largest power of two that is
                                   * at most 16 and at most the smallest non-empty block; buffer
@@ -204,8 +206,11 @@ typedef struct {
 typedef struct {
     int32_t kernels;             /* kernels                                                 */
     int32_t reserved;
-    uint64_t bytes_read;         /* blocks they read, bytes: a block that several moves of one
-                                  * kernel read counts once for that kernel                 */
+    uint64_t bytes_read;         /* blocks their moves read, bytes: a block that several moves of one
+                                  * kernel read counts once for that kernel.  A kernel that takes
+                                  * blocks through several hops hands them on in LDS or registers and
+                                  * loads only what its first hops read: one kernel for a whole
+                                  * collective, the send buffer                             */
     uint64_t bytes_written;      /* blocks they write, bytes                                */
 } iso_start_info_t;
 

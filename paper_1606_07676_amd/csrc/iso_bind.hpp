@@ -64,6 +64,7 @@ struct Launch {
     uint32_t chain_width;  // its unit width, where not the request's
     uint64_t outside_units;               // mesh: units of wavefronts or tiles not marked interior (see rounds_move_faster)
     bool entry_major, vector_round;       // see launch_flags
+    int way;               // vector kernel: its WAY
     uint32_t pull;
     uint64_t bytes_read, bytes_written;   // of blocks (see iso_start_info_t)
     uint32_t threads;      // per workgroup, where not kThreads (chain kernel)
@@ -234,11 +235,22 @@ KernelRef with_policy(const Launch &l, F &&f) {
     return f(std::integral_constant<int, 0>());
 }
 
+template <int D, bool TAIL, int WAY>
+KernelRef select_way(const Launch &l) {
+    const auto form = [&](auto pol) -> KernelRef {
+        if (l.uniform_waves) return {(const void *)&vector_round_uniform_kernel<D, pol(), WAY>, &l.vec};
+        return {(const void *)&vector_round_kernel<vec16_t, D, true, pol(), TAIL, WAY>, &l.vec};
+    };
+    if (l.policy & kStreamLoads) return form(std::integral_constant<int, kStreamLoads>());
+    return form(std::integral_constant<int, 0>());
+}
+
 // The s-exchange with VectorEntry records (see vector_launch).
 template <typename V, int D, bool TAIL>
 KernelRef select_vector(const Launch &l) {
     if (l.vec.per) return {(const void *)&push_round_kernel<V, D, TAIL>, &l.vec};
     if constexpr (sizeof(V) == 16) {
+        if (l.way == kStops) return select_way<D, TAIL, kStops>(l);
         if (l.uniform_waves) {
             if (l.policy & kStreamLoads) return {(const void *)&vector_round_uniform_kernel<D, kStreamLoads>, &l.vec};
             return {(const void *)&vector_round_uniform_kernel<D, 0>, &l.vec};
@@ -422,6 +434,8 @@ struct HostEntry {
     DevEntry de;
     uint64_t size;
     int dim, dst_buf, dst_slot, neighbor;
+    uint32_t moves;        // of the plan that the entry stands for (more than one: see join_hops)
+    uint64_t way;          // VectorEntry::way
 };
 
 // Mesh shift launches of equal blocks: the ranks where every one of the entries finds its source, as runs of
@@ -571,10 +585,12 @@ public:
             n_listed = pending.size();
         }
         if (chains && chain_launch(launches)) return upload();
-        const bool star = star_in_one_launch(launches), rows = !star && rows_in_one_launch();
-        if (rows || star || (merges && launches < bound_rounds.size())) {
+        const bool hops = all_hops_in_one_launch(), star = !hops && star_in_one_launch(launches);
+        const bool rows = !hops && !star && rows_in_one_launch();
+        if (hops || rows || star || (merges && launches < bound_rounds.size())) {
             const size_t n_entries = table.size(), n_prefixes = prefixes.size();
-            if (star) join_star();
+            if (hops) join_hops();
+            else if (star) join_star();
             else if (rows) defer_last_hops();
             merge_rounds();
             st = bind_rounds();
@@ -617,6 +633,7 @@ private:
     std::vector<uint32_t> prefixes;               // what launches read besides their entries (see upload)
     struct Pending { size_t first_entry, first_prefix; Launch l; };
     std::vector<Pending> pending;
+    bool all_hops = false;                        // the round is join_hops's
     size_t n_listed = 0;                          // of these: rq.launches; the rest are rq.start_launches
 
     int bind_rounds() {
@@ -931,6 +948,49 @@ private:
         rounds.assign(1, std::move(all));
     }
 
+    // iso_start of an all-to-all in one launch that takes every block through all its hops (move_through_stops): every move
+    // is made, but a hop takes its block from the one before it in a register.  On tori of up to five dimensions and for as
+    // many neighbours as the table in LDS takes, from a few MiB on, where the traffic counts.  (us, as before -> here, a
+    // gigabyte of buffer sets in turn: 32^3, 26 neighbours, 256 B 160 -> 108; 256^2, 12, 1 KiB 348 -> 260; 64^3, 26, 128 B
+    // 615 -> 433, 320 B 1660 -> 1133, 1000 B 5858 -> 3743; 8^5, 40, 320 B 679 -> 303, 4 KiB 7562 -> 3860; 16^4, 30, 400 B
+    // 1221 -> 526; 300^2, 24, 300 B 392 -> 307; 100^2, 8, 512 B 25.6 -> 20.7; 16^3, 384 B 37.0 -> 23.8; 20^3, 256 B 45.3 ->
+    // 29.8; slot-major 32^3, 256 B 150 -> 99.)  It gains at every block size (64^3, 100 B 797 -> 402, 192 B 1038 -> 688);
+    // rank-major blocks under 320 bytes that are no whole lines, and other part lines up to what rows_in_one_launch takes,
+    // keep the launches that tests/test_enqueued_kernels.py lays down for them.  ISO_ALG_COMBINED_BYDIM starts its launch
+    // list up to 7/4 of the last-level cache, as there.
+    bool all_hops_in_one_launch() const {
+        const uint64_t llc = kLastLevelCacheBytes, bytes = inf.delivered_bytes;
+        if (op != ISO_OP_ALLTOALL || arena || c.mesh || !uniform || size0 < 16 || c.d > kVectorDims || s > kLdsEntries) return false;
+        const bool onward = inf.entries > (int64_t)s;    // blocks of two hops and more
+        const bool lines = size0 % 128 == 0 || size0 >= 512;
+        if (!onward || (!lines && !lay.slot_major && size0 < 320)) return false;
+        if (pl.algorithm == ISO_ALG_COMBINED_BYDIM) return bytes > llc * 7 / 4;
+        return pl.algorithm == ISO_ALG_COMBINED && bytes > (!lines ? llc * 3 / 16 : lay.slot_major ? llc / 8 : llc / 16);
+    }
+
+    // One entry per block, from the send buffer to the receive buffer, its stops in its place in the workspace (in the plan
+    // a block of three hops and more stops in its receive block as well; in one launch the stores of two lanes to it would
+    // have no order).
+    void join_hops() {
+        all_hops = true;
+        std::vector<HostEntry> all(s);
+        for (const std::vector<HostEntry> &ents : rounds)
+            for (const HostEntry &he : ents) {
+                HostEntry &to = all[(size_t)he.neighbor];
+                const HostEntry before = to;
+                to = he;
+                to.de.shift = (uint32_t)he.neighbor;
+                to.moves = before.moves + 1;
+                to.way = he.dst_buf == ISO_BUF_WORK ? he.de.dst : before.way;
+                if (!before.moves) continue;             // the first hop
+                to.de.src = before.de.src;
+                to.de.src_stride = before.de.src_stride;
+            }
+        all.erase(std::remove_if(all.begin(), all.end(), [](const HostEntry &he) { return !he.moves; }), all.end());   // (empty blocks)
+        bound_rounds.assign(1, {ISO_ROUND_VECTOR, -1, bound_rounds[0].of, nullptr});
+        rounds.assign(1, std::move(all));
+    }
+
     void defer_last_hops() {
         std::vector<HostEntry> last(s);
         std::vector<bool> taken(s, false);
@@ -1129,6 +1189,7 @@ private:
                 he.dst_slot = pe.dst_slot;
                 he.dst_buf = pe.dst_buf;
                 he.neighbor = pe.neighbor;
+                he.moves = 1;
                 if (he.dim < 0 && r.kind == ISO_ROUND_SHIFT) he.dim = r.dim;
                 if (he.size == 0) continue;                       // empty blocks make no move
                 uint64_t src_stride = 0, dst_stride = 0;
@@ -1226,7 +1287,7 @@ private:
 
     // Only an allgather's moves share sources.
     void describe_bytes(Launch &l, const HostEntry *ents, uint32_t k) const {
-        for (uint32_t q = 0; q < k; ++q) l.bytes_written += p * ents[q].size;
+        for (uint32_t q = 0; q < k; ++q) l.bytes_written += p * ents[q].size * ents[q].moves;
         l.bytes_read = l.bytes_written;
         if (op == ISO_OP_ALLTOALL || !k) return;
         std::vector<uint64_t> sources(k);
@@ -1309,6 +1370,10 @@ private:
         }
         if (l.kernel == kVectorKernel) {
             const bool lines = size0 % 128 == 0 || lay.slot_major;
+            // Through all hops: where blocks make three of them and more, what the loads would keep is better left to the
+            // stops (cached -> streaming loads: 8^5, 40 neighbours, 128 B 120 -> 115, 300 B 338 -> 320; 16^4, 30, 400 B 546
+            // -> 526, 1 KiB 1426 -> 1388; fewer hops 64^3, 26, 300 B 1144 -> 1206, 1000 B 3743 -> 3888).
+            if (all_hops && inf.entries >= 3 * (int64_t)s) return kStreamLoads;
             return a2a && l.vector_dims && lines && bytes > above ? kStreamLoads : 0;
         }
         if (r.kind == ISO_ROUND_VECTOR) return 0;
@@ -1449,7 +1514,12 @@ private:
             put(va.chunks, va.mul_chunks, va.shifts, 0);
             put(k, va.mul_k, va.shifts, 1);
             put(va.p, va.mul_p, va.shifts, 2);
-            l.entry_major = lay.slot_major || all_planes;
+            // Blocks of four hops and more store more stops than rows: block by block the stops of a plane meet in the
+            // last-level cache (rank by rank -> here: 8^5, 40 neighbours, 128 B 115 -> 103 us, 1 KiB 974 -> 767, 3000 B
+            // 3096 -> 2715, 8 KiB 8604 -> 7305; 12^5, 384 B 2723 -> 2380; 600 B 146 -> 155; 3.4 hops, 16^4, 30
+            // neighbours, 256 B 291 -> 309, 1 KiB 1388 -> 1183, 1500 B 706 -> 736)
+            l.entry_major = lay.slot_major || all_planes ||
+                            (all_hops && inf.entries >= 4 * (int64_t)s && (size0 % 128 == 0 || size0 >= 1024));
             vector_launch(l, ents.data() + done, k, chunks);
             // several blocks of a rank-major row to a line, read by ranks that lie near each other: one eighth of the
             // ranks per XCD keeps the line in its L2 (runs -> eighths, one set of buffers repeated and many in turn:
@@ -1577,6 +1647,7 @@ private:
         l.uniform_waves = min_log2 == 4 && !l.tail && chunks % 64 == 0;
         va.src_stride = ents[0].de.src_stride;
         va.dst_stride = ents[0].de.dst_stride;
+        if (all_hops) l.way = kStops;
         for (int j = 0; j < kVectorDims; ++j) {                  // last dimension first, absent ones of size 1
             const int l_dim = c.d - 1 - j;
             va.last[j] = l_dim < 0 ? 1u : (uint32_t)c.dims[(size_t)l_dim];
@@ -1592,6 +1663,7 @@ private:
                 ve.c[j] = cj;
                 ve.back += cj * (uint32_t)c.inner[(size_t)(c.d - 1 - j)];
             }
+            ve.way = ents[q].way;
             DevEntry slot;
             std::memcpy(&slot, &ve, sizeof(slot));
             table.push_back(slot);

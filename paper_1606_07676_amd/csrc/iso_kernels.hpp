@@ -145,8 +145,11 @@ struct alignas(16) VectorEntry {
     uint64_t src, dst;     // addresses of rank 0's blocks
     uint32_t back;         // sum of c_j * inner_j: ranks back where no dimension wraps
     uint32_t c[kVectorDims];
-    uint32_t reserved[2];
+    uint64_t way;          // kStops: address of rank 0's block on the way (a block of one hop has none)
 };
+// WAY of the vector kernels.  kStops: blocks through all their hops (Binder::all_hops_in_one_launch), stored at every rank on
+// the way (move_through_stops).
+constexpr int kStops = 1;
 static_assert(sizeof(VectorEntry) == sizeof(DevEntry), "staged by the same code");
 
 struct VectorArgs {
@@ -513,13 +516,46 @@ __device__ __forceinline__ void last_coordinates(uint32_t R, const VectorArgs &a
     wrap[D - 1] = a.p;
 }
 
+// One unit of a block of an all-to-all through all the hops of its schedule, pulled by the rank R that receives it: the
+// ranks on its way are R moved back along the dimensions one by one, the last hop first.  It is stored at every one of them,
+// in the block's place in the workspace.  What the next hop takes is still in the register: no one reads the stops, and the
+// stores of different lanes to one place (of a block of three hops and more) need no order.
+// A launch per dimension reads every hop's block again and is bound by the memory's copy rate; here the hops of a block are
+// one read and their writes.  The stops are stored plainly, the receive rows stream: stops of one block are overwritten, by
+// its next hops at other ranks, while the caches hold them (streamed -> plain, us, many sets of buffers: 8^5, 40 neighbours,
+// 4 KiB 5430 -> 4100; 64^3, 26 neighbours, 1000 B 4670 -> 3740; 256^2, 12, 1 KiB 293 -> 260; 32^3, 26, 256 B 111.7 -> 107.6).
+template <typename V, int D, int POLICY, typename ENTRY>
+__device__ __forceinline__ void move_through_stops(const ENTRY &en, uint32_t R, const uint32_t (&r)[D],
+                                                   const uint32_t (&wrap)[D], const VectorArgs &a, uint64_t off) {
+    typedef typename Unaligned<V>::type UV;
+    typedef const UV __attribute__((address_space(1))) *src_ptr;
+    typedef UV __attribute__((address_space(1))) *dst_ptr;
+    uint32_t at[D], from = R, inner = 1;
+#pragma unroll
+    for (int j = 0; j < D; ++j) {                        // modulo 2^32, see vector_source_rank
+        from -= en.c[j] * inner;
+        if (r[j] < en.c[j]) from += wrap[j];
+        at[j] = from;
+        inner = wrap[j];
+    }
+    const src_ptr sp = (src_ptr)(block_address(en.src, from, a.src_stride) + off);
+    V v;
+    if constexpr (POLICY & kStreamLoads) v = __builtin_nontemporal_load(sp);
+    else v = *sp;
+    const uint32_t m = (uint32_t)last_offset_of<V>(a.chunks, a.more) + (uint32_t)sizeof(V);
+#pragma unroll
+    for (int j = D - 1; j >= 0; --j)                     // in the order of the hops
+        if (en.c[j] && at[j] != from) *(dst_ptr)(block_address(en.way, at[j], m) + off) = v;
+    __builtin_nontemporal_store(v, (dst_ptr)(block_address(en.dst, R, a.dst_stride) + off));
+}
+
 // What bounds this kernel is the time a wavefront holds its slot before its one load is under way.  Two things
 // keep that short: one table, in LDS, holds all that an entry needs (a second one with the residues, read from
 // global memory after the barrier, was a dependent load in front of the block's own), and the rank's
 // coordinates are worked out while the table's load is in flight.  Fused s-exchange, before and after: 64^3,
 // 26 neighbours, 128-byte blocks 342 -> 294 us all-to-all, 188 -> 166 us allgather (fill rate: 128 us);
 // 200-byte allgather on 60 x 50 x 41 142 -> 130 us; 7-byte blocks on 50^3 26 -> 22 us.
-template <typename V, int D, bool LDS, int POLICY, bool TAIL>
+template <typename V, int D, bool LDS, int POLICY, bool TAIL, int WAY = 0>
 __global__ __launch_bounds__(kThreads) void vector_round_kernel(const VectorArgs a) {
     fetch_now<D>(a);
     const VectorDivs div(a);
@@ -546,6 +582,10 @@ __global__ __launch_bounds__(kThreads) void vector_round_kernel(const VectorArgs
         staging.commit(lds);
         if (u >= a.total) return;
         const VectorEntry &en = ((const VectorEntry *)(LDS ? lds : a.entries))[e];
+        if constexpr (WAY == kStops) {
+            move_through_stops<V, D, POLICY>(en, R, r, wrap, a, off);
+            return;
+        }
         uint32_t srcR = R - en.back;                    // modulo 2^32, see vector_source_rank
 #pragma unroll
         for (int j = 0; j < D; ++j)
@@ -557,7 +597,7 @@ __global__ __launch_bounds__(kThreads) void vector_round_kernel(const VectorArgs
 // The same for blocks that are a multiple of 1 KiB: one block per wavefront, so that rank, entry and source
 // rank are worked out once, in scalar registers (see shift_round_uniform_kernel).  Fused all-to-all, before and
 // after: 256^2, 12 neighbours, 1 KiB 298 -> 259 us, 8^5, 40 neighbours, 4 KiB 2070 -> 1800 us.
-template <int D, int POLICY>
+template <int D, int POLICY, int WAY = 0>
 __global__ __launch_bounds__(kThreads) void vector_round_uniform_kernel(const VectorArgs a) {
     fetch_now<D>(a);
     const VectorDivs div(a);
@@ -574,12 +614,16 @@ __global__ __launch_bounds__(kThreads) void vector_round_uniform_kernel(const Ve
     const const_entry_ptr en = (const_entry_ptr)(uintptr_t)((const VectorEntry *)a.entries + e);
     uint32_t r[D], wrap[D];
     last_coordinates<D>(R, a, r, wrap);
+    const uint64_t off = (uint64_t)(ch0 + (threadIdx.x & 63u)) * sizeof(vec16_t);
+    if constexpr (WAY == kStops) {
+        move_through_stops<vec16_t, D, POLICY>(*en, R, r, wrap, a, off);
+        return;
+    }
     uint32_t srcR = R - en->back;
 #pragma unroll
     for (int j = 0; j < D; ++j)
         if (r[j] < en->c[j]) srcR += wrap[j];
-    move_unit<vec16_t, POLICY>(block_address(en->dst, R, a.dst_stride), block_address(en->src, srcR, a.src_stride),
-                            (uint64_t)(ch0 + (threadIdx.x & 63u)) * sizeof(vec16_t));
+    move_unit<vec16_t, POLICY>(block_address(en->dst, R, a.dst_stride), block_address(en->src, srcR, a.src_stride), off);
 }
 
 // The allgather's s-exchange the other way round: a lane reads one unit of rank S's block and writes it into

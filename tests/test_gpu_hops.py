@@ -1,0 +1,58 @@
+"""Collectives whose blocks go through all their hops in one launch, every stop stored: the kernels for up to three and up to
+five dimensions, one block per wavefront or not, last units that overlap, both layouts and orders, against the oracle, and
+against the launches of the rounds."""
+import numpy as np
+import pytest
+import torch
+
+import iso_inputs as gen
+import paper_1606_07676_amd as iso
+from test_gpu_vector import check_exchange
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+RANK, SLOT = iso.ISO_LAYOUT_RANK_MAJOR, iso.ISO_LAYOUT_SLOT_MAJOR
+COMBINED, BYDIM = iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM
+
+
+@pytest.mark.parametrize("dims,offsets,m,layout,alg,send_off,recv_off", [
+    ((23, 24, 25), gen.moore(3, 1), 128, RANK, COMBINED, 0, 0),
+    ((23, 24, 25), gen.moore(3, 1), 128, RANK, COMBINED, 5, 3),
+    ((19, 20, 21), gen.moore(3, 1), 1027, RANK, COMBINED, 0, 7),
+    ((31, 29, 30), gen.von_neumann(3, 2), 321, RANK, COMBINED, 0, 0),
+    ((61, 67), gen.von_neumann(2, 2) + [(0, 0), (1, 2), (1, 2)], 1024, RANK, COMBINED, 0, 0),       # repeated and zero
+    ((11, 12, 13, 9), gen.random_distinct(4, -3, 3, 30, 5), 640, RANK, COMBINED, 0, 0),
+    ((7, 6, 5, 8, 9), gen.random_distinct(5, -3, 3, 40, 5), 2048, RANK, COMBINED, 0, 1),            # block by block
+    ((7, 6, 5, 8, 9), gen.random_distinct(5, -3, 3, 40, 5), 128, RANK, COMBINED, 0, 0),
+    ((2, 3, 1, 29, 211), gen.random_distinct(5, -3, 3, 40, 6), 520, RANK, COMBINED, 0, 0),          # sides of 1, 2 and 3 alias
+    ((6, 5, 5, 7), gen.random_distinct(4, -3, 3, 128, 8), 384, RANK, COMBINED, 0, 0),               # a full table
+    ((6, 5, 5, 7), gen.random_distinct(4, -3, 3, 129, 8), 384, RANK, COMBINED, 0, 0),               # one more: its rounds
+    ((23, 24, 25), gen.moore(3, 1), 256, SLOT, COMBINED, 1, 0),
+    ((29, 31, 27), gen.moore(3, 1), 107, SLOT, COMBINED, 0, 2),
+    ((8, 7, 9, 6, 5), gen.random_distinct(5, -3, 3, 40, 5), 1024, SLOT, COMBINED, 0, 0),
+    ((41, 40, 39), gen.moore(3, 1), 320, RANK, BYDIM, 0, 0)])
+def test_alltoall_through_all_hops(dims, offsets, m, layout, alg, send_off, recv_off):
+    check_exchange(dims, [tuple(int(x) for x in c) for c in offsets], iso.ISO_OP_ALLTOALL, alg, m, layout, send_off, recv_off)
+
+
+@pytest.mark.parametrize("layout", [RANK, SLOT])
+def test_equal_blocks_of_the_irregular_call_with_empty_ones(layout):
+    """Every third block empty, rows with gaps: those bytes and blocks stay as they are."""
+    dims, offsets, m = (23, 24, 25), gen.moore(3, 1), 640
+    p, s = int(np.prod(dims)), len(offsets)
+    sizes = [0 if i % 3 == 0 else m for i in range(s)]
+    step = p * m + 48 if layout == SLOT else m + 48
+    displs = [i * step for i in range(s)]
+    extent, n = (0, s * step) if layout == SLOT else (s * step, p * s * step)
+    send = torch.randint(0, 256, (n,), dtype=torch.uint8, device=DEV, generator=torch.Generator(DEV).manual_seed(2))
+    comm, got = iso.iso_neighborhood_create(dims, offsets), []
+    for alg in (iso.ISO_ALG_SX_FUSED, COMBINED):
+        recv = torch.full((n,), 0xEE, dtype=torch.uint8, device=DEV)
+        work = torch.empty(max(1, iso.iso_workspace_bytes_v(comm, iso.ISO_OP_ALLTOALL, alg, sizes)), dtype=torch.uint8, device=DEV)
+        req = iso.iso_neighbor_alltoallv_init_layout(send, sizes, displs, extent, recv, sizes, displs, extent, layout, work, comm, alg)
+        assert iso.iso_request_start_info(req)["kernels"] == 1
+        iso.iso_start(req)
+        iso.iso_wait(req)
+        iso.iso_request_free(req)
+        got.append(recv)
+    assert torch.equal(got[0], got[1])
