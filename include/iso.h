@@ -59,17 +59,17 @@ enum iso_algorithm {
      * takes moves that touch disjoint blocks together in one kernel launch: the
      * rounds of one dimension; where every block makes one move, all rounds; in
      * all-to-alls of small or odd blocks the last move of every block, so that
-     * receive rows are written whole; in all-to-alls beyond a few MiB all moves, every
-     * block handed on from hop to hop inside the kernel and stored at every stop, for
-     * which its place in the workspace serves.  All-to-all uses the alternating receive/intermediate buffer
+     * receive rows are written whole; in collectives beyond a few MiB all moves, every
+     * block handed on from hop to hop inside the kernel and stored at every stop (an
+     * all-to-all's in its place in the workspace).  All-to-all uses the alternating receive/intermediate buffer
      * rule of Algorithm 1; allgather routes along the prefix trie of
      * Section 3.2. */
     ISO_ALG_COMBINED       = 0,
     /* Same schedule, all rounds of one dimension as a single round of the plan and
      * of the launch list (they touch disjoint blocks; the k-ported remark of
      * Section 3).  iso_start takes the launch list, but well above the last-level
-     * cache: there all moves of an all-to-all go together, or its receive rows are
-     * written whole, as above. */
+     * cache: there all moves go together, or an all-to-all's receive rows are written
+     * whole, as above. */
     ISO_ALG_COMBINED_BYDIM = 1,
     /* Straightforward algorithm (first listing of Section 3): one exchange,
      * here one launch, per neighbour; s launches. */
@@ -188,8 +188,8 @@ typedef struct {
                                   * kernels, or fewer (iso_request_start_info): ISO_ALG_COMBINED
                                   * takes the rounds of a dimension together and single moves
                                   * out of the send buffer all at once, it and
-                                  * ISO_ALG_COMBINED_BYDIM all moves of an all-to-all, or the
-                                  * last ones into small or odd blocks; small collectives of the three combined algorithms
+                                  * ISO_ALG_COMBINED_BYDIM all moves of large collectives, or
+                                  * the last ones into small or odd blocks; small collectives of the three combined algorithms
                                   * run all their rounds in one kernel                      */
     int32_t vector_bytes;        /* width of the loads/stores: the largest power of two that is
                                   * at most 16 and at most the smallest non-empty block; buffer

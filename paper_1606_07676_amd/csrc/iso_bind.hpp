@@ -241,16 +241,21 @@ KernelRef select_way(const Launch &l) {
         if (l.uniform_waves) return {(const void *)&vector_round_uniform_kernel<D, pol(), WAY>, &l.vec};
         return {(const void *)&vector_round_kernel<vec16_t, D, true, pol(), TAIL, WAY>, &l.vec};
     };
-    if (l.policy & kStreamLoads) return form(std::integral_constant<int, kStreamLoads>());
+    if constexpr (WAY == kStrides) {                     // (an allgather loads through the caches)
+        if (l.vec.per) return {(const void *)&push_round_kernel<vec16_t, D, TAIL, WAY>, &l.vec};
+    } else {
+        if (l.policy & kStreamLoads) return form(std::integral_constant<int, kStreamLoads>());
+    }
     return form(std::integral_constant<int, 0>());
 }
 
 // The s-exchange with VectorEntry records (see vector_launch).
 template <typename V, int D, bool TAIL>
 KernelRef select_vector(const Launch &l) {
-    if (l.vec.per) return {(const void *)&push_round_kernel<V, D, TAIL>, &l.vec};
+    if (l.vec.per && !l.way) return {(const void *)&push_round_kernel<V, D, TAIL>, &l.vec};
     if constexpr (sizeof(V) == 16) {
         if (l.way == kStops) return select_way<D, TAIL, kStops>(l);
+        if (l.way == kStrides) return select_way<D, TAIL, kStrides>(l);
         if (l.uniform_waves) {
             if (l.policy & kStreamLoads) return {(const void *)&vector_round_uniform_kernel<D, kStreamLoads>, &l.vec};
             return {(const void *)&vector_round_uniform_kernel<D, 0>, &l.vec};
@@ -434,7 +439,10 @@ struct HostEntry {
     DevEntry de;
     uint64_t size;
     int dim, dst_buf, dst_slot, neighbor;
-    uint32_t moves;        // of the plan that the entry stands for (more than one: see join_hops)
+    // launches that take blocks through all their hops (join_hops)
+    uint32_t moves;        // of the plan that the entry stands for
+    uint32_t along;        // the dimensions that it moves along, of its neighbour's vector
+    uint64_t reads;        // the block that its last move reads in the plan
     uint64_t way;          // VectorEntry::way
 };
 
@@ -948,44 +956,72 @@ private:
         rounds.assign(1, std::move(all));
     }
 
-    // iso_start of an all-to-all in one launch that takes every block through all its hops (move_through_stops): every move
-    // is made, but a hop takes its block from the one before it in a register.  On tori of up to five dimensions and for as
-    // many neighbours as the table in LDS takes, from a few MiB on, where the traffic counts.  (us, as before -> here, a
-    // gigabyte of buffer sets in turn: 32^3, 26 neighbours, 256 B 160 -> 108; 256^2, 12, 1 KiB 348 -> 260; 64^3, 26, 128 B
-    // 615 -> 433, 320 B 1660 -> 1133, 1000 B 5858 -> 3743; 8^5, 40, 320 B 679 -> 303, 4 KiB 7562 -> 3860; 16^4, 30, 400 B
-    // 1221 -> 526; 300^2, 24, 300 B 392 -> 307; 100^2, 8, 512 B 25.6 -> 20.7; 16^3, 384 B 37.0 -> 23.8; 20^3, 256 B 45.3 ->
-    // 29.8; slot-major 32^3, 256 B 150 -> 99.)  It gains at every block size (64^3, 100 B 797 -> 402, 192 B 1038 -> 688);
-    // rank-major blocks under 320 bytes that are no whole lines, and other part lines up to what rows_in_one_launch takes,
-    // keep the launches that tests/test_enqueued_kernels.py lays down for them.  ISO_ALG_COMBINED_BYDIM starts its launch
-    // list up to 7/4 of the last-level cache, as there.
+    // iso_start in one launch (one for each table that LDS takes) of all blocks through all their hops: every move is made, but a hop takes its block from
+    // the one before it in a register (move_through_stops), in an allgather from the send buffer as all others do.  On tori
+    // of up to five dimensions, from a few MiB on, where the traffic counts.
+    // All-to-all (us, as before -> here, a gigabyte of buffer sets in turn): 32^3, 26 neighbours, 256 B 160 -> 108; 256^2, 12,
+    // 1 KiB 348 -> 304; 64^3, 26, 128 B 615 -> 433, 320 B 1660 -> 1133, 1000 B 5858 -> 3743; 8^5, 40, 320 B 679 -> 303, 4 KiB
+    // 7562 -> 3800; 16^4, 30, 400 B 1221 -> 526; 300^2, 24, 300 B 392 -> 307; 100^2, 8, 512 B 25.6 -> 20.7; 16^3, 384 B 37.0 ->
+    // 23.8; 20^3, 256 B 45.3 -> 29.8; slot-major 32^3, 256 B 150 -> 99.
+    // Allgather: 64^3, 26 neighbours, 128 B 205 -> 135; 20^3, 128 B 13.8 -> 6.8; 32^3, 1000 B 282 -> 150; 300^2, 24, 512 B 229
+    // -> 157, 10, 1300 B 436 -> 265; 8^5, 40, 500 B 823 -> 459, 4 KiB 5187 -> 2975; 16^4, 30, 256 B 386 -> 222; slot-major 64^3,
+    // 128 B 197 -> 152, 100 B 168 -> 128.
+    // It gains at every block size (all-to-all 64^3, 100 B 797 -> 402, 192 B 1038 -> 688; allgather 13 x 11 x 12 x 9 x 8, 40
+    // neighbours, 200 B 1563 -> 895).  Rank-major blocks that are no whole lines, of under 320 bytes (allgather 256), and
+    // all-to-alls of other part lines up to what rows_in_one_launch takes, keep the launches that
+    // tests/test_enqueued_kernels.py lays down for them.  ISO_ALG_COMBINED_BYDIM starts its launch list up to 7/4 of the
+    // last-level cache, as there.
     bool all_hops_in_one_launch() const {
         const uint64_t llc = kLastLevelCacheBytes, bytes = inf.delivered_bytes;
-        if (op != ISO_OP_ALLTOALL || arena || c.mesh || !uniform || size0 < 16 || c.d > kVectorDims || s > kLdsEntries) return false;
-        const bool onward = inf.entries > (int64_t)s;    // blocks of two hops and more
-        const bool lines = size0 % 128 == 0 || size0 >= 512;
-        if (!onward || (!lines && !lay.slot_major && size0 < 320)) return false;
+        const bool a2a = op == ISO_OP_ALLTOALL, lines = size0 % 128 == 0 || size0 >= 512;
+        if (arena || c.mesh || !uniform || size0 < 16 || c.d > kVectorDims) return false;
+        bool onward = false;                             // a hop of what another one has brought
+        for (const Round &r : pl.rounds)
+            for (const iso_plan_entry_t &e : r.entries) onward = onward || e.src_buf != ISO_BUF_SEND;
+        if (!onward || (!lines && !lay.slot_major && size0 < (a2a ? 320u : 256u))) return false;
         if (pl.algorithm == ISO_ALG_COMBINED_BYDIM) return bytes > llc * 7 / 4;
-        return pl.algorithm == ISO_ALG_COMBINED && bytes > (!lines ? llc * 3 / 16 : lay.slot_major ? llc / 8 : llc / 16);
+        if (pl.algorithm != ISO_ALG_COMBINED) return false;
+        return bytes > (!a2a ? llc / 64 : !lines ? llc * 3 / 16 : lay.slot_major ? llc / 8 : llc / 16);
     }
 
-    // One entry per block, from the send buffer to the receive buffer, its stops in its place in the workspace (in the plan
-    // a block of three hops and more stops in its receive block as well; in one launch the stores of two lanes to it would
-    // have no order).
+    // All-to-all: one entry per block, from the send buffer to the receive buffer, its stops in its place in the workspace (in
+    // the plan a block of three hops and more stops in its receive block as well; in one launch the stores of two lanes to it
+    // would have no order).  Allgather: an entry for every node of the trie, all from the send buffer; what lies in the
+    // workspace is read by no one, so that nodes may share a place there.
     void join_hops() {
         all_hops = true;
-        std::vector<HostEntry> all(s);
-        for (const std::vector<HostEntry> &ents : rounds)
-            for (const HostEntry &he : ents) {
-                HostEntry &to = all[(size_t)he.neighbor];
+        const bool a2a = op == ISO_OP_ALLTOALL;
+        std::vector<HostEntry> all;
+        if (a2a) all.resize(s);
+        else all.reserve((size_t)inf.entries);
+        uint32_t routed = 0;                             // the dimensions up to that of the round
+        size_t next_dim = 0;
+        for (size_t ri = 0; ri < rounds.size(); ++ri) {
+            const BoundRound &r = bound_rounds[ri];
+            if (!a2a && r.kind == ISO_ROUND_SHIFT)
+                while (!(routed >> r.dim & 1u)) routed |= 1u << pl.dim_order[next_dim++];
+            for (const HostEntry &he : rounds[ri]) {
+                if (!a2a) all.push_back(HostEntry{});
+                HostEntry &to = a2a ? all[(size_t)he.neighbor] : all.back();
                 const HostEntry before = to;
                 to = he;
-                to.de.shift = (uint32_t)he.neighbor;
-                to.moves = before.moves + 1;
-                to.way = he.dst_buf == ISO_BUF_WORK ? he.de.dst : before.way;
-                if (!before.moves) continue;             // the first hop
-                to.de.src = before.de.src;
-                to.de.src_stride = before.de.src_stride;
+                if (a2a) {
+                    to.de.shift = (uint32_t)he.neighbor;
+                    to.moves = before.moves + 1;
+                    to.way = he.dst_buf == ISO_BUF_WORK ? he.de.dst : before.way;
+                    if (!before.moves) continue;         // the first hop
+                    to.de.src = before.de.src;
+                    to.de.src_stride = before.de.src_stride;
+                } else {
+                    uint64_t stride = 0;
+                    place(ISO_BUF_SEND, 0, to.de.src, stride);
+                    to.de.src_stride = (uint32_t)stride;
+                    to.de.shift = he.de.ref;
+                    to.along = he.dim < 0 ? 0u : routed;
+                    to.way = he.de.dst_stride;
+                }
             }
+        }
         all.erase(std::remove_if(all.begin(), all.end(), [](const HostEntry &he) { return !he.moves; }), all.end());   // (empty blocks)
         bound_rounds.assign(1, {ISO_ROUND_VECTOR, -1, bound_rounds[0].of, nullptr});
         rounds.assign(1, std::move(all));
@@ -1190,6 +1226,7 @@ private:
                 he.dst_buf = pe.dst_buf;
                 he.neighbor = pe.neighbor;
                 he.moves = 1;
+                he.along = ~0u;
                 if (he.dim < 0 && r.kind == ISO_ROUND_SHIFT) he.dim = r.dim;
                 if (he.size == 0) continue;                       // empty blocks make no move
                 uint64_t src_stride = 0, dst_stride = 0;
@@ -1197,6 +1234,7 @@ private:
                 place(pe.dst_buf, pe.dst_slot, he.de.dst, dst_stride);
                 // the kernels multiply a rank by a 32-bit stride
                 if ((src_stride | dst_stride) >> 32) return ISO_ERR_TOO_LARGE;
+                he.reads = he.de.src;
                 he.de.src_stride = (uint32_t)src_stride;
                 he.de.dst_stride = (uint32_t)dst_stride;
                 he.de.shift = r.kind == ISO_ROUND_VECTOR ? (uint32_t)pe.neighbor : (uint32_t)pe.shift;
@@ -1291,7 +1329,7 @@ private:
         l.bytes_read = l.bytes_written;
         if (op == ISO_OP_ALLTOALL || !k) return;
         std::vector<uint64_t> sources(k);
-        for (uint32_t q = 0; q < k; ++q) sources[q] = ents[q].de.src;
+        for (uint32_t q = 0; q < k; ++q) sources[q] = ents[q].reads;
         std::sort(sources.begin(), sources.end());
         l.bytes_read = p * ents[0].size * (uint64_t)(std::unique(sources.begin(), sources.end()) - sources.begin());
     }
@@ -1373,7 +1411,7 @@ private:
             // Through all hops: where blocks make three of them and more, what the loads would keep is better left to the
             // stops (cached -> streaming loads: 8^5, 40 neighbours, 128 B 120 -> 115, 300 B 338 -> 320; 16^4, 30, 400 B 546
             // -> 526, 1 KiB 1426 -> 1388; fewer hops 64^3, 26, 300 B 1144 -> 1206, 1000 B 3743 -> 3888).
-            if (all_hops && inf.entries >= 3 * (int64_t)s) return kStreamLoads;
+            if (all_hops && a2a && inf.entries >= 3 * (int64_t)s) return kStreamLoads;
             return a2a && l.vector_dims && lines && bytes > above ? kStreamLoads : 0;
         }
         if (r.kind == ISO_ROUND_VECTOR) return 0;
@@ -1498,6 +1536,10 @@ private:
         const uint64_t per_entry = p * chunks;
         if (chunks > 0x7FFFFFFFu || per_entry > kMaxUnits) return ISO_ERR_TOO_LARGE;
         k = (uint32_t)std::min<uint64_t>(kMaxUnits / per_entry, ents.size() - done);
+        if (all_hops) {                                  // a table in LDS for each launch, of equal parts
+            const uint32_t parts = ((uint32_t)ents.size() + kLdsEntries - 1) / kLdsEntries;
+            k = std::min(k, ((uint32_t)ents.size() + parts - 1) / parts);
+        }
         total = per_entry * k;
         l.kernel = r.kind == ISO_ROUND_VECTOR ? kVectorKernel : c.mesh ? kMeshShiftKernel : kShiftKernel;
         // one block per wavefront: blocks that are a multiple of 1 KiB; on rank-major buffers only up
@@ -1640,14 +1682,17 @@ private:
     void vector_launch(Launch &l, const HostEntry *ents, uint32_t k, uint64_t chunks) {
         VectorArgs &va = l.vec;
         bool packed = c.d <= kVectorDims && k <= kLdsEntries;
-        for (uint32_t q = 0; packed && q < k; ++q)
-            packed = ents[q].de.src_stride == ents[0].de.src_stride && ents[q].de.dst_stride == ents[0].de.dst_stride;
+        bool one_stride = true;
+        for (uint32_t q = 0; packed && q < k; ++q) {
+            one_stride = one_stride && ents[q].de.dst_stride == ents[0].de.dst_stride;
+            packed = ents[q].de.src_stride == ents[0].de.src_stride && (one_stride || all_hops);
+        }
         if (!packed) return;
         l.vector_dims = c.d <= 3 ? 3 : kVectorDims;
         l.uniform_waves = min_log2 == 4 && !l.tail && chunks % 64 == 0;
         va.src_stride = ents[0].de.src_stride;
         va.dst_stride = ents[0].de.dst_stride;
-        if (all_hops) l.way = kStops;
+        if (all_hops) l.way = op == ISO_OP_ALLTOALL ? kStops : one_stride ? 0 : kStrides;
         for (int j = 0; j < kVectorDims; ++j) {                  // last dimension first, absent ones of size 1
             const int l_dim = c.d - 1 - j;
             va.last[j] = l_dim < 0 ? 1u : (uint32_t)c.dims[(size_t)l_dim];
@@ -1659,6 +1704,7 @@ private:
             ve.src = ents[q].de.src;
             ve.dst = ents[q].de.dst;
             for (int j = 0; j < c.d; ++j) {
+                if (!(ents[q].along >> (c.d - 1 - j) & 1u)) continue;
                 const uint32_t cj = (uint32_t)c.c((int)ents[q].de.shift, c.d - 1 - j);
                 ve.c[j] = cj;
                 ve.back += cj * (uint32_t)c.inner[(size_t)(c.d - 1 - j)];
@@ -1687,10 +1733,15 @@ private:
     //   buffer for every entry.  Push from where that eighth no longer fits its L2 (64^3, 128 B 231 -> 152 us,
     //   300 B 563 -> 491; 25 MiB to send: pull 126, push 166).  Here push writes runs of consecutive ranks, 4
     //   entries at a time being 2 to 8 % faster than 8 or all.
+    //   Trie nodes in the workspace beside the receive blocks: push 4 at a time (8^5, 40 random neighbours, 4 KiB 2, 4, 8 at a
+    //   time 3507, 2975, 3029; 1 KiB slot-major 865, 724, 755; pull 3807 and 1085), slot-major also where the eighth fits, 2 at
+    //   a time (16^4, 30, 256 B pull 272, push 195; 300 B 350 and 311; 8^5, 500 B 495 and 415).
     void allgather_order(Launch &l, const HostEntry *ents, uint32_t k) {
         const uint64_t l2 = uint64_t(4) << 20, sent = p * size0;
+        const bool nodes = all_hops && pl.work_slots > 0;
         if (lay.slot_major) {
             if (l.vector_dims && sent > 7 * l2) l.vec.per = std::min(k, 4u);
+            else if (l.vector_dims && nodes) l.vec.per = std::min(k, 2u);
             return;
         }
         int64_t lo = 0, hi = 0;                                  // the neighbours' linear distances, shortest way round
@@ -1709,7 +1760,7 @@ private:
         const uint64_t run = uint64_t(128) * kThreads << min_log2;      // bytes written by a run of tiles (set_grid)
         l.eighths = sent > l2 && 4 * window_ranks * k * size0 > run;
         if (l.vector_dims && lines && (window > 3 * l2 || (window > l2 && sent > kLastLevelCacheBytes))) {
-            l.vec.per = std::min(k, 8u);
+            l.vec.per = std::min(k, nodes ? 4u : 8u);
             l.eighths = false;
         }
     }

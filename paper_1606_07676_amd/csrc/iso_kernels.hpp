@@ -145,11 +145,12 @@ struct alignas(16) VectorEntry {
     uint64_t src, dst;     // addresses of rank 0's blocks
     uint32_t back;         // sum of c_j * inner_j: ranks back where no dimension wraps
     uint32_t c[kVectorDims];
-    uint64_t way;          // kStops: address of rank 0's block on the way (a block of one hop has none)
+    uint64_t way;          // kStops: address of rank 0's block on the way (a block of one hop has none); kStrides: of `dst`
 };
-// WAY of the vector kernels.  kStops: blocks through all their hops (Binder::all_hops_in_one_launch), stored at every rank on
-// the way (move_through_stops).
-constexpr int kStops = 1;
+// WAY of the vector kernels, for launches that take blocks through all their hops (Binder::all_hops_in_one_launch).
+// kStops, all-to-all: a block is stored at every rank on its way as well (move_through_stops).  kStrides, allgather: every
+// node of the trie is an entry, in the receive buffer or in the workspace, with the stride of its own destination.
+constexpr int kStops = 1, kStrides = 2;
 static_assert(sizeof(VectorEntry) == sizeof(DevEntry), "staged by the same code");
 
 struct VectorArgs {
@@ -590,7 +591,8 @@ __global__ __launch_bounds__(kThreads) void vector_round_kernel(const VectorArgs
 #pragma unroll
         for (int j = 0; j < D; ++j)
             if (r[j] < en.c[j]) srcR += wrap[j];
-        move_unit<V, POLICY>(block_address(en.dst, R, a.dst_stride), block_address(en.src, srcR, a.src_stride), off);
+        const uint32_t dst_stride = WAY == kStrides ? (uint32_t)en.way : a.dst_stride;
+        move_unit<V, POLICY>(block_address(en.dst, R, dst_stride), block_address(en.src, srcR, a.src_stride), off);
     }
 }
 
@@ -623,14 +625,15 @@ __global__ __launch_bounds__(kThreads) void vector_round_uniform_kernel(const Ve
 #pragma unroll
     for (int j = 0; j < D; ++j)
         if (r[j] < en->c[j]) srcR += wrap[j];
-    move_unit<vec16_t, POLICY>(block_address(en->dst, R, a.dst_stride), block_address(en->src, srcR, a.src_stride), off);
+    const uint32_t dst_stride = WAY == kStrides ? (uint32_t)en->way : a.dst_stride;
+    move_unit<vec16_t, POLICY>(block_address(en->dst, R, dst_stride), block_address(en->src, srcR, a.src_stride), off);
 }
 
 // The allgather's s-exchange the other way round: a lane reads one unit of rank S's block and writes it into
 // the receive blocks of `per` neighbours (R = S (+) C^e), so the send buffer is read k / per times instead of
 // k times.  Taken where the pull form's reads miss the L2 (see vector_launch): they then cross the fabric
 // beside the writes, and both together were what bounded it.
-template <typename V, int D, bool TAIL>
+template <typename V, int D, bool TAIL, int WAY = 0>
 __global__ __launch_bounds__(kThreads) void push_round_kernel(const VectorArgs a) {
     fetch_now<D>(a);
     const VectorDivs div(a);
@@ -662,7 +665,8 @@ __global__ __launch_bounds__(kThreads) void push_round_kernel(const VectorArgs a
 #pragma unroll
         for (int j = 0; j < D; ++j)
             if (r[j] + en.c[j] >= a.last[j]) R -= wrap[j];
-        const dst_ptr dp = (dst_ptr)(block_address(en.dst, R, a.dst_stride) + off);
+        const uint32_t dst_stride = WAY == kStrides ? (uint32_t)en.way : a.dst_stride;
+        const dst_ptr dp = (dst_ptr)(block_address(en.dst, R, dst_stride) + off);
         if constexpr (sizeof(V) == 16) __builtin_nontemporal_store(v, dp);
         else *dp = v;
     }

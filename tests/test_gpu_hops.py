@@ -35,6 +35,25 @@ def test_alltoall_through_all_hops(dims, offsets, m, layout, alg, send_off, recv
     check_exchange(dims, [tuple(int(x) for x in c) for c in offsets], iso.ISO_OP_ALLTOALL, alg, m, layout, send_off, recv_off)
 
 
+@pytest.mark.parametrize("dims,offsets,m,layout,alg,send_off,recv_off", [
+    ((23, 24, 25), gen.moore(3, 1), 128, RANK, COMBINED, 0, 0),                                      # all nodes are receive blocks
+    ((23, 24, 25), gen.moore(3, 1), 257, RANK, COMBINED, 3, 1),
+    ((61, 67), gen.moore(2, 2) + [(0, 0), (1, 2), (1, 2)], 1024, RANK, COMBINED, 0, 0),
+    ((23, 24, 25), gen.random_distinct(3, -3, 3, 20, 5) + [(0, 0, 0), (2, -2, 1), (2, -2, 1)], 1000, RANK, COMBINED, 0, 0),
+    ((7, 6, 5, 8, 9), gen.random_distinct(5, -3, 3, 40, 5), 128, RANK, COMBINED, 0, 0),              # pull, an order of its own
+    ((8, 9, 8, 7, 5), gen.random_distinct(5, -3, 3, 36, 7), 1152, RANK, COMBINED, 0, 0),             # push
+    ((8, 9, 8, 7, 5), gen.random_distinct(5, -3, 3, 36, 7), 1152, RANK, COMBINED, 0, 16),
+    ((8, 9, 8, 7, 5), gen.random_distinct(5, -3, 3, 36, 7), 1025, RANK, COMBINED, 0, 16),
+    ((2, 3, 1, 29, 211), gen.random_distinct(5, -3, 3, 30, 6), 640, RANK, COMBINED, 0, 0),
+    ((9, 8, 7, 11), gen.random_distinct(4, -3, 3, 30, 5), 100, SLOT, COMBINED, 0, 0),                # push, 2 at a time
+    ((33, 31, 35), gen.random_distinct(3, -3, 3, 9, 5), 900, SLOT, COMBINED, 0, 5),                  # 4 at a time
+    ((23, 24, 25), gen.moore(3, 1), 16, SLOT, COMBINED, 0, 0),
+    ((41, 40, 39), gen.moore(3, 1), 320, RANK, BYDIM, 0, 0),
+    ((8, 9, 8, 7, 5), gen.random_distinct(5, -3, 3, 36, 7), 1024, RANK, BYDIM, 0, 0)])
+def test_allgather_through_all_hops(dims, offsets, m, layout, alg, send_off, recv_off):
+    check_exchange(dims, [tuple(int(x) for x in c) for c in offsets], iso.ISO_OP_ALLGATHER, alg, m, layout, send_off, recv_off)
+
+
 @pytest.mark.parametrize("layout", [RANK, SLOT])
 def test_equal_blocks_of_the_irregular_call_with_empty_ones(layout):
     """Every third block empty, rows with gaps: those bytes and blocks stay as they are."""
