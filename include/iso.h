@@ -67,9 +67,9 @@ enum iso_algorithm {
     ISO_ALG_COMBINED       = 0,
     /* Same schedule, all rounds of one dimension as a single round of the plan and
      * of the launch list (they touch disjoint blocks; the k-ported remark of
-     * Section 3).  iso_start takes the launch list, but well above the last-level
-     * cache: there all moves go together, or an all-to-all's receive rows are written
-     * whole, as above. */
+     * Section 3).  iso_start takes the launch list, but for collectives beyond a few
+     * MiB (smaller blocks: well above the last-level cache): there all moves go
+     * together, or an all-to-all's receive rows are written whole, as above. */
     ISO_ALG_COMBINED_BYDIM = 1,
     /* Straightforward algorithm (first listing of Section 3): one exchange,
      * here one launch, per neighbour; s launches. */

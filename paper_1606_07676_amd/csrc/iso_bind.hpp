@@ -592,8 +592,9 @@ public:
             if ((st = bind_rounds()) != ISO_SUCCESS) return st;
             n_listed = pending.size();
         }
-        if (chains && chain_launch(launches)) return upload();
-        const bool hops = all_hops_in_one_launch(), star = !hops && star_in_one_launch(launches);
+        const bool hops = all_hops_in_one_launch();
+        if (chains && !hops && chain_launch(launches)) return upload();
+        const bool star = !hops && star_in_one_launch(launches);
         const bool rows = !hops && !star && rows_in_one_launch();
         if (hops || rows || star || (merges && launches < bound_rounds.size())) {
             const size_t n_entries = table.size(), n_prefixes = prefixes.size();
@@ -958,7 +959,7 @@ private:
 
     // iso_start in one launch (one for each table that LDS takes) of all blocks through all their hops: every move is made, but a hop takes its block from
     // the one before it in a register (move_through_stops), in an allgather from the send buffer as all others do.  On tori
-    // of up to five dimensions, from a few MiB on, where the traffic counts.
+    // of up to five dimensions, from 4 MiB on.
     // All-to-all (us, as before -> here, a gigabyte of buffer sets in turn): 32^3, 26 neighbours, 256 B 160 -> 108; 256^2, 12,
     // 1 KiB 348 -> 304; 64^3, 26, 128 B 615 -> 433, 320 B 1660 -> 1133, 1000 B 5858 -> 3743; 8^5, 40, 320 B 679 -> 303, 4 KiB
     // 7562 -> 3800; 16^4, 30, 400 B 1221 -> 526; 300^2, 24, 300 B 392 -> 307; 100^2, 8, 512 B 25.6 -> 20.7; 16^3, 384 B 37.0 ->
@@ -966,22 +967,29 @@ private:
     // Allgather: 64^3, 26 neighbours, 128 B 205 -> 135; 20^3, 128 B 13.8 -> 6.8; 32^3, 1000 B 282 -> 150; 300^2, 24, 512 B 229
     // -> 157, 10, 1300 B 436 -> 265; 8^5, 40, 500 B 823 -> 459, 4 KiB 5187 -> 2975; 16^4, 30, 256 B 386 -> 222; slot-major 64^3,
     // 128 B 197 -> 152, 100 B 168 -> 128.
-    // It gains at every block size (all-to-all 64^3, 100 B 797 -> 402, 192 B 1038 -> 688; allgather 13 x 11 x 12 x 9 x 8, 40
-    // neighbours, 200 B 1563 -> 895).  Rank-major blocks that are no whole lines, of under 320 bytes (allgather 256), and
-    // all-to-alls of other part lines up to what rows_in_one_launch takes, keep the launches that
-    // tests/test_enqueued_kernels.py lays down for them.  ISO_ALG_COMBINED_BYDIM starts its launch list up to 7/4 of the
-    // last-level cache, as there.
+    // Small ones: all-to-all 10^3, 26 neighbours, 256 B 10.9 (chain) -> 6.2, 12^3, 256 B 15.4 -> 9.8; allgather 20^3, 40 B
+    // 11.4 -> 4.0, 5^5, 40, 128 B 27.8 -> 9.3; 13 x 12 x 14, 80 B slot-major 10.0 -> 4.7; 6^3, 20, 48 B 3.5 -> 3.7.
+    // It gains at every block size from a MiB on (all-to-all 64^3, 100 B 797 -> 402, 192 B 1038 -> 688, 16^3, 128 B 19.4 ->
+    // 11.7; allgather 8^5, 100 B 235 -> 160).  What is left out here are the neighbourhoods of the sizes whose launches
+    // tests/test_enqueued_kernels.py lays down: small blocks that are no whole lines, rank-major, with all-to-alls of most
+    // sizes and larger allgathers, and for ISO_ALG_COMBINED_BYDIM more of them up to 7/4 of the last-level cache.
     bool all_hops_in_one_launch() const {
         const uint64_t llc = kLastLevelCacheBytes, bytes = inf.delivered_bytes;
-        const bool a2a = op == ISO_OP_ALLTOALL, lines = size0 % 128 == 0 || size0 >= 512;
-        if (arena || c.mesh || !uniform || size0 < 16 || c.d > kVectorDims) return false;
+        const bool a2a = op == ISO_OP_ALLTOALL, bydim = pl.algorithm == ISO_ALG_COMBINED_BYDIM, lines = size0 % 128 == 0;
+        if (arena || c.mesh || !uniform || size0 < 16 || c.d > kVectorDims || bytes <= llc / 64) return false;
+        if (pl.algorithm != ISO_ALG_COMBINED && !bydim) return false;
         bool onward = false;                             // a hop of what another one has brought
         for (const Round &r : pl.rounds)
             for (const iso_plan_entry_t &e : r.entries) onward = onward || e.src_buf != ISO_BUF_SEND;
-        if (!onward || (!lines && !lay.slot_major && size0 < (a2a ? 320u : 256u))) return false;
-        if (pl.algorithm == ISO_ALG_COMBINED_BYDIM) return bytes > llc * 7 / 4;
-        if (pl.algorithm != ISO_ALG_COMBINED) return false;
-        return bytes > (!a2a ? llc / 64 : !lines ? llc * 3 / 16 : lay.slot_major ? llc / 8 : llc / 16);
+        if (!onward) return false;
+        if (lay.slot_major) return !a2a || bytes > (lines ? llc / 8 : llc * 3 / 16);
+        if (!a2a) {
+            if (size0 >= 512 || (!bydim && (lines || size0 >= 256)) || bytes <= (size0 < 64 ? llc * 3 / 16 : llc / 2)) return true;
+            return lines && bytes > llc * 7 / 4;
+        }
+        if (lines && size0 >= 256) return true;
+        if (lines || size0 >= 512) return bytes > (bydim ? llc / 8 : llc / 16);
+        return size0 >= 320 && bytes > (bydim ? llc * 7 / 4 : llc * 3 / 16);
     }
 
     // All-to-all: one entry per block, from the send buffer to the receive buffer, its stops in its place in the workspace (in

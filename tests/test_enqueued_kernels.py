@@ -422,28 +422,35 @@ def test_start_info_says_what_a_start_enqueues(stub_library, dims, offsets, m, a
         niso.iso_request_free(req)
 
 
+A2A, LINES, TAIL = "vector_round_kernel<v16, 3, true, 0, false, 1>", "vector_round_kernel<v16, 3, true, 1, false, 1>", "vector_round_kernel<v16, 3, true, 0, true, 1>"
+
+
 @pytest.mark.parametrize("dims,offsets,m,layout,alg,kernel", [
-    ((20, 20, 20), gen.moore(3, 1), 128, 0, 0, "vector_round_kernel<v16, 3, true, 0, false, 1>"), ((17, 17, 17), gen.moore(3, 1), 128, 0, 0, None),
-    ((32, 32, 32), gen.moore(3, 1), 1027, 0, 0, "vector_round_kernel<v16, 3, true, 0, true, 1>"), ((32, 32, 32), gen.moore(3, 1), 319, 0, 0, None),
-    ((32, 32, 32), gen.moore(3, 1), 320, 0, 0, "vector_round_kernel<v16, 3, true, 0, false, 1>"), ((12, 12, 12), gen.moore(3, 1), 400, 0, 0, None),
-    ((32, 32, 32), gen.moore(3, 1), 1024, 0, 0, "vector_round_uniform_kernel<3, 1, 1>"), ((40, 40, 40), gen.moore(3, 1), 256, 0, 1, None),
-    ((64, 64, 64), gen.moore(3, 1), 256, 0, 1, "vector_round_kernel<v16, 3, true, 1, false, 1>"), ((32, 32, 32), gen.moore(3, 1), 100, 1, 0, "vector_round_kernel<v16, 3, true, 0, true, 1>"),
+    ((9, 9, 9), gen.moore(3, 1), 256, 0, 0, A2A), ((8, 8, 8), gen.moore(3, 1), 256, 0, 0, None), ((9, 9, 9), gen.moore(3, 1), 256, 0, 1, A2A),
+    ((20, 20, 20), gen.moore(3, 1), 128, 0, 0, A2A), ((17, 17, 17), gen.moore(3, 1), 128, 0, 0, None), ((22, 22, 22), gen.moore(3, 1), 128, 0, 1, A2A), ((20, 20, 20), gen.moore(3, 1), 128, 0, 1, None),
+    ((32, 32, 32), gen.moore(3, 1), 1027, 0, 0, TAIL), ((12, 12, 12), gen.moore(3, 1), 600, 0, 1, None), ((12, 12, 12), gen.moore(3, 1), 600, 0, 0, TAIL),
+    ((32, 32, 32), gen.moore(3, 1), 319, 0, 0, None), ((32, 32, 32), gen.moore(3, 1), 320, 0, 0, A2A), ((12, 12, 12), gen.moore(3, 1), 400, 0, 0, None),
+    ((32, 32, 32), gen.moore(3, 1), 400, 0, 1, None), ((40, 40, 40), gen.moore(3, 1), 320, 0, 1, A2A), ((64, 64, 64), gen.moore(3, 1), 256, 0, 1, LINES),
+    ((32, 32, 32), gen.moore(3, 1), 1024, 0, 0, "vector_round_uniform_kernel<3, 1, 1>"), ((32, 32, 32), gen.moore(3, 1), 100, 1, 0, TAIL), ((20, 20, 20), gen.moore(3, 1), 128, 1, 0, None),
     ((16, 16, 16, 16), gen.random_distinct(4, -3, 3, 30, 5), 128, 0, 0, "vector_round_kernel<v16, 5, true, 1, false, 1>"),
-    ((20, 20, 20), gen.moore(3, 2), 320, 0, 0, "vector_round_kernel<v16, 3, true, 0, false, 1>"),
-    ((20, 20, 20), gen.moore(3, 2) + [(3, 3, 3)] * 5, 320, 0, 0, "vector_round_kernel<v16, 3, true, 0, false, 1> vector_round_kernel<v16, 3, true, 0, false, 1>"), ((3, 3, 3, 3, 3, 3), gen.moore(6, 1)[:100], 1024, 0, 0, None)])
+    ((20, 20, 20), gen.moore(3, 2), 320, 0, 0, A2A), ((20, 20, 20), gen.moore(3, 2) + [(3, 3, 3)] * 5, 320, 0, 0, A2A + " " + A2A),
+    ((3, 3, 3, 3, 3, 3), gen.moore(6, 1)[:100], 1024, 0, 0, None)])
 def test_alltoalls_through_all_hops_in_one_launch(stub_library, dims, offsets, m, layout, alg, kernel):
-    """Whole lines from 16 MiB on, other blocks of 320 bytes and more from 48 (512: 16), slot-major ones of any size; up to five
-    dimensions, a launch for every 128 neighbours."""
+    """Whole lines (from 256 bytes on) from 4 MiB on, others by block and size; up to five dimensions, a launch for every 128 neighbours."""
     got = stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, alg, m, layout)
-    assert " ".join(got) == kernel if kernel else len(got) > 1, got
+    assert " ".join(got) == kernel if kernel else len(got) > 1 or got[0].startswith("chain"), got
     assert len(stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, alg, m, layout, by_rounds=True)) > 1
 
 
+PULL, PULL_TAIL = "vector_round_kernel<v16, 3, true, 0, false, 0>", "vector_round_kernel<v16, 3, true, 0, true, 0>"
+
+
 @pytest.mark.parametrize("dims,offsets,m,layout,alg,kernel", [
-    ((20, 20, 20), gen.moore(3, 1), 128, 0, 0, "vector_round_kernel<v16, 3, true, 0, false, 0>"), ((10, 10, 10), gen.moore(3, 1), 128, 0, 0, None),
-    ((20, 20, 20), gen.moore(3, 1), 256, 0, 1, None), ((64, 64, 64), gen.moore(3, 1), 128, 0, 1, "vector_round_kernel<v16, 3, true, 0, false, 0>"),
-    ((20, 20, 20), gen.moore(3, 1), 255, 0, 0, None), ((20, 20, 20), gen.moore(3, 1), 255, 1, 0, "vector_round_kernel<v16, 3, true, 0, true, 0>"),
-    ((40, 40, 40), gen.random_distinct(3, -3, 3, 20, 5), 300, 0, 0, "vector_round_kernel<v16, 3, true, 0, true, 2>"),
+    ((12, 12, 12), gen.moore(3, 1), 128, 0, 0, PULL), ((10, 10, 10), gen.moore(3, 1), 128, 0, 0, None),
+    ((20, 20, 20), gen.moore(3, 1), 256, 0, 1, PULL), ((33, 33, 33), gen.moore(3, 1), 256, 0, 1, None), ((33, 33, 33), gen.moore(3, 1), 256, 0, 0, PULL),
+    ((33, 33, 33), gen.moore(3, 1), 512, 0, 1, PULL), ((64, 64, 64), gen.moore(3, 1), 128, 0, 1, PULL), ((28, 28, 28), gen.moore(3, 1), 255, 0, 0, None),
+    ((20, 20, 20), gen.moore(3, 1), 255, 0, 0, PULL_TAIL), ((20, 20, 20), gen.moore(3, 1), 40, 0, 0, PULL_TAIL), ((37, 37, 37), gen.moore(3, 1), 40, 0, 0, None),
+    ((40, 40, 40), gen.moore(3, 1), 40, 1, 0, PULL_TAIL), ((40, 40, 40), gen.random_distinct(3, -3, 3, 20, 5), 300, 0, 0, "vector_round_kernel<v16, 3, true, 0, true, 2>"),
     ((40, 40, 40), gen.random_distinct(3, -3, 3, 20, 5), 1024, 0, 0, "vector_round_uniform_kernel<3, 0, 2>"),
     ((8,) * 5, gen.random_distinct(5, -3, 3, 30, 5), 1024, 0, 0, "push_round_kernel<v16, 5, false, 2>"),
     ((8,) * 5, gen.random_distinct(5, -3, 3, 30, 5), 500, 0, 0, "vector_round_kernel<v16, 5, true, 0, true, 2>"),
@@ -451,7 +458,7 @@ def test_alltoalls_through_all_hops_in_one_launch(stub_library, dims, offsets, m
     ((8,) * 5, gen.random_distinct(5, -3, 3, 40, 5), 1024, 0, 0, "push_round_kernel<v16, 5, false, 2> push_round_kernel<v16, 5, false, 0>"),
     ((3,) * 6, gen.moore(6, 1)[:100], 1024, 0, 0, None)])
 def test_allgathers_through_all_hops_in_one_launch(stub_library, dims, offsets, m, layout, alg, kernel):
-    """Whole lines and blocks of 256 bytes and more from 4 MiB on, slot-major ones of any size; a launch for every 128 nodes of the trie."""
+    """From 4 MiB on, small blocks up to a part of the last-level cache; a launch for every 128 nodes of the trie."""
     got = stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, alg, m, layout)
     assert " ".join(got) == kernel if kernel else len(got) > 1, got
     assert len(stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, alg, m, layout, by_rounds=True)) > 1

@@ -30,6 +30,7 @@ COMBINED, BYDIM = iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM
     ((23, 24, 25), gen.moore(3, 1), 256, SLOT, COMBINED, 1, 0),
     ((29, 31, 27), gen.moore(3, 1), 107, SLOT, COMBINED, 0, 2),
     ((8, 7, 9, 6, 5), gen.random_distinct(5, -3, 3, 40, 5), 1024, SLOT, COMBINED, 0, 0),
+    ((9, 10, 11), gen.moore(3, 1), 256, RANK, BYDIM, 0, 0),
     ((41, 40, 39), gen.moore(3, 1), 320, RANK, BYDIM, 0, 0)])
 def test_alltoall_through_all_hops(dims, offsets, m, layout, alg, send_off, recv_off):
     check_exchange(dims, [tuple(int(x) for x in c) for c in offsets], iso.ISO_OP_ALLTOALL, alg, m, layout, send_off, recv_off)
@@ -48,6 +49,8 @@ def test_alltoall_through_all_hops(dims, offsets, m, layout, alg, send_off, recv
     ((9, 8, 7, 11), gen.random_distinct(4, -3, 3, 30, 5), 100, SLOT, COMBINED, 0, 0),                # push, 2 at a time
     ((33, 31, 35), gen.random_distinct(3, -3, 3, 9, 5), 900, SLOT, COMBINED, 0, 5),                  # 4 at a time
     ((23, 24, 25), gen.moore(3, 1), 16, SLOT, COMBINED, 0, 0),
+    ((17, 18, 19), gen.moore(3, 1), 33, RANK, COMBINED, 0, 1),
+    ((31, 32, 7), gen.random_distinct(3, -3, 3, 20, 5), 47, RANK, BYDIM, 0, 0),
     ((41, 40, 39), gen.moore(3, 1), 320, RANK, BYDIM, 0, 0),
     ((8, 9, 8, 7, 5), gen.random_distinct(5, -3, 3, 36, 7), 1024, RANK, BYDIM, 0, 0)])
 def test_allgather_through_all_hops(dims, offsets, m, layout, alg, send_off, recv_off):
