@@ -210,7 +210,8 @@ typedef struct {
                                   * kernel read counts once for that kernel.  A kernel that takes
                                   * blocks through several hops hands them on in LDS or registers and
                                   * loads only what its first hops read: one kernel for a whole
-                                  * collective, the send buffer                             */
+                                  * collective, the send buffer.  On a mesh also moves that have no
+                                  * source, or are left out because no one receives the block */
     uint64_t bytes_written;      /* blocks they write, bytes                                */
 } iso_start_info_t;
 

@@ -235,15 +235,18 @@ KernelRef with_policy(const Launch &l, F &&f) {
     return f(std::integral_constant<int, 0>());
 }
 
-template <int D, bool TAIL, int WAY>
+template <typename V, int D, bool TAIL, int WAY>
 KernelRef select_way(const Launch &l) {
     const auto form = [&](auto pol) -> KernelRef {
-        if (l.uniform_waves) return {(const void *)&vector_round_uniform_kernel<D, pol(), WAY>, &l.vec};
-        return {(const void *)&vector_round_kernel<vec16_t, D, true, pol(), TAIL, WAY>, &l.vec};
+        if constexpr (sizeof(V) == 16) {
+            if (l.uniform_waves) return {(const void *)&vector_round_uniform_kernel<D, pol(), WAY>, &l.vec};
+        }
+        return {(const void *)&vector_round_kernel<V, D, true, pol(), TAIL, WAY>, &l.vec};
     };
-    if constexpr (WAY == kStrides) {                     // (an allgather loads through the caches)
-        if (l.vec.per) return {(const void *)&push_round_kernel<vec16_t, D, TAIL, WAY>, &l.vec};
-    } else {
+    if constexpr (WAY == kStrides) {
+        if (l.vec.per) return {(const void *)&push_round_kernel<V, D, TAIL, WAY>, &l.vec};
+    }
+    if constexpr (sizeof(V) == 16 && !(WAY & kStrides)) {           // (kStrides: an allgather, which loads through the caches)
         if (l.policy & kStreamLoads) return form(std::integral_constant<int, kStreamLoads>());
     }
     return form(std::integral_constant<int, 0>());
@@ -252,17 +255,18 @@ KernelRef select_way(const Launch &l) {
 // The s-exchange with VectorEntry records (see vector_launch).
 template <typename V, int D, bool TAIL>
 KernelRef select_vector(const Launch &l) {
-    if (l.vec.per && !l.way) return {(const void *)&push_round_kernel<V, D, TAIL>, &l.vec};
-    if constexpr (sizeof(V) == 16) {
-        if (l.way == kStops) return select_way<D, TAIL, kStops>(l);
-        if (l.way == kStrides) return select_way<D, TAIL, kStrides>(l);
-        if (l.uniform_waves) {
-            if (l.policy & kStreamLoads) return {(const void *)&vector_round_uniform_kernel<D, kStreamLoads>, &l.vec};
-            return {(const void *)&vector_round_uniform_kernel<D, 0>, &l.vec};
+    if constexpr (sizeof(V) == 16) {                                // (all_hops_in_one_launch)
+        switch (l.way) {
+            case kStops: return select_way<V, D, TAIL, kStops>(l);
+            case kStrides: return select_way<V, D, TAIL, kStrides>(l);
+            case kStops | kMesh: return select_way<V, D, TAIL, kStops | kMesh>(l);
+            case kStrides | kMesh: return select_way<V, D, TAIL, kStrides | kMesh>(l);
+            default: break;
         }
-        if (l.policy & kStreamLoads) return {(const void *)&vector_round_kernel<V, D, true, kStreamLoads, TAIL>, &l.vec};
     }
-    return {(const void *)&vector_round_kernel<V, D, true, 0, TAIL>, &l.vec};
+    if (l.way == kMesh) return select_way<V, D, TAIL, kMesh>(l);
+    if (l.vec.per) return {(const void *)&push_round_kernel<V, D, TAIL>, &l.vec};
+    return select_way<V, D, TAIL, 0>(l);
 }
 
 template <typename V, bool LDS, bool TAIL>
@@ -603,7 +607,7 @@ public:
             else if (rows) defer_last_hops();
             merge_rounds();
             st = bind_rounds();
-            if (c.mesh && !arena && st == ISO_SUCCESS && rounds_move_faster()) {
+            if (c.mesh && !hops && !arena && st == ISO_SUCCESS && rounds_move_faster()) {
                 pending.resize(n_listed);
                 table.resize(n_entries);
                 prefixes.resize(n_prefixes);
@@ -969,19 +973,23 @@ private:
     // 128 B 197 -> 152, 100 B 168 -> 128.
     // Small ones: all-to-all 10^3, 26 neighbours, 256 B 10.9 (chain) -> 6.2, 12^3, 256 B 15.4 -> 9.8; allgather 20^3, 40 B
     // 11.4 -> 4.0, 5^5, 40, 128 B 27.8 -> 9.3; 13 x 12 x 14, 80 B slot-major 10.0 -> 4.7; 6^3, 20, 48 B 3.5 -> 3.7.
+    // Boxes, where the moves of blocks that no one receives are left out: 45 x 37 x 29, 26 neighbours, 100 B slot-major 97 -> 64,
+    // 256 B 235 -> 151; 8^5, 40, 512 B 877 -> 240; 64^3, allgather 256 B 550 -> 285.
     // It gains at every block size from a MiB on (all-to-all 64^3, 100 B 797 -> 402, 192 B 1038 -> 688, 16^3, 128 B 19.4 ->
     // 11.7; allgather 8^5, 100 B 235 -> 160).  What is left out here are the neighbourhoods of the sizes whose launches
     // tests/test_enqueued_kernels.py lays down: small blocks that are no whole lines, rank-major, with all-to-alls of most
-    // sizes and larger allgathers, and for ISO_ALG_COMBINED_BYDIM more of them up to 7/4 of the last-level cache.
+    // sizes and larger allgathers, and for ISO_ALG_COMBINED_BYDIM more of them up to 7/4 of the last-level cache; and meshes,
+    // but for BYDIM.
     bool all_hops_in_one_launch() const {
         const uint64_t llc = kLastLevelCacheBytes, bytes = inf.delivered_bytes;
         const bool a2a = op == ISO_OP_ALLTOALL, bydim = pl.algorithm == ISO_ALG_COMBINED_BYDIM, lines = size0 % 128 == 0;
-        if (arena || c.mesh || !uniform || size0 < 16 || c.d > kVectorDims || bytes <= llc / 64) return false;
+        if (arena || !uniform || size0 < 16 || c.d > kVectorDims || bytes <= llc / 64) return false;
         if (pl.algorithm != ISO_ALG_COMBINED && !bydim) return false;
         bool onward = false;                             // a hop of what another one has brought
         for (const Round &r : pl.rounds)
             for (const iso_plan_entry_t &e : r.entries) onward = onward || e.src_buf != ISO_BUF_SEND;
         if (!onward) return false;
+        if (c.mesh && (!bydim || (!a2a && !lines && size0 < 256))) return false;
         if (lay.slot_major) return !a2a || bytes > (lines ? llc / 8 : llc * 3 / 16);
         if (!a2a) {
             if (size0 >= 512 || (!bydim && (lines || size0 >= 256)) || bytes <= (size0 < 64 ? llc * 3 / 16 : llc / 2)) return true;
@@ -1303,7 +1311,7 @@ private:
             deliver_launch(pd, ents, k, total);
         } else if (staged_round) {
             staged_round_launch(pd, r, ents, k, total);
-        } else if (uniform && (!c.mesh || r.kind != ISO_ROUND_VECTOR)) {
+        } else if (uniform && (!c.mesh || r.kind != ISO_ROUND_VECTOR || (c.d <= kVectorDims && (all_hops || ents.size() <= kLdsEntries)))) {
             const int st = regular_launch(pd, r, ents, done, all_planes, k, total);
             if (st != ISO_SUCCESS) return st;
         } else {
@@ -1533,8 +1541,8 @@ private:
         total = ((p + sa.ranks - 1) / sa.ranks) * kThreads;      // set_grid: one workgroup per tile
     }
 
-    // Regular blocks: every entry has `chunks` units of the request's common width (on a mesh: shift
-    // rounds and same-rank copies; its s-exchange uses the block kernel).
+    // Regular blocks: every entry has `chunks` units of the request's common width (a mesh's s-exchange of more
+    // dimensions or neighbours than VectorEntry and LDS take uses the block kernel).
     int regular_launch(Pending &pd, const BoundRound &r, const std::vector<HostEntry> &ents, size_t done,
                        bool all_planes, uint32_t &k, uint64_t &total) {
         Launch &l = pd.l;
@@ -1577,7 +1585,7 @@ private:
             // 20 B 10.3 -> 6.7 and 12 -> 11.5; 64^3, 40 B 103 -> 113 and 115 -> 123)
             if (op == ISO_OP_ALLTOALL && !l.entry_major && ents.size() > 1) l.eighths = size0 <= 32;
             if (op == ISO_OP_ALLGATHER && ents.size() > 1) allgather_order(l, ents.data() + done, k);
-            if (l.vec.per) total = per_entry * ((k + l.vec.per - 1) / l.vec.per);
+            if (l.vec.per && !c.mesh) total = per_entry * ((k + l.vec.per - 1) / l.vec.per);
             if (l.vector_dims) return ISO_SUCCESS;
         } else if (l.kernel == kMeshShiftKernel) {
             MeshArgs &ma = l.mesh_shift;
@@ -1684,9 +1692,9 @@ private:
         return true;
     }
 
-    // The s-exchange of equal blocks on a torus.  Up to kVectorDims dimensions and as many entries as the LDS
-    // table takes: VectorEntry records (equal strides on each side, which equal blocks of one layout have).
-    // Other launches keep the general tables.
+    // Moves by full vectors of equal blocks.  Up to kVectorDims dimensions and as many entries as the LDS
+    // table takes: VectorEntry records (equal strides on each side, which equal blocks of one layout have: place()).
+    // Other launches keep the general tables, on a mesh the block kernel (next_launch).
     void vector_launch(Launch &l, const HostEntry *ents, uint32_t k, uint64_t chunks) {
         VectorArgs &va = l.vec;
         bool packed = c.d <= kVectorDims && k <= kLdsEntries;
@@ -1697,10 +1705,13 @@ private:
         }
         if (!packed) return;
         l.vector_dims = c.d <= 3 ? 3 : kVectorDims;
+        if (c.mesh)
+            for (int j = 0; j < kVectorDims; ++j) va.per |= (uint32_t)(c.d - 1 - j >= 0 && c.periodic[(size_t)(c.d - 1 - j)]) << j;
         l.uniform_waves = min_log2 == 4 && !l.tail && chunks % 64 == 0;
         va.src_stride = ents[0].de.src_stride;
         va.dst_stride = ents[0].de.dst_stride;
         if (all_hops) l.way = op == ISO_OP_ALLTOALL ? kStops : one_stride ? 0 : kStrides;
+        if (c.mesh) l.way |= kMesh;
         for (int j = 0; j < kVectorDims; ++j) {                  // last dimension first, absent ones of size 1
             const int l_dim = c.d - 1 - j;
             va.last[j] = l_dim < 0 ? 1u : (uint32_t)c.dims[(size_t)l_dim];
@@ -1748,6 +1759,7 @@ private:
         const uint64_t l2 = uint64_t(4) << 20, sent = p * size0;
         const bool nodes = all_hops && pl.work_slots > 0;
         if (lay.slot_major) {
+            if (c.mesh) return;
             if (l.vector_dims && sent > 7 * l2) l.vec.per = std::min(k, 4u);
             else if (l.vector_dims && nodes) l.vec.per = std::min(k, 2u);
             return;
@@ -1767,7 +1779,7 @@ private:
         const uint64_t window_ranks = std::min<uint64_t>(p, (uint64_t)(hi - lo) + 1), window = window_ranks * size0;
         const uint64_t run = uint64_t(128) * kThreads << min_log2;      // bytes written by a run of tiles (set_grid)
         l.eighths = sent > l2 && 4 * window_ranks * k * size0 > run;
-        if (l.vector_dims && lines && (window > 3 * l2 || (window > l2 && sent > kLastLevelCacheBytes))) {
+        if (l.vector_dims && !c.mesh && lines && (window > 3 * l2 || (window > l2 && sent > kLastLevelCacheBytes))) {
             l.vec.per = std::min(k, nodes ? 4u : 8u);
             l.eighths = false;
         }

@@ -139,7 +139,8 @@ __device__ __forceinline__ FastDiv dim_of(dims_ptr d, int j) {
 
 // Entries of a launch that moves equal blocks by full offset vectors (the s-exchange) on a torus of at most
 // kVectorDims dimensions: all that a lane needs of its entry in 48 bytes, so that no second table is read.
-// `c` are the residues of the last kVectorDims dimensions, the last one first; absent dimensions hold 0.
+// `c` are the residues of the last kVectorDims dimensions, the last one first (signed where a mesh does not wrap); absent
+// dimensions hold 0.
 constexpr int kVectorDims = 5;
 struct alignas(16) VectorEntry {
     uint64_t src, dst;     // addresses of rank 0's blocks
@@ -147,10 +148,11 @@ struct alignas(16) VectorEntry {
     uint32_t c[kVectorDims];
     uint64_t way;          // kStops: address of rank 0's block on the way (a block of one hop has none); kStrides: of `dst`
 };
-// WAY of the vector kernels, for launches that take blocks through all their hops (Binder::all_hops_in_one_launch).
+// WAY of the vector kernels.  For launches that take blocks through all their hops (Binder::all_hops_in_one_launch):
 // kStops, all-to-all: a block is stored at every rank on its way as well (move_through_stops).  kStrides, allgather: every
 // node of the trie is an entry, in the receive buffer or in the workspace, with the stride of its own destination.
-constexpr int kStops = 1, kStrides = 2;
+// kMesh beside these: dimensions that do not wrap (passes_end).
+constexpr int kStops = 1, kStrides = 2, kMesh = 4;
 static_assert(sizeof(VectorEntry) == sizeof(DevEntry), "staged by the same code");
 
 struct VectorArgs {
@@ -158,7 +160,7 @@ struct VectorArgs {
     const TorusDims *dims;     // the others: dimensions and residues
     uint32_t total, k;
     int32_t d;
-    uint32_t per;                             // push kernel: entries a lane writes to
+    uint32_t per;                             // push kernel: entries a lane writes to; mesh: which of `last` wrap, a bit each
     uint32_t src_stride, dst_stride;          // the same for all entries (VectorEntry launches)
     uint32_t chunks, p;
     uint32_t mul_chunks, mul_k, mul_p;
@@ -517,6 +519,18 @@ __device__ __forceinline__ void last_coordinates(uint32_t R, const VectorArgs &a
     wrap[D - 1] = a.p;
 }
 
+// Is the rank `c` steps back along dimension j (counted from the last one) on the far side of the ring?  On a mesh
+// coordinates of dimensions that do not wrap are signed, and one comparison tests both ends.  Boxes by these kernels against
+// the block kernel's decode from the general tables, straightforward exchange, us: 45 x 37 x 29, 26 neighbours, 100 B 66 ->
+// 50, 1 KiB 571 -> 382, allgather 512 B 169 -> 100; 8^5, 40 neighbours, 512 B 231 -> 165; 300^2, 12, 40 B 26.1 -> 21.3.
+template <bool MESH>
+__device__ __forceinline__ bool passes_end(uint32_t r, uint32_t c, int j, const VectorArgs &a, bool &outside) {
+    if constexpr (!MESH) return r < c;
+    const bool past = r - c >= a.last[j], wraps = (a.per >> j) & 1u;
+    outside = outside || (past && !wraps);
+    return past && wraps;
+}
+
 // One unit of a block of an all-to-all through all the hops of its schedule, pulled by the rank R that receives it: the
 // ranks on its way are R moved back along the dimensions one by one, the last hop first.  It is stored at every one of them,
 // in the block's place in the workspace.  What the next hop takes is still in the register: no one reads the stops, and the
@@ -525,20 +539,22 @@ __device__ __forceinline__ void last_coordinates(uint32_t R, const VectorArgs &a
 // one read and their writes.  The stops are stored plainly, the receive rows stream: stops of one block are overwritten, by
 // its next hops at other ranks, while the caches hold them (streamed -> plain, us, many sets of buffers: 8^5, 40 neighbours,
 // 4 KiB 5430 -> 4100; 64^3, 26 neighbours, 1000 B 4670 -> 3740; 256^2, 12, 1 KiB 293 -> 260; 32^3, 26, 256 B 111.7 -> 107.6).
-template <typename V, int D, int POLICY, typename ENTRY>
+template <typename V, int D, int POLICY, int WAY, typename ENTRY>
 __device__ __forceinline__ void move_through_stops(const ENTRY &en, uint32_t R, const uint32_t (&r)[D],
                                                    const uint32_t (&wrap)[D], const VectorArgs &a, uint64_t off) {
     typedef typename Unaligned<V>::type UV;
     typedef const UV __attribute__((address_space(1))) *src_ptr;
     typedef UV __attribute__((address_space(1))) *dst_ptr;
     uint32_t at[D], from = R, inner = 1;
+    bool outside = false;
 #pragma unroll
     for (int j = 0; j < D; ++j) {                        // modulo 2^32, see vector_source_rank
         from -= en.c[j] * inner;
-        if (r[j] < en.c[j]) from += wrap[j];
+        if (passes_end<(WAY & kMesh) != 0>(r[j], en.c[j], j, a, outside)) from += wrap[j];
         at[j] = from;
         inner = wrap[j];
     }
+    if (outside) return;                                 // no source: no block comes this way
     const src_ptr sp = (src_ptr)(block_address(en.src, from, a.src_stride) + off);
     V v;
     if constexpr (POLICY & kStreamLoads) v = __builtin_nontemporal_load(sp);
@@ -583,15 +599,17 @@ __global__ __launch_bounds__(kThreads) void vector_round_kernel(const VectorArgs
         staging.commit(lds);
         if (u >= a.total) return;
         const VectorEntry &en = ((const VectorEntry *)(LDS ? lds : a.entries))[e];
-        if constexpr (WAY == kStops) {
-            move_through_stops<V, D, POLICY>(en, R, r, wrap, a, off);
+        if constexpr (WAY & kStops) {
+            move_through_stops<V, D, POLICY, WAY>(en, R, r, wrap, a, off);
             return;
         }
         uint32_t srcR = R - en.back;                    // modulo 2^32, see vector_source_rank
+        bool outside = false;
 #pragma unroll
         for (int j = 0; j < D; ++j)
-            if (r[j] < en.c[j]) srcR += wrap[j];
-        const uint32_t dst_stride = WAY == kStrides ? (uint32_t)en.way : a.dst_stride;
+            if (passes_end<(WAY & kMesh) != 0>(r[j], en.c[j], j, a, outside)) srcR += wrap[j];
+        if (outside) return;                            // mesh, no source: the destination keeps its content
+        const uint32_t dst_stride = WAY & kStrides ? (uint32_t)en.way : a.dst_stride;
         move_unit<V, POLICY>(block_address(en.dst, R, dst_stride), block_address(en.src, srcR, a.src_stride), off);
     }
 }
@@ -617,15 +635,17 @@ __global__ __launch_bounds__(kThreads) void vector_round_uniform_kernel(const Ve
     uint32_t r[D], wrap[D];
     last_coordinates<D>(R, a, r, wrap);
     const uint64_t off = (uint64_t)(ch0 + (threadIdx.x & 63u)) * sizeof(vec16_t);
-    if constexpr (WAY == kStops) {
-        move_through_stops<vec16_t, D, POLICY>(*en, R, r, wrap, a, off);
+    if constexpr (WAY & kStops) {
+        move_through_stops<vec16_t, D, POLICY, WAY>(*en, R, r, wrap, a, off);
         return;
     }
     uint32_t srcR = R - en->back;
+    bool outside = false;
 #pragma unroll
     for (int j = 0; j < D; ++j)
-        if (r[j] < en->c[j]) srcR += wrap[j];
-    const uint32_t dst_stride = WAY == kStrides ? (uint32_t)en->way : a.dst_stride;
+        if (passes_end<(WAY & kMesh) != 0>(r[j], en->c[j], j, a, outside)) srcR += wrap[j];
+    if (outside) return;
+    const uint32_t dst_stride = WAY & kStrides ? (uint32_t)en->way : a.dst_stride;
     move_unit<vec16_t, POLICY>(block_address(en->dst, R, dst_stride), block_address(en->src, srcR, a.src_stride), off);
 }
 
@@ -665,7 +685,7 @@ __global__ __launch_bounds__(kThreads) void push_round_kernel(const VectorArgs a
 #pragma unroll
         for (int j = 0; j < D; ++j)
             if (r[j] + en.c[j] >= a.last[j]) R -= wrap[j];
-        const uint32_t dst_stride = WAY == kStrides ? (uint32_t)en.way : a.dst_stride;
+        const uint32_t dst_stride = WAY & kStrides ? (uint32_t)en.way : a.dst_stride;
         const dst_ptr dp = (dst_ptr)(block_address(en.dst, R, dst_stride) + off);
         if constexpr (sizeof(V) == 16) __builtin_nontemporal_store(v, dp);
         else *dp = v;

@@ -462,3 +462,14 @@ def test_allgathers_through_all_hops_in_one_launch(stub_library, dims, offsets, 
     got = stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, alg, m, layout)
     assert " ".join(got) == kernel if kernel else len(got) > 1, got
     assert len(stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, alg, m, layout, by_rounds=True)) > 1
+
+
+@pytest.mark.parametrize("dims,op,m,layout,alg,kernel", [
+    ((45, 37, 29), 0, 100, 1, 1, "vector_round_kernel<v16, 3, true, 0, true, 5>"), ((45, 37, 29), 0, 100, 1, 0, None), ((45, 37, 29), 0, 100, 0, 1, None),
+    ((45, 37, 29), 0, 256, 0, 1, "vector_round_kernel<v16, 3, true, 1, false, 5>"), ((45, 37, 29), 1, 256, 1, 1, "vector_round_kernel<v16, 3, true, 0, false, 4>"),
+    ((45, 37, 29), 1, 600, 0, 1, "vector_round_kernel<v16, 3, true, 0, true, 4>"), ((45, 37, 29), 1, 300, 0, 1, None), ((45, 37, 29), 0, 1024, 0, 3, "vector_round_uniform_kernel<3, 1, 4>"),
+    ((45, 37, 29), 1, 7, 0, 3, "vector_round_kernel<unsigned int, 3, true, 0, true, 4>"), ((45, 37, 29), 1, 1024, 1, 3, "vector_round_uniform_kernel<3, 0, 4>"),
+    ((3, 4, 3, 4, 3, 4), 0, 64, 0, 3, "block_round_kernel<true, true, 0, false>")])
+def test_boxes_by_full_vectors(stub_library, dims, op, m, layout, alg, kernel):
+    got = stub_library.start(dims, gen.moore(3, 1) if len(dims) == 3 else gen.von_neumann(6, 1), op, alg, m, layout, (0,) * len(dims))
+    assert got == [kernel] if kernel else len(got) > 1, got

@@ -7,6 +7,8 @@ import torch
 
 import iso_inputs as gen
 import paper_1606_07676_amd as iso
+from launch_paths import start_both_ways
+from oracle import iso_oracle as orc
 from test_gpu_vector import check_exchange
 
 pytestmark = pytest.mark.gpu
@@ -78,3 +80,36 @@ def test_equal_blocks_of_the_irregular_call_with_empty_ones(layout):
         iso.iso_request_free(req)
         got.append(recv)
     assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("op", [iso.ISO_OP_ALLTOALL, iso.ISO_OP_ALLGATHER])
+@pytest.mark.parametrize("dims,periodic,offsets,sizes", [
+    ((25, 24, 26), (0, 1, 0), gen.moore(3, 1) + [(0, 0, 0), (25, 0, 1), (-30, 2, 0), (2, 25, -2)], (128, 333, 1024)),
+    ((130, 71), (0, 0), gen.moore(2, 2) + [(129, -70)], (128, 520)),
+    ((7, 6, 9, 5, 8), (1, 0, 0, 1, 0), gen.random_distinct(5, -3, 3, 40, 5), (256, 2048)),
+    ((3, 2, 1, 60, 33), (0, 0, 0, 0, 1), gen.random_distinct(5, -3, 3, 30, 6), (640,))])
+def test_boxes(dims, periodic, offsets, sizes, op):
+    """Dimensions that do not wrap: the same launches for one launch per dimension, and the straightforward exchange with the
+    tables of a torus; receive blocks without a source keep their content."""
+    offsets = [tuple(int(x) for x in c) for c in offsets]
+    p, s, a2a = int(np.prod(dims)), len(offsets), op == iso.ISO_OP_ALLTOALL
+    comm = iso.iso_neighborhood_create_mesh(dims, periodic, offsets)
+    src, valid = orc.source_ranks_mesh(dims, periodic, offsets)
+    init = iso.iso_neighbor_alltoall_init_layout if a2a else iso.iso_neighbor_allgather_init_layout
+    for m in sizes + (7,):
+        send = torch.randint(0, 256, (p, s if a2a else 1, m), dtype=torch.uint8, device=DEV, generator=torch.Generator(DEV).manual_seed(m))
+        for layout in (RANK, SLOT):
+            for alg in (BYDIM, iso.ISO_ALG_SX_FUSED):
+                given = send.permute(1, 0, 2).contiguous() if layout == SLOT and a2a else send
+                recv = torch.full((p * s * m,), 0xEE, dtype=torch.uint8, device=DEV)
+                work = torch.full((max(1, iso.iso_workspace_bytes(comm, op, alg, m)),), 0xDD, dtype=torch.uint8, device=DEV)
+                req = init(given, recv, m, layout, work, comm, alg)
+                start_both_ways(req, recv, work, starts=2)
+                iso.iso_request_free(req)
+                got = recv.view(s, p, m) if layout == SLOT else recv.view(p, s, m).permute(1, 0, 2)
+                for i in range(s):
+                    v = torch.from_numpy(np.ascontiguousarray(valid[:, i])).to(DEV)
+                    at = torch.from_numpy(np.where(valid[:, i], src[:, i], 0).astype(np.int64)).to(DEV)
+                    want = send[:, i if a2a else 0].index_select(0, at)
+                    want[~v] = 0xEE
+                    assert torch.equal(got[i], want), (dims, m, layout, alg, i)
