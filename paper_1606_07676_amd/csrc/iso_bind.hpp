@@ -61,7 +61,7 @@ struct Launch {
     uint32_t tile_units;   // the staged schedule's kernels: kTileUnits or kSmallTileUnits
     ChainHead chain;       // chain kernel: its hops in the request's table
     const ChainArgs *chain_by_value;      // or BoundRequest::chain, where there is no table
-    uint32_t chain_width;  // its unit width, where not the request's
+    uint32_t chain_width;  // its unit width, where not the request's (vector kernel: blocks of one size among others)
     uint64_t outside_units;               // mesh: units of wavefronts or tiles not marked interior (see rounds_move_faster)
     bool entry_major, vector_round;       // see launch_flags
     int way;               // vector kernel: its WAY
@@ -316,6 +316,12 @@ KernelRef select_width(const Launch &l) {
     return select_regular<V, false, false>(l);
 }
 
+template <int POLICY>
+KernelRef select_block_hops(const Launch &l) {
+    if (l.vector_dims == 3) return {(const void *)&block_round_kernel<true, true, POLICY, false, 3>, &l.block};
+    return {(const void *)&block_round_kernel<true, true, POLICY, false, kVectorDims>, &l.block};
+}
+
 template <bool LDS, bool MESH>
 KernelRef select_block(const Launch &l) {
     const auto form = [&](auto pol) -> KernelRef {
@@ -376,6 +382,7 @@ inline KernelRef select_kernel(int vector_bytes, const Launch &l) {
                                                    : KernelRef{(const void *)&deliver_kernel<vec16_t, pol(), kLarge>, &l.deliver};
         });
     if (l.kernel == kBlockKernel) {
+        if (l.way) return l.policy == kBySize ? select_block_hops<kBySize>(l) : select_block_hops<kPlainStores>(l);
         if (l.mesh) return l.lds_table ? select_block<true, true>(l) : select_block<false, true>(l);
         return l.lds_table ? select_block<true, false>(l) : select_block<false, false>(l);
     }
@@ -596,13 +603,14 @@ public:
             if ((st = bind_rounds()) != ISO_SUCCESS) return st;
             n_listed = pending.size();
         }
-        const bool hops = all_hops_in_one_launch();
+        const bool by_size = all_hops_by_size(), hops = by_size || all_hops_in_one_launch();
         if (chains && !hops && chain_launch(launches)) return upload();
         const bool star = !hops && star_in_one_launch(launches);
         const bool rows = !hops && !star && rows_in_one_launch();
         if (hops || rows || star || (merges && launches < bound_rounds.size())) {
             const size_t n_entries = table.size(), n_prefixes = prefixes.size();
             if (hops) join_hops();
+            if (by_size) split_by_size();
             else if (star) join_star();
             else if (rows) defer_last_hops();
             merge_rounds();
@@ -647,6 +655,8 @@ private:
     struct Pending { size_t first_entry, first_prefix; Launch l; };
     std::vector<Pending> pending;
     bool all_hops = false;                        // the round is join_hops's
+    bool one_size = false;                        // the rounds are split_by_size's
+    std::vector<uint64_t> large_sizes;
     size_t n_listed = 0;                          // of these: rq.launches; the rest are rq.start_launches
 
     int bind_rounds() {
@@ -1043,6 +1053,43 @@ private:
         rounds.assign(1, std::move(all));
     }
 
+    // Unequal blocks through all their hops: the larger ones a launch for every size, by the vector kernel, those of up to
+    // kSmallUnits units in one launch of the block kernel, if that is fewer launches than one per dimension.  A launch then
+    // moves blocks of one kind, and the larger ones need no search for a unit's entry.  (Stencils, us, a launch per dimension
+    // -> here: 32^3, 64 B 338 -> 291, 25 B 90 -> 78; 64^3, 16 B 379 -> 323, 4 B 150 -> 133, 80^3, 8 B 558 -> 400;
+    // 16^4, 8 B 373 -> 342; 8^5, 4 B 512 -> 391; 500^2, 64 B 81 -> 57; 8^3, 64 B 15.8 -> 11.8, 40^2, 64 B 6.3 -> 3.9.)  Small
+    // blocks that are no whole units lose it again in more dimensions, and among themselves in three (16^4, 6 B 285 -> 303;
+    // 64^3, 11 B 303 -> 361; 22^4, 3 B 673 -> 822), as many launches as before gain nothing (300^2, 200 B 57 -> 60).
+    // ISO_ALG_COMBINED_BYDIM: where kBySize was taken (60 x 50 x 41, 25 B 318 -> 296; 20^4, 8 B 1099 -> 832).
+    bool all_hops_by_size() {
+        const uint64_t llc = kLastLevelCacheBytes, bytes = inf.delivered_bytes;
+        if (op != ISO_OP_ALLTOALL || arena || uniform || lay.slot_major || c.d < 2 || c.d > kVectorDims || wl.bytes >> 36)
+            return false;
+        bool small = false, units = true;
+        for (const std::vector<HostEntry> &round : rounds)
+            for (const HostEntry &he : round) {
+                if (he.de.units <= kSmallUnits) small = true, units = units && (he.size < 16 || he.size % 16 == 0);
+                else if (std::find(large_sizes.begin(), large_sizes.end(), he.size) == large_sizes.end()) large_sizes.push_back(he.size);
+                if (large_sizes.size() + small >= (size_t)c.d) return false;
+            }
+        if (pl.algorithm == ISO_ALG_COMBINED_BYDIM) return !c.mesh && small && !large_sizes.empty() && bytes > llc / 4;
+        return pl.algorithm == ISO_ALG_COMBINED && (units || c.d == 2 || (c.d == 3 && !large_sizes.empty()));
+    }
+
+    void split_by_size() {
+        const std::vector<HostEntry> all = std::move(rounds[0]);
+        const BoundRound whole = bound_rounds[0];
+        rounds.assign(large_sizes.size() + 1, {});
+        for (const HostEntry &he : all) {
+            const size_t at = he.de.units <= kSmallUnits ? large_sizes.size()
+                                                         : (size_t)(std::find(large_sizes.begin(), large_sizes.end(), he.size) - large_sizes.begin());
+            rounds[at].push_back(he);
+        }
+        if (rounds.back().empty()) rounds.pop_back();
+        bound_rounds.assign(rounds.size(), whole);
+        one_size = true;
+    }
+
     void defer_last_hops() {
         std::vector<HostEntry> last(s);
         std::vector<bool> taken(s, false);
@@ -1290,6 +1337,12 @@ private:
         Launch &l = pd.l;
         std::memset(&l, 0, sizeof(l));
         l.round = r.of;
+        if (one_size) {                                  // split_by_size: the last round is that of the small blocks
+            uniform = ri < large_sizes.size();
+            size0 = ents[0].size;
+            min_log2 = unit_log2_of(size0);
+            l.chain_width = 1u << min_log2;
+        }
         uint32_t k = 0;
         uint64_t total = 0;
         // staged schedule, last launch: whole receive rows through LDS (left as one round only for
@@ -1430,6 +1483,7 @@ private:
             if (all_hops && a2a && inf.entries >= 3 * (int64_t)s) return kStreamLoads;
             return a2a && l.vector_dims && lines && bytes > above ? kStreamLoads : 0;
         }
+        if (l.kernel == kBlockKernel && all_hops) return !c.mesh && !large_sizes.empty() && bytes > kLastLevelCacheBytes / 4 ? kBySize : kPlainStores;
         if (r.kind == ISO_ROUND_VECTOR) return 0;
         if (l.kernel == kBlockKernel) {
             if (inf.block_bytes < 128 && l.block.equal_units <= 1 && !lay.slot_major && bytes <= kLastLevelCacheBytes / 4)
@@ -1799,13 +1853,14 @@ private:
         const uint64_t scale = entry_major ? p : 1;    // prefix counts all ranks' units, or one row's
         uint64_t row_units = 0;
         prefixes.push_back(0);
-        while (done + k < ents.size()) {
+        while (done + k < ents.size() && (!all_hops || k < kLdsEntries)) {
             const uint64_t next = row_units + ents[done + k].de.units;
             if (next * p > kMaxUnits) break;
             row_units = next;
             DevEntry de = ents[done + k].de;
             const FastDiv by_units = make_fastdiv(de.units);
             de.meta |= (by_units.sh1 << 24) | (by_units.sh2 << 25);
+            if (all_hops) de.ref = ents[done + k].way ? (uint32_t)((ents[done + k].way - (uint64_t)(uintptr_t)workspace) / 16) : 0u;
             table.push_back(de);
             prefixes.push_back((uint32_t)(row_units * scale));
             ++k;
@@ -1815,6 +1870,11 @@ private:
         total = row_units * p;
         l.entry_major = entry_major;
         l.vector_round = r.kind == ISO_ROUND_VECTOR;
+        if (all_hops) {
+            l.way = kStops;
+            l.vector_dims = c.d <= 3 ? 3 : kVectorDims;
+            b.work = (uint64_t)(uintptr_t)workspace;
+        }
         b.equal_units = ents[done].de.units;
         for (uint32_t q = 1; q < k; ++q)
             if (ents[done + q].de.units != b.equal_units) b.equal_units = 0;

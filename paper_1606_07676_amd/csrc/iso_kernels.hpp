@@ -731,6 +731,7 @@ struct BlockArgs {
                                // ordered (entry, rank, unit) and prefix[e] counts the units of all ranks before
                                // entry e; else (rank, entry, unit)
     uint32_t torus;            // torus_bits
+    uint64_t work;             // HOPS: the workspace; DevEntry::ref counts the 16 bytes in front of the block's place there
 };
 static_assert(sizeof(BlockArgs) <= kCheapArguments, "launch cost");
 
@@ -870,9 +871,46 @@ __device__ __forceinline__ void fetch_now(const BlockArgs &a) {
                  "s"(a.mul_plane), "s"(a.mul_group_row), "s"(a.shifts), "s"(a.more));
 }
 
-template <bool LDS, bool MESH, int POLICY, bool GROUPS = false>
+// HOPS: a unit of rank R's block through all the hops of an all-to-all (see move_through_stops), on at most HOPS dimensions.
+// For blocks of a few units: loads through the caches, plain stores, as kBySize takes them.  A torus is a mesh here of
+// which all dimensions wrap (MESH).
+template <typename V, int HOPS>
+__device__ __forceinline__ void block_through_stops(const BlockArgs &a, const DevEntry &en, uint32_t R, uint64_t off) {
+    typedef typename Unaligned<V>::type UV;
+    typedef const UV __attribute__((address_space(1))) *src_ptr;
+    typedef UV __attribute__((address_space(1))) *dst_ptr;
+    const dims_ptr dims = const_dims(a.dims);
+    const int d = (int)(a.torus & 31u);
+    const uint32_t *c = offsets_after(a.dims) + (size_t)en.shift * d;
+    uint32_t at[HOPS], from = R, rem = R;
+    bool outside = false;
+#pragma unroll
+    for (int t = 0; t < HOPS; ++t) {                     // the last hop first, modulo 2^32
+        at[t] = from;
+        if (t >= d) continue;
+        const int j = d - 1 - t;
+        uint32_t q, rj;
+        fast_divmod(rem, dim_of(dims, j), q, rj);
+        rem = q;
+        const uint32_t cj = c[j], inner = dims->inner[j];
+        const bool past = rj - cj >= dims->d_dims[j].div, wraps = (a.torus >> (16 + j)) & 1u;      // (see passes_end)
+        from -= cj * inner;
+        if (past && wraps) from += dims->d_dims[j].div * inner;
+        outside = outside || (past && !wraps);
+        at[t] = from;
+    }
+    if (outside) return;
+    const V v = *(src_ptr)(block_address(en.src, from, en.src_stride) + off);
+    const uint32_t m = (uint32_t)en.last_offset + (uint32_t)sizeof(V);
+#pragma unroll
+    for (int t = HOPS - 1; t >= 0; --t)                  // ranks on the way, each once
+        if (at[t] != from && at[t] != (t ? at[t - 1] : R)) *(dst_ptr)(block_address(a.work + (uint64_t)en.ref * 16u, at[t], m) + off) = v;
+    *(dst_ptr)(block_address(en.dst, R, en.dst_stride) + off) = v;
+}
+
+template <bool LDS, bool MESH, int POLICY, bool GROUPS = false, int HOPS = 0>
 __global__ __launch_bounds__(kThreads) void block_round_kernel(const BlockArgs a) {
-    if constexpr (!MESH) fetch_now(a);
+    if constexpr (!MESH || HOPS) fetch_now(a);
     const FastDiv d_row = fastdiv_of(a.mul_row, a.row, a.shifts, 0), d_inner = fastdiv_of(a.mul_inner, a.inner, a.shifts, 1),
                   d_pj = fastdiv_of(a.mul_pj, a.pj, a.shifts, 2),
                   d_units = fastdiv_of(a.mul_units, a.equal_units ? a.equal_units : 1u, a.shifts, 3),
@@ -936,6 +974,16 @@ __global__ __launch_bounds__(kThreads) void block_round_kernel(const BlockArgs a
         uint32_t rank_in_span;
         fast_divmod(in_plane, by_units, rank_in_span, ch);
         R += rank_in_span;
+    }
+    if constexpr (HOPS > 0) {
+        switch (en.meta & 0xFFu) {
+            case 4: block_through_stops<vec16_t, HOPS>(a, en, R, unit_offset<vec16_t>(ch, en.last_offset)); break;
+            case 3: block_through_stops<vec8_t, HOPS>(a, en, R, unit_offset<vec8_t>(ch, en.last_offset)); break;
+            case 2: block_through_stops<uint32_t, HOPS>(a, en, R, unit_offset<uint32_t>(ch, en.last_offset)); break;
+            case 1: block_through_stops<uint16_t, HOPS>(a, en, R, unit_offset<uint16_t>(ch, en.last_offset)); break;
+            default: block_through_stops<uint8_t, HOPS>(a, en, R, ch); break;
+        }
+        return;
     }
     uint32_t srcR = R;                                    // modulo 2^32, see vector_source_rank
     if constexpr (MESH) {

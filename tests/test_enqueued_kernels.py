@@ -469,7 +469,21 @@ def test_allgathers_through_all_hops_in_one_launch(stub_library, dims, offsets, 
     ((45, 37, 29), 0, 256, 0, 1, "vector_round_kernel<v16, 3, true, 1, false, 5>"), ((45, 37, 29), 1, 256, 1, 1, "vector_round_kernel<v16, 3, true, 0, false, 4>"),
     ((45, 37, 29), 1, 600, 0, 1, "vector_round_kernel<v16, 3, true, 0, true, 4>"), ((45, 37, 29), 1, 300, 0, 1, None), ((45, 37, 29), 0, 1024, 0, 3, "vector_round_uniform_kernel<3, 1, 4>"),
     ((45, 37, 29), 1, 7, 0, 3, "vector_round_kernel<unsigned int, 3, true, 0, true, 4>"), ((45, 37, 29), 1, 1024, 1, 3, "vector_round_uniform_kernel<3, 0, 4>"),
-    ((3, 4, 3, 4, 3, 4), 0, 64, 0, 3, "block_round_kernel<true, true, 0, false>")])
+    ((3, 4, 3, 4, 3, 4), 0, 64, 0, 3, "block_round_kernel<true, true, 0, false, 0>")])
 def test_boxes_by_full_vectors(stub_library, dims, op, m, layout, alg, kernel):
     got = stub_library.start(dims, gen.moore(3, 1) if len(dims) == 3 else gen.von_neumann(6, 1), op, alg, m, layout, (0,) * len(dims))
     assert got == [kernel] if kernel else len(got) > 1, got
+
+
+@pytest.mark.parametrize("dims,sizes,alg,kernels", [
+    ((32, 32, 32), gen.stencil_block_sizes(gen.moore(3, 1), 64), 0, "vector_round_uniform_kernel<3, 1, 1> block_round_kernel<true, true, 4, false, 3>"),
+    ((32, 32, 32), gen.stencil_block_sizes(gen.moore(3, 1), 25), 1, "vector_round_kernel<v16, 3, true, 0, true, 1> block_round_kernel<true, true, 4, false, 3>"),
+    ((20, 20, 20), gen.stencil_block_sizes(gen.moore(3, 1), 25), 0, "vector_round_kernel<v16, 3, true, 0, true, 1> block_round_kernel<true, true, 2, false, 3>"),
+    ((20, 20, 20), gen.stencil_block_sizes(gen.moore(3, 1), 8), 0, "block_round_kernel<true, true, 2, false, 3>"), ((20, 20, 20), gen.stencil_block_sizes(gen.moore(3, 1), 8), 1, None),
+    ((20, 20, 20), gen.stencil_block_sizes(gen.moore(3, 1), 9), 0, None),
+    ((8, 8, 8), [200 + 16 * (i % 2) for i in range(26)], 0, "vector_round_kernel<v16, 3, true, 0, true, 1> vector_round_kernel<v16, 3, true, 0, true, 1>"),
+    ((8, 8, 8), [200 + 16 * (i % 2) for i in range(25)] + [8], 0, None)])
+def test_unequal_blocks_by_size(stub_library, dims, sizes, alg, kernels):
+    """Fewer launches than dimensions: one for every size of more than eight units, one for all smaller blocks."""
+    got = stub_library.start_unequal(dims, gen.moore(3, 1), alg, list(sizes))
+    assert " ".join(got) == kernels if kernels else all(k.startswith("block_round_kernel<true, false, ") and k.endswith(", 0>") for k in got), got

@@ -113,3 +113,34 @@ def test_boxes(dims, periodic, offsets, sizes, op):
                     want = send[:, i if a2a else 0].index_select(0, at)
                     want[~v] = 0xEE
                     assert torch.equal(got[i], want), (dims, m, layout, alg, i)
+
+
+@pytest.mark.parametrize("box", [False, True])
+@pytest.mark.parametrize("dims,offsets,sizes", [
+    ((21, 20, 19), gen.moore(3, 1), gen.stencil_block_sizes(gen.moore(3, 1), 51)), ((33, 31), gen.moore(2, 1), gen.stencil_block_sizes(gen.moore(2, 1), 37)),
+    ((9, 8, 7, 6), gen.moore(4, 1), gen.stencil_block_sizes(gen.moore(4, 1), 7)), ((5, 4, 3, 4, 5), gen.moore(5, 1), gen.stencil_block_sizes(gen.moore(5, 1), 3)),
+    ((2, 3, 1, 29, 31), gen.random_distinct(5, -3, 3, 30, 6), [(1, 2, 3, 4, 7, 8, 15, 16, 17, 33, 127, 128, 129, 640, 0)[i % 15] for i in range(30)]),
+    ((17, 18, 19), gen.moore(3, 1) + [(0, 0, 0), (1, 1, 1), (2, 0, -1)], [(300, 5, 0, 128, 129)[i % 5] for i in range(29)]),
+    ((17, 18, 19), gen.moore(3, 1), [200 if i % 2 else 300 for i in range(26)])])                     # no small ones
+def test_unequal_blocks_through_all_hops(dims, offsets, sizes, box):
+    """Every unit width, blocks of one size among others and empty ones, packed rows and rows with gaps, against the oracle."""
+    offsets = [tuple(int(x) for x in c) for c in offsets]
+    p, s, sizes = int(np.prod(dims)), len(offsets), [int(x) for x in sizes]
+    periodic = [0 if box and j != 1 else 1 for j in range(len(dims))]
+    comm = iso.iso_neighborhood_create_mesh(dims, periodic, offsets)
+    src, valid = orc.source_ranks_mesh(dims, periodic, offsets)
+    src = torch.from_numpy(np.where(valid, src, 0).astype(np.int64)).to(DEV)
+    valid = torch.from_numpy(np.ascontiguousarray(valid)).to(DEV)
+    for align in (1, 16):
+        displs, row = gen.packed_displacements(sizes, align)
+        send = torch.randint(0, 256, (p, row), dtype=torch.uint8, device=DEV, generator=torch.Generator(DEV).manual_seed(align))
+        for alg in (COMBINED, BYDIM):
+            recv = torch.full((p, row), 0xEE, dtype=torch.uint8, device=DEV)
+            work = torch.full((max(1, iso.iso_workspace_bytes_v(comm, iso.ISO_OP_ALLTOALL, alg, sizes)),), 0xDD, dtype=torch.uint8, device=DEV)
+            req = iso.iso_neighbor_alltoallv_init(send, sizes, displs, row, recv, sizes, displs, row, work, comm, alg)
+            start_both_ways(req, recv, work, starts=2)
+            iso.iso_request_free(req)
+            want = torch.full((p, row), 0xEE, dtype=torch.uint8, device=DEV)
+            for i, (at, m) in enumerate(zip(displs, sizes)):
+                want[valid[:, i], at:at + m] = send[:, at:at + m].index_select(0, src[valid[:, i], i])
+            assert torch.equal(recv, want), (dims, align, alg)
