@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Benchmark of the hot path on one MI355X: persistent isomorphic all-to-all and
-allgather with the message-combining (torus-direct) schedule, one kernel per
-dimension, on synthetic workloads held entirely in HBM.
+allgather with the message-combining (torus-direct) schedule, every block taken
+through its hops by one kernel, on synthetic workloads held entirely in HBM.
 
 One step = one iso_start of every collective the workload names (e.g. config 5:
 all-to-all, then allgather), enqueued back to back on one stream.  Inputs are
@@ -55,7 +55,7 @@ def parse():
     ap.add_argument("--layout", choices=("rank", "slot"), default="rank",
                     help="buffers of the timed requests: rank = the paper's [p][s][m] (default), slot = [s][p][m]")
     ap.add_argument("--algorithm", choices=("combined", "bydim", "sx_fused", "sx_rounds", "onehop", "staged"),
-                    default="combined", help="algorithm of the timed requests (default: combined, one kernel per dimension)")
+                    default="combined", help="algorithm of the timed requests (default: combined)")
     ap.add_argument("--pad", type=int, default=0,
                     help="all-to-all only: every rank's row padded by this many bytes (irregular interface, equal blocks)")
     ap.add_argument("--mesh", action="store_true", help="the torus taken as a box: no dimension wraps (Section 7)")
@@ -368,12 +368,31 @@ class Bench:
         if args.graph:
             for r in self.reqs:
                 iso.iso_request_set_graph(r, args.graph)
-        # the kernels of a step, and the blocks that they read and write: a block that an allgather's kernel
-        # sends on to several blocks counts as read once
-        starts = [iso.iso_request_start_info(r) for r in self.reqs]
-        self.moved = sum(i["bytes_read"] + i["bytes_written"] for i in starts)
-        self.launches = sum(i["kernels"] for i in starts)
+        # the kernels of a step, and the blocks that they load and store
+        self.through_hops = all(self.all_hops(r) for r in self.reqs)
+        self.moved = sum(self.memory_bytes(r) for r in self.reqs)
+        self.launches = sum(iso.iso_request_start_info(r)["kernels"] for r in self.reqs)
         self.requested = sum(i["bytes_read"] + i["bytes_written"] for i in self.infos)
+
+    # -- what a start moves ----------------------------------------------------------
+    def all_hops(self, req):
+        """Fewer kernels than dimensions with moves: they take blocks through all their hops."""
+        iso, plan = self.iso, self.iso.iso_request_plan(req)
+        dims_moved = set()
+        for q in range(iso.iso_plan_info(plan)["launches"]):
+            dims_moved.update(e["dim"] for e in iso.iso_plan_entries(plan, q) if e["dim"] >= 0)
+        return iso.iso_request_start_info(req)["kernels"] < len(dims_moved)
+
+    def memory_bytes(self, req):
+        """Bytes that the kernels of a start load and store.  A block that an allgather's kernel sends on to several
+        blocks is loaded once; kernels that take blocks through all their hops load the send buffer and store every
+        stop."""
+        info, start = self.iso.iso_request_info(req), self.iso.iso_request_start_info(req)
+        loaded = start["bytes_read"]
+        if self.all_hops(req):
+            loaded = (info["delivered_bytes"] if info["op"] == self.iso.ISO_OP_ALLTOALL
+                      else start["kernels"] * info["p"] * info["block_bytes"])
+        return loaded + start["bytes_written"]
 
     # -- requests ------------------------------------------------------------------
     def make_request(self, op, alg, timed_buffers=False):
@@ -515,13 +534,17 @@ class Bench:
         avg_launch_ms = ms_per_step / self.launches
         achieved = alg_bytes_per_launch / (avg_launch_ms * 1e-3) / 1e9
         kernel = ("vector_round_kernel" if args.algorithm.startswith("sx") else
+                  "vector_round_uniform_kernel" if self.through_hops and m % 1024 == 0 else
+                  "vector_round_kernel" if self.through_hops else
                   "deliver_kernel" if args.algorithm == "staged" and m % 16 == 0 and s * (m // 16) <= 2048 and s <= 128
                   and not (args.irregular or args.mesh or args.pad or self.slot) else
                   "block_round_kernel" if args.irregular else
                   "mesh_shift_round_kernel" if args.mesh else
                   "shift_round_uniform_kernel" if m % 1024 == 0 and (self.slot or m <= 2048) else
                   "shift_round_kernel") + "<16B>"
-        if self.moved < self.requested and not args.algorithm.startswith("sx") and not args.mesh:
+        if self.through_hops:
+            kernel += ", allgather: also push_round_kernel<16B>" if len(self.ops) > 1 and cfg.d > 3 else ""
+        elif self.moved < self.requested and not args.algorithm.startswith("sx") and not args.mesh:
             kernel += ", allgather: also shift_push_kernel<16B>"
         tag = self.tag()
         roofline = {
@@ -537,7 +560,8 @@ class Bench:
                 "workload": f"{cfg.name if m == cfg.m else cfg.name.rsplit('_m', 1)[0] + f'_m{m}'}: torus "
                             f"{'x'.join(map(str, cfg.dims))} (p={p}), s={s}, m={m} B, "
                             f"{'+'.join(self.op_name[o] for o in self.ops)} per step, "
-                            + ("message-combining schedule, one kernel per dimension" if args.algorithm == "combined"
+                            + ("message-combining schedule, " + ("all hops of a block in one kernel" if self.through_hops
+                                                                  else "one kernel per dimension") if args.algorithm == "combined"
                                else f"algorithm {args.algorithm}"),
                 "layout": "[s][p][m] (slot-major)" if self.slot else "[p][s][m] (rank-major, the paper's)",
                 "algorithm": args.algorithm, "seed": args.seed, "profile_tag": tag,
@@ -615,12 +639,11 @@ class Bench:
         ksteps = max(5, K // 4)
 
         def rate(rs, ms, hbm_label=True):
-            """`moved_GBs` counts the blocks that the kernels read and write (a block that a kernel sends
-            on to several blocks is read once), which is what HBM carries for the message-combining
-            schedules.  The s-exchange allgather is given by the bytes its moves ask for, every source block
+            """`moved_GBs` counts the blocks that the kernels load and store (memory_bytes), which is what HBM
+            carries for the message-combining schedules but for stops that the caches hold.  The s-exchange allgather is given by the bytes its moves ask for, every source block
             s times: mostly from cache, so the figure is not HBM traffic and gets no fraction."""
             starts = [iso.iso_request_start_info(r) for r in rs]
-            mv = (sum(i["bytes_read"] + i["bytes_written"] for i in starts) if hbm_label
+            mv = (sum(self.memory_bytes(r) for r in rs) if hbm_label
                   else sum(iso.iso_request_info(r)["bytes_read"] * 2 for r in rs))
             dl = sum(iso.iso_request_info(r)["delivered_bytes"] for r in rs)
             d = {"ms_per_step": round(ms, 5), "delivered_GBs": round(dl / ms / 1e6, 1),
