@@ -95,7 +95,8 @@ enum iso_algorithm {
      * receive buffer that cannot wait (its block is read again, or its source is
      * overwritten later: allgather trie nodes) goes to an extra workspace slot and is
      * copied from there by the last launch; the workspace grows by one plane of
-     * p*m bytes per such block.  Rounds left empty disappear.  The row-writing
+     * p*m bytes per such block.  Rounds left empty disappear.  iso_start of an
+     * all-to-all takes the first two of the rounds in one kernel.  The row-writing
      * launch takes equal blocks in dense rank-major rows with s <= 128 and
      * s*m <= 32 KiB (a little less for blocks that are no multiple of 16 bytes,
      * which are moved in overlapping units); any other request runs the same plan on

@@ -347,16 +347,16 @@ KernelRef select_deliver_bytes(const Launch &l) {
 
 template <typename V>
 KernelRef select_staged_round(const Launch &l) {
-    return with_policy<V>(l, [&](auto pol) -> KernelRef {
+    const auto form = [&](auto pol, auto tail, auto two) -> KernelRef {
         constexpr uint32_t kSmall = kSmallTileUnits / kThreads, kLarge = kTileUnits / kThreads;
-        const bool small = l.tile_units == kSmallTileUnits;
+        if (l.tile_units == kSmallTileUnits) return {(const void *)&staged_round_kernel<V, pol(), kSmall, tail(), two()>, &l.staged};
+        return {(const void *)&staged_round_kernel<V, pol(), kLarge, tail(), two()>, &l.staged};
+    };
+    return with_policy<V>(l, [&](auto pol) -> KernelRef {
         if constexpr (sizeof(V) > 1) {
-            if (l.tail)
-                return small ? KernelRef{(const void *)&staged_round_kernel<V, pol(), kSmall, true>, &l.staged}
-                             : KernelRef{(const void *)&staged_round_kernel<V, pol(), kLarge, true>, &l.staged};
+            if (l.tail) return l.staged.inner2 ? form(pol, std::true_type(), std::true_type()) : form(pol, std::true_type(), std::false_type());
         }
-        return small ? KernelRef{(const void *)&staged_round_kernel<V, pol(), kSmall, false>, &l.staged}
-                     : KernelRef{(const void *)&staged_round_kernel<V, pol(), kLarge, false>, &l.staged};
+        return l.staged.inner2 ? form(pol, std::false_type(), std::true_type()) : form(pol, std::false_type(), std::false_type());
     });
 }
 
@@ -605,6 +605,11 @@ public:
         }
         const bool by_size = all_hops_by_size(), hops = by_size || all_hops_in_one_launch();
         if (chains && !hops && chain_launch(launches)) return upload();
+        if (two_staged_rounds()) {
+            join_two_rounds();
+            st = bind_rounds();
+            return st == ISO_SUCCESS ? upload() : st;
+        }
         const bool star = !hops && star_in_one_launch(launches);
         const bool rows = !hops && !star && rows_in_one_launch();
         if (hops || rows || star || (merges && launches < bound_rounds.size())) {
@@ -656,6 +661,7 @@ private:
     std::vector<Pending> pending;
     bool all_hops = false;                        // the round is join_hops's
     bool one_size = false;                        // the rounds are split_by_size's
+    int second_dim = -1;                          // the first round is join_two_rounds's
     std::vector<uint64_t> large_sizes;
     size_t n_listed = 0;                          // of these: rq.launches; the rest are rq.start_launches
 
@@ -1088,6 +1094,54 @@ private:
         if (rounds.back().empty()) rounds.pop_back();
         bound_rounds.assign(rounds.size(), whole);
         one_size = true;
+    }
+
+    // iso_start of ISO_ALG_COMBINED_STAGED, all-to-all: its first two rounds in one launch (staged_round_kernel, TWO), where
+    // the blocks that either of them takes out of a send-buffer row fit a tile.
+    bool two_staged_rounds() const {
+        if (pl.algorithm != ISO_ALG_COMBINED_STAGED || op != ISO_OP_ALLTOALL || arena || !uniform || bound_rounds.size() < 3 || !retiled()) return false;
+        if (bound_rounds[0].kind != ISO_ROUND_SHIFT || bound_rounds[1].kind != ISO_ROUND_SHIFT || !bound_rounds.back().whole ||
+            bound_rounds.back().kind != ISO_ROUND_DELIVER || bound_rounds[0].dim == bound_rounds[1].dim)
+            return false;
+        const uint64_t upb = (size0 + (uint64_t(1) << min_log2) - 1) >> min_log2;
+        size_t n = rounds[0].size();
+        if (n > kLdsEntries || rounds[1].size() > kLdsEntries) return false;
+        for (const HostEntry &a : rounds[0])
+            if (a.dst_buf != ISO_BUF_WORK || a.de.src_stride == size0) return false;
+        for (const HostEntry &b : rounds[1]) {
+            const bool onward = first_hop_of(b) >= 0;    // else out of a send-buffer row
+            if (b.dst_buf != ISO_BUF_WORK || (!onward && b.de.src_stride == size0)) return false;
+            n += !onward;
+        }
+        return n <= kLdsEntries && n * upb <= kTileUnits && p * upb <= kMaxUnits;
+    }
+    // the entry of the first round that brings what `he` of the second one reads
+    int first_hop_of(const HostEntry &he) const {
+        for (size_t q = 0; q < rounds[0].size(); ++q)
+            if (rounds[0][q].de.dst == he.de.src) return (int)q;
+        return -1;
+    }
+
+    void join_two_rounds() {
+        std::vector<HostEntry> joined = rounds[0];
+        for (HostEntry &he : joined) he.de.units = 0, he.de.last_offset = 0;
+        for (const HostEntry &b : rounds[1]) {
+            const int q = first_hop_of(b);
+            if (q < 0) {
+                joined.push_back(b);
+                joined.back().de.dst = 0;
+                joined.back().de.shift = 0;
+                joined.back().moves = 0;
+            }
+            HostEntry &to = q < 0 ? joined.back() : joined[(size_t)q];
+            to.de.units = b.de.shift;
+            to.de.last_offset = b.de.dst;
+            ++to.moves;
+        }
+        second_dim = bound_rounds[1].dim;
+        rounds[1] = std::move(joined);
+        rounds.erase(rounds.begin());
+        bound_rounds.erase(bound_rounds.begin() + 1);
     }
 
     void defer_last_hops() {
@@ -1591,6 +1645,12 @@ private:
         put(sa.plane, sa.mul_plane, sa.shifts, 2);
         put(sa.inner, sa.mul_inner, sa.shifts, 3);
         put(sa.pj, sa.mul_pj, sa.more, 0);
+        if (second_dim >= 0 && &r == &bound_rounds[0]) {
+            sa.inner2 = (uint32_t)c.inner[second_dim];
+            sa.pj2 = (uint32_t)c.dims[second_dim];
+            put(sa.inner2, sa.mul_inner2, sa.shifts2, 0);
+            put(sa.pj2, sa.mul_pj2, sa.shifts2, 1);
+        }
         l.dyn_lds = (uint32_t)(k * ((uint64_t)sa.ranks * sa.upb + 1) * width);
         total = ((p + sa.ranks - 1) / sa.ranks) * kThreads;      // set_grid: one workgroup per tile
     }

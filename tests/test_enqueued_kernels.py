@@ -487,3 +487,14 @@ def test_unequal_blocks_by_size(stub_library, dims, sizes, alg, kernels):
     """Fewer launches than dimensions: one for every size of more than eight units, one for all smaller blocks."""
     got = stub_library.start_unequal(dims, gen.moore(3, 1), alg, list(sizes))
     assert " ".join(got) == kernels if kernels else all(k.startswith("block_round_kernel<true, false, ") and k.endswith(", 0>") for k in got), got
+
+
+@pytest.mark.parametrize("dims,offsets,m,kernels", [
+    ((64, 64, 64), gen.moore(3, 1), 16, "staged_round_kernel<v16, 2, 4u, false, true> deliver_kernel<v16, 0, 4u>"),
+    ((40, 40, 40), gen.moore(3, 1), 64, "staged_round_kernel<v16, 0, 4u, false, true> deliver_kernel<v16, 0, 4u>"),
+    ((32, 32, 32), gen.moore(3, 2), 256, "staged_round_kernel<v16, 1, 8u, false, true> deliver_kernel<v16, 1, 8u>"),
+    ((100, 100), gen.moore(2, 1), 64, None), ((20, 20, 20), gen.moore(3, 1), 40, None)])
+def test_first_two_rounds_of_the_staged_schedule(stub_library, dims, offsets, m, kernels):
+    """One launch for both where the rounds are re-tiled: whole units, or beyond 48 MiB."""
+    got = stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_STAGED, m)
+    assert " ".join(got) == kernels if kernels else not any(k.endswith("true>") for k in got), got

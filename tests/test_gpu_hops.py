@@ -144,3 +144,15 @@ def test_unequal_blocks_through_all_hops(dims, offsets, sizes, box):
             for i, (at, m) in enumerate(zip(displs, sizes)):
                 want[valid[:, i], at:at + m] = send[:, at:at + m].index_select(0, src[valid[:, i], i])
             assert torch.equal(recv, want), (dims, align, alg)
+
+
+@pytest.mark.parametrize("dims,offsets", [
+    ((5, 4, 7), gen.moore(3, 1)), ((23, 2, 31), gen.moore(3, 2)), ((17, 1, 19), gen.random_distinct(3, -3, 3, 40, 3)),
+    ((6, 7, 5, 9), gen.random_distinct(4, -3, 3, 30, 5)), ((4, 5, 3, 4, 6), gen.random_distinct(5, -3, 3, 40, 5)),
+    ((40, 41, 39), [(1, 0, 1), (0, 1, 1), (1, 1, 0), (2, 1, 3), (1, 1, 1), (1, 1, 1), (0, 0, 0)])])
+def test_staged_rounds_of_two_dimensions(dims, offsets):
+    """One and several hops before the last, along either dimension or both, sides of 1 and 2, repeated neighbours."""
+    offsets = [tuple(int(x) for x in c) for c in offsets]
+    for m in (16, 48, 256):
+        check_exchange(dims, offsets, iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_STAGED, m, RANK, send_off=3, recv_off=1)
+    check_exchange((64, 65, 66), gen.moore(3, 1), iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_STAGED, 9, RANK)      # last units that overlap
