@@ -547,10 +547,11 @@ class Bench:
         elif self.moved < self.requested and not args.algorithm.startswith("sx") and not args.mesh:
             kernel += ", allgather: also shift_push_kernel<16B>"
         tag = self.tag()
+        recorded = tag + ("_all_hops" if self.through_hops else "")
         roofline = {
             "kernel": kernel, "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-            "traffic": recorded_traffic(tag)[0], "traffic_source": recorded_traffic(tag)[1],
+            "traffic": recorded_traffic(recorded)[0], "traffic_source": recorded_traffic(recorded)[1],
             "algorithmic_bytes_per_launch": int(alg_bytes_per_launch),
             "avg_launch_us": round(avg_launch_ms * 1e3, 2), "launches_per_step": self.launches,
         }
