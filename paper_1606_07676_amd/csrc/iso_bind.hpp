@@ -1060,7 +1060,9 @@ private:
     }
 
     // Unequal blocks through all their hops: the larger ones a launch for every size, by the vector kernel, those of up to
-    // kSmallUnits units in one launch of the block kernel, if that is fewer launches than one per dimension.  A launch then
+    // kSmallUnits units in one launch of the block kernel, if that is fewer launches than one per dimension that blocks move
+    // along (one for every kLdsEntries blocks of a size; as many or more lose: 32^2, 440 neighbours, 4 and 8 B, 4 launches
+    // against 2, 15.3 us against 9.5; 8^5, four sizes along one dimension, 4 against 1, 28.1 against 19.3).  A launch then
     // moves blocks of one kind, and the larger ones need no search for a unit's entry.  (Stencils, us, a launch per dimension
     // -> here: 32^3, 64 B 338 -> 291, 25 B 90 -> 78; 64^3, 16 B 379 -> 323, 4 B 150 -> 133, 80^3, 8 B 558 -> 400;
     // 16^4, 8 B 373 -> 342; 8^5, 4 B 512 -> 391; 500^2, 64 B 81 -> 57; 8^3, 64 B 15.8 -> 11.8, 40^2, 64 B 6.3 -> 3.9.)  Small
@@ -1071,15 +1073,39 @@ private:
         const uint64_t llc = kLastLevelCacheBytes, bytes = inf.delivered_bytes;
         if (op != ISO_OP_ALLTOALL || arena || uniform || lay.slot_major || c.d < 2 || c.d > kVectorDims || wl.bytes >> 36)
             return false;
-        bool small = false, units = true;
-        for (const std::vector<HostEntry> &round : rounds)
-            for (const HostEntry &he : round) {
-                if (he.de.units <= kSmallUnits) small = true, units = units && (he.size < 16 || he.size % 16 == 0);
-                else if (std::find(large_sizes.begin(), large_sizes.end(), he.size) == large_sizes.end()) large_sizes.push_back(he.size);
-                if (large_sizes.size() + small >= (size_t)c.d) return false;
+        std::vector<uint64_t> blocks;                    // of every large size
+        uint64_t small = 0;
+        bool units = true;
+        for (size_t i = 0; i < s; ++i) {
+            const uint64_t m = lay.size[i];
+            if (!m) continue;
+            const uint32_t l2 = unit_log2_of(m);
+            if ((m + (uint64_t(1) << l2) - 1) >> l2 <= kSmallUnits) {
+                ++small;
+                units = units && (m < 16 || m % 16 == 0);
+                continue;
             }
+            const size_t at = (size_t)(std::find(large_sizes.begin(), large_sizes.end(), m) - large_sizes.begin());
+            if (at == large_sizes.size()) {
+                large_sizes.push_back(m);
+                blocks.push_back(0);
+                if (large_sizes.size() >= (size_t)c.d) return false;
+            }
+            ++blocks[at];
+        }
+        uint64_t launches = (small + kLdsEntries - 1) / kLdsEntries;
+        for (const uint64_t n : blocks) launches += (n + kLdsEntries - 1) / kLdsEntries;
+        if (launches >= dimensions_moved()) return false;
         if (pl.algorithm == ISO_ALG_COMBINED_BYDIM) return !c.mesh && small && !large_sizes.empty() && bytes > llc / 4;
         return pl.algorithm == ISO_ALG_COMBINED && (units || c.d == 2 || (c.d == 3 && !large_sizes.empty()));
+    }
+
+    // The dimensions that some block moves along: launches of iso_start with one for each.
+    uint64_t dimensions_moved() const {
+        uint32_t moved = 0;
+        for (size_t ri = 0; ri < rounds.size(); ++ri)
+            if (bound_rounds[ri].kind == ISO_ROUND_SHIFT && !rounds[ri].empty()) moved |= 1u << bound_rounds[ri].dim;
+        return (uint64_t)__builtin_popcount(moved);
     }
 
     void split_by_size() {

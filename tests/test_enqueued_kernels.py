@@ -498,3 +498,16 @@ def test_first_two_rounds_of_the_staged_schedule(stub_library, dims, offsets, m,
     """One launch for both where the rounds are re-tiled: whole units, or beyond 48 MiB."""
     got = stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_STAGED, m)
     assert " ".join(got) == kernels if kernels else not any(k.endswith("true>") for k in got), got
+
+
+@pytest.mark.parametrize("dims,offsets,sizes,kernels", [
+    ((32, 32), gen.moore(2, 10), [4 + 4 * (i % 2) for i in range(440)], 2), ((32, 32), gen.moore(2, 5), [4 + 4 * (i % 2) for i in range(120)], 1),
+    ((8, 8, 8), gen.moore(3, 3), [4 + 4 * (i % 2) for i in range(342)], 3), ((8, 8, 8), gen.moore(3, 3)[:256], [4 + 4 * (i % 2) for i in range(256)], 2),
+    ((8,) * 5, [(i, 0, 0, 0, 0) for i in (1, 2, 3, 4)], [200, 300, 400, 500], 1), ((8,) * 5, [(i, 0, 0, 0, 0) for i in (1, 2, 3, 4)], [20, 30, 40, 50], 1),
+    ((8,) * 4, [(1, 0, 0, 0), (2, 0, 0, 0), (0, 3, 0, 0), (0, 2, 0, 0), (1, 1, 0, 0)], [200, 300, 400, 200, 300], 2)])
+@pytest.mark.parametrize("box", [False, True])
+def test_unequal_blocks_take_no_more_launches_than_one_per_dimension(stub_library, dims, offsets, sizes, kernels, box):
+    """Launches and not sizes count, each of at most 128 blocks, against the dimensions that some block moves along."""
+    offsets = [tuple(int(x) for x in c) for c in offsets]
+    got = stub_library.start_unequal(dims, offsets, iso.ISO_ALG_COMBINED, sizes, (0,) * len(dims) if box else None)
+    assert len(got) == kernels, got
