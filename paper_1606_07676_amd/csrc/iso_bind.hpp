@@ -603,8 +603,8 @@ public:
             if ((st = bind_rounds()) != ISO_SUCCESS) return st;
             n_listed = pending.size();
         }
-        const bool by_size = all_hops_by_size(), hops = by_size || all_hops_in_one_launch();
-        if (chains && !hops && chain_launch(launches)) return upload();
+        const bool by_size = all_hops_by_size(), hops = by_size || all_hops_in_one_launch(launches);
+        if (chains && (!hops || hops_launches() > 1) && chain_launch(launches)) return upload();
         if (two_staged_rounds()) {
             join_two_rounds();
             st = bind_rounds();
@@ -989,6 +989,13 @@ private:
     // 128 B 197 -> 152, 100 B 168 -> 128.
     // Small ones: all-to-all 10^3, 26 neighbours, 256 B 10.9 (chain) -> 6.2, 12^3, 256 B 15.4 -> 9.8; allgather 20^3, 40 B
     // 11.4 -> 4.0, 5^5, 40, 128 B 27.8 -> 9.3; 13 x 12 x 14, 80 B slot-major 10.0 -> 4.7; 6^3, 20, 48 B 3.5 -> 3.7.
+    // More than one table: the chain of a small collective stays (5^2, 440 neighbours, 384 B 3.9 us, here in four launches
+    // 12.0; 7^2, 224, 768 B 5.3 and 6.5), and up to 32 MiB for each launch here, at most the last-level cache, so do fewer
+    // launches (us, before -> here: 3^3, 728, 4 launches against 6, all-to-all 1280 B 27.7 -> 33.3, 5 KiB 79 -> 81, 21 KiB 297
+    // -> 225; 5^2, 440, 3 against 4, 4480 B 33.7 -> 39.4, 18 KiB 113 -> 108; 8^2, 960, 3 against 8, 3200 B 128 -> 134, 6784 B
+    // 265 -> 250, allgather 768 B 17.5 -> 23.0, 6784 B 81 -> 77; 4^4, 2400, 4 against 19, allgather 256 B 52 -> 61, 640 B 116
+    // -> 100; 32^2, 440, 2 against 4, 384 B 128 -> 112; what gains and stays: 5^4, 624, 4 against 5, 256 B 124 -> 89).  As
+    // many: 5^3, 342, 384 B 22.6 -> 20.9.
     // Boxes, where the moves of blocks that no one receives are left out: 45 x 37 x 29, 26 neighbours, 100 B slot-major 97 -> 64,
     // 256 B 235 -> 151; 8^5, 40, 512 B 877 -> 240; 64^3, allgather 256 B 550 -> 285.
     // It gains at every block size from a MiB on (all-to-all 64^3, 100 B 797 -> 402, 192 B 1038 -> 688, 16^3, 128 B 19.4 ->
@@ -996,7 +1003,7 @@ private:
     // tests/test_enqueued_kernels.py lays down: small blocks that are no whole lines, rank-major, with all-to-alls of most
     // sizes and larger allgathers, and for ISO_ALG_COMBINED_BYDIM more of them up to 7/4 of the last-level cache; and meshes,
     // but for BYDIM.
-    bool all_hops_in_one_launch() const {
+    bool all_hops_in_one_launch(uint64_t launches) const {
         const uint64_t llc = kLastLevelCacheBytes, bytes = inf.delivered_bytes;
         const bool a2a = op == ISO_OP_ALLTOALL, bydim = pl.algorithm == ISO_ALG_COMBINED_BYDIM, lines = size0 % 128 == 0;
         if (arena || !uniform || size0 < 16 || c.d > kVectorDims || bytes <= llc / 64) return false;
@@ -1005,6 +1012,7 @@ private:
         for (const Round &r : pl.rounds)
             for (const iso_plan_entry_t &e : r.entries) onward = onward || e.src_buf != ISO_BUF_SEND;
         if (!onward) return false;
+        if (hops_launches() > launches && bytes <= std::min(llc, hops_launches() * llc / 8)) return false;
         if (c.mesh && (!bydim || (!a2a && !lines && size0 < 256))) return false;
         if (lay.slot_major) return !a2a || bytes > (lines ? llc / 8 : llc * 3 / 16);
         if (!a2a) {
@@ -1014,6 +1022,14 @@ private:
         if (lines && size0 >= 256) return true;
         if (lines || size0 >= 512) return bytes > (bydim ? llc / 8 : llc / 16);
         return size0 >= 320 && bytes > (bydim ? llc * 7 / 4 : llc * 3 / 16);
+    }
+
+    // Launches of join_hops's entries, which are the blocks of an all-to-all and the nodes of an allgather's trie.
+    uint64_t hops_launches() const {
+        uint64_t n = 0;
+        if (op == ISO_OP_ALLTOALL) n = s - (uint64_t)std::count(lay.size.begin(), lay.size.end(), uint64_t(0));
+        else for (const std::vector<HostEntry> &round : rounds) n += round.size();
+        return (n + kLdsEntries - 1) / kLdsEntries;
     }
 
     // All-to-all: one entry per block, from the send buffer to the receive buffer, its stops in its place in the workspace (in

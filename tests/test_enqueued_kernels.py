@@ -511,3 +511,14 @@ def test_unequal_blocks_take_no_more_launches_than_one_per_dimension(stub_librar
     offsets = [tuple(int(x) for x in c) for c in offsets]
     got = stub_library.start_unequal(dims, offsets, iso.ISO_ALG_COMBINED, sizes, (0,) * len(dims) if box else None)
     assert len(got) == kernels, got
+
+
+@pytest.mark.parametrize("dims,offsets,m,op,kernels", [
+    ((5, 5), gen.moore(2, 10), 384, 0, ["chain_kernel"]), ((5, 5), gen.moore(2, 10), 768, 1, ["chain_kernel"]), ((7, 7), gen.moore(2, 7), 768, 0, ["chain_kernel"]),
+    ((5, 5), gen.moore(2, 10), 4480, 0, 3), ((5, 5), gen.moore(2, 10), 4480, 1, 3), ((8, 8), gen.moore(2, 15), 768, 1, 3), ((3, 3, 3), gen.moore(3, 4), 1280, 0, 4),
+    ((8, 8), gen.moore(2, 15), 6784, 0, ["vector_round_kernel"] * 8), ((32, 32), gen.moore(2, 10), 384, 0, ["vector_round_kernel"] * 4), ((32, 32), gen.moore(2, 10), 256, 0, 2), ((5, 5, 5), gen.moore(3, 3), 384, 0, ["vector_round_kernel"] * 3)])
+@pytest.mark.parametrize("alg", [iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM])
+def test_more_neighbours_than_one_table_takes(stub_library, dims, offsets, m, op, kernels, alg):
+    """The chain stays, and up to 32 MiB a launch and the size of the last-level cache so do fewer launches."""
+    got = _names(stub_library.start(dims, offsets, op, alg, m))
+    assert got == kernels if isinstance(kernels, list) else len(got) == kernels and "vector_round_kernel" not in got, got
