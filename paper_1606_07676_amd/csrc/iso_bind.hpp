@@ -249,6 +249,9 @@ KernelRef select_way(const Launch &l) {
     if constexpr (sizeof(V) == 16 && !(WAY & kStrides)) {           // (kStrides: an allgather, which loads through the caches)
         if (l.policy & kStreamLoads) return form(std::integral_constant<int, kStreamLoads>());
     }
+    if constexpr (WAY == kStrides) {                                // (less than a sector: no whole wavefronts)
+        if (l.policy & kPlainStores) return {(const void *)&vector_round_kernel<V, D, true, kPlainStores, TAIL, WAY>, &l.vec};
+    }
     return form(std::integral_constant<int, 0>());
 }
 
@@ -1577,6 +1580,14 @@ private:
             // stops (cached -> streaming loads: 8^5, 40 neighbours, 128 B 120 -> 115, 300 B 338 -> 320; 16^4, 30, 400 B 546
             // -> 526, 1 KiB 1426 -> 1388; fewer hops 64^3, 26, 300 B 1144 -> 1206, 1000 B 3743 -> 3888).
             if (all_hops && a2a && inf.entries >= 3 * (int64_t)s) return kStreamLoads;
+            // Trie nodes beside the receive blocks, less than a sector: many of them, or beyond the cache, have to meet there
+            // as those of the rounds do, before a sector is written (streaming -> plain stores: 9 x 8 x 8 x 9 x 8, 40 random
+            // neighbours with 87 nodes more, 16 B 96 -> 29 and 108 -> 31, a launch per dimension 52 and 54; 16 x 16 x 15 x 15,
+            // 30 and 42, 20 B 88 -> 30 and 73 -> 38; 12 x 12 x 11 x 12 x 12, 10 and 26, 20 B 96 -> 48 and 80 -> 53; fewer
+            // 24 x 25 x 24, 40 and 23, 16 B 6.6 -> 6.6 and 7.1 -> 8.7; 16 x 16 x 16 x 15, 10 and 19, 32 B 20 -> 14 and 17 -> 20).
+            if (all_hops && l.way == kStrides && size0 < 64 &&
+                (inf.entries > (int64_t)s + 32 || inf.bytes_written > kLastLevelCacheBytes / 2))
+                return kPlainStores;
             return a2a && l.vector_dims && lines && bytes > above ? kStreamLoads : 0;
         }
         if (l.kernel == kBlockKernel && all_hops) return !c.mesh && !large_sizes.empty() && bytes > kLastLevelCacheBytes / 4 ? kBySize : kPlainStores;

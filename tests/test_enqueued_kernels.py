@@ -522,3 +522,14 @@ def test_more_neighbours_than_one_table_takes(stub_library, dims, offsets, m, op
     """The chain stays, and up to 32 MiB a launch and the size of the last-level cache so do fewer launches."""
     got = _names(stub_library.start(dims, offsets, op, alg, m))
     assert got == kernels if isinstance(kernels, list) else len(got) == kernels and "vector_round_kernel" not in got, got
+
+
+@pytest.mark.parametrize("dims,n,m,policy", [
+    ((9, 8, 8, 9, 8), 40, 16, 2), ((16, 16, 15, 15), 30, 20, 2), ((7,) * 5, 40, 56, 2), ((7,) * 5, 40, 64, 0), ((12, 12, 11, 12, 12), 10, 20, 2),
+    ((12, 12, 11, 12, 12), 10, 16, 0), ((16, 16, 16, 15), 10, 32, 0), ((24, 25, 24), 40, 16, 0), ((40, 40, 36), 40, 20, 0)])
+def test_small_allgather_blocks_through_all_hops_meet_in_the_caches(stub_library, dims, n, m, policy):
+    """More than 32 trie nodes beside the receive blocks, or more than half the cache to write: plain stores under a sector."""
+    offsets = gen.random_distinct(len(dims), -3, 3, n, gen.configs.CONFIG5_NEIGHBOURHOOD_SEED)
+    for alg in (iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM):
+        (got,) = stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, alg, m)
+        assert got.endswith(", 2>") and _policies([got]) == {("vector", policy)}, got

@@ -59,6 +59,14 @@ def test_allgather_through_all_hops(dims, offsets, m, layout, alg, send_off, rec
     check_exchange(dims, [tuple(int(x) for x in c) for c in offsets], iso.ISO_OP_ALLGATHER, alg, m, layout, send_off, recv_off)
 
 
+@pytest.mark.parametrize("dims,n,m,send_off,recv_off", [((9, 8, 8, 9, 8), 40, 16, 0, 0), ((7, 8, 7, 6, 7), 40, 17, 1, 3), ((11, 12, 11, 13), 30, 63, 0, 0),
+                                                        ((12, 12, 11, 12, 12), 10, 21, 5, 0)])
+def test_small_allgather_blocks_and_many_nodes(dims, n, m, send_off, recv_off):
+    """Plain stores, under a sector: whole units and last units that overlap, any address."""
+    offsets = [tuple(int(x) for x in c) for c in gen.random_distinct(len(dims), -3, 3, n, 160607676)]
+    check_exchange(dims, offsets, iso.ISO_OP_ALLGATHER, COMBINED, m, RANK, send_off, recv_off)
+
+
 @pytest.mark.parametrize("layout", [RANK, SLOT])
 def test_equal_blocks_of_the_irregular_call_with_empty_ones(layout):
     """Every third block empty, rows with gaps: those bytes and blocks stay as they are."""
