@@ -1922,13 +1922,20 @@ private:
     //   Trie nodes in the workspace beside the receive blocks: push 4 at a time (8^5, 40 random neighbours, 4 KiB 2, 4, 8 at a
     //   time 3507, 2975, 3029; 1 KiB slot-major 865, 724, 755; pull 3807 and 1085), slot-major also where the eighth fits, 2 at
     //   a time (16^4, 30, 256 B pull 272, push 195; 300 B 350 and 311; 8^5, 500 B 495 and 415).
+    //   All receive blocks, slot-major: an XCD meets the same ranks in every plane, and its reads stay in its L2, only if a
+    //   plane is nearly a multiple of the runs of all XCDs (set_grid).  20^3, 26 neighbours, pull and push 2 at a time: 1024
+    //   to 1072 B, up to 3/8 of a run off 32 to 42 and 37 to 48, 1104 B, 7/8 off, 58 and 48, 1120 B 62 and 52; half as many
+    //   XCDs off, 784 B 24 and 33, 800 B, 1/4 of a run further, 35 and 34.  Else push 2 at a time from 6 MiB to send on (a
+    //   launch per dimension, pull, push: 191 x 177, 24 neighbours, 640 B 109, 137, 108; 41 x 49 x 53, 24, 192 B 106, 120,
+    //   106; 20 x 21 x 24, 26, 1788 B 115, 129, 104; 12 x 10^3, 40, 1813 B 212, 233, 192; 7 x 5 x 8 x 8, 80, 2500 B (5.3 MiB)
+    //   116, 82, 95).
     void allgather_order(Launch &l, const HostEntry *ents, uint32_t k) {
         const uint64_t l2 = uint64_t(4) << 20, sent = p * size0;
         const bool nodes = all_hops && pl.work_slots > 0;
         if (lay.slot_major) {
             if (c.mesh) return;
             if (l.vector_dims && sent > 7 * l2) l.vec.per = std::min(k, 4u);
-            else if (l.vector_dims && nodes) l.vec.per = std::min(k, 2u);
+            else if (l.vector_dims && (nodes || (all_hops && sent > l2 * 3 / 2 && !planes_meet()))) l.vec.per = std::min(k, 2u);
             return;
         }
         int64_t lo = 0, hi = 0;                                  // the neighbours' linear distances, shortest way round
@@ -1950,6 +1957,13 @@ private:
             l.vec.per = std::min(k, nodes ? 4u : 8u);
             l.eighths = false;
         }
+    }
+
+    // Slot-major: do the runs of one XCD hold the same ranks in every plane?  (see allgather_order)
+    bool planes_meet() const {
+        const uint64_t run = uint64_t(128) * kThreads, plane = p * ((size0 + (uint64_t(1) << min_log2) - 1) >> min_log2);
+        const uint64_t off = plane % (8 * run), far = std::min(off, 8 * run - off);
+        return far <= run * 3 / 8 || (far >= 4 * run - run / 8 && far <= 4 * run);
     }
 
     // Irregular blocks, or a mesh's s-exchange: as many entries as fit the 32-bit unit index.

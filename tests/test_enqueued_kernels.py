@@ -533,3 +533,14 @@ def test_small_allgather_blocks_through_all_hops_meet_in_the_caches(stub_library
     for alg in (iso.ISO_ALG_COMBINED, iso.ISO_ALG_COMBINED_BYDIM):
         (got,) = stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, alg, m)
         assert got.endswith(", 2>") and _policies([got]) == {("vector", policy)}, got
+
+
+@pytest.mark.parametrize("dims,offsets,m,push", [
+    ((191, 177), gen.moore(2, 2), 640, True), ((41, 49, 53), gen.von_neumann(3, 2), 192, True), ((12, 10, 10, 10), gen.von_neumann(4, 2), 1813, True),
+    ((20, 20, 20), gen.moore(3, 1), 992, True), ((20, 20, 20), gen.moore(3, 1), 1024, False), ((20, 20, 20), gen.moore(3, 1), 1040, False), ((20, 20, 20), gen.moore(3, 1), 1072, False),
+    ((20, 20, 20), gen.moore(3, 1), 1088, True), ((20, 20, 20), gen.moore(3, 1), 1304, False), ((20, 20, 20), gen.moore(3, 1), 1320, True), ((20, 20, 20), gen.moore(3, 1), 1296, True),
+    ((20, 20, 20), gen.moore(3, 1), 784, False), ((64, 64, 64), gen.moore(3, 1), 32, False), ((64, 64, 64), gen.moore(3, 1), 128, True), ((45, 37, 29), gen.moore(3, 1), 128, False)])
+def test_slot_major_allgathers_through_all_hops_where_planes_do_not_meet(stub_library, dims, offsets, m, push):
+    """From 6 MiB to send on: pushed, unless a plane is a multiple of the runs of all XCDs, or of half of them; above 28 MiB always."""
+    (got,) = _names(stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, iso.ISO_ALG_COMBINED, m, iso.ISO_LAYOUT_SLOT_MAJOR))
+    assert (got == "push_round_kernel") == push, got

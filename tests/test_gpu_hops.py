@@ -67,6 +67,13 @@ def test_small_allgather_blocks_and_many_nodes(dims, n, m, send_off, recv_off):
     check_exchange(dims, offsets, iso.ISO_OP_ALLGATHER, COMBINED, m, RANK, send_off, recv_off)
 
 
+@pytest.mark.parametrize("dims,offsets,m,send_off,recv_off", [((20, 21, 24), gen.moore(3, 1), 901, 0, 5), ((29, 31, 27), gen.moore(3, 1)[:25], 272, 3, 0),
+                                                              ((10, 11, 9, 8), gen.von_neumann(4, 2), 1040, 0, 0), ((181, 177), gen.moore(2, 1) + [(0, 0)], 210, 0, 0)])
+def test_slot_major_allgathers_pushed_two_at_a_time(dims, offsets, m, send_off, recv_off):
+    """All nodes are receive blocks, an even and an odd number of them."""
+    check_exchange(dims, [tuple(int(x) for x in c) for c in offsets], iso.ISO_OP_ALLGATHER, COMBINED, m, SLOT, send_off, recv_off)
+
+
 @pytest.mark.parametrize("layout", [RANK, SLOT])
 def test_equal_blocks_of_the_irregular_call_with_empty_ones(layout):
     """Every third block empty, rows with gaps: those bytes and blocks stay as they are."""
