@@ -999,6 +999,9 @@ private:
     // 265 -> 250, allgather 768 B 17.5 -> 23.0, 6784 B 81 -> 77; 4^4, 2400, 4 against 19, allgather 256 B 52 -> 61, 640 B 116
     // -> 100; 32^2, 440, 2 against 4, 384 B 128 -> 112; what gains and stays: 5^4, 624, 4 against 5, 256 B 124 -> 89).  As
     // many: 5^3, 342, 384 B 22.6 -> 20.9.
+    // Two dimensions, allgathers of parts of lines with more to send than the last-level cache holds: not pushed
+    // (allgather_order), and what the pulls miss comes from memory every time (250 x 260, 10 neighbours, 4300 B 951 -> 799,
+    // 4416 B 820 -> 1031, 6432 B 1232 -> 1498; 8, 5600 B 794 -> 903; three 64^3, 26, 1168 B 2545 -> 2361).
     // Boxes, where the moves of blocks that no one receives are left out: 45 x 37 x 29, 26 neighbours, 100 B slot-major 97 -> 64,
     // 256 B 235 -> 151; 8^5, 40, 512 B 877 -> 240; 64^3, allgather 256 B 550 -> 285.
     // It gains at every block size from a MiB on (all-to-all 64^3, 100 B 797 -> 402, 192 B 1038 -> 688, 16^3, 128 B 19.4 ->
@@ -1018,6 +1021,7 @@ private:
         if (hops_launches() > launches && bytes <= std::min(llc, hops_launches() * llc / 8)) return false;
         if (c.mesh && (!bydim || (!a2a && !lines && size0 < 256))) return false;
         if (lay.slot_major) return !a2a || bytes > (lines ? llc / 8 : llc * 3 / 16);
+        if (!a2a && c.d == 2 && p * size0 > llc * 17 / 16 && !whole_lines()) return false;
         if (!a2a) {
             if (size0 >= 512 || (!bydim && (lines || size0 >= 256)) || bytes <= (size0 < 64 ? llc * 3 / 16 : llc / 2)) return true;
             return lines && bytes > llc * 7 / 4;
@@ -1025,6 +1029,14 @@ private:
         if (lines && size0 >= 256) return true;
         if (lines || size0 >= 512) return bytes > (bydim ? llc / 8 : llc / 16);
         return size0 >= 320 && bytes > (bydim ? llc * 7 / 4 : llc * 3 / 16);
+    }
+
+    // Every destination begins and ends with a 128-byte line.
+    bool whole_lines() const {
+        uint64_t bits = size0;
+        for (const std::vector<HostEntry> &round : rounds)
+            for (const HostEntry &he : round) bits |= he.de.dst | he.de.dst_stride;
+        return (bits & 127u) == 0;
     }
 
     // Launches of join_hops's entries, which are the blocks of an all-to-all and the nodes of an allgather's trie.
@@ -1922,6 +1934,9 @@ private:
     //   Trie nodes in the workspace beside the receive blocks: push 4 at a time (8^5, 40 random neighbours, 4 KiB 2, 4, 8 at a
     //   time 3507, 2975, 3029; 1 KiB slot-major 865, 724, 755; pull 3807 and 1085), slot-major also where the eighth fits, 2 at
     //   a time (16^4, 30, 256 B pull 272, push 195; 300 B 350 and 311; 8^5, 500 B 495 and 415).
+    //   All hops of blocks of whole lines push whatever the window, where the send buffer exceeds the last-level cache
+    //   (a launch per dimension, pull, push: 400 x 420, 8 neighbours, 2 KiB 677, 860, 580; 250 x 260, 8, 5 KiB 686, 804,
+    //   577; 400 x 420, 10, 2 KiB 937, 1236, 933).
     //   All receive blocks, slot-major: an XCD meets the same ranks in every plane, and its reads stay in its L2, only if a
     //   plane is nearly a multiple of the runs of all XCDs (set_grid).  20^3, 26 neighbours, pull and push 2 at a time: 1024
     //   to 1072 B, up to 3/8 of a run off 32 to 42 and 37 to 48, 1104 B, 7/8 off, 58 and 48, 1120 B 62 and 52; half as many
@@ -1953,7 +1968,7 @@ private:
         const uint64_t window_ranks = std::min<uint64_t>(p, (uint64_t)(hi - lo) + 1), window = window_ranks * size0;
         const uint64_t run = uint64_t(128) * kThreads << min_log2;      // bytes written by a run of tiles (set_grid)
         l.eighths = sent > l2 && 4 * window_ranks * k * size0 > run;
-        if (l.vector_dims && !c.mesh && lines && (window > 3 * l2 || (window > l2 && sent > kLastLevelCacheBytes))) {
+        if (l.vector_dims && !c.mesh && lines && (window > 3 * l2 || ((window > l2 || all_hops) && sent > kLastLevelCacheBytes))) {
             l.vec.per = std::min(k, nodes ? 4u : 8u);
             l.eighths = false;
         }

@@ -74,6 +74,12 @@ def test_slot_major_allgathers_pushed_two_at_a_time(dims, offsets, m, send_off, 
     check_exchange(dims, [tuple(int(x) for x in c) for c in offsets], iso.ISO_OP_ALLGATHER, COMBINED, m, SLOT, send_off, recv_off)
 
 
+@pytest.mark.parametrize("m", [4224, 4480 + 16])
+def test_two_dimensional_allgather_of_more_than_the_cache_holds(m):
+    """Whole lines, pushed from a window that the L2 holds; parts of lines, a launch per dimension."""
+    check_exchange((260, 257), [tuple(int(x) for x in c) for c in gen.moore(2, 1)], iso.ISO_OP_ALLGATHER, COMBINED, m, RANK)
+
+
 @pytest.mark.parametrize("layout", [RANK, SLOT])
 def test_equal_blocks_of_the_irregular_call_with_empty_ones(layout):
     """Every third block empty, rows with gaps: those bytes and blocks stay as they are."""
