@@ -554,3 +554,15 @@ def test_allgathers_of_more_than_the_cache_holds(stub_library, dims, offsets, m,
     """Whole lines are pushed; others stay a launch per dimension in two dimensions."""
     got = _names(stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, iso.ISO_ALG_COMBINED, m))
     assert got == [want] if isinstance(want, str) else len(got) == want and got[0].startswith("shift"), got
+
+
+@pytest.mark.parametrize("dims,edge,box,joined", [
+    ((64, 64, 64), 3, False, False), ((64, 64, 64), 2, False, False), ((64, 64, 64), 4, False, True), ((32, 32, 32), 3, False, True), ((48, 48, 48), 3, False, False),
+    ((512, 512), 3, False, False), ((512, 512), 11, False, False), ((512, 512), 15, False, True), ((200, 200), 3, False, True), ((512, 512), 3, True, True),
+    ((16,) * 4, 2, False, False), ((9,) * 5, 2, False, False), ((8,) * 5, 4, False, True), ((64, 64, 64), 8, True, False), ((64, 64, 64), 8, False, True), ((64, 64, 64), 4, True, False),
+    ((32, 32, 32), 8, True, True), ((64, 64, 64), 16, True, True), ((20,) * 4, 4, True, False)])
+def test_blocks_of_a_few_bytes_on_large_tori(stub_library, dims, edge, box, joined):
+    """A launch per dimension for blocks of a few bytes, and on boxes for small ones alone, from about a million moves on."""
+    sizes = [int(x) for x in gen.stencil_block_sizes(gen.moore(len(dims), 1), edge)]
+    got = stub_library.start_unequal(dims, gen.moore(len(dims), 1), iso.ISO_ALG_COMBINED, sizes, (0,) * len(dims) if box else None)
+    assert (len(got) < len(dims)) == joined, got
