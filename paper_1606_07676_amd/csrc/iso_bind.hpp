@@ -319,10 +319,9 @@ KernelRef select_width(const Launch &l) {
     return select_regular<V, false, false>(l);
 }
 
-template <int POLICY>
-KernelRef select_block_hops(const Launch &l) {
-    if (l.vector_dims == 3) return {(const void *)&block_round_kernel<true, true, POLICY, false, 3>, &l.block};
-    return {(const void *)&block_round_kernel<true, true, POLICY, false, kVectorDims>, &l.block};
+inline KernelRef select_block_hops(const Launch &l) {
+    if (l.vector_dims == 3) return {(const void *)&block_round_kernel<true, true, kPlainStores, false, 3>, &l.block};
+    return {(const void *)&block_round_kernel<true, true, kPlainStores, false, kVectorDims>, &l.block};
 }
 
 template <bool LDS, bool MESH>
@@ -385,7 +384,7 @@ inline KernelRef select_kernel(int vector_bytes, const Launch &l) {
                                                    : KernelRef{(const void *)&deliver_kernel<vec16_t, pol(), kLarge>, &l.deliver};
         });
     if (l.kernel == kBlockKernel) {
-        if (l.way) return l.policy == kBySize ? select_block_hops<kBySize>(l) : select_block_hops<kPlainStores>(l);
+        if (l.way) return select_block_hops(l);
         if (l.mesh) return l.lds_table ? select_block<true, true>(l) : select_block<false, true>(l);
         return l.lds_table ? select_block<true, false>(l) : select_block<false, false>(l);
     }
@@ -1613,7 +1612,7 @@ private:
                 return kPlainStores;
             return a2a && l.vector_dims && lines && bytes > above ? kStreamLoads : 0;
         }
-        if (l.kernel == kBlockKernel && all_hops) return !c.mesh && !large_sizes.empty() && bytes > kLastLevelCacheBytes / 4 ? kBySize : kPlainStores;
+        if (l.kernel == kBlockKernel && all_hops) return kPlainStores;       // (block_through_stops)
         if (r.kind == ISO_ROUND_VECTOR) return 0;
         if (l.kernel == kBlockKernel) {
             if (inf.block_bytes < 128 && l.block.equal_units <= 1 && !lay.slot_major && bytes <= kLastLevelCacheBytes / 4)

@@ -295,12 +295,16 @@ def test_rounds_of_unequal_blocks(stub_library, dims, sizes, periodic, want):
     assert got == {("block", want)}
 
 
-@pytest.mark.parametrize("dims,edge,periodic,alg,want", [
-    ((32, 32, 32), 64, None, 0, True), ((32, 32, 32), 64, None, 1, True), ((32, 32, 32), 64, None, 5, False), ((32, 32, 32), 64, (0, 0, 0), 0, False),
-    ((24, 24, 24), 25, None, 0, False), ((32, 32, 32), 25, None, 0, True), ((64, 64, 64), 11, None, 0, False), ((64, 64, 64), 12, None, 0, True)])
-def test_small_and_large_blocks_by_their_size(stub_library, dims, edge, periodic, alg, want):
+FIVE = [(8, 200, 300, 400, 500)[i % 5] for i in range(26)]          # too many sizes for a launch each
+
+
+@pytest.mark.parametrize("dims,sizes,periodic,alg,want", [
+    ((32, 32, 32), FIVE, None, 0, True), ((32, 32, 32), FIVE, None, 1, True), ((32, 32, 32), FIVE, None, 5, False), ((32, 32, 32), FIVE, (0, 0, 0), 0, False),
+    ((20, 20, 20), FIVE, None, 0, False), ((32, 32, 32), [max(200, x) for x in FIVE], None, 0, False), ((32, 32, 32), 64, None, 5, False), ((32, 32, 32), 64, (0, 0, 0), 0, False),
+    ((24, 24, 24), 25, None, 0, False), ((64, 64, 64), 11, None, 0, False)])
+def test_small_and_large_blocks_by_their_size(stub_library, dims, sizes, periodic, alg, want):
     """Blocks of up to 128 bytes and larger ones in one launch, a quarter of the cache and more; 11 x 11 is not larger."""
-    sizes = list(gen.stencil_block_sizes(gen.moore(3, 1), edge))
+    sizes = sizes if isinstance(sizes, list) else [int(x) for x in gen.stencil_block_sizes(gen.moore(3, 1), sizes)]
     got = _policies(stub_library.start_unequal(dims, gen.moore(3, 1), alg, sizes, periodic))
     assert (("block", 4) in got) == want, got
 
@@ -476,8 +480,10 @@ def test_boxes_by_full_vectors(stub_library, dims, op, m, layout, alg, kernel):
 
 
 @pytest.mark.parametrize("dims,sizes,alg,kernels", [
-    ((32, 32, 32), gen.stencil_block_sizes(gen.moore(3, 1), 64), 0, "vector_round_uniform_kernel<3, 1, 1> block_round_kernel<true, true, 4, false, 3>"),
-    ((32, 32, 32), gen.stencil_block_sizes(gen.moore(3, 1), 25), 1, "vector_round_kernel<v16, 3, true, 0, true, 1> block_round_kernel<true, true, 4, false, 3>"),
+    ((32, 32, 32), gen.stencil_block_sizes(gen.moore(3, 1), 64), 0, "vector_round_uniform_kernel<3, 1, 1> block_round_kernel<true, true, 2, false, 3>"),
+    ((32, 32, 32), gen.stencil_block_sizes(gen.moore(3, 1), 25), 1, "vector_round_kernel<v16, 3, true, 0, true, 1> block_round_kernel<true, true, 2, false, 3>"),
+    ((32, 32, 32), gen.stencil_block_sizes(gen.moore(3, 1), 64), 1, "vector_round_uniform_kernel<3, 1, 1> block_round_kernel<true, true, 2, false, 3>"), ((64, 64, 64), gen.stencil_block_sizes(gen.moore(3, 1), 12), 0, "vector_round_kernel<v16, 3, true, 0, false, 1> block_round_kernel<true, true, 2, false, 3>"),
+    ((32, 32, 32), gen.stencil_block_sizes(gen.moore(3, 1), 25), 0, "vector_round_kernel<v16, 3, true, 0, true, 1> block_round_kernel<true, true, 2, false, 3>"),
     ((20, 20, 20), gen.stencil_block_sizes(gen.moore(3, 1), 25), 0, "vector_round_kernel<v16, 3, true, 0, true, 1> block_round_kernel<true, true, 2, false, 3>"),
     ((20, 20, 20), gen.stencil_block_sizes(gen.moore(3, 1), 8), 0, "block_round_kernel<true, true, 2, false, 3>"), ((20, 20, 20), gen.stencil_block_sizes(gen.moore(3, 1), 8), 1, None),
     ((20, 20, 20), gen.stencil_block_sizes(gen.moore(3, 1), 9), 0, None),
