@@ -369,30 +369,24 @@ class Bench:
             for r in self.reqs:
                 iso.iso_request_set_graph(r, args.graph)
         # the kernels of a step, and the blocks that they load and store
-        self.through_hops = all(self.all_hops(r) for r in self.reqs)
-        self.moved = sum(self.memory_bytes(r) for r in self.reqs)
-        self.launches = sum(iso.iso_request_start_info(r)["kernels"] for r in self.reqs)
-        self.requested = sum(i["bytes_read"] + i["bytes_written"] for i in self.infos)
+        starts = [iso.iso_request_start_info(r) for r in self.reqs]
+        self.joined = {r: self.joined_hops(r) for r in self.reqs}
+        self.through_hops = all(form == "all hops" for form in self.joined.values())
+        self.moved = sum(i["bytes_read"] + i["bytes_written"] for i in starts)
+        self.launches = sum(i["kernels"] for i in starts)
 
-    # -- what a start moves ----------------------------------------------------------
-    def all_hops(self, req):
-        """Fewer kernels than dimensions with moves: they take blocks through all their hops."""
+    def joined_hops(self, req):
+        """"chain" or "all hops" where a start's kernels take blocks through several hops and load the send buffer alone,
+        else None."""
         iso, plan = self.iso, self.iso.iso_request_plan(req)
-        dims_moved = set()
-        for q in range(iso.iso_plan_info(plan)["launches"]):
-            dims_moved.update(e["dim"] for e in iso.iso_plan_entries(plan, q) if e["dim"] >= 0)
-        return iso.iso_request_start_info(req)["kernels"] < len(dims_moved)
-
-    def memory_bytes(self, req):
-        """Bytes that the kernels of a start load and store.  A block that an allgather's kernel sends on to several
-        blocks is loaded once; kernels that take blocks through all their hops load the send buffer and store every
-        stop."""
-        info, start = self.iso.iso_request_info(req), self.iso.iso_request_start_info(req)
-        loaded = start["bytes_read"]
-        if self.all_hops(req):
-            loaded = (info["delivered_bytes"] if info["op"] == self.iso.ISO_OP_ALLTOALL
-                      else start["kernels"] * info["p"] * info["block_bytes"])
-        return loaded + start["bytes_written"]
+        info, start = iso.iso_request_info(req), iso.iso_request_start_info(req)
+        sent = (info["delivered_bytes"] if info["op"] == iso.ISO_OP_ALLTOALL
+                else start["kernels"] * info["p"] * info["block_bytes"])
+        onward = any(e["src_buf"] != iso.ISO_BUF_SEND for q in range(iso.iso_plan_info(plan)["launches"])
+                     for e in iso.iso_plan_entries(plan, q))
+        if not onward or start["bytes_read"] != sent:
+            return None
+        return "all hops" if self.args.irregular or info["delivered_bytes"] > LAST_LEVEL_CACHE_BYTES // 64 else "chain"
 
     # -- requests ------------------------------------------------------------------
     def make_request(self, op, alg, timed_buffers=False):
@@ -534,7 +528,8 @@ class Bench:
         avg_launch_ms = ms_per_step / self.launches
         achieved = alg_bytes_per_launch / (avg_launch_ms * 1e-3) / 1e9
         kernel = ("vector_round_kernel" if args.algorithm.startswith("sx") else
-                  "vector_round_uniform_kernel" if self.through_hops and m % 1024 == 0 else
+                  "chain_kernel" if all(form == "chain" for form in self.joined.values()) else
+                  "vector_round_uniform_kernel" if self.through_hops and infos[0]["block_bytes"] % 1024 == 0 else
                   "vector_round_kernel" if self.through_hops else
                   "deliver_kernel" if args.algorithm == "staged" and m % 16 == 0 and s * (m // 16) <= 2048 and s <= 128
                   and not (args.irregular or args.mesh or args.pad or self.slot) else
@@ -542,9 +537,12 @@ class Bench:
                   "mesh_shift_round_kernel" if args.mesh else
                   "shift_round_uniform_kernel" if m % 1024 == 0 and (self.slot or m <= 2048) else
                   "shift_round_kernel") + "<16B>"
+        gathers = [r for r, i in zip(reqs, infos) if i["op"] == iso.ISO_OP_ALLGATHER and not self.joined[r]]
         if self.through_hops:
+            kernel += ", smaller blocks: block_round_kernel" if args.irregular else ""
             kernel += ", allgather: also push_round_kernel<16B>" if len(self.ops) > 1 and cfg.d > 3 else ""
-        elif self.moved < self.requested and not args.algorithm.startswith("sx") and not args.mesh:
+        elif not args.algorithm.startswith("sx") and not args.mesh and any(
+                iso.iso_request_start_info(r)["bytes_read"] < iso.iso_request_info(r)["bytes_read"] for r in gathers):
             kernel += ", allgather: also shift_push_kernel<16B>"
         tag = self.tag()
         recorded = tag + ("_all_hops" if self.through_hops else "")
@@ -640,11 +638,12 @@ class Bench:
         ksteps = max(5, K // 4)
 
         def rate(rs, ms, hbm_label=True):
-            """`moved_GBs` counts the blocks that the kernels load and store (memory_bytes), which is what HBM
-            carries for the message-combining schedules but for stops that the caches hold.  The s-exchange allgather is given by the bytes its moves ask for, every source block
-            s times: mostly from cache, so the figure is not HBM traffic and gets no fraction."""
+            """`moved_GBs` counts the blocks that the kernels load and store, which is what HBM carries for the
+            message-combining schedules but for stops that the caches hold.  The s-exchange allgather is given by the
+            bytes its moves ask for, every source block s times: mostly from cache, so the figure is not HBM traffic
+            and gets no fraction."""
             starts = [iso.iso_request_start_info(r) for r in rs]
-            mv = (sum(self.memory_bytes(r) for r in rs) if hbm_label
+            mv = (sum(i["bytes_read"] + i["bytes_written"] for i in starts) if hbm_label
                   else sum(iso.iso_request_info(r)["bytes_read"] * 2 for r in rs))
             dl = sum(iso.iso_request_info(r)["delivered_bytes"] for r in rs)
             d = {"ms_per_step": round(ms, 5), "delivered_GBs": round(dl / ms / 1e6, 1),

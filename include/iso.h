@@ -207,13 +207,12 @@ typedef struct {
 typedef struct {
     int32_t kernels;             /* kernels                                                 */
     int32_t reserved;
-    uint64_t bytes_read;         /* blocks their moves read, bytes: a block that several moves of one
-                                  * kernel read counts once for that kernel.  A kernel that takes
-                                  * blocks through several hops hands them on in LDS or registers and
-                                  * loads only what its first hops read: one kernel for a whole
-                                  * collective, the send buffer.  On a mesh also moves that have no
-                                  * source, or are left out because no one receives the block */
-    uint64_t bytes_written;      /* blocks they write, bytes                                */
+    uint64_t bytes_read;         /* blocks they load, bytes: a block that several moves of one kernel
+                                  * read counts once for that kernel, and a kernel that takes blocks
+                                  * through several hops, handing them on in LDS or registers, loads
+                                  * only what their first hops read.  On a mesh also moves that have
+                                  * no source, or are left out because no one receives the block */
+    uint64_t bytes_written;      /* blocks they store, bytes, at every stop (on a mesh as above)   */
 } iso_start_info_t;
 
 /* ---- neighbourhood set-up (Section 2, set-up listing) ----------------------

@@ -455,7 +455,6 @@ struct HostEntry {
     // launches that take blocks through all their hops (join_hops)
     uint32_t moves;        // of the plan that the entry stands for
     uint32_t along;        // the dimensions that it moves along, of its neighbour's vector
-    uint64_t reads;        // the block that its last move reads in the plan
     uint64_t way;          // VectorEntry::way
 };
 
@@ -838,7 +837,7 @@ private:
         if (own > (wide ? 12288 : 6144) || all > (launches - 1) * (wide ? 192 : 48) * 1024) return false;
         l.threads = std::min<uint32_t>(kChainThreads, (ca.n_units + 63) & ~63u);
         l.dyn_lds = longest > 1 ? ca.n_units * (uint32_t)width : 0;
-        describe_chain_bytes(l, hops);
+        describe_chain_bytes(l, hops, n_chains);
         l.chain = ca;
         const uint32_t *words = (const uint32_t *)table_hops.data();
         const size_t n_words = table_hops.size() * sizeof(ChainHop) / 4;
@@ -856,20 +855,15 @@ private:
         return true;
     }
 
-    // An all-to-all's hops share no blocks; ways of an allgather's trie do.
-    void describe_chain_bytes(Launch &l, const std::vector<const HostEntry *> &hops) const {
-        l.bytes_read = l.bytes_written = p * size0 * hops.size();
+    // A chain's first hop loads, from the send buffer; all of them store, ways of an allgather's trie in part to the same places.
+    void describe_chain_bytes(Launch &l, const std::vector<const HostEntry *> &hops, uint32_t n_chains) const {
+        l.bytes_read = p * size0 * (op == ISO_OP_ALLTOALL ? n_chains : 1);
+        l.bytes_written = p * size0 * hops.size();
         if (op == ISO_OP_ALLTOALL) return;
-        std::vector<uint64_t> sources, targets;
-        for (const HostEntry *he : hops) {
-            sources.push_back(he->de.src);
-            targets.push_back(he->de.dst);
-        }
-        for (std::vector<uint64_t> *v : {&sources, &targets}) {
-            std::sort(v->begin(), v->end());
-            v->erase(std::unique(v->begin(), v->end()), v->end());
-        }
-        l.bytes_read = p * size0 * sources.size();
+        std::vector<uint64_t> targets;
+        for (const HostEntry *he : hops) targets.push_back(he->de.dst);
+        std::sort(targets.begin(), targets.end());
+        targets.erase(std::unique(targets.begin(), targets.end()), targets.end());
         l.bytes_written = p * size0 * targets.size();
     }
 
@@ -1418,7 +1412,6 @@ private:
                 place(pe.dst_buf, pe.dst_slot, he.de.dst, dst_stride);
                 // the kernels multiply a rank by a 32-bit stride
                 if ((src_stride | dst_stride) >> 32) return ISO_ERR_TOO_LARGE;
-                he.reads = he.de.src;
                 he.de.src_stride = (uint32_t)src_stride;
                 he.de.dst_stride = (uint32_t)dst_stride;
                 he.de.shift = r.kind == ISO_ROUND_VECTOR ? (uint32_t)pe.neighbor : (uint32_t)pe.shift;
@@ -1513,13 +1506,15 @@ private:
     // 100 B 33 -> 34).
     bool retiled() const { return size0 % 16 == 0 || inf.delivered_bytes > kLastLevelCacheBytes * 3 / 16; }
 
-    // Only an allgather's moves share sources.
+    // An entry loads its block once, whatever the moves that it stands for.  Only an allgather's share sources.
     void describe_bytes(Launch &l, const HostEntry *ents, uint32_t k) const {
-        for (uint32_t q = 0; q < k; ++q) l.bytes_written += p * ents[q].size * ents[q].moves;
-        l.bytes_read = l.bytes_written;
+        for (uint32_t q = 0; q < k; ++q) {
+            l.bytes_written += p * ents[q].size * ents[q].moves;
+            l.bytes_read += p * ents[q].size;
+        }
         if (op == ISO_OP_ALLTOALL || !k) return;
         std::vector<uint64_t> sources(k);
-        for (uint32_t q = 0; q < k; ++q) sources[q] = ents[q].reads;
+        for (uint32_t q = 0; q < k; ++q) sources[q] = ents[q].de.src;
         std::sort(sources.begin(), sources.end());
         l.bytes_read = p * ents[0].size * (uint64_t)(std::unique(sources.begin(), sources.end()) - sources.begin());
     }
