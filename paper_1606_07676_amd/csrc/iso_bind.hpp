@@ -1703,7 +1703,8 @@ private:
         sa.p = (uint32_t)p;
         sa.k = k;
         sa.upb = (uint32_t)upb;
-        l.tile_units = k * upb <= kSmallTileUnits ? kSmallTileUnits : kTileUnits;
+        const bool joined = second_dim >= 0 && &r == &bound_rounds[0];
+        l.tile_units = k * upb <= kSmallTileUnits && !(joined && parts_of_sectors(k, upb)) ? kSmallTileUnits : kTileUnits;
         sa.ranks = (uint32_t)std::min<uint64_t>(p, l.tile_units / (k * upb));
         const bool shift = r.kind == ISO_ROUND_SHIFT;
         sa.inner = shift ? (uint32_t)c.inner[r.dim] : 1u;
@@ -1715,7 +1716,7 @@ private:
         put(sa.plane, sa.mul_plane, sa.shifts, 2);
         put(sa.inner, sa.mul_inner, sa.shifts, 3);
         put(sa.pj, sa.mul_pj, sa.more, 0);
-        if (second_dim >= 0 && &r == &bound_rounds[0]) {
+        if (joined) {
             sa.inner2 = (uint32_t)c.inner[second_dim];
             sa.pj2 = (uint32_t)c.dims[second_dim];
             put(sa.inner2, sa.mul_inner2, sa.shifts2, 0);
@@ -1723,6 +1724,15 @@ private:
         }
         l.dyn_lds = (uint32_t)(k * ((uint64_t)sa.ranks * sa.upb + 1) * width);
         total = ((p + sa.ranks - 1) / sa.ranks) * kThreads;      // set_grid: one workgroup per tile
+    }
+
+    // Two rounds in one launch hold more blocks of a rank, and a small tile fewer ranks; where their pieces of the planes end
+    // inside a sector, large tiles beyond half the last-level cache (two launches, one with small tiles, with large ones: 8^5,
+    // 40 neighbours, 112 B 228, 239, 217, 208 B 439, 475, 406, 224 B 441, 491, 424; 16^4, 80, 48 B 318, 324, 284, 144 B 1020,
+    // 1225, 969; small to large tiles otherwise: whole sectors 16^4, 96 B +7 %, smaller ones 20^3, 288 B with many sets +7 %).
+    bool parts_of_sectors(uint64_t k, uint64_t upb) const {
+        const uint64_t ranks = kSmallTileUnits / (k * upb);
+        return ranks <= 5 && ranks * size0 % 64 && inf.delivered_bytes > kLastLevelCacheBytes / 2;
     }
 
     // Regular blocks: every entry has `chunks` units of the request's common width (a mesh's s-exchange of more

@@ -577,3 +577,12 @@ def test_blocks_of_a_few_bytes_on_large_tori(stub_library, dims, edge, box, join
     sizes = [int(x) for x in gen.stencil_block_sizes(gen.moore(len(dims), 1), edge)]
     got = stub_library.start_unequal(dims, gen.moore(len(dims), 1), iso.ISO_ALG_COMBINED, sizes, (0,) * len(dims) if box else None)
     assert (len(got) < len(dims)) == joined, got
+
+
+@pytest.mark.parametrize("dims,n,m,units", [((8,) * 5, 40, 208, 8), ((8,) * 5, 40, 224, 8), ((8,) * 5, 40, 112, 8), ((8,) * 5, 40, 192, 4), ((8,) * 5, 40, 160, 4),
+                                            ((5,) * 5, 40, 208, 4), ((8,) * 5, 40, 107, 8), ((8,) * 5, 40, 90, 4)])
+def test_tiles_of_the_first_two_staged_rounds(stub_library, dims, n, m, units):
+    """Large ones where few ranks of a small tile end inside a sector, beyond half the last-level cache."""
+    offsets = gen.random_distinct(5, -3, 3, n, gen.configs.CONFIG5_NEIGHBOURHOOD_SEED)
+    got = stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_STAGED, m)
+    assert got[0].startswith("staged_round_kernel") and got[0].endswith("true>") and f", {units}u, " in got[0], got

@@ -177,3 +177,10 @@ def test_staged_rounds_of_two_dimensions(dims, offsets):
     for m in (16, 48, 256):
         check_exchange(dims, offsets, iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_STAGED, m, RANK, send_off=3, recv_off=1)
     check_exchange((64, 65, 66), gen.moore(3, 1), iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_STAGED, 9, RANK)      # last units that overlap
+
+
+@pytest.mark.parametrize("dims,n,m", [((7, 8, 7, 8, 8), 40, 208), ((8, 7, 9, 8, 7), 40, 121), ((13, 14, 12, 13), 30, 177)])
+def test_large_tiles_of_the_first_two_staged_rounds(dims, n, m):
+    """Few ranks of a small tile would end inside a sector: whole units and last units that overlap."""
+    offsets = [tuple(int(x) for x in c) for c in gen.random_distinct(len(dims), -3, 3, n, 160607676)]
+    check_exchange(dims, offsets, iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_STAGED, m, RANK, send_off=3, recv_off=1)
