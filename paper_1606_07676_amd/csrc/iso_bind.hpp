@@ -1092,26 +1092,29 @@ private:
     // 16^4, 8 B 373 -> 342; 8^5, 4 B 512 -> 391; 500^2, 64 B 81 -> 57; 8^3, 64 B 15.8 -> 11.8, 40^2, 64 B 6.3 -> 3.9.)  Small
     // blocks that are no whole units lose it again in more dimensions, and among themselves in three (16^4, 6 B 285 -> 303;
     // 64^3, 11 B 303 -> 361; 22^4, 3 B 673 -> 822), as many launches as before gain nothing (300^2, 200 B 57 -> 60).
-    // Blocks of a few bytes, a unit of work each, lose on larger tori what fewer launches save (stencils, edge: 32^3, 3 B 20 ->
-    // 19, 48^3, 2 B 30.5 -> 31.1, 3 B 47 -> 59, 4 B 45 -> 38, 64^3, 2 B 60 -> 75, 3 B 94 -> 132, 4 B 87 -> 84; 16^4, 2 B 83 ->
-    // 102; 9^5, 2 B 269 -> 397; 200^2, 3 B 6.9 -> 5.3, 280^2, 4 B 6.8 -> 6.6 and with many sets 7.0 -> 7.5, 512^2, 3 B 17.2 ->
-    // 20.2, 11 B 21.0 -> 22.0, 15 B 25 -> 23.5), on boxes of three and more dimensions small blocks of any size (32^3, 8 B 24.5
-    // -> 22.8, 48^3 58 -> 65, 64^3 135 -> 164, 4 B 80.5 -> 83.1; 20^4, 4 B 301 -> 330; with larger ones beside them 64^3, 16
-    // B 407 -> 290).
+    // Blocks of a few bytes lose, from a million or two of their units on, what fewer launches save (stencils, edge, one set
+    // of buffers and many: 32^3, 3 B 19.6 -> 18.6 and 22.9 -> 22.6, 40^3 30 -> 33 and 35 -> 39, 48^3, 2 B 30.5 -> 31.1 and 35
+    // -> 38, 4 B 45 -> 38, 64^3, 2 B 60 -> 75, 3 B 94 -> 132, 4 B 87 -> 84; 16^4, 2 B 83 -> 102; 9^5, 2 B 269 -> 397; 280^2,
+    // 3 B 9.0 -> 8.2 and 9.6 -> 9.0, 360^2 10.8 -> 11.3 and 12.3 -> 13.5, 400^2, 4 B 10.1 -> 9.6 and 12.2 -> 12.6, 450^2 11.8
+    // -> 12.2 and 14.5 -> 16.0, 512^2, 3 B 17.2 -> 20.2, 11 B 21 -> 23, 15 B 24.5 -> 23.5), on boxes of three and more
+    // dimensions small blocks of any size (32^3, 8 B 24.5 -> 22.8, 48^3 58 -> 65, 64^3 135 -> 164, 4 B 80.5 -> 83.1; 20^4, 4 B
+    // 301 -> 330; with larger ones beside them 64^3, 16 B 407 -> 290).
     // ISO_ALG_COMBINED_BYDIM: where kBySize was taken (60 x 50 x 41, 25 B 318 -> 296; 20^4, 8 B 1099 -> 832).
     bool all_hops_by_size() {
         const uint64_t llc = kLastLevelCacheBytes, bytes = inf.delivered_bytes;
         if (op != ISO_OP_ALLTOALL || arena || uniform || lay.slot_major || c.d < 2 || c.d > kVectorDims || wl.bytes >> 36)
             return false;
         std::vector<uint64_t> blocks;                    // of every large size
-        uint64_t small = 0, small_bytes = 0;
+        uint64_t small = 0, small_units = 0, small_bytes = 0;
         bool units = true;
         for (size_t i = 0; i < s; ++i) {
             const uint64_t m = lay.size[i];
             if (!m) continue;
             const uint32_t l2 = unit_log2_of(m);
-            if ((m + (uint64_t(1) << l2) - 1) >> l2 <= kSmallUnits) {
+            const uint64_t upb = (m + (uint64_t(1) << l2) - 1) >> l2;
+            if (upb <= kSmallUnits) {
                 ++small;
+                small_units += upb;
                 small_bytes += m;
                 units = units && (m < 16 || m % 16 == 0);
                 continue;
@@ -1128,9 +1131,9 @@ private:
         for (const uint64_t n : blocks) launches += (n + kLdsEntries - 1) / kLdsEntries;
         if (launches >= dimensions_moved()) return false;
         constexpr uint64_t kMi = uint64_t(1) << 20;
-        const uint64_t moves = p * small;
-        if (c.d == 2 ? !c.mesh && moves > kMi / 2 && small_bytes <= 6 * small : moves > kMi && small_bytes < 5 * small) return false;
-        if (c.d > 2 && c.mesh && large_sizes.empty() && moves > 2 * kMi) return false;
+        const uint64_t work = p * small_units;
+        if (c.d == 2 ? !c.mesh && work > kMi * 11 / 8 && small_bytes <= 6 * small : work > 2 * kMi && small_bytes < 5 * small) return false;
+        if (c.d > 2 && c.mesh && large_sizes.empty() && work > 4 * kMi) return false;
         if (pl.algorithm == ISO_ALG_COMBINED_BYDIM) return !c.mesh && small && !large_sizes.empty() && bytes > llc / 4;
         return pl.algorithm == ISO_ALG_COMBINED && (units || c.d == 2 || (c.d == 3 && !large_sizes.empty()));
     }

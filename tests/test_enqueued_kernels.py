@@ -570,10 +570,11 @@ def test_allgathers_of_more_than_the_cache_holds(stub_library, dims, offsets, m,
 @pytest.mark.parametrize("dims,edge,box,joined", [
     ((64, 64, 64), 3, False, False), ((64, 64, 64), 2, False, False), ((64, 64, 64), 4, False, True), ((32, 32, 32), 3, False, True), ((48, 48, 48), 3, False, False),
     ((512, 512), 3, False, False), ((512, 512), 11, False, False), ((512, 512), 15, False, True), ((200, 200), 3, False, True), ((512, 512), 3, True, True),
+    ((360, 360), 3, False, False), ((360, 360), 4, False, True), ((400, 400), 4, False, True), ((450, 450), 4, False, False),
     ((16,) * 4, 2, False, False), ((9,) * 5, 2, False, False), ((8,) * 5, 4, False, True), ((64, 64, 64), 8, True, False), ((64, 64, 64), 8, False, True), ((64, 64, 64), 4, True, False),
     ((32, 32, 32), 8, True, True), ((64, 64, 64), 16, True, True), ((20,) * 4, 4, True, False)])
 def test_blocks_of_a_few_bytes_on_large_tori(stub_library, dims, edge, box, joined):
-    """A launch per dimension for blocks of a few bytes, and on boxes for small ones alone, from about a million moves on."""
+    """A launch per dimension for blocks of a few bytes, and on boxes for small ones alone, from a million units or more on."""
     sizes = [int(x) for x in gen.stencil_block_sizes(gen.moore(len(dims), 1), edge)]
     got = stub_library.start_unequal(dims, gen.moore(len(dims), 1), iso.ISO_ALG_COMBINED, sizes, (0,) * len(dims) if box else None)
     assert (len(got) < len(dims)) == joined, got
