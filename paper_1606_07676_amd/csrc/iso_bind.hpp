@@ -992,9 +992,11 @@ private:
     // 265 -> 250, allgather 768 B 17.5 -> 23.0, 6784 B 81 -> 77; 4^4, 2400, 4 against 19, allgather 256 B 52 -> 61, 640 B 116
     // -> 100; 32^2, 440, 2 against 4, 384 B 128 -> 112; what gains and stays: 5^4, 624, 4 against 5, 256 B 124 -> 89).  As
     // many: 5^3, 342, 384 B 22.6 -> 20.9.
-    // Two dimensions, allgathers of parts of lines with more to send than the last-level cache holds: not pushed
-    // (allgather_order), and what the pulls miss comes from memory every time (250 x 260, 10 neighbours, 4300 B 951 -> 799,
-    // 4416 B 820 -> 1031, 6432 B 1232 -> 1498; 8, 5600 B 794 -> 903; three 64^3, 26, 1168 B 2545 -> 2361).
+    // Two dimensions, allgathers of whole units that are parts of lines, with more to send than the last-level cache holds: not
+    // pushed (allgather_order), and what the pulls miss comes from memory every time (250 x 260, 10 neighbours, 4416 B 820 ->
+    // 1031, 6432 B 1232 -> 1498; 8, 5600 B 794 -> 903; up to it 4096 B and 12 728 -> 653; three dimensions 64^3, 26, 1168 B
+    // 2545 -> 2361).  Other sizes cost a launch per dimension more (250 x 260, 4531 B, 8 neighbours 819 -> 757, 12 1176 ->
+    // 1037; 267 x 335, 10, 4893 B 1706 -> 1638; 400 x 420, 10, 3037 B 1881 -> 1685, but 2724 B 1642 -> 1800).
     // Boxes, where the moves of blocks that no one receives are left out: 45 x 37 x 29, 26 neighbours, 100 B slot-major 97 -> 64,
     // 256 B 235 -> 151; 8^5, 40, 512 B 877 -> 240; 64^3, allgather 256 B 550 -> 285.
     // It gains at every block size from a MiB on (all-to-all 64^3, 100 B 797 -> 402, 192 B 1038 -> 688, 16^3, 128 B 19.4 ->
@@ -1014,7 +1016,7 @@ private:
         if (hops_launches() > launches && bytes <= std::min(llc, hops_launches() * llc / 8)) return false;
         if (c.mesh && (!bydim || (!a2a && !lines && size0 < 256))) return false;
         if (lay.slot_major) return !a2a || bytes > (lines ? llc / 8 : llc * 3 / 16);
-        if (!a2a && c.d == 2 && p * size0 > llc * 17 / 16 && !whole_lines()) return false;
+        if (!a2a && c.d == 2 && size0 % 16 == 0 && p * size0 > llc * 17 / 16 && !whole_lines()) return false;
         if (!a2a) {
             if (size0 >= 512 || (!bydim && (lines || size0 >= 256)) || bytes <= (size0 < 64 ? llc * 3 / 16 : llc / 2)) return true;
             return lines && bytes > llc * 7 / 4;

@@ -558,11 +558,11 @@ def test_slot_major_allgathers_through_all_hops_where_planes_do_not_meet(stub_li
 
 
 @pytest.mark.parametrize("dims,offsets,m,want", [
-    ((250, 260), gen.moore(2, 1), 5600, 2), ((250, 260), gen.von_neumann(2, 2), 4416, 2), ((250, 260), gen.random_distinct(2, -3, 3, 10, 5), 6432, 2), ((250, 260), gen.moore(2, 1), 4300, "vector_round_kernel"),
+    ((250, 260), gen.moore(2, 1), 5600, 2), ((250, 260), gen.von_neumann(2, 2), 4416, 2), ((250, 260), gen.random_distinct(2, -3, 3, 10, 5), 6432, 2), ((250, 260), gen.moore(2, 1), 4240, "vector_round_kernel"), ((250, 260), gen.moore(2, 1), 5601, "vector_round_kernel"),
     ((250, 260), gen.moore(2, 1), 5120, "push_round_kernel"), ((400, 420), gen.moore(2, 1), 2048, "push_round_kernel"), ((250, 260), gen.moore(2, 1), 4096, "vector_round_uniform_kernel"),
     ((64, 64, 64), gen.moore(3, 1), 1168, "vector_round_kernel")])
 def test_allgathers_of_more_than_the_cache_holds(stub_library, dims, offsets, m, want):
-    """Whole lines are pushed; others stay a launch per dimension in two dimensions."""
+    """Whole lines are pushed; other whole units stay a launch per dimension in two dimensions."""
     got = _names(stub_library.start(dims, offsets, iso.ISO_OP_ALLGATHER, iso.ISO_ALG_COMBINED, m))
     assert got == [want] if isinstance(want, str) else len(got) == want and got[0].startswith("shift"), got
 
