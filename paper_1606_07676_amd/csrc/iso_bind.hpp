@@ -1163,14 +1163,17 @@ private:
     }
 
     // iso_start of ISO_ALG_COMBINED_STAGED, all-to-all: its first two rounds in one launch (staged_round_kernel, TWO), where
-    // the blocks that either of them takes out of a send-buffer row fit a tile.
+    // the blocks that either of them takes out of a send-buffer row fit a tile.  If none of them makes a hop in both, nothing is
+    // read less, and beyond the last-level cache the longer tiles cost what the launch saves (stars of radius two: 32^3, 24
+    // neighbours, 200 MB 0.95 to 0.98 of two launches; 48^3, 240 B 370 -> 385, 80^3, 144 B 1061 -> 1095, 208 B 1515 -> 1558;
+    // 18^4, 40, 160 and 208 B 1.04 and 1.05 of two).
     bool two_staged_rounds() const {
         if (pl.algorithm != ISO_ALG_COMBINED_STAGED || op != ISO_OP_ALLTOALL || arena || !uniform || bound_rounds.size() < 3 || !retiled()) return false;
         if (bound_rounds[0].kind != ISO_ROUND_SHIFT || bound_rounds[1].kind != ISO_ROUND_SHIFT || !bound_rounds.back().whole ||
             bound_rounds.back().kind != ISO_ROUND_DELIVER || bound_rounds[0].dim == bound_rounds[1].dim)
             return false;
         const uint64_t upb = (size0 + (uint64_t(1) << min_log2) - 1) >> min_log2;
-        size_t n = rounds[0].size();
+        size_t n = rounds[0].size(), both = 0;
         if (n > kLdsEntries || rounds[1].size() > kLdsEntries) return false;
         for (const HostEntry &a : rounds[0])
             if (a.dst_buf != ISO_BUF_WORK || a.de.src_stride == size0) return false;
@@ -1178,7 +1181,9 @@ private:
             const bool onward = first_hop_of(b) >= 0;    // else out of a send-buffer row
             if (b.dst_buf != ISO_BUF_WORK || (!onward && b.de.src_stride == size0)) return false;
             n += !onward;
+            both += onward;
         }
+        if (!both && inf.delivered_bytes > kLastLevelCacheBytes) return false;
         return n <= kLdsEntries && n * upb <= kTileUnits && p * upb <= kMaxUnits;
     }
     // the entry of the first round that brings what `he` of the second one reads

@@ -587,3 +587,12 @@ def test_tiles_of_the_first_two_staged_rounds(stub_library, dims, n, m, units):
     offsets = gen.random_distinct(5, -3, 3, n, gen.configs.CONFIG5_NEIGHBOURHOOD_SEED)
     got = stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_STAGED, m)
     assert got[0].startswith("staged_round_kernel") and got[0].endswith("true>") and f", {units}u, " in got[0], got
+
+
+@pytest.mark.parametrize("dims,offsets,m,two", [
+    ((32, 32, 32), gen.von_neumann(3, 2), 256, True), ((48, 48, 48), gen.von_neumann(3, 2), 240, False), ((48, 48, 48), gen.moore(3, 1), 240, True),
+    ((18,) * 4, gen.von_neumann(4, 2), 160, False), ((13,) * 4, gen.von_neumann(4, 2), 160, True)])
+def test_first_two_staged_rounds_that_share_no_block(stub_library, dims, offsets, m, two):
+    """In one launch up to the size of the last-level cache."""
+    got = stub_library.start(dims, offsets, iso.ISO_OP_ALLTOALL, iso.ISO_ALG_COMBINED_STAGED, m)
+    assert any(k.startswith("staged_round_kernel") and k.endswith("true>") for k in got) == two, got
