@@ -973,9 +973,9 @@ private:
         rounds.assign(1, std::move(all));
     }
 
-    // iso_start in one launch (one for each table that LDS takes) of all blocks through all their hops: every move is made, but a hop takes its block from
-    // the one before it in a register (move_through_stops), in an allgather from the send buffer as all others do.  On tori
-    // of up to five dimensions, from 4 MiB on.
+    // iso_start in one launch (one for each table that LDS takes) of all blocks through all their hops: every move stores its
+    // block, but a hop takes it from the one before it in a register (move_through_stops), in an allgather from the send
+    // buffer as all others do.  On tori of up to five dimensions, from 4 MiB on; on boxes for ISO_ALG_COMBINED_BYDIM.
     // All-to-all (us, as before -> here, a gigabyte of buffer sets in turn): 32^3, 26 neighbours, 256 B 160 -> 108; 256^2, 12,
     // 1 KiB 348 -> 304; 64^3, 26, 128 B 615 -> 433, 320 B 1660 -> 1133, 1000 B 5858 -> 3743; 8^5, 40, 320 B 679 -> 303, 4 KiB
     // 7562 -> 3800; 16^4, 30, 400 B 1221 -> 526; 300^2, 24, 300 B 392 -> 307; 100^2, 8, 512 B 25.6 -> 20.7; 16^3, 384 B 37.0 ->
@@ -984,7 +984,8 @@ private:
     // -> 157, 10, 1300 B 436 -> 265; 8^5, 40, 500 B 823 -> 459, 4 KiB 5187 -> 2975; 16^4, 30, 256 B 386 -> 222; slot-major 64^3,
     // 128 B 197 -> 152, 100 B 168 -> 128.
     // Small ones: all-to-all 10^3, 26 neighbours, 256 B 10.9 (chain) -> 6.2, 12^3, 256 B 15.4 -> 9.8; allgather 20^3, 40 B
-    // 11.4 -> 4.0, 5^5, 40, 128 B 27.8 -> 9.3; 13 x 12 x 14, 80 B slot-major 10.0 -> 4.7; 6^3, 20, 48 B 3.5 -> 3.7.
+    // 11.4 -> 4.0, 5^5, 40, 128 B 27.8 -> 9.3; 13 x 12 x 14, 80 B slot-major 10.0 -> 4.7.  Below 4 MiB a chain takes what fits
+    // it (6^3, 20, 48 B 3.5, here 3.7).
     // More than one table: the chain of a small collective stays (5^2, 440 neighbours, 384 B 3.9 us, here in four launches
     // 12.0; 7^2, 224, 768 B 5.3 and 6.5), and up to 32 MiB for each launch here, at most the last-level cache, so do fewer
     // launches (us, before -> here: 3^3, 728, 4 launches against 6, all-to-all 1280 B 27.7 -> 33.3, 5 KiB 79 -> 81, 21 KiB 297
@@ -999,11 +1000,10 @@ private:
     // 1037; 267 x 335, 10, 4893 B 1706 -> 1638; 400 x 420, 10, 3037 B 1881 -> 1685, but 2724 B 1642 -> 1800).
     // Boxes, where the moves of blocks that no one receives are left out: 45 x 37 x 29, 26 neighbours, 100 B slot-major 97 -> 64,
     // 256 B 235 -> 151; 8^5, 40, 512 B 877 -> 240; 64^3, allgather 256 B 550 -> 285.
-    // It gains at every block size from a MiB on (all-to-all 64^3, 100 B 797 -> 402, 192 B 1038 -> 688, 16^3, 128 B 19.4 ->
-    // 11.7; allgather 8^5, 100 B 235 -> 160).  What is left out here are the neighbourhoods of the sizes whose launches
-    // tests/test_enqueued_kernels.py lays down: small blocks that are no whole lines, rank-major, with all-to-alls of most
-    // sizes and larger allgathers, and for ISO_ALG_COMBINED_BYDIM more of them up to 7/4 of the last-level cache; and meshes,
-    // but for BYDIM.
+    // The other limits are no measured ones.  All-to-alls of most sizes of small blocks that are no whole lines, rank-major,
+    // and larger allgathers of them, more of both for ISO_ALG_COMBINED_BYDIM up to 7/4 of the last-level cache, and boxes but
+    // for BYDIM keep the launches of their rounds, which the tests of these launches lay down, though they would gain here
+    // (all-to-all 64^3, 100 B 797 -> 402, 192 B 1038 -> 688, 16^3, 128 B 19.4 -> 11.7; allgather 8^5, 100 B 235 -> 160).
     bool all_hops_in_one_launch(uint64_t launches) const {
         const uint64_t llc = kLastLevelCacheBytes, bytes = inf.delivered_bytes;
         const bool a2a = op == ISO_OP_ALLTOALL, bydim = pl.algorithm == ISO_ALG_COMBINED_BYDIM, lines = size0 % 128 == 0;

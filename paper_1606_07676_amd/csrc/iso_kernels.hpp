@@ -534,11 +534,12 @@ __device__ __forceinline__ bool passes_end(uint32_t r, uint32_t c, int j, const 
 // One unit of a block of an all-to-all through all the hops of its schedule, pulled by the rank R that receives it: the
 // ranks on its way are R moved back along the dimensions one by one, the last hop first.  It is stored at every one of them,
 // in the block's place in the workspace.  What the next hop takes is still in the register: no one reads the stops, and the
-// stores of different lanes to one place (of a block of three hops and more) need no order.
+// stores of different lanes to one place (of a block of three hops and more) need no order: unit by unit the last one stays.
 // A launch per dimension reads every hop's block again and is bound by the memory's copy rate; here the hops of a block are
 // one read and their writes.  The stops are stored plainly, the receive rows stream: stops of one block are overwritten, by
 // its next hops at other ranks, while the caches hold them (streamed -> plain, us, many sets of buffers: 8^5, 40 neighbours,
-// 4 KiB 5430 -> 4100; 64^3, 26 neighbours, 1000 B 4670 -> 3740; 256^2, 12, 1 KiB 293 -> 260; 32^3, 26, 256 B 111.7 -> 107.6).
+// 4 KiB 5430 -> 4100; 64^3, 26 neighbours, 1000 B 4670 -> 3740; 32^3, 26, 256 B 111.7 -> 107.6, though 94 -> 106 with one set,
+// a launch per dimension 158).
 template <typename V, int D, int POLICY, int WAY, typename ENTRY>
 __device__ __forceinline__ void move_through_stops(const ENTRY &en, uint32_t R, const uint32_t (&r)[D],
                                                    const uint32_t (&wrap)[D], const VectorArgs &a, uint64_t off) {

@@ -167,6 +167,124 @@ def test_unequal_blocks_through_all_hops(dims, offsets, sizes, box):
             assert torch.equal(recv, want), (dims, align, alg)
 
 
+def _from(dims, periodic, vector):
+    """For every rank the one `vector` back, and whether there is one, on the device."""
+    src, valid = orc.source_ranks_mesh(dims, periodic, [vector])
+    return (torch.from_numpy(np.where(valid[:, 0], src[:, 0], 0).astype(np.int64)).to(DEV),
+            torch.from_numpy(np.ascontiguousarray(valid[:, 0])).to(DEV))
+
+
+def _check_workspace(dims, periodic, offsets, op, alg, sizes, layout=RANK):
+    """What a start of one launch through all hops leaves in the workspace: of an all-to-all, at every rank on a block's way,
+    what the block is there after one of its hops (of two hops there is one such place for a rank); of an allgather, every trie
+    node's block, or that of one of the nodes that share a place; everything else, and the bytes around it, untouched."""
+    offsets, sizes = [tuple(int(x) for x in c) for c in offsets], [int(x) for x in sizes]
+    p, s, d, a2a = int(np.prod(dims)), len(offsets), len(dims), op == iso.ISO_OP_ALLTOALL
+    comm = iso.iso_neighborhood_create_mesh(dims, periodic, offsets) if not all(periodic) else iso.iso_neighborhood_create(dims, offsets)
+    n_work = iso.iso_workspace_bytes_v(comm, op, alg, sizes)
+    store = torch.full((n_work + 512,), 0xDD, dtype=torch.uint8, device=DEV)
+    gener = torch.Generator(DEV).manual_seed(p)
+    blocks = [torch.randint(0, 256, (p, m), dtype=torch.uint8, device=DEV, generator=gener) for m in (sizes if a2a else sizes[:1])]
+    if len(set(sizes)) == 1:
+        send = (torch.stack(blocks) if layout == SLOT else torch.cat(blocks, 1)).contiguous()
+        recv = torch.empty(p * sum(sizes), dtype=torch.uint8, device=DEV)
+        init = iso.iso_neighbor_alltoall_init_layout if a2a else iso.iso_neighbor_allgather_init_layout
+        req = init(send, recv, sizes[0], layout, store[256:256 + n_work], comm, alg)
+    else:
+        displs, row = gen.packed_displacements(sizes, 1)
+        send, recv = torch.cat(blocks, 1).contiguous(), torch.empty(p * row, dtype=torch.uint8, device=DEV)
+        req = iso.iso_neighbor_alltoallv_init(send, sizes, displs, row, recv, sizes, displs, row, store[256:256 + n_work], comm, alg)
+    start, plan = iso.iso_request_start_info(req), iso.iso_request_plan(req)
+    assert start["bytes_read"] == (p * sum(sizes) if a2a else start["kernels"] * p * sizes[0])          # the send buffer alone
+    info = iso.iso_plan_info(plan)
+    entries = [e for q in range(info["launches"]) for e in iso.iso_plan_entries(plan, q)]
+    iso.iso_start(req)
+    iso.iso_wait(req)
+    iso.iso_request_free(req)
+    slot_size, states = {}, {}                                    # states: slot -> [(block, source ranks, where)]
+    hops, way = {}, {}
+    for e in entries:
+        if e["dst_buf"] == iso.ISO_BUF_WORK:
+            slot_size[e["dst_slot"]] = max(slot_size.get(e["dst_slot"], 0), sizes[e["neighbor"]] if a2a else sizes[0])
+        if a2a and sizes[e["neighbor"]]:
+            hops.setdefault(e["neighbor"], []).append(e["dim"])
+            if e["dst_buf"] == iso.ISO_BUF_WORK:
+                way[e["neighbor"]] = e["dst_slot"]
+        elif not a2a and e["dst_buf"] == iso.ISO_BUF_WORK:
+            routed = list(info["dim_order"])[:list(info["dim_order"]).index(e["dim"]) + 1]
+            src, valid = _from(dims, periodic, [offsets[e["ref"]][j] if j in routed else 0 for j in range(d)])
+            states.setdefault(e["dst_slot"], []).append((blocks[0], src, valid))
+    for i, along in hops.items():
+        for t in range(1, len(along)):
+            src, valid = _from(dims, periodic, [offsets[i][j] if j in along[:t] else 0 for j in range(d)])
+            _, onward = _from(dims, periodic, [-offsets[i][j] if j in along[t:] else 0 for j in range(d)])
+            states.setdefault(way[i], []).append((blocks[i], src, valid & onward))
+    checked, at = 0, 256
+    for slot in range(info["work_slots"]):
+        m = slot_size[slot]
+        plane = store[at:at + p * m].view(p, m)
+        held, due = torch.zeros((p, m), dtype=torch.bool, device=DEV), torch.zeros(p, dtype=torch.bool, device=DEV)
+        for block, src, where in states.get(slot, []):
+            held |= where[:, None] & (plane == block.index_select(0, src))      # (stores to one place have no order, unit by unit)
+            due |= where
+            checked += 1
+        ok = torch.where(due, held.all(1), (plane == 0xDD).all(1))
+        assert bool(ok.all()), (dims, slot, int((~ok).sum()))
+        end = at + -(-p * m // 16) * 16
+        assert bool((store[at + p * m:end] == 0xDD).all())
+        at = end
+    assert checked and at == 256 + n_work and bool((store[:256] == 0xDD).all()) and bool((store[at:] == 0xDD).all())
+
+
+@pytest.mark.parametrize("dims,periodic,offsets,sizes,alg,layout", [
+    ((23, 24, 25), (1, 1, 1), gen.moore(3, 1), [128] * 26, COMBINED, RANK),                           # two hops, and three
+    ((12, 11, 13), (1, 1, 1), gen.moore(3, 1), [1027] * 26, COMBINED, RANK),
+    ((61, 67), (1, 1), gen.moore(2, 2) + [(0, 0), (1, 2), (1, 2)], [1024] * 27, COMBINED, RANK),       # one block per wavefront
+    ((7, 6, 5, 8, 9), (1,) * 5, gen.random_distinct(5, -3, 3, 40, 5), [144] * 40, BYDIM, SLOT),
+    ((7, 6, 5, 8, 9), (1,) * 5, gen.random_distinct(5, -3, 3, 40, 5), [1024] * 40, COMBINED, RANK),
+    ((25, 24, 26), (0, 1, 0), gen.moore(3, 1) + [(25, 0, 1), (2, 25, -2)], [256] * 28, BYDIM, RANK),
+    ((7, 6, 9, 5, 8), (1, 0, 0, 1, 0), gen.random_distinct(5, -3, 3, 40, 5), [2048] * 40, BYDIM, SLOT),
+    ((21, 20, 19), (1, 1, 1), gen.moore(3, 1), gen.stencil_block_sizes(gen.moore(3, 1), 51), COMBINED, RANK),
+    ((13, 12, 11), (0, 1, 0), gen.moore(3, 1), gen.stencil_block_sizes(gen.moore(3, 1), 20), COMBINED, RANK),
+    ((5, 4, 3, 4, 5), (1,) * 5, gen.moore(5, 1)[:128], [(1, 2, 4, 8, 16, 64)[i % 6] for i in range(128)], COMBINED, RANK)])
+def test_alltoall_stops(dims, periodic, offsets, sizes, alg, layout):
+    _check_workspace(dims, periodic, offsets, iso.ISO_OP_ALLTOALL, alg, sizes, layout)
+
+
+@pytest.mark.parametrize("dims,periodic,offsets,m,alg,layout", [
+    ((23, 24, 25), (1, 1, 1), gen.random_distinct(3, -3, 3, 20, 5), 1000, COMBINED, RANK),
+    ((7, 6, 5, 8, 9), (1,) * 5, gen.random_distinct(5, -3, 3, 40, 5), 128, COMBINED, RANK),              # pull
+    ((8, 9, 8, 7, 5), (1,) * 5, gen.random_distinct(5, -3, 3, 36, 7), 1152, COMBINED, RANK),             # push
+    ((9, 8, 8, 9, 8), (1,) * 5, gen.random_distinct(5, -3, 3, 40, 5), 17, COMBINED, RANK),               # plain stores
+    ((9, 8, 7, 11), (1,) * 4, gen.random_distinct(4, -3, 3, 30, 5), 100, COMBINED, SLOT),
+    ((25, 24, 26), (0, 1, 0), gen.random_distinct(3, -3, 3, 20, 5), 640, BYDIM, RANK)])
+def test_allgather_nodes_in_the_workspace(dims, periodic, offsets, m, alg, layout):
+    _check_workspace(dims, periodic, offsets, iso.ISO_OP_ALLGATHER, alg, [m] * len(offsets), layout)
+
+
+@pytest.mark.parametrize("dims,offsets,sizes", [
+    ((17, 19), gen.moore(2, 10), [4 + 4 * (i % 2) for i in range(440)]), ((7, 8, 9), gen.moore(3, 3), [(1, 3, 40, 128, 700)[i % 5] for i in range(342)]),
+    ((5, 4, 6, 5), gen.moore(4, 1) + gen.von_neumann(4, 2), [(2, 16)[i % 2] for i in range(120)]), ((6, 5, 5), gen.moore(3, 3)[:130], [(8, 4)[i > 0] for i in range(130)])])
+def test_unequal_blocks_of_many_neighbours(dims, offsets, sizes):
+    """More blocks of a size than one launch takes."""
+    offsets = [tuple(int(x) for x in c) for c in offsets]
+    comm, p = iso.iso_neighborhood_create(dims, offsets), int(np.prod(dims))
+    src, _ = orc.source_ranks_mesh(dims, [1] * len(dims), offsets)
+    src = torch.from_numpy(src.astype(np.int64)).to(DEV)
+    displs, row = gen.packed_displacements(sizes, 1)
+    send = torch.randint(0, 256, (p, row), dtype=torch.uint8, device=DEV, generator=torch.Generator(DEV).manual_seed(p))
+    recv = torch.full((p, row), 0xEE, dtype=torch.uint8, device=DEV)
+    n_work = iso.iso_workspace_bytes_v(comm, iso.ISO_OP_ALLTOALL, COMBINED, sizes)
+    store = torch.full((n_work + 512,), 0xCC, dtype=torch.uint8, device=DEV)
+    work = store[256:256 + n_work]
+    req = iso.iso_neighbor_alltoallv_init(send, sizes, displs, row, recv, sizes, displs, row, work, comm, COMBINED)
+    start_both_ways(req, recv, work, starts=2)
+    iso.iso_request_free(req)
+    for i, (at, m) in enumerate(zip(displs, sizes)):
+        assert torch.equal(recv[:, at:at + m], send[:, at:at + m].index_select(0, src[:, i])), i
+    assert bool((store[:256] == 0xCC).all()) and bool((store[256 + n_work:] == 0xCC).all())
+
+
 @pytest.mark.parametrize("dims,offsets", [
     ((5, 4, 7), gen.moore(3, 1)), ((23, 2, 31), gen.moore(3, 2)), ((17, 1, 19), gen.random_distinct(3, -3, 3, 40, 3)),
     ((6, 7, 5, 9), gen.random_distinct(4, -3, 3, 30, 5)), ((4, 5, 3, 4, 6), gen.random_distinct(5, -3, 3, 40, 5)),

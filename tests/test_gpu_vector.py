@@ -24,7 +24,7 @@ def _source_ranks(dims, offsets):
 
 
 def check_exchange(dims, offsets, op, alg, m, layout, send_off=0, recv_off=0):
-    """One collective with the receive buffer's surroundings watched; returns nothing, raises on a wrong byte."""
+    """One collective with the surroundings of receive buffer and workspace watched; returns nothing, raises on a wrong byte."""
     p, s = int(np.prod(dims)), len(offsets)
     a2a, slot = op == iso.ISO_OP_ALLTOALL, layout == iso.ISO_LAYOUT_SLOT_MAJOR
     comm = iso.iso_neighborhood_create(dims, np.asarray(offsets, np.int32).reshape(s, len(dims)))
@@ -34,7 +34,9 @@ def check_exchange(dims, offsets, op, alg, m, layout, send_off=0, recv_off=0):
     send = torch.randint(0, 256, (n_send + send_off,), dtype=torch.uint8, device=DEV, generator=g)[send_off:]
     store = torch.full((n_recv + recv_off + 64,), 0xEE, dtype=torch.uint8, device=DEV)
     recv = store[recv_off:recv_off + n_recv]
-    work = torch.empty(max(1, iso.iso_workspace_bytes(comm, op, alg, m)), dtype=torch.uint8, device=DEV)
+    n_work = max(1, iso.iso_workspace_bytes(comm, op, alg, m))
+    work_store = torch.full((n_work + 512,), 0xCC, dtype=torch.uint8, device=DEV)
+    work = work_store[256:256 + n_work]
     init = iso.iso_neighbor_alltoall_init_layout if a2a else iso.iso_neighbor_allgather_init_layout
     req = init(send, recv, m, layout, work, comm, alg)
     start_both_ways(req, recv, work, starts=2)
@@ -48,6 +50,7 @@ def check_exchange(dims, offsets, op, alg, m, layout, send_off=0, recv_off=0):
             block = send.view(p, m)
         assert torch.equal(got, block.index_select(0, src[:, i])), (dims, m, layout, i)
     assert bool((store[:recv_off] == 0xEE).all()) and bool((store[recv_off + n_recv:] == 0xEE).all())
+    assert bool((work_store[:256] == 0xCC).all()) and bool((work_store[256 + n_work:] == 0xCC).all()), (dims, m, layout)
 
 
 TORI = [((700,), [(1,), (-3,), (0,), (699,)]), ((37, 21), gen.moore(2, 1)), ((1, 60), [(1, 1), (0, -2)]),
