@@ -164,11 +164,13 @@ def test_staged_schedule_by_what_the_last_level_cache_holds(dims, m, op):
     check_exchange(dims, gen.moore(3, 1), op, iso.ISO_ALG_COMBINED_STAGED, m, iso.ISO_LAYOUT_RANK_MAJOR, recv_off=16)
 
 
-@pytest.mark.parametrize("dims,edge,align", [((32, 32, 32), 25, 16), ((21, 20, 19), 51, 1), ((64, 63, 65), 12, 1), ((16, 17, 16, 17), 6, 4)])
+@pytest.mark.parametrize("dims,edge,align", [((32, 32, 32), 25, 16), ((21, 20, 19), 51, 1), ((64, 63, 65), 12, 1), ((16, 17, 16, 17), 6, 4),
+                                             ((31, 32, 33), (8, 200, 300, 400, 500), 1), ((31, 32, 33), (16, 144, 256, 400, 1024), 16)])
 def test_small_and_large_blocks_by_their_size(dims, edge, align):
-    """Blocks of up to 128 bytes and larger ones together in rounds of 64 MiB and more, against the straightforward exchange."""
+    """Blocks of up to 128 bytes and larger ones together, 64 MiB and more, against the straightforward exchange: sizes with a
+    launch each, and too many of them for that, which the rounds' kernel takes by size."""
     offsets = gen.moore(len(dims), 1)
-    p, sizes = int(np.prod(dims)), list(gen.stencil_block_sizes(offsets, edge))
+    p, sizes = int(np.prod(dims)), list(gen.stencil_block_sizes(offsets, edge) if isinstance(edge, int) else [edge[i % 5] for i in range(26)])
     displs, row = gen.packed_displacements(sizes, align)
     assert p * sum(sizes) > 64 << 20
     comm = iso.iso_neighborhood_create(dims, offsets)
